@@ -17,7 +17,8 @@ extern "C" {
  * contraction used by every stage forward / backward of a tick (Sec. 3.1: the forward and
  * backward computation of a stage on one micro-batch).
  *   dtype      0 fp32, 1 bf16 (operand element type)
- *   tile_shape 0: 128x128, 1: 64x128, 2: 64x64 workgroup tile of the generic kernel;
+ *   tile_shape 0: 128x128, 1: 64x128, 2: 64x64 workgroup tile of the generic kernel (with a_kmajor =
+ *              b_kmajor = 0, a weight gradient, all three run the tiles the Linear stages use for it);
  *              3: 64x64, 4: 64x128 tile of the weight-streaming kernel the Linear stages
  *              use; 5: the same kernel as launched by the engine, which gives problems of
  *              at most 32 rows with 16-byte-chunked operands 32x32 tiles whose waves split

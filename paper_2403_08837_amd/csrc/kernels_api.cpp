@@ -27,6 +27,15 @@ int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void
   p.epi = EPI_FWD;
   p.flags = GF_OUT_F32;
   p.splits = 1;
+  if (!a_kmajor && !b_kmajor) {
+    // Both operands run along the output (a weight gradient): the weight-gradient tiles of the Linear launch read them
+    // as they lie and transpose on the way out of LDS, where the generic kernel scatters 2- or 4-byte elements into
+    // LDS.  Measured against the generic kernel's best tile over outputs of 64 x 64 to 4096 x 4096, 8 to 4096 rows:
+    // faster at every one (fp32 64 x 64 x 8 13 -> 7 us, bf16 4096 x 4096 x 64 52 -> 16 us, 4096^3 1124 -> 271 us).
+    p.epi = EPI_WGRAD;
+    p.flags = 0;
+    return launch_linear_tick(b, dtype, false, false, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
+  }
   if (tile_shape >= TILE_COUNT)
     return launch_linear_tick(b, dtype, tile_shape == TILE_COUNT + 1, tile_shape == TILE_COUNT + 2, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
   return launch_gemm_batch(b, dtype, tile_shape, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;

@@ -51,6 +51,28 @@ def test_gemm_all_layouts(dtype, shape, a_k, b_k, M, N, K):
     assert np.abs(got - ref).max() <= tol, np.abs(got - ref).max()
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("M,N,K,lda,ldb", [(512, 1024, 64, 512, 1024),     # smallest matrix that is walked in runs of two column tiles
+                                           (520, 1160, 33, 528, 1168),     # the same with a ragged run and padded rows
+                                           (512, 1024, 65, 512, 1024),     # one row more than a staged slab: single tiles
+                                           (96, 136, 200, 100, 137),       # several slabs, rows that are not whole chunks
+                                           (33, 1, 1, 33, 1)])
+def test_gemm_weight_gradient_tiles(dtype, M, N, K, lda, ldb):
+    """C = A^T B with both operands row-contiguous, at the edges of the weight-gradient tiles."""
+    torch = _torch()
+    A = wl.random_normal(1, 10 * M + K, K * lda).reshape(K, lda)
+    Bm = wl.random_normal(2, 10 * N + K, K * ldb).reshape(K, ldb)
+    ref = _rnd(A, dtype)[:, :M].T @ _rnd(Bm, dtype)[:, :N]
+    Ad, Bd = _dev(A, dtype), _dev(Bm, dtype)
+    Cd = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    b.cdp_k_gemm(dtype, 0, 0, 0, Ad.data_ptr(), Bd.data_ptr(), Cd.data_ptr(), M, N, K, lda, ldb)
+    torch.cuda.synchronize()
+    got = Cd.cpu().numpy().astype(np.float64)
+    # products of exactly representable inputs, fp32 sums of K terms: K 2^-24 of the largest magnitude bounds the error
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= 2e-5 * np.sqrt(K) * max(1.0, np.abs(ref).max())
+
+
 CONV_CASES = [
     # B, H, W, Cin, Cout, ks, stride, pad
     (2, 8, 8, 8, 16, 3, 1, 1),
