@@ -1,0 +1,534 @@
+// The self-attention core in bf16: one kernel forward, two backward, nothing but the probabilities travelling
+// through memory between the products.
+//
+// What bounds them: 32 samples x 12 heads x 196 tokens of width 64 are 68 MB forward and 97 MB backward (q, k, v, d out,
+// the probabilities, the results) against 3.8 and 7.6 GFLOP, so memory; the contractions are short and the softmax
+// sits between them, so what costs time is everything that is not one of those bytes.  Every wavefront computes score
+// blocks TRANSPOSED (rows = keys, columns = the 32 queries of its lanes): a lane then holds 4 neighbouring keys per
+// group of accumulator registers for one query, row sums and maxima are sums inside the lane plus one exchange with
+// lane +- 32, and the rounded probabilities are, in the registers they are in, the column operand of the next
+// product: lane half `hi` holds keys 16 s + 4 hi + 0..3 and 16 s + 8 + 4 hi + 0..3 of a 16-key step, and the row operand
+// is read from LDS (transposing reads) in that same order of keys, which a contraction is free to choose.
+// A workgroup is four wavefronts of 32 queries (or keys) each; k and v (or q and d out) of the head are staged in LDS
+// once, without padding for heads of width 64 (16-byte chunks swizzled by the row instead) so that three workgroups
+// fit a CU: 768 workgroups for the shape above, three per CU.
+// The limit in tokens is LDS (64-wide heads: 624); past 256 tokens the forward contracts the scores twice instead of
+// keeping them (8 x 400 tokens, 8 heads of 64: 43 -> 22 us forward, 84 -> 49 us backward against separate kernels).
+// Measured there (us, forward / backward): score rows and products as kernels of their own 50 / 101; these three
+// 20 / 52 (dq 27, dkv 29 under the profiler).  What is left above the bytes (13 / 28 at the rate of a large copy, the
+// backward reading q, v, d out and P once per kernel) is that the resident workgroups move in step: they stage, contract
+// and store together; 192 workgroups, less than one per CU, take 10 us already.
+#include "elem.h"
+#include "kernels.h"
+
+#include <algorithm>
+
+namespace cdp {
+
+namespace {
+
+typedef short att_v4s __attribute__((ext_vector_type(4)));
+
+struct AttnArgs {
+  const uint16_t* qkv;   // [B][NT][3 D]
+  uint16_t* P;           // [B][heads][NT][NT]: written forward, read backward
+  const uint16_t* dout;  // backward: [B][NT][D]
+  uint16_t* out;         // forward: [B][NT][D]; backward: d qkv [B][NT][3 D]
+  float* delta;          // backward: [B][heads][NT], rowsum(dP * P)
+  int NT, D, heads;
+  int blocks;            // workgroups per (sample, head)
+  int vec;               // rows of P are whole, aligned 8-byte groups
+  int dvec;              // rows of delta are whole, aligned 16-byte groups
+  float scale;
+};
+
+// Tile of `rows` token rows of one head in LDS: 16-byte chunk c of row r at chunk (c ^ (r & SWZ)) of the row.
+template <int KS> struct AttnTile {
+  static constexpr int DH = 16 * KS, CPR = DH / 8;
+  static constexpr int SWZ = CPR == 8 ? 7 : 0;
+  static constexpr int PITCH = CPR == 8 ? DH : DH + 8;  // elements
+  __device__ static __forceinline__ int at(int row, int col) { return row * PITCH + (((col >> 3) ^ (row & SWZ)) << 3) + (col & 7); }
+};
+
+// Both tiles of a workgroup (`rows`: the tokens rounded up to 16): rows past the last token are zero.  All chunks of a pass are requested before the first is
+// written to LDS.
+template <int KS>
+__device__ __forceinline__ void stage_two(uint16_t* t0, uint16_t* t1, const uint16_t* s0, const uint16_t* s1, int64_t ld0, int64_t ld1, int NT,
+                                          int rows) {
+  using Tile = AttnTile<KS>;
+  constexpr int CPR = Tile::CPR, U = 4;
+  const int total = rows * CPR;
+  for (int e0 = threadIdx.x; e0 < total; e0 += 256 * U) {
+    uint4 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + 256 * u, r = e / CPR, c = (e - r * CPR) * 8;
+      const bool in = e < total && r < NT;
+      a[u] = in ? *reinterpret_cast<const uint4*>(s0 + (int64_t)r * ld0 + c) : make_uint4(0, 0, 0, 0);
+      b[u] = in ? *reinterpret_cast<const uint4*>(s1 + (int64_t)r * ld1 + c) : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + 256 * u, r = e / CPR, c = (e - r * CPR) * 8;
+      if (e >= total) continue;
+      *reinterpret_cast<uint4*>(t0 + Tile::at(r, c)) = a[u];
+      *reinterpret_cast<uint4*>(t1 + Tile::at(r, c)) = b[u];
+    }
+  }
+}
+
+// Row operand (rows r0 .. r0 + 31 of the tile, columns 16 ks ..) of a 32x32x16 product that reduces over the head width.
+// Where the tile ends after 16 of them the upper 16 rows repeat the lower ones; what comes of them is masked or skipped.
+template <int KS>
+__device__ __forceinline__ uint4 frag_rows(const uint16_t* tile, int r0, int ks, int lane, int rows) {
+  const int r = r0 + (r0 + 32 <= rows ? lane & 31 : lane & 15);
+  return *reinterpret_cast<const uint4*>(tile + AttnTile<KS>::at(r, 16 * ks + 8 * (lane >> 5)));
+}
+// Row operand whose rows are tile columns c0 .. c0 + 31 and whose reduction index is the tile row, taken in the order in
+// which an accumulator holds rows: lane half hi gets rows r0 + 4 hi + 0..3, then r0 + 8 + 4 hi + 0..3.
+template <int KS>
+__device__ __forceinline__ uint4 frag_cols(const uint16_t* tile, int r0, int c0, int lane) {
+  const int rho = lane & 15, row = r0 + 4 * (lane >> 5) + (rho >> 2), col = c0 + 16 * ((lane >> 4) & 1) + 4 * (rho & 3);
+  typedef __attribute__((address_space(3))) att_v4s* lds_ptr;
+  union { att_v4s v[2]; uint4 u; } f;
+  f.v[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(tile + AttnTile<KS>::at(row, col)));
+  f.v[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(tile + AttnTile<KS>::at(row + 8, col)));
+  return f.u;
+}
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) { return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16); }
+__device__ __forceinline__ float lo16(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float hi16(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
+__device__ __forceinline__ v16f_t zero16() {
+  v16f_t a;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) a[v] = 0.f;
+  return a;
+}
+
+// The 16 probabilities of a lane for keys k0 .. k0 + 15 of its query, w[0] = keys 4 hi + 0..3 and w[1] = 8 + 4 hi + 0..3,
+// from / to the query's row in memory (nullptr: zeros / nothing), where a lane half moves 8 neighbouring keys: with
+// 8-byte pieces a wavefront's 32 rows cost twice the instructions and the store rate of the CU bounded the kernel.
+struct __attribute__((packed, aligned(8))) P8 { uint32_t u[4]; };
+__device__ __forceinline__ void swap_halves(uint2 (&w)[2]) {  // (its own inverse)
+  auto x = __builtin_amdgcn_permlane32_swap(w[0].x, w[1].x, false, false);
+  auto y = __builtin_amdgcn_permlane32_swap(w[0].y, w[1].y, false, false);
+  w[0] = make_uint2(x[0], y[0]);
+  w[1] = make_uint2(x[1], y[1]);
+}
+__device__ __forceinline__ void load_p16(const uint16_t* row, int k0, int hi, int NT, int vec, uint2 (&w)[2]) {
+  const int k = k0 + 8 * hi;
+  w[0] = w[1] = make_uint2(0, 0);
+  if (row != nullptr) {
+    if (vec && k + 8 <= NT) {
+      const P8 p = *reinterpret_cast<const P8*>(row + k);
+      w[0] = make_uint2(p.u[0], p.u[1]);
+      w[1] = make_uint2(p.u[2], p.u[3]);
+    } else if (vec) {
+      if (k < NT) w[0] = *reinterpret_cast<const uint2*>(row + k);
+    } else {
+      uint32_t e[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) e[i] = k + i < NT ? row[k + i] : 0u;
+      w[0] = make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16));
+      w[1] = make_uint2(e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+    }
+  }
+}
+__device__ __forceinline__ void store_p16(uint16_t* row, int k0, int hi, int NT, int vec, uint2 a, uint2 b) {
+  uint2 w[2] = {a, b};
+  swap_halves(w);
+  const int k = k0 + 8 * hi;
+  if (row == nullptr) return;
+  if (vec && k + 8 <= NT) {
+    *reinterpret_cast<P8*>(row + k) = P8{{w[0].x, w[0].y, w[1].x, w[1].y}};
+  } else if (vec) {
+    if (k < NT) *reinterpret_cast<uint2*>(row + k) = w[0];
+  } else {
+    const uint32_t e[4] = {w[0].x, w[0].y, w[1].x, w[1].y};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (k + i < NT) row[k + i] = (uint16_t)(e[i >> 1] >> (16 * (i & 1)));
+  }
+}
+// Transposed 32-column block of a result (rows = head columns 32 ob .., column = the lane's token) -> the token's row.
+template <int KS>
+__device__ __forceinline__ void store_cols(uint16_t* dst, int ob, int hi, const v16f_t& acc) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int j = 32 * ob + 8 * g + 4 * hi;
+    if (j < 16 * KS) *reinterpret_cast<uint2*>(dst + j) = make_uint2(pack2(acc[4 * g], acc[4 * g + 1]), pack2(acc[4 * g + 2], acc[4 * g + 3]));
+  }
+}
+
+// ---- forward: P = softmax(scale q k^T), out = P v ---------------------------------------------------------------------
+// NB > 0: all score blocks of a wavefront's 32 queries stay in registers (at most 32 NB keys).  NB = 0: any number of
+// keys, in two passes over the blocks, the first for the row maximum and sum.
+template <int KS, int NB>
+__global__ __launch_bounds__(256, NB == 8 && KS == 5 ? 2 : 3) void attn_fwd_kernel(const AttnArgs a) {
+  using Tile = AttnTile<KS>;
+  constexpr int OB = (KS + 1) / 2, DH = Tile::DH;
+  extern __shared__ __attribute__((aligned(16))) unsigned char att_smem[];
+  const int NT = a.NT, rows = (NT + 15) & ~15, nblk = (NT + 31) >> 5;
+  uint16_t* Ks = reinterpret_cast<uint16_t*>(att_smem);
+  uint16_t* Vs = Ks + rows * Tile::PITCH;
+  const int id = xcd_block_cyclic(blockIdx.x, gridDim.x, a.blocks);  // the workgroups of a head share an XCD's L2
+  const int z = id / a.blocks, sample = z / a.heads, head = z % a.heads;
+  const int lane = threadIdx.x & 63, l31 = lane & 31, hi = lane >> 5;
+  const int q = ((id % a.blocks) * 4 + (threadIdx.x >> 6)) * 32 + l31;
+  const int64_t tok = 3ll * a.D;
+  const uint16_t* base = a.qkv + sample * NT * tok + head * DH;
+  const uint16_t* qrow = base + (int64_t)min(q, NT - 1) * tok;  // rows past the end repeat the last one; nothing of them is stored
+  uint4 qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const uint4*>(qrow + 16 * ks + 8 * hi);
+  stage_two<KS>(Ks, Vs, base + a.D, base + 2 * a.D, tok, tok, NT, rows);
+  __syncthreads();
+  const float c = a.scale * 1.44269504088896340736f;
+  auto scores = [&](int b) {
+    v16f_t s = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s = mfma_bf16(frag_rows<KS>(Ks, 32 * b, ks, lane, rows), qf[ks], s);
+    if (32 * b + 32 > NT) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (32 * b + 8 * (v >> 2) + 4 * hi + (v & 3) >= NT) s[v] = -INFINITY;
+    }
+    return s;
+  };
+  auto block_max = [&](const v16f_t& s) {
+    float m = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) m = fmaxf(m, s[v]);
+    return m;
+  };
+  v16f_t o[OB];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) o[ob] = zero16();
+  uint16_t* prow = q < NT ? a.P + ((int64_t)z * NT + q) * NT : nullptr;
+  // a finished block of probabilities: to memory, and as the column operand of out^T = v^T P^T
+  auto finish = [&](int b, const v16f_t& p) {
+    uint2 w[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) w[g] = make_uint2(pack2(p[4 * g], p[4 * g + 1]), pack2(p[4 * g + 2], p[4 * g + 3]));
+#pragma unroll
+    for (int s = 0; s < 2; ++s) store_p16(prow, 32 * b + 16 * s, hi, NT, a.vec, w[2 * s], w[2 * s + 1]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if (32 * b + 16 * s < rows)
+#pragma unroll
+      for (int ob = 0; ob < OB; ++ob)
+        o[ob] = mfma_bf16(frag_cols<KS>(Vs, 32 * b + 16 * s, 32 * ob, lane), make_uint4(w[2 * s].x, w[2 * s].y, w[2 * s + 1].x, w[2 * s + 1].y), o[ob]);
+  };
+  if constexpr (NB > 0) {
+    v16f_t s[NB];
+    float m = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b < nblk) {
+        s[b] = scores(b);
+        m = fmaxf(m, block_max(s[b]));
+      }
+    m = fmaxf(m, __shfl_xor(m, 32, 64)) * c;  // finite: key 0 is always there
+    float sum = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b < nblk) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          s[b][v] = __builtin_amdgcn_exp2f(s[b][v] * c - m);
+          sum += s[b][v];
+        }
+      }
+    const float inv = __builtin_amdgcn_rcpf(sum + __shfl_xor(sum, 32, 64));
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b < nblk) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[b][v] *= inv;
+        finish(b, s[b]);
+      }
+  } else {
+    float m = -INFINITY, sum = 0.f;
+    for (int b = 0; b < nblk; ++b) {
+      const v16f_t s = scores(b);
+      const float mb = block_max(s);
+      const float mn = fmaxf(m, fmaxf(mb, __shfl_xor(mb, 32, 64)) * c);  // the same in both lanes of a query
+      sum *= __builtin_amdgcn_exp2f(m - mn);
+      m = mn;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(s[v] * c - m);
+    }
+    const float inv = __builtin_amdgcn_rcpf(sum + __shfl_xor(sum, 32, 64));
+    for (int b = 0; b < nblk; ++b) {
+      v16f_t s = scores(b);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s[v] = __builtin_amdgcn_exp2f(s[v] * c - m) * inv;
+      finish(b, s);
+    }
+  }
+  if (q < NT) {
+    uint16_t* dst = a.out + ((int64_t)sample * NT + q) * a.D + head * DH;
+#pragma unroll
+    for (int ob = 0; ob < OB; ++ob) store_cols<KS>(dst, ob, hi, o[ob]);
+  }
+}
+
+// ---- backward, queries: delta = rowsum(dP * P) and dq = dS k, with dP = d out v^T, dS = P * (dP - delta) * scale -------
+// Two passes over the key blocks, dP contracted in both: keeping all of it for the second costs a workgroup per CU.
+template <int KS>
+__global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const AttnArgs a) {
+  using Tile = AttnTile<KS>;
+  constexpr int OB = (KS + 1) / 2, DH = Tile::DH;
+  extern __shared__ __attribute__((aligned(16))) unsigned char att_smem[];
+  const int NT = a.NT, rows = (NT + 15) & ~15, nblk = (NT + 31) >> 5;
+  uint16_t* Vs = reinterpret_cast<uint16_t*>(att_smem);
+  uint16_t* Ks = Vs + rows * Tile::PITCH;
+  const int id = xcd_block_cyclic(blockIdx.x, gridDim.x, a.blocks);
+  const int z = id / a.blocks, sample = z / a.heads, head = z % a.heads;
+  const int lane = threadIdx.x & 63, l31 = lane & 31, hi = lane >> 5;
+  const int q = ((id % a.blocks) * 4 + (threadIdx.x >> 6)) * 32 + l31;
+  const int64_t tok = 3ll * a.D;
+  const uint16_t* base = a.qkv + sample * NT * tok + head * DH;
+  const uint16_t* drow = a.dout + ((int64_t)sample * NT + min(q, NT - 1)) * a.D + head * DH;
+  uint4 df[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) df[ks] = *reinterpret_cast<const uint4*>(drow + 16 * ks + 8 * hi);
+  stage_two<KS>(Vs, Ks, base + 2 * a.D, base + a.D, tok, tok, NT, rows);
+  __syncthreads();
+  const uint16_t* prow = q < NT ? a.P + ((int64_t)z * NT + q) * NT : nullptr;
+  auto load_block = [&](int b, uint2 (&w)[2][2]) {  // as they lie in memory: swap_halves where they are used
+#pragma unroll
+    for (int t = 0; t < 2; ++t) load_p16(prow, 32 * b + 16 * t, hi, NT, a.vec, w[t]);
+  };
+  auto dp_block = [&](int b) {
+    v16f_t s = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s = mfma_bf16(frag_rows<KS>(Vs, 32 * b, ks, lane, rows), df[ks], s);
+    return s;
+  };
+  float delta = 0.f;
+  uint2 w[2][2], nw[2][2];
+  load_block(0, w);
+  for (int b = 0; b < nblk; ++b) {
+    load_block(b + 1 < nblk ? b + 1 : 0, nw);  // the next block's probabilities (at the end: the first's, for the second pass)
+    const v16f_t s = dp_block(b);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      swap_halves(w[t]);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int v = 8 * t + 4 * g;
+        delta += lo16(w[t][g].x) * s[v] + hi16(w[t][g].x) * s[v + 1];
+        delta += lo16(w[t][g].y) * s[v + 2] + hi16(w[t][g].y) * s[v + 3];
+        w[t][g] = nw[t][g];
+      }
+    }
+  }
+  delta += __shfl_xor(delta, 32, 64);
+  if (q < NT && hi == 0) a.delta[(int64_t)z * NT + q] = delta;
+  v16f_t o[OB];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) o[ob] = zero16();
+  for (int b = 0; b < nblk; ++b) {
+    if (b + 1 < nblk) load_block(b + 1, nw);
+    const v16f_t s = dp_block(b);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      swap_halves(w[t]);
+      uint2 d[2];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int v = 8 * t + 4 * g;
+        d[g].x = pack2(lo16(w[t][g].x) * (s[v] - delta) * a.scale, hi16(w[t][g].x) * (s[v + 1] - delta) * a.scale);
+        d[g].y = pack2(lo16(w[t][g].y) * (s[v + 2] - delta) * a.scale, hi16(w[t][g].y) * (s[v + 3] - delta) * a.scale);
+        w[t][g] = nw[t][g];
+      }
+      if (32 * b + 16 * t < rows)
+#pragma unroll
+        for (int ob = 0; ob < OB; ++ob)
+          o[ob] = mfma_bf16(frag_cols<KS>(Ks, 32 * b + 16 * t, 32 * ob, lane), make_uint4(d[0].x, d[0].y, d[1].x, d[1].y), o[ob]);
+    }
+  }
+  if (q < NT) {
+    uint16_t* dst = a.out + ((int64_t)sample * NT + q) * tok + head * DH;
+#pragma unroll
+    for (int ob = 0; ob < OB; ++ob) store_cols<KS>(dst, ob, hi, o[ob]);
+  }
+}
+
+// ---- backward, keys: dv = P^T d out, dk = dS^T q -----------------------------------------------------------------------
+// A wavefront owns 32 keys (its lanes) and walks the queries: dP is contracted the other way round (rows = queries), so
+// P and dS are again the column operand in the registers they are in, now reducing over queries.
+template <int KS>
+__global__ __launch_bounds__(256, KS <= 4 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnArgs a) {
+  using Tile = AttnTile<KS>;
+  constexpr int OB = (KS + 1) / 2, DH = Tile::DH;
+  extern __shared__ __attribute__((aligned(16))) unsigned char att_smem[];
+  const int NT = a.NT, rows = (NT + 15) & ~15, nblk = (NT + 31) >> 5;
+  uint16_t* Qs = reinterpret_cast<uint16_t*>(att_smem);
+  uint16_t* Os = Qs + rows * Tile::PITCH;
+  const int id = xcd_block_cyclic(blockIdx.x, gridDim.x, a.blocks);
+  const int z = id / a.blocks, sample = z / a.heads, head = z % a.heads;
+  const int lane = threadIdx.x & 63, l31 = lane & 31, hi = lane >> 5;
+  const int k = ((id % a.blocks) * 4 + (threadIdx.x >> 6)) * 32 + l31;
+  const int64_t tok = 3ll * a.D;
+  const uint16_t* base = a.qkv + sample * NT * tok + head * DH;
+  const int kc = min(k, NT - 1);  // lanes past the last key repeat it; nothing of them is stored
+  const uint16_t* vrow = base + 2 * a.D + (int64_t)kc * tok;
+  uint4 vf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) vf[ks] = *reinterpret_cast<const uint4*>(vrow + 16 * ks + 8 * hi);
+  stage_two<KS>(Qs, Os, base, a.dout + (int64_t)sample * NT * a.D + head * DH, tok, a.D, NT, rows);
+  // P[q][k] and delta[q] of a block of 32 queries, in accumulator order.  Uniform row address + one 32-bit offset per lane:
+  // 64-bit addresses per element were a third of the kernel's vector instructions.
+  const uint16_t* pbase = a.P + (int64_t)z * NT * NT;
+  const float* dbase = a.delta + (int64_t)z * NT;
+  const uint32_t plane = (uint32_t)(4 * hi * NT + kc) * 2u, dlane = 16u * hi;
+  auto load_p = [&](int b, uint16_t (&p)[16]) {
+    if (32 * b + 32 <= NT) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int q = 32 * b + 8 * (v >> 2) + (v & 3);
+        p[v] = *reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(pbase + (int64_t)q * NT) + plane);
+      }
+    } else {  // rows past the last query: the last one's values, times zero rows of q and d out
+#pragma unroll
+      for (int v = 0; v < 16; ++v) p[v] = pbase[(uint32_t)(min(32 * b + 8 * (v >> 2) + 4 * hi + (v & 3), NT - 1) * NT + kc)];
+    }
+  };
+  auto load_delta = [&](int b, float (&dl)[16]) {
+    if (a.dvec && 32 * b + 32 <= NT) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 f = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(dbase + 32 * b + 8 * g) + dlane);
+        dl[4 * g] = f.x; dl[4 * g + 1] = f.y; dl[4 * g + 2] = f.z; dl[4 * g + 3] = f.w;
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) dl[v] = dbase[min(32 * b + 8 * (v >> 2) + 4 * hi + (v & 3), NT - 1)];
+    }
+  };
+  v16f_t dv[OB], dk[OB];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) { dv[ob] = zero16(); dk[ob] = zero16(); }
+  uint16_t p[16], np[16];
+  load_p(0, p);
+  __syncthreads();
+  for (int b = 0; b < nblk; ++b) {
+    float dl[16];
+    load_delta(b, dl);  // a few lines that the whole workgroup reads: cache hits
+    if (b + 1 < nblk) load_p(b + 1, np);
+    v16f_t s = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s = mfma_bf16(frag_rows<KS>(Os, 32 * b, ks, lane, rows), vf[ks], s);
+    uint32_t w[8], d[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      w[e] = (uint32_t)p[2 * e] | ((uint32_t)p[2 * e + 1] << 16);
+      d[e] = pack2(lo16(w[e]) * (s[2 * e] - dl[2 * e]) * a.scale, hi16(w[e]) * (s[2 * e + 1] - dl[2 * e + 1]) * a.scale);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (32 * b + 16 * t >= rows) continue;
+      const uint4 pw = make_uint4(w[4 * t], w[4 * t + 1], w[4 * t + 2], w[4 * t + 3]);
+      const uint4 dw = make_uint4(d[4 * t], d[4 * t + 1], d[4 * t + 2], d[4 * t + 3]);
+#pragma unroll
+      for (int ob = 0; ob < OB; ++ob) {
+        dv[ob] = mfma_bf16(frag_cols<KS>(Os, 32 * b + 16 * t, 32 * ob, lane), pw, dv[ob]);
+        dk[ob] = mfma_bf16(frag_cols<KS>(Qs, 32 * b + 16 * t, 32 * ob, lane), dw, dk[ob]);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) p[v] = np[v];
+  }
+  if (k < NT) {
+    uint16_t* dst = a.out + ((int64_t)sample * NT + k) * tok + head * DH;
+#pragma unroll
+    for (int ob = 0; ob < OB; ++ob) {
+      store_cols<KS>(dst + a.D, ob, hi, dk[ob]);
+      store_cols<KS>(dst + 2 * a.D, ob, hi, dv[ob]);
+    }
+  }
+}
+
+constexpr size_t ATTN_LDS = 160 * 1024;
+size_t attn_lds(int NT, int dh) {
+  const size_t pitch = dh == 64 ? dh : dh + 8;
+  // the transposing reads of a head whose width is an odd multiple of 16 run 16 columns past the last row
+  return 2 * (size_t)((NT + 15) & ~15) * pitch * 2 + 64;
+}
+
+template <typename K>
+hipError_t launch_attn(K kernel, const AttnArgs& a, int batch, size_t lds, hipStream_t stream) {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)batch * (unsigned)a.blocks), dim3(256), lds, stream, a);
+  return hipGetLastError();
+}
+template <int KS>
+hipError_t launch_attn_ks(const AttnArgs& a, int pass, int batch, size_t lds, hipStream_t stream) {
+  if (pass == 1) return launch_attn(&attn_bwd_dq_kernel<KS>, a, batch, lds, stream);
+  if (pass == 2) return launch_attn(&attn_bwd_dkv_kernel<KS>, a, batch, lds, stream);
+  if (a.NT <= 64) return launch_attn(&attn_fwd_kernel<KS, 2>, a, batch, lds, stream);
+  if (a.NT <= 128) return launch_attn(&attn_fwd_kernel<KS, 4>, a, batch, lds, stream);
+  if (a.NT <= 256) return launch_attn(&attn_fwd_kernel<KS, 8>, a, batch, lds, stream);
+  return launch_attn(&attn_fwd_kernel<KS, 0>, a, batch, lds, stream);
+}
+hipError_t launch_attn_pass(const AttnArgs& a, int dh, int pass, int batch, hipStream_t stream) {
+  if (batch <= 0 || batch > 65535) return hipErrorInvalidValue;
+  const size_t lds = attn_lds(a.NT, dh);
+  switch (dh / 16) {
+    case 1: return launch_attn_ks<1>(a, pass, batch, lds, stream);
+    case 2: return launch_attn_ks<2>(a, pass, batch, lds, stream);
+    case 3: return launch_attn_ks<3>(a, pass, batch, lds, stream);
+    case 4: return launch_attn_ks<4>(a, pass, batch, lds, stream);
+    default: return launch_attn_ks<5>(a, pass, batch, lds, stream);
+  }
+}
+bool aligned(const void* p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; }
+AttnArgs attn_args(const void* qkv, const void* P, int B, int NT, int D, int heads) {
+  AttnArgs a;
+  a.qkv = static_cast<const uint16_t*>(qkv);
+  a.P = static_cast<uint16_t*>(const_cast<void*>(P));
+  a.dout = nullptr; a.out = nullptr; a.delta = nullptr;
+  a.NT = NT; a.D = D; a.heads = heads;
+  a.blocks = (NT + 127) / 128;
+  a.vec = NT % 4 == 0 && aligned(P, 8);
+  a.dvec = 0;
+  a.scale = 1.0f / sqrtf((float)(D / heads));
+  return a;
+}
+
+}  // namespace
+
+// Heads whose width is a whole number of 16-wide reduction steps up to 80 (the accumulators of a wider one leave a
+// single workgroup per CU), two tiles of all tokens in LDS; the launches below also want aligned rows.
+bool attention_fused(int NT, int D, int heads, int dtype) {
+  if (dtype != DT_BF16 || heads <= 0 || NT <= 0 || D % heads) return false;
+  const int dh = D / heads;
+  return dh % 16 == 0 && dh <= 80 && attn_lds(NT, dh) <= ATTN_LDS;
+}
+bool attention_fused_fwd_ok(const void* qkv, const void* out, int NT, int D, int heads, int dtype) {
+  return attention_fused(NT, D, heads, dtype) && aligned(qkv, 16) && aligned(out, 8);
+}
+bool attention_fused_bwd_ok(const void* qkv, const void* dout, const void* dqkv, int NT, int D, int heads, int dtype) {
+  return attention_fused(NT, D, heads, dtype) && aligned(qkv, 16) && aligned(dout, 16) && aligned(dqkv, 8);
+}
+
+hipError_t launch_attention_fused_fwd(const void* qkv, void* P, void* out, int B, int NT, int D, int heads, hipStream_t stream) {
+  AttnArgs a = attn_args(qkv, P, B, NT, D, heads);
+  a.out = static_cast<uint16_t*>(out);
+  return launch_attn_pass(a, D / heads, 0, B * heads, stream);
+}
+hipError_t launch_attention_fused_bwd(const void* qkv, const void* P, const void* dout, void* dqkv, float* delta, int B, int NT, int D, int heads,
+                                      hipStream_t stream) {
+  AttnArgs a = attn_args(qkv, P, B, NT, D, heads);
+  a.dout = static_cast<const uint16_t*>(dout);
+  a.out = static_cast<uint16_t*>(dqkv);
+  a.delta = delta;
+  a.dvec = NT % 4 == 0 && aligned(delta, 16);
+  hipError_t e = launch_attn_pass(a, D / heads, 1, B * heads, stream);
+  return e != hipSuccess ? e : launch_attn_pass(a, D / heads, 2, B * heads, stream);
+}
+
+}  // namespace cdp
