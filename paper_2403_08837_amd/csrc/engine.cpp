@@ -902,7 +902,7 @@ int launch_level(cdp_ctx* c, std::vector<Item>& items) {
         bb.p[q] = LnBwdProb{grp[q]->p0, grp[q]->p1, grp[q]->p5, static_cast<const float*>(grp[q]->p3), grp[q]->p2,
                             static_cast<float*>(grp[q]->p4), static_cast<float*>(grp[q]->p6), static_cast<float*>(grp[q]->p7)};
       HIP_TRY(c, launch_layernorm_bwd_batch(bb, first.i[0], first.i[1], dt, c->stream));
-      c->stats.kernel_launches += 3;
+      c->stats.kernel_launches += 2;
     }
     for (Item* it : grp) it->done = true;
   }
@@ -939,7 +939,7 @@ int launch_level(cdp_ctx* c, std::vector<Item>& items) {
       case IT_LN_B:
         HIP_TRY(c, launch_layernorm_bwd(it.p0, it.p1, it.p5, static_cast<const float*>(it.p3), it.p2, static_cast<float*>(it.p4),
                                         static_cast<float*>(it.p6), static_cast<float*>(it.p7), it.i[0], it.i[1], dt, c->stream));
-        c->stats.kernel_launches += 2;  // three kernels
+        c->stats.kernel_launches += layernorm_batchable(it.p0, it.p1, it.p5, it.p2, it.i[1], dt) ? 1 : 2;  // two kernels, or three
         break;
       case IT_GELU_F:
         HIP_TRY(c, launch_gelu_fwd(it.p0, it.p2, it.n0, dt, c->stream));

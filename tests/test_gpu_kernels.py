@@ -301,3 +301,30 @@ def test_attention_fused_edges(B, T, D, heads):
     """Edges of the fused kernels: token counts that end on 16 of a block of 32, one token past a step of 16, more than
     256 tokens (scores contracted twice), the last count that fits LDS and one past it (separate kernels)."""
     test_attention_kernels_match_oracle(wl.BF16, B, T, D, heads)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("rows,C", [(1, 8), (17, 1024), (33, 64), (4100, 520), (8200, 16)])
+def test_layernorm_whole_chunk_edges(dtype, rows, C):
+    """The one-pass backward: one row, the widest row, a wavefront without a row, several rows per wavefront."""
+    test_layernorm_kernels_match_oracle(dtype, rows, C)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+def test_gelu_over_the_whole_range(dtype):
+    """Tails, zeros and infinities: Phi of large negative arguments has to vanish, the derivative too."""
+    torch = _torch()
+    tdt = torch.bfloat16 if dtype == wl.BF16 else torch.float32
+    x = np.concatenate([np.linspace(-40.0, 40.0, 8003), [0.0, -0.0, 1e-30, -1e-30, 3e38, -3e38]])
+    dy = np.ones_like(x)
+    xr = _rnd(x, dtype)
+    xd, dyd = _dev(x, dtype), _dev(dy, dtype)
+    y, dx = torch.empty_like(xd), torch.empty_like(xd)
+    b.cdp_k_gelu(dtype, 0, xd.data_ptr(), 0, y.data_ptr(), x.size)
+    b.cdp_k_gelu(dtype, 1, xd.data_ptr(), dyd.data_ptr(), dx.data_ptr(), x.size)
+    torch.cuda.synchronize()
+    # half a unit in the last place of the stored type plus the fp32 error of Phi (2e-7) times |x|
+    ulp = 2.0 ** -8 if dtype == wl.BF16 else 2.0 ** -23
+    for got, ref in ((y, L.gelu_fwd(xr)), (dx, L.gelu_bwd(xr, dy))):
+        g = got.float().cpu().numpy().astype(np.float64)
+        assert (np.abs(g - ref) <= ulp * np.abs(ref) + 4e-7 * np.maximum(1.0, np.minimum(np.abs(xr), 10.0))).all()
