@@ -15,6 +15,7 @@
 //     produces d gamma and d beta.
 #include <algorithm>
 
+#include "conv_tile.h"
 #include "elem.h"
 #include "kernels.h"
 #include "mfma_frag.h"
@@ -28,10 +29,10 @@ constexpr int XCD_RUN = 8;
 
 // ---------------------------------------------------------------------------------
 // forward / data gradient: 128 x BN tile, waves 2 x 2, reduction slab BK (a divisor of the
-// channel count).  The epilogue goes through LDS so that results, residuals and masks move
-// as 16-byte vectors along the channel dimension.
+// channel count).  Results, residuals and masks move as 16-byte vectors along the
+// channel dimension (conv_epilogue).
 template <typename T, int BM, int BN, int BK, bool DB>
-__global__ __launch_bounds__(256) void conv_gemm_kernel(const GemmBatch batch) {
+__global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gemm_kernel(const GemmBatch batch) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC, LDP = BK + VEC;
   constexpr int WTM = BM / 2, MI = WTM / 32;   // wave tile WTM x WTN
@@ -39,8 +40,7 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(const GemmBatch batch) {
   constexpr int NA = BM * CPR / 256;           // A chunks per thread
   constexpr int NB = BN * CPR / 256;           // B chunks per thread
   constexpr int WTN = BN / 2, NI = WTN / 32;
-  constexpr int SP = WTN + 4;                  // pitch (floats) of a wave's 32-row staging area
-  // one or two (DB) operand buffers; the epilogue staging reuses the space.
+  // one or two (DB) operand buffers; the staging areas of the epilogue reuse the space.
   // Size: conv_gemm_lds_bytes<T, BM, BN, BK, DB>().
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int BUF = (BM + BN) * LDP;  // elements per operand buffer
@@ -78,28 +78,7 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(const GemmBatch batch) {
         abase[i] = r * P.lda;
         amask[i] = 1u;
       } else {
-        const int b = r / (g.OH * g.OW);
-        const int rem = r - b * (g.OH * g.OW);
-        const int oh = rem / g.OW, ow = rem - oh * g.OW;
-        if (mode == OP_CONV_FWD) {
-          const int ih0 = oh * g.stride - g.pad, iw0 = ow * g.stride - g.pad;
-          abase[i] = ((b * g.H + ih0) * g.W + iw0) * g.C;
-          // taps inside the image: the columns kw with 0 <= iw0 + kw < W, for every row kh with 0 <= ih0 + kh < H
-          const int kw_lo = max(0, -iw0), kw_hi = min(g.KW, g.W - iw0);
-          const unsigned cols = kw_hi > kw_lo ? ((1u << kw_hi) - 1u) & ~((1u << kw_lo) - 1u) : 0u;
-          for (int kh = max(0, -ih0); kh < min(g.KH, g.H - ih0); ++kh) amask[i] |= cols << (kh * g.KW);
-        } else {  // OP_CONV_DGRAD: (oh, ow) is an input position, the gathered tensor is dy
-          const int qh = (oh + g.pad) / g.stride, eh = (oh + g.pad) - qh * g.stride;
-          const int qw = (ow + g.pad) / g.stride, ew = (ow + g.pad) - qw * g.stride;
-          abase[i] = ((b * g.H + qh) * g.W + qw) * g.C;
-          for (int kh = 0; kh < g.KH; ++kh)
-            for (int kw = 0; kw < g.KW; ++kw) {
-              const int uh = kh / g.stride, uw = kw / g.stride;
-              if (kh - uh * g.stride == eh && kw - uw * g.stride == ew && qh - uh >= 0 && qh - uh < g.H && qw - uw >= 0 &&
-                  qw - uw < g.W)
-                amask[i] |= 1u << (kh * g.KW + kw);
-            }
-        }
+        conv_row(g, mode, r, abase[i], amask[i]);
       }
     }
   }
@@ -168,7 +147,7 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(const GemmBatch batch) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = mfma_bf16(a[i], b[j], acc[i][j]);
+          for (int j = 0; j < NI; ++j) acc[i][j] = mfma_bf16(b[j], a[i], acc[i][j]);  // transposed: see conv_epilogue
       } else {
         float a[MI], b[NI];
 #pragma unroll
@@ -178,7 +157,7 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(const GemmBatch batch) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j], a[i], acc[i][j], 0, 0, 0);
       }
     }
   };
@@ -212,32 +191,6 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(const GemmBatch batch) {
       if (it + 1 < nslab) fetch(kbeg + (it + 1) * BK);
       contract(As0);
     }
-  }
-
-  // The epilogue's own operand (forward: the residual, data gradient: the ReLU mask) for all of the tile's
-  // staging passes is requested here in one go, into the registers the operand prefetch no longer needs: its
-  // round trip to memory overlaps the staging of the first pass instead of being paid once per pass (what
-  // counts for the short reductions of the 1x1 layers, whose tiles are a chain of memory latencies).
-  constexpr int CPS = WTN / VEC;             // chunks per staged row of the epilogue
-  constexpr int NCH = 32 * CPS / 64;         // chunks per lane and pass
-  uint4 pa[MI][NCH];
-  float bias[VEC];  // forward: the bias of this lane's columns (the same columns in every pass and chunk: CPS divides 64)
-  static_assert(64 % CPS == 0, "a lane keeps its columns from chunk to chunk");
-  if (P.epi == EPI_FWD && P.aux0) {
-    const int c = col0 + wn * WTN + (lane % CPS) * VEC;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) bias[e] = c < P.N ? static_cast<const float*>(P.aux0)[c + e] : 0.f;
-  }
-  if (P.aux1) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int t = 0; t < NCH; ++t) {
-        const int q = lane + 64 * t;
-        const int r = row0 + wm * WTM + i * 32 + q / CPS, c = col0 + wn * WTN + (q % CPS) * VEC;
-        pa[i][t] = (r < P.M && c < P.N) ? *reinterpret_cast<const uint4*>(static_cast<const T*>(P.aux1) + (int64_t)r * P.ldo + c)
-                                        : make_uint4(0, 0, 0, 0);
-      }
   }
 
   if (SPLIT && ks > 1) {
@@ -296,67 +249,8 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(const GemmBatch batch) {
     }
   }
 
-  // ---- epilogue: 32 rows of the wave tile at a time through LDS (fp32), then 16-byte rows
-  const int flags = P.flags;
-  const bool fwd = P.epi == EPI_FWD;
-  float* stage = reinterpret_cast<float*>(smem) + wave * (32 * SP);
-  T* outp = static_cast<T*>(P.out);
-#pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    __syncthreads();  // operand tiles (first pass) or the previous staging pass are consumed
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) stage[((v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)) * SP + j * 32 + (lane & 31)] = acc[i][j][v];
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NCH; ++t) {
-      const int q = lane + 64 * t;
-      const int sr = q / CPS, sc = (q % CPS) * VEC;
-      const int r = row0 + wm * WTM + i * 32 + sr, c = col0 + wn * WTN + sc;
-      if (r >= P.M || c >= P.N) continue;  // N is a multiple of VEC on this path
-      const int64_t o = (int64_t)r * P.ldo + c;
-      float val[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) val[e] = stage[sr * SP + sc + e];
-      Chunk16<T> x0, x1, x2, res;
-      if (fwd) {
-        if (P.aux0) {
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) val[e] += bias[e];
-        }
-        if (P.aux1) {
-          x1.v = pa[i][t];
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) val[e] += E::to_f32(x1.e[e]);
-        }
-        if (flags & GF_RELU) {
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) val[e] = fmaxf(val[e], 0.f);
-        }
-      } else {
-        if (P.aux0) {
-          x0.v = *reinterpret_cast<const uint4*>(static_cast<const T*>(P.aux0) + o);
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) val[e] += E::to_f32(x0.e[e]);
-        }
-        if (flags & GF_ACCUM) {
-          x2.v = *reinterpret_cast<const uint4*>(outp + o);
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) val[e] += E::to_f32(x2.e[e]);
-        }
-        if (P.aux1) {
-          x1.v = pa[i][t];
-#pragma unroll
-          for (int e = 0; e < VEC; ++e)
-            if (!(E::to_f32(x1.e[e]) > 0.f)) val[e] = 0.f;
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) res.e[e] = E::from_f32(val[e]);
-      *reinterpret_cast<uint4*>(outp + o) = res.v;
-    }
-  }
+  __syncthreads();  // the operand tiles are consumed
+  conv_epilogue_rows<T, MI, NI>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane, reinterpret_cast<float*>(smem) + wave * conv_stage_floats(NI));
 }
 
 // ---------------------------------------------------------------------------------
@@ -860,8 +754,7 @@ bool conv_fast_eligible(const GemmProb& p, int dtype) {
 
 template <typename T, int BM, int BN, int BK, bool DB>
 constexpr int conv_gemm_lds_bytes() {
-  constexpr int oper = (DB ? 2 : 1) * (BM + BN) * (BK + 16 / (int)sizeof(T)) * (int)sizeof(T);
-  constexpr int stage = 4 * 32 * (BN / 2 + 4) * 4;
+  constexpr int oper = (DB ? 2 : 1) * (BM + BN) * (BK + 16 / (int)sizeof(T)) * (int)sizeof(T), stage = 4 * conv_stage_floats(BN / 64) * 4;
   return oper > stage ? oper : stage;
 }
 
@@ -905,12 +798,14 @@ void conv_gemm_tile(const GemmProb* p, int n, int* bm, int* bn) {
   }
 }
 
+// (bf16 launches short of workgroups run on the direct-to-LDS tiles instead, whatever tile was asked for)
 hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
   if (b.n > GEMM_MAX_PROBS) return hipErrorInvalidValue;
   if ((bm != 64 && bm != 128) || (bn != 64 && bn != 128)) return hipErrorInvalidValue;
   const int bk = dtype == DT_BF16 ? 32 : 16;
   int total = 0;
+  if (const int dl = conv_dl_tile(b.p, b.n, dtype)) return launch_conv_dl(b, dtype, dl, stream);
   bool deep = true;  // every problem allows the double-depth slab
   for (int i = 0; i < b.n; ++i) {
     GemmProb& p = b.p[i];

@@ -1,0 +1,191 @@
+// What the forward / data-gradient kernels of conv_kernels.hip and conv256_kernels.hip share: the taps of a tile row and
+// the epilogue.
+#pragma once
+#include "elem.h"
+#include "kernels.h"
+
+namespace cdp {
+
+// Address base (elements) and valid taps (bit kh * KW + kw) of output position r of the gathered operand.  The valid taps are
+// the columns that are inside for every row that is, so rows and columns are looked at apart: tap by tap, with a division
+// each, the nine taps of a 3x3 data gradient took 2 us per tile.
+__device__ __forceinline__ void conv_row(const ConvGeom& g, int mode, int r, int& base, unsigned& mask) {
+  const int b = r / (g.OH * g.OW);
+  const int rem = r - b * (g.OH * g.OW);
+  const int oh = rem / g.OW, ow = rem - oh * g.OW;
+  mask = 0;
+  if (mode == OP_CONV_FWD) {
+    const int ih0 = oh * g.stride - g.pad, iw0 = ow * g.stride - g.pad;
+    base = ((b * g.H + ih0) * g.W + iw0) * g.C;
+    const int kw_lo = max(0, -iw0), kw_hi = min(g.KW, g.W - iw0);
+    const unsigned cols = kw_hi > kw_lo ? ((1u << kw_hi) - 1u) & ~((1u << kw_lo) - 1u) : 0u;
+    for (int kh = max(0, -ih0); kh < min(g.KH, g.H - ih0); ++kh) mask |= cols << (kh * g.KW);
+  } else {  // OP_CONV_DGRAD: (oh, ow) is an input position, the gathered tensor is dy
+    const int qh = (oh + g.pad) / g.stride, eh = (oh + g.pad) - qh * g.stride;
+    const int qw = (ow + g.pad) / g.stride, ew = (ow + g.pad) - qw * g.stride;
+    base = ((b * g.H + qh) * g.W + qw) * g.C;
+    unsigned cols = 0;  // taps on the stride lattice whose source lies inside dy
+    for (int kw = 0; kw < g.KW; ++kw) {
+      const int uw = kw / g.stride;
+      if (kw - uw * g.stride == ew && (unsigned)(qw - uw) < (unsigned)g.W) cols |= 1u << kw;
+    }
+    for (int kh = 0; kh < g.KH; ++kh) {
+      const int uh = kh / g.stride;
+      if (kh - uh * g.stride == eh && (unsigned)(qh - uh) < (unsigned)g.H) mask |= cols << (kh * g.KW);
+    }
+  }
+}
+
+// Arithmetic of one 16-byte piece of the result: forward act(acc + bias + residual), data gradient mask(acc + addend (+ old)).
+// x1: the piece's residual / mask.
+template <typename T>
+__device__ __forceinline__ void conv_finish(const GemmProb& P, int64_t o, float* val, const float* bias, uint4 x1v) {
+  using E = Elem<T>;
+  constexpr int VEC = E::VEC;
+  T* outp = static_cast<T*>(P.out);
+  Chunk16<T> x0, x1, x2, res;
+  x1.v = x1v;
+  if (P.epi == EPI_FWD) {
+    if (P.aux0) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) val[e] += bias[e];
+    }
+    if (P.aux1) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) val[e] += E::to_f32(x1.e[e]);
+    }
+    if (P.flags & GF_RELU) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) val[e] = fmaxf(val[e], 0.f);
+    }
+  } else {
+    if (P.aux0) {
+      x0.v = *reinterpret_cast<const uint4*>(static_cast<const T*>(P.aux0) + o);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) val[e] += E::to_f32(x0.e[e]);
+    }
+    if (P.flags & GF_ACCUM) {
+      x2.v = *reinterpret_cast<const uint4*>(outp + o);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) val[e] += E::to_f32(x2.e[e]);
+    }
+    if (P.aux1) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        if (!(E::to_f32(x1.e[e]) > 0.f)) val[e] = 0.f;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) res.e[e] = E::from_f32(val[e]);
+  *reinterpret_cast<uint4*>(outp + o) = res.v;
+}
+
+// Epilogues of a wave tile of MI x NI blocks of 32 x 32.  The blocks are contracted TRANSPOSED (the weight rows are the row
+// operand): a lane holds one tile row (its lane % 32) and, per group of four accumulator registers, four neighbouring
+// columns of it.
+//
+// Out of the registers: four columns are 16 bytes of an fp32 result; for bf16 one exchange between the lane halves makes
+// eight of them.  No LDS traffic and no barrier, but an instruction touches 32 rows, which the address path of the CU
+// takes at less than half the rate of whole rows.
+template <typename T, int MI, int NI>
+__device__ __forceinline__ void conv_epilogue(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
+  constexpr int VEC = Elem<T>::VEC, NS = 32 * NI / (2 * VEC);  // pieces of 2 VEC columns, VEC per lane half
+  const int l31 = lane & 31, hi = lane >> 5;
+  const T* aux1 = static_cast<const T*>(P.aux1);
+  auto column = [&](int s) { return col0 + 2 * VEC * s + VEC * hi; };
+  auto row = [&](int i) { return row0 + 32 * i + l31; };
+  // The residual / mask of the whole tile is requested before the first store (a store may alias the next load for all
+  // the compiler knows), where it fits the registers that the operand fragments no longer need.
+  constexpr bool AHEAD = MI * NS <= 8;
+  uint4 pa[AHEAD ? MI : 1][AHEAD ? NS : 1];
+  if (AHEAD && aux1) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        pa[AHEAD ? i : 0][AHEAD ? s : 0] = row(i) < P.M && column(s) < P.N ? *reinterpret_cast<const uint4*>(aux1 + (int64_t)row(i) * P.ldo + column(s))
+                                                                          : make_uint4(0, 0, 0, 0);
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int c = column(s);
+    float bias[VEC];
+    if (P.epi == EPI_FWD && P.aux0) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) bias[e] = c < P.N ? static_cast<const float*>(P.aux0)[c + e] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      float val[VEC];
+      if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][s >> 1][8 * (s & 1) + e]),
+                                                          __float_as_uint(acc[i][s >> 1][8 * (s & 1) + 4 + e]), false, false);
+          val[e] = __uint_as_float(x[0]);
+          val[VEC - 4 + e] = __uint_as_float(x[1]);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) val[e] = acc[i][s >> 2][4 * (s & 3) + e];
+      }
+      const int r = row(i);
+      if (r >= P.M || c >= P.N) continue;  // N is a multiple of VEC on these paths
+      const int64_t o = (int64_t)r * P.ldo + c;
+      conv_finish<T>(P, o, val, bias, !aux1 ? make_uint4(0, 0, 0, 0) : AHEAD ? pa[AHEAD ? i : 0][AHEAD ? s : 0] : *reinterpret_cast<const uint4*>(aux1 + o));
+    }
+  }
+}
+
+// Through LDS, 32 rows at a time and in fp32: every instruction then moves whole rows.  `stage`: conv_stage_floats(NI) floats of
+// the wave's own, which no wave reads any more.  The residual / mask of all passes is requested in one go before the
+// first, into the registers the operand prefetch no longer needs (once per pass it is a memory round trip per pass).
+constexpr int conv_stage_floats(int NI) { return 32 * (32 * NI + 4); }
+template <typename T, int MI, int NI>
+__device__ __forceinline__ void conv_epilogue_rows(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane, float* stage) {
+  constexpr int VEC = Elem<T>::VEC, SP = 32 * NI + 4;          // pitch: rows 4 banks apart
+  constexpr int CPS = 32 * NI / VEC, NCH = 32 * CPS / 64;      // chunks per staged row, per lane and pass
+  static_assert(64 % CPS == 0, "a lane keeps its columns from chunk to chunk");
+  const int l31 = lane & 31, hi = lane >> 5;
+  const int c = col0 + (lane % CPS) * VEC;
+  const T* aux1 = static_cast<const T*>(P.aux1);
+  uint4 pa[MI][NCH];
+  float bias[VEC];
+  if (P.epi == EPI_FWD && P.aux0) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) bias[e] = c < P.N ? static_cast<const float*>(P.aux0)[c + e] : 0.f;
+  }
+  if (aux1) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int t = 0; t < NCH; ++t) {
+        const int r = row0 + i * 32 + (lane + 64 * t) / CPS;
+        pa[i][t] = (r < P.M && c < P.N) ? *reinterpret_cast<const uint4*>(aux1 + (int64_t)r * P.ldo + c) : make_uint4(0, 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();  // the previous pass's reads are done
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(stage + l31 * SP + 32 * j + 8 * g + 4 * hi) = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int t = 0; t < NCH; ++t) {
+      const int sr = (lane + 64 * t) / CPS, r = row0 + i * 32 + sr;
+      if (r >= P.M || c >= P.N) continue;  // N is a multiple of VEC on these paths
+      float val[VEC];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) val[e] = stage[sr * SP + (lane % CPS) * VEC + e];
+      conv_finish<T>(P, (int64_t)r * P.ldo + c, val, bias, aux1 ? pa[i][t] : make_uint4(0, 0, 0, 0));
+    }
+  }
+}
+
+}  // namespace cdp

@@ -803,7 +803,7 @@ int launch_level(cdp_ctx* c, std::vector<Item>& items) {
         conv_gemm_tile(batch.p, batch.n, &bm, &bn);
         HIP_TRY(c, launch_conv_gemm(batch, c->plan.dtype, bm, bn, c->stream));
       }
-      else if (key == LC_CONV_256) HIP_TRY(c, launch_conv_gemm256(batch, c->plan.dtype, c->stream));
+      else if (key == LC_CONV_256) HIP_TRY(c, launch_conv_dl(batch, c->plan.dtype, DL_256x256, c->stream));
       else if (key == LC_CWGRAD_128) HIP_TRY(c, launch_conv_wgrad_mixed(batch, c->plan.dtype, c->stream));
       else HIP_TRY(c, launch_gemm_batch(batch, c->plan.dtype, (key - LC_GEN_FIRST) / 2, c->stream));
       if (timed) {

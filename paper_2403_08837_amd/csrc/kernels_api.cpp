@@ -57,7 +57,7 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
   ConvGeom& g = p.g;
   g.KH = ks; g.KW = ks; g.stride = stride; g.pad = pad;
   const bool force256 = which >= 3 && which <= 6;  // the direct-to-LDS tile regardless of the launch heuristic
-  const int forced_tile = which >= 5 ? 128 : 256;
+  const int forced_tile = which >= 5 ? DL_256x128 : DL_256x256;
   if (force256) which -= which >= 5 ? 5 : 3;
   if (which == 0) {
     p.M = B * Ho * Wo; p.N = Cout; p.K = ks * ks * Cin;
@@ -97,9 +97,9 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
     }
   } else if (force256) {
     if (!conv_gemm256_eligible(p, dtype)) return CDP_EINVAL;
-    return launch_conv_gemm256(b, dtype, st, forced_tile) == hipSuccess ? CDP_OK : CDP_EHIP;
+    return launch_conv_dl(b, dtype, forced_tile, st) == hipSuccess ? CDP_OK : CDP_EHIP;
   } else if (conv_fast_eligible(p, dtype)) {
-    if (conv_gemm256_wanted(&p, 1, dtype)) return launch_conv_gemm256(b, dtype, st) == hipSuccess ? CDP_OK : CDP_EHIP;
+    if (conv_gemm256_wanted(&p, 1, dtype)) return launch_conv_dl(b, dtype, DL_256x256, st) == hipSuccess ? CDP_OK : CDP_EHIP;
     int bm, bn;
     conv_gemm_tile(&p, 1, &bm, &bn);
     return launch_conv_gemm(b, dtype, bm, bn, st) == hipSuccess ? CDP_OK : CDP_EHIP;

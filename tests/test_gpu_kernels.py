@@ -328,3 +328,29 @@ def test_gelu_over_the_whole_range(dtype):
     for got, ref in ((y, L.gelu_fwd(xr)), (dx, L.gelu_bwd(xr, dy))):
         g = got.float().cpu().numpy().astype(np.float64)
         assert (np.abs(g - ref) <= ulp * np.abs(ref) + 4e-7 * np.maximum(1.0, np.minimum(np.abs(xr), 10.0))).all()
+
+
+def _conv_1x1_bf16(which, rows, cin, cout, seed=3):
+    """A 1x1 convolution over `rows` positions through cdp_k_conv against the fp64 product."""
+    torch = _torch()
+    red, out = (cin, cout) if which == 0 else (cout, cin)
+    a = wl.random_normal(seed, 1, rows * red).reshape(rows, red)
+    w = wl.random_normal(seed, 2, out * red).reshape(out, red) / np.sqrt(red)
+    ref = _rnd(a, wl.BF16) @ _rnd(w, wl.BF16).T
+    ad, wd = _dev(a, wl.BF16), _dev(w, wl.BF16)
+    got = torch.full((rows, out), float("nan"), dtype=torch.bfloat16, device="cuda")
+    b.cdp_k_conv(wl.BF16, which, ad.data_ptr(), wd.data_ptr(), got.data_ptr(), 1, 1, rows, cin, cout, 1, 1, 0)
+    torch.cuda.synchronize()
+    g = got.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(g).all()
+    assert np.abs(g - ref).max() / np.abs(ref).max() <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("rows,out", [(4100, 1032), (19300, 120), (700, 200), (190, 72), (513, 40)])
+@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 6, 7, 16, 17, 18])
+def test_conv_short_of_workgroups(rows, out, slabs):
+    """Every tile of the launches that do not fill the chip (256 x 128, 64 x 128, 64 x 64 with slabs of 64 and of 32), ragged
+    in both directions, with every number of slabs that the unrolled pipeline can end on; forward and data gradient."""
+    for red in ((64 * slabs, 32 * slabs) if slabs <= 7 else (64 * slabs,)):
+        _conv_1x1_bf16(0, rows, red, out)
+        _conv_1x1_bf16(1, rows, out, red)
