@@ -14,6 +14,7 @@
 //     into an LDS table.  wgrad_reduce_kernel folds the ranges into G (scaled by gamma) and
 //     produces d gamma and d beta.
 #include <algorithm>
+#include <cmath>
 
 #include "conv_tile.h"
 #include "elem.h"
@@ -548,7 +549,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WReduceBatch ba
     for (int e = 0; e < 4; ++e) {
       gold[e] = wpl[e] = 0.f;
       if (c + e < P.Ncol) {
-        gold[e] = P.G[row + c + e];
+        if (!P.overwrite) gold[e] = P.G[row + c + e];
         if (P.wplain) wpl[e] = E::to_f32(static_cast<const T*>(P.wplain)[row + c + e]);
       }
     }
@@ -634,7 +635,7 @@ __global__ __launch_bounds__(256) void wgrad_fold_rows_kernel(const WReduceBatch
       float4 v[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] = q < splits ? *reinterpret_cast<const float4*>(src + q * stride) : make_float4(0.f, 0.f, 0.f, 0.f);
-      const float4 gold = *reinterpret_cast<const float4*>(P.G + row + c);
+      const float4 gold = P.overwrite ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4*>(P.G + row + c);
       float wpl[4] = {0.f, 0.f, 0.f, 0.f};
       if (wplain) {
 #pragma unroll
@@ -729,6 +730,33 @@ int conv_wgrad_splits(const GemmProb& p, int dtype, int wanted) {
   const int tiles = ((p.M + to - 1) / to) * ((p.N + 127) / 128);
   const int min_splits = std::min((nslab + WG_MAX_SLABS - 1) / WG_MAX_SLABS, (1024 + tiles - 1) / tiles);
   return std::max(1, std::min(nslab, std::max(wanted, min_splits)));
+}
+
+// Ranges of a problem launched on its own, at most `room` of them: the cheapest by what the launch costs.  Fitted to
+// measured launches of 14 shapes with 1 to 256 ranges each (5 to 144 tiles, 13 to 1568 slabs), which it follows within
+// about 15 %:
+//   bf16: a workgroup takes 1.6 us per slab alone on its CU (a chain of latencies), 1.75 us beside one other and 2.2 us
+//         beside two, which fill it; fp32: 3.3 us, matrix cores and all, so a second workgroup on a CU doubles it;
+//   every range writes its partial matrix once and the fold reads it once, at about 3.5 TB/s together.
+// (3072 x 768 over 6272 rows 86 -> 72 us against three ranges or one per 16 slabs, 128 x 1152 over 25088 37 -> 35,
+// 256 x 1024 over 6272 32 -> 27, fp32 128 x 576 over 800 37 -> 26)
+int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room) {
+  const bool bf16 = dtype == DT_BF16;
+  const int nslab = (p.K + wg_slab(dtype) - 1) / wg_slab(dtype), to = p.M >= 128 ? 128 : 64;
+  const double tiles = (double)((p.M + to - 1) / to) * ((p.N + 127) / 128);
+  const double range_us = 2.0 * 4.0 * p.M * (double)p.N / 3.5e6;
+  int best = 1;
+  double best_us = 1e30;
+  for (int len = 1; len <= nslab; len += 1 + len / 8) {  // slabs per range
+    const int s = (nslab + len - 1) / len;
+    if (s > std::max(1, room)) continue;
+    const double wgs = tiles * s, per_cu = std::ceil(wgs / 256.0);
+    const double rounds = bf16 ? std::ceil(per_cu / 3.0) : 1.0;
+    const double slab_us = bf16 ? (per_cu >= 3 ? 2.2 : per_cu >= 2 ? 1.75 : 1.6) : 3.3 * per_cu;
+    const double us = rounds * len * slab_us + s * range_us;
+    if (us < best_us) { best_us = us; best = s; }
+  }
+  return best;
 }
 
 // ---------------------------------------------------------------------------------

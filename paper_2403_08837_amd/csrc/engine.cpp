@@ -603,7 +603,7 @@ int build_backward(cdp_ctx* c, int i, int j, int version, Program* prog, bool fi
         rd.r.G = G + o.w_off; rd.r.Ggamma = o.has_gamma ? G + o.g_off : nullptr; rd.r.Gbeta = o.b_off >= 0 ? G + o.b_off : nullptr;
         rd.r.gamma = static_cast<const float*>(w.g.aux0); rd.r.wplain = w.g.aux1;
         rd.r.Cout = o.Cout; rd.r.Ncol = (int)o.K(); rd.r.splits = w.g.splits;
-        rd.r.gpart = nullptr; rd.r.cnt = nullptr;
+        rd.r.gpart = nullptr; rd.r.cnt = nullptr; rd.r.overwrite = 0;
         const int chunks = ((int)o.K() + 127) / 128;
         if (o.has_gamma && chunks > 1) {  // shares of d gamma per 128-column chunk, added in chunk order by the fold
           Block gp;

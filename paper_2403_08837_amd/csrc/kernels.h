@@ -180,6 +180,7 @@ hipError_t launch_conv_dl(GemmBatch& batch, int dtype, int tile, hipStream_t str
 // ceil(K / conv_wgrad_slab), conv_wgrad_splits gives what a problem launched on its own wants),
 // launch_wgrad_reduce folds them into the accumulators.
 int conv_wgrad_splits(const GemmProb& p, int dtype, int wanted);
+int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room);  // the same for a single call, at most `room` ranges
 int conv_wgrad_slab(int dtype);  // output positions per reduction slab; a problem takes 1 .. ceil(K / slab) ranges
 hipError_t launch_conv_wgrad(GemmBatch& batch, int dtype, bool wide, hipStream_t stream);
 // the same with the tile height chosen per problem (128 rows for matrices of 128 rows and more, 64 below)
@@ -197,6 +198,7 @@ struct WReduceProb {
   // row, fixed order); without them (or with one chunk) the shares meet in a float atomic add / a plain add.
   float* gpart;
   unsigned int* cnt;
+  int overwrite;  // G = fold instead of G += fold (single calls; G need not be cleared before)
 };
 constexpr int FOLD_COUNTERS = 1 << 16;  // counters the engine keeps for the fold launches
 constexpr int WREDUCE_MAX_PROBS = 32;

@@ -1,6 +1,7 @@
 // C ABI of the kernel-level entry points (include/cdp_kernels.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 
 #include "../../include/cdp.h"
@@ -80,8 +81,10 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
   hipStream_t st = static_cast<hipStream_t>(stream);
   // same kernel choice as the engine: the fast implicit-GEMM paths where the shape allows
   if (which == 2) {
-    const int splits = conv_wgrad_splits(p, dtype, 3);
-    if (conv_fast_eligible(p, dtype) && workspace && workspace_bytes >= (size_t)splits * p.M * p.N * 4) {
+    const size_t range_bytes = (size_t)p.M * p.N * 4;
+    const int room = (int)std::min<size_t>((size_t)p.K / 512 + 4, workspace ? workspace_bytes / range_bytes : 0);
+    if (conv_fast_eligible(p, dtype) && room >= 1) {
+      const int splits = conv_wgrad_splits_alone(p, dtype, room);
       // two phases as in the engine: partial sums per reduction range, then the fold
       WReduceBatch rb;
       memset(&rb, 0, sizeof(rb));
@@ -89,9 +92,9 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
       rb.p[0].part = static_cast<const float*>(workspace);
       rb.p[0].G = static_cast<float*>(out);
       rb.p[0].Cout = p.M; rb.p[0].Ncol = p.N; rb.p[0].splits = splits;
+      rb.p[0].overwrite = 1;
       p.out = workspace;
       p.splits = splits;
-      if (launch_fill_f32(static_cast<float*>(out), (int64_t)p.M * p.N, 0.f, st) != hipSuccess) return CDP_EHIP;
       if (launch_conv_wgrad(b, dtype, p.M >= 128, st) != hipSuccess) return CDP_EHIP;
       return launch_wgrad_reduce(rb, dtype, st) == hipSuccess ? CDP_OK : CDP_EHIP;
     }

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -77,22 +78,24 @@ extern "C" int cdp_k_conv_wgrad_static(int dtype, const void* dy, const void* x,
   if (need > SCRATCH_BYTES)
     return fail(CDP_ENOMEM, "cdp_k_conv_wgrad_static: needs " + std::to_string(need) + " bytes of partial sums, the static scratch holds " +
                                 std::to_string(SCRATCH_BYTES) + "; use cdp_k_conv with a workspace");
+  const int room = (int)std::min<size_t>((size_t)p.K / 512 + 4, SCRATCH_BYTES / ((size_t)p.M * (size_t)p.N * 4));
+  const int ranges = conv_wgrad_splits_alone(p, dtype, room);
   void* ws = nullptr;
   int rc = scratch_ptr(&ws);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // every range writes its whole partial tile (an empty range writes zeros), so nothing in the scratch
-  // has to start at zero; the output does, because the fold adds into it
+  // has to start at zero, and the fold overwrites the output
   WReduceBatch rb;
   memset(&rb, 0, sizeof(rb));
   rb.n = 1;
   rb.p[0].part = static_cast<const float*>(ws);
   rb.p[0].G = dw;
-  rb.p[0].Cout = p.M; rb.p[0].Ncol = p.N; rb.p[0].splits = splits;
+  rb.p[0].Cout = p.M; rb.p[0].Ncol = p.N; rb.p[0].splits = ranges;
+  rb.p[0].overwrite = 1;
   p.out = ws;
-  p.splits = splits;
-  hipError_t e = launch_fill_f32(dw, (int64_t)p.M * p.N, 0.f, st);
-  if (e == hipSuccess) e = launch_conv_wgrad(b, dtype, p.M >= 128, st);
+  p.splits = ranges;
+  hipError_t e = launch_conv_wgrad(b, dtype, p.M >= 128, st);
   if (e == hipSuccess) e = launch_wgrad_reduce(rb, dtype, st);
   if (e != hipSuccess) return fail(CDP_EHIP, std::string("cdp_k_conv_wgrad_static: ") + hipGetErrorString(e));
   return CDP_OK;
