@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "../../include/cdp.h"
+#include "host_copy.h"
 #include "kernels.h"
 #include "plan.h"
 
@@ -141,6 +142,7 @@ struct cdp_ctx {
   struct ProfRec { hipEvent_t a, b; double flops, bytes; };
   std::vector<ProfRec> prof;
   std::vector<hipEvent_t> event_pool;
+  HostReader reader;                          // cdp_get_weights
 
   void* ptr(int64_t off) const { return reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(arena) + (uintptr_t)off); }
   float* fptr(int64_t off) const { return static_cast<float*>(ptr(off)); }
@@ -1456,8 +1458,7 @@ int cdp_get_weights(cdp_ctx* c, int stage, int version, float* host, size_t cap,
   if (version < 0) version = ss.ver;
   if (c->dry) return fail(c, CDP_ESTATE, "no weights in a dry run");
   if (version == ss.ver) {
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipMemcpy(host, c->fptr(ss.master), (size_t)sp.n_params * 4, hipMemcpyDeviceToHost));
+    HIP_TRY(c, c->reader.read(host, c->fptr(ss.master), (size_t)sp.n_params * 4, c->stream));
     return CDP_OK;
   }
   if (version != ss.ver - 1 || ss.ring_ver[version & 1] != version) return fail(c, CDP_ESTATE, "that weight version is no longer in the ring");

@@ -1,0 +1,81 @@
+#include "host_copy.h"
+
+#include <algorithm>
+#include <cstring>
+#include <system_error>
+#include <thread>
+
+namespace cdp {
+
+HostReader::~HostReader() { release(); }
+
+void HostReader::release() {
+  for (hipEvent_t& e : event_)
+    if (e) { (void)hipEventDestroy(e); e = nullptr; }
+  if (pinned_) (void)hipHostFree(pinned_);
+  pinned_ = nullptr;
+}
+
+bool HostReader::prepare() {
+  if (pinned_) return true;
+  bool ok = hipHostMalloc(reinterpret_cast<void**>(&pinned_), THREADS * DEPTH * PIECE, hipHostMallocDefault) == hipSuccess;
+  for (hipEvent_t& e : event_) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();  // a plain copy does without
+    release();
+  }
+  return ok;
+}
+
+// Pieces thread, thread + THREADS, ... of the range.
+hipError_t HostReader::work(int thread, char* dst, const char* src, size_t bytes, hipStream_t stream) {
+  const size_t pieces = (bytes + PIECE - 1) / PIECE;
+  auto len = [&](size_t p) { return std::min(PIECE, bytes - p * PIECE); };
+  auto buffer = [&](size_t n) { return pinned_ + ((size_t)thread * DEPTH + n % DEPTH) * PIECE; };
+  auto request = [&](size_t n) -> hipError_t {  // the thread's n-th piece
+    const size_t p = thread + n * THREADS;
+    if (p >= pieces) return hipSuccess;
+    hipError_t e = hipMemcpyAsync(buffer(n), src + p * PIECE, len(p), hipMemcpyDeviceToHost, stream);
+    return e != hipSuccess ? e : hipEventRecord(event_[thread * DEPTH + n % DEPTH], stream);
+  };
+  hipError_t e = request(0);
+  for (size_t n = 0; e == hipSuccess && thread + n * THREADS < pieces; ++n) {
+    if ((e = request(n + 1)) != hipSuccess) break;
+    if ((e = hipEventSynchronize(event_[thread * DEPTH + n % DEPTH])) != hipSuccess) break;
+    const size_t p = thread + n * THREADS;
+    memcpy(dst + p * PIECE, buffer(n), len(p));
+  }
+  return e;
+}
+
+hipError_t HostReader::read(void* dst, const void* src, size_t bytes, hipStream_t stream) {
+  int device = 0;
+  if (bytes < WORTH || hipGetDevice(&device) != hipSuccess || !prepare()) {
+    hipError_t e = hipStreamSynchronize(stream);
+    return e != hipSuccess ? e : hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+  }
+  char* to = static_cast<char*>(dst);
+  const char* from = static_cast<const char*>(src);
+  std::thread helper[THREADS];
+  hipError_t result[THREADS];
+  int started = 1;
+  try {
+    for (; started < THREADS; ++started)
+      helper[started] = std::thread([this, started, device, to, from, bytes, stream, &result] {
+        hipError_t e = hipSetDevice(device);  // the current device is the thread's own
+        result[started] = e != hipSuccess ? e : work(started, to, from, bytes, stream);
+      });
+  } catch (const std::system_error&) {  // no more threads to be had: their pieces are this thread's too
+  }
+  result[0] = work(0, to, from, bytes, stream);
+  for (int t = started; t < THREADS; ++t) result[t] = work(t, to, from, bytes, stream);
+  hipError_t e = hipSuccess;
+  for (int t = 0; t < THREADS; ++t) {
+    if (helper[t].joinable()) helper[t].join();
+    if (e == hipSuccess) e = result[t];
+  }
+  if (e != hipSuccess) (void)hipStreamSynchronize(stream);  // nothing is left in flight into the pinned buffers
+  return e;
+}
+
+}  // namespace cdp
