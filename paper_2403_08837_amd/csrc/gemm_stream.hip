@@ -1,0 +1,149 @@
+// C[M][N] (fp32) = A B^T for one problem of few rows, both operands k-contiguous in whole 16-byte chunks: a Linear layer on a
+// small batch on its own.
+//
+// It streams B once (33 MB for 4096 x 4096 in bf16, 6.5 us at the rate of a large copy) and is otherwise a chain of
+// memory latencies, so what counts is how many CUs take part and how many bytes each has in flight.  The tiles of the
+// tick launch are 64 (or 32) columns wide, which suits the sixteen problems of a tick and leaves one problem on 64 CUs.
+// Here a workgroup owns 16 columns of up to 64 rows, and its eight wavefronts share the reduction: wavefront w takes the
+// 128-byte pieces w, w + 8, ... of every row, two pieces ahead.  A load covers 8 rows x 128 bytes and the fragments are read
+// back out of a staging block of the wavefront's own in LDS (no barrier); loaded in fragment layout, 16 rows x 64 bytes,
+// the address path of the CU bounds the kernel at 14 bytes per cycle (64 rows, 4096 x 4096: 20.3 us).  The partial tiles
+// meet in LDS and are added in wavefront order.
+// 64 rows, 4096 x 4096, bf16: 26.9 us on the tick launch's tiles, 12.4 us so; 32 rows 15.6 -> 8.3; fp32 97 -> 32 us.
+#include "elem.h"
+#include "kernels.h"
+
+namespace cdp {
+
+namespace {
+
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+
+struct StreamArgs {
+  const void* A;
+  const void* B;
+  float* C;
+  int M, N, K, lda, ldb;
+};
+
+constexpr int GS_WAVES = 8;
+
+// 64 bytes of k of 16 x 16 outputs: a lane holds one 16-byte chunk of row lane % 16 of either operand.
+template <typename T> __device__ __forceinline__ v4f_t stream_mfma(uint4 a, uint4 b, v4f_t c) {
+  if constexpr (sizeof(T) == 2) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf16_t, a), __builtin_bit_cast(v8bf16_t, b), c, 0, 0, 0);
+  } else {  // four steps of four k, in an order that both operands share
+    const float4 x = __builtin_bit_cast(float4, a), y = __builtin_bit_cast(float4, b);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.x, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, y.y, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, y.z, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, y.w, c, 0, 0, 0);
+  }
+}
+
+// MT: blocks of 16 rows.
+template <typename T, int MT>
+__global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const StreamArgs g) {
+  constexpr int VEC = Elem<T>::VEC, PIECE = 8 * VEC;   // elements of a 128-byte piece
+  constexpr int NL = 2 * MT + 2;                       // loads per piece: 8 rows x 128 bytes each, A's then B's
+  constexpr int PITCH = PIECE + VEC;                   // rows of a staged piece: 144 bytes
+  constexpr int STAGE = 8 * NL * PITCH * (int)sizeof(T), PART = MT * 16 * 17 * 4;
+  static_assert(PART <= STAGE, "the partial tile takes the place of the staged piece");
+  __shared__ __attribute__((aligned(16))) unsigned char smem[GS_WAVES * STAGE];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, q = lane >> 4;
+  const int col0 = blockIdx.x * 16, row0 = blockIdx.y * (16 * MT);
+  T* const st = reinterpret_cast<T*>(smem + wave * STAGE);
+  const int lr = lane >> 3, lk = (lane & 7) * VEC;
+  // rows and columns past the end repeat the last one: they only reach outputs that are not stored
+  const T* src[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j)
+    src[j] = j < 2 * MT ? static_cast<const T*>(g.A) + (int64_t)min(row0 + 8 * j + lr, g.M - 1) * g.lda + lk
+                        : static_cast<const T*>(g.B) + (int64_t)min(col0 + 8 * (j - 2 * MT) + lr, g.N - 1) * g.ldb + lk;
+  const int step = GS_WAVES * PIECE;
+  auto load = [&](uint4 (&r)[NL], int k) {
+    if (k + PIECE <= g.K) {
+#pragma unroll
+      for (int j = 0; j < NL; ++j) r[j] = *reinterpret_cast<const uint4*>(src[j] + k);
+    } else {  // past the last whole piece (K is whole chunks)
+#pragma unroll
+      for (int j = 0; j < NL; ++j) r[j] = k + lk < g.K ? *reinterpret_cast<const uint4*>(src[j] + k) : make_uint4(0, 0, 0, 0);
+    }
+  };
+  v4f_t acc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i] = v4f_t{0.f, 0.f, 0.f, 0.f};
+  // The staged piece is the wavefront's own, whose LDS instructions execute in order: no barrier.
+  auto product = [&](const uint4 (&r)[NL]) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) *reinterpret_cast<uint4*>(st + (8 * j + lr) * PITCH + lk) = r[j];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const T* f = st + l15 * PITCH + (4 * h + q) * VEC;
+      const uint4 b = *reinterpret_cast<const uint4*>(f + 16 * MT * PITCH);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) acc[i] = stream_mfma<T>(*reinterpret_cast<const uint4*>(f + 16 * i * PITCH), b, acc[i]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  uint4 r0[NL], r1[NL], r2[NL];
+  int k = wave * PIECE;
+  if (k < g.K) load(r0, k);
+  if (k + step < g.K) load(r1, k + step);
+  for (; k < g.K; k += 3 * step) {  // two pieces ahead
+    if (k + 2 * step < g.K) load(r2, k + 2 * step);
+    product(r0);
+    if (k + step >= g.K) break;
+    if (k + 3 * step < g.K) load(r0, k + 3 * step);
+    product(r1);
+    if (k + 2 * step >= g.K) break;
+    if (k + 4 * step < g.K) load(r1, k + 4 * step);
+    product(r2);
+  }
+  float (*part)[17] = reinterpret_cast<float (*)[17]>(smem + wave * STAGE);
+  // acc[i][v]: row 16 i + 4 q + v, column l15
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[16 * i + 4 * q + v][l15] = acc[i][v];
+  __syncthreads();
+  for (int e = threadIdx.x; e < MT * 256; e += 64 * GS_WAVES) {
+    const int r = e >> 4, c = e & 15;
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < GS_WAVES; ++w) s += reinterpret_cast<const float*>(smem + w * STAGE)[r * 17 + c];
+    if (row0 + r < g.M && col0 + c < g.N) g.C[(int64_t)(row0 + r) * g.N + col0 + c] = s;
+  }
+}
+
+template <typename T>
+void launch_stream(const StreamArgs& g, hipStream_t stream) {
+  const dim3 cols((g.N + 15) / 16, 1), block(64 * GS_WAVES);
+  if (g.M <= 16) hipLaunchKernelGGL((gemm_stream_kernel<T, 1>), cols, block, 0, stream, g);
+  else if (g.M <= 32) hipLaunchKernelGGL((gemm_stream_kernel<T, 2>), cols, block, 0, stream, g);
+  else hipLaunchKernelGGL((gemm_stream_kernel<T, 4>), dim3(cols.x, (g.M + 63) / 64), block, 0, stream, g);
+}
+
+}  // namespace
+
+// Up to two workgroups per CU: past that the wider tiles of the tick launch fill the chip too and read A less often (us, tick
+// launch / here: 64 rows bf16 8192 x 512 8.6 / 5.8, 16384 x 4096 30 / 42; 128 rows 4096 x 4096 27.5 / 22.5, 8192 x 512 9.0 / 10.4;
+// fp32 64 rows 4096 x 4096 97 / 32, 16384 x 4096 102 / 115).  Measured for 4 to 128 rows.
+bool gemm_stream_wanted(const void* A, const void* B, int M, int N, int K, int lda, int ldb, int dtype) {
+  const int vec = dtype == DT_BF16 ? 8 : 4;
+  if (K % vec || lda % vec || ldb % vec || ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15)) return false;
+  return M <= 128 && (int64_t)((N + 15) / 16) * (M <= 64 ? 1 : 2) <= 512;
+}
+
+hipError_t launch_gemm_stream(const void* A, const void* B, float* C, int M, int N, int K, int lda, int ldb, int dtype, hipStream_t stream) {
+  const StreamArgs g{A, B, C, M, N, K, lda, ldb};
+  if (dtype == DT_BF16) launch_stream<uint16_t>(g, stream);
+  else launch_stream<float>(g, stream);
+  return hipGetLastError();
+}
+
+}  // namespace cdp

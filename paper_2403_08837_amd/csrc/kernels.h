@@ -149,6 +149,11 @@ void tile_dims(int shape, int* bm, int* bn);
 // Fills tiles_n / tile_begin / total_tiles for the chosen tile shape and launches.
 hipError_t launch_gemm_batch(GemmBatch& batch, int dtype, int tile_shape, hipStream_t stream);
 
+// C = A B^T (fp32 result, ldc = N), both operands k-contiguous, for one problem of few rows (gemm_stream.hip); _wanted: it takes
+// the problem and is the faster way.
+bool gemm_stream_wanted(const void* A, const void* B, int M, int N, int K, int lda, int ldb, int dtype);
+hipError_t launch_gemm_stream(const void* A, const void* B, float* C, int M, int N, int K, int lda, int ldb, int dtype, hipStream_t stream);
+
 // HBM-streaming variants for Linear layers with a small batch (plain operands only):
 //   skinny: forward / data gradient, operands both k-contiguous; wide = 128-column tiles.
 //   dw:     weight gradient G (+)= dY^T X with A = dY (OP_PLAIN_R), B = X (OP_PLAIN_R),

@@ -37,6 +37,8 @@ int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void
     p.flags = 0;
     return launch_linear_tick(b, dtype, false, false, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
   }
+  if (tile_shape == TILE_COUNT + 2 && gemm_stream_wanted(A, B, M, N, K, lda, ldb, dtype))
+    return launch_gemm_stream(A, B, C, M, N, K, lda, ldb, dtype, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
   if (tile_shape >= TILE_COUNT)
     return launch_linear_tick(b, dtype, tile_shape == TILE_COUNT + 1, tile_shape == TILE_COUNT + 2, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
   return launch_gemm_batch(b, dtype, tile_shape, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;

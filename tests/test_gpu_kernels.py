@@ -73,6 +73,26 @@ def test_gemm_weight_gradient_tiles(dtype, M, N, K, lda, ldb):
     assert np.abs(got - ref).max() <= 2e-5 * np.sqrt(K) * max(1.0, np.abs(ref).max())
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("M", [1, 16, 17, 32, 33, 64, 65, 128, 129])
+def test_gemm_few_rows(dtype, M):
+    """The kernel for one problem of few rows: edges of its row blocks (129: the tick launch's tiles), ragged columns, and
+    reductions of less than one piece per wavefront up to several, whole and not."""
+    torch = _torch()
+    for N, K in ((1, 8), (40, 264), (17, 1032), (130, 1536), (4096, 24), (4099, 40), (8200, 64)):
+        A = wl.random_normal(1, 10 * M + K, M * K).reshape(M, K)
+        Bm = wl.random_normal(2, 10 * N + K, N * K).reshape(N, K)
+        ref = _rnd(A, dtype) @ _rnd(Bm, dtype).T
+        Ad, Bd = _dev(A, dtype), _dev(Bm, dtype)
+        Cd = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        b.cdp_k_gemm(dtype, 5, 1, 1, Ad.data_ptr(), Bd.data_ptr(), Cd.data_ptr(), M, N, K, K, K)
+        torch.cuda.synchronize()
+        got = Cd.cpu().numpy().astype(np.float64)
+        # products of exactly representable inputs, fp32 sums of K terms: as in test_gemm_all_layouts
+        assert np.isfinite(got).all()
+        assert np.abs(got - ref).max() <= 2e-5 * np.sqrt(K) * max(1.0, np.abs(ref).max()), (N, K)
+
+
 CONV_CASES = [
     # B, H, W, Cin, Cout, ks, stride, pad
     (2, 8, 8, 8, 16, 3, 1, 1),
