@@ -1,6 +1,6 @@
-// Implicit-GEMM convolution passes of a CDP tick on gfx950, for channel counts that are a
-// multiple of the reduction slab (bf16: 32, fp32: 16); other shapes (the 3-channel stem)
-// run on the generic kernel of gemm.hip.
+// Implicit-GEMM convolution passes of a CDP tick on gfx950, for channel counts that are whole 16-byte chunks, best
+// multiples of the reduction slab (bf16: 32, fp32: 16); other shapes (the 3-channel stem) run on the generic kernel of
+// gemm.hip.
 //
 //   conv_gemm_kernel   forward   y[(b,oh,ow)][o]  = sum_{tap,c} x[b][oh*s-p+kh][ow*s-p+kw][c] * wf[o][tap][c]
 //                      data grad dx[(b,ih,iw)][c] = sum_{tap,o} dy[b][(ih+p-kh)/s][(iw+p-kw)/s][o] * wt[c][tap][o]
@@ -32,7 +32,10 @@ constexpr int XCD_RUN = 8;
 // forward / data gradient: 128 x BN tile, waves 2 x 2, reduction slab BK (a divisor of the
 // channel count).  Results, residuals and masks move as 16-byte vectors along the
 // channel dimension (conv_epilogue).
-template <typename T, int BM, int BN, int BK, bool DB>
+// RAGGED: channel counts that are whole 16-byte chunks but not whole slabs.  A chunk still lies inside one tap, but a slab
+// does not, so tap and address delta are the lane's own (all its rows load the same chunk column), found with a division
+// per slab; the last slab may be partial.
+template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>
 __global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gemm_kernel(const GemmBatch batch) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC, LDP = BK + VEC;
@@ -93,12 +96,29 @@ __global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gemm
 
   uint4 ra[NA], rb[NB];
   // wavefront-uniform position of the current slab: tap index, channel offset inside the tap
-  const int nslab_all = P.K / BK, per = (nslab_all + ks - 1) / ks;
+  const int nslab_all = RAGGED ? (P.K + BK - 1) / BK : P.K / BK, per = (nslab_all + ks - 1) / ks;
   const int s_begin = split * per, nslab = max(0, min(nslab_all, s_begin + per) - s_begin);
   const int kbeg = s_begin * BK;
   int tap = kbeg / C, c0 = kbeg - tap * C, kh = 0, kw = 0;
   if (mode != OP_PLAIN_K) { kh = tap / g.KW; kw = tap - kh * g.KW; }
   auto fetch = [&](int k0) {
+    if constexpr (RAGGED) {
+      const int k = k0 + akc, t = k / C, c = k - t * C;  // one tap when the operand is plain
+      int d = c;
+      if (mode != OP_PLAIN_K) {
+        const int th = t / g.KW, tw = t - th * g.KW;
+        if (mode == OP_CONV_FWD) d += (th * g.W + tw) * g.C;
+        else if (g.stride == 1) d -= (th * g.W + tw) * g.C;
+        else d -= ((th / g.stride) * g.W + (tw / g.stride)) * g.C;
+      }
+      const bool in = k < P.K;
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+        ra[i] = in && ((amask[i] >> t) & 1u) ? *reinterpret_cast<const uint4*>(Ap + abase[i] + d) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) rb[i] = in && boff[i] >= 0 ? *reinterpret_cast<const uint4*>(Bp + boff[i] + k0) : make_uint4(0, 0, 0, 0);
+      return;
+    }
     int delta;
     if (mode == OP_PLAIN_K) delta = c0;
     else if (mode == OP_CONV_FWD) delta = (kh * g.W + kw) * g.C + c0;
@@ -761,7 +781,7 @@ int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room) {
 
 // ---------------------------------------------------------------------------------
 bool conv_fast_eligible(const GemmProb& p, int dtype) {
-  const int bk = dtype == DT_BF16 ? 32 : 16, vec = dtype == DT_BF16 ? 8 : 4;
+  const int vec = dtype == DT_BF16 ? 8 : 4;
   if (p.epi == EPI_WGRAD) {
     if (p.a_mode != OP_PLAIN_R) return false;
     if (p.b_mode == OP_CONV_WGRAD) {
@@ -773,10 +793,17 @@ bool conv_fast_eligible(const GemmProb& p, int dtype) {
     }
     return (p.M % vec) == 0 && (p.lda % vec) == 0;
   }
-  if (p.b_mode != OP_PLAIN_K || p.ldb != p.K || (p.K % bk)) return false;
+  if (p.b_mode != OP_PLAIN_K || p.ldb != p.K || (p.K % vec)) return false;
   if ((p.flags & GF_OUT_F32) || (p.N % vec) || (p.ldo % vec)) return false;
+  const int C = p.a_mode == OP_PLAIN_K ? p.K : p.g.C;
+  if (C % (dtype == DT_BF16 ? 32 : 16)) {  // the ragged kernel: pieces of 16 bytes at 32-bit offsets
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B) | reinterpret_cast<uintptr_t>(p.out) |
+                         reinterpret_cast<uintptr_t>(p.aux1) | (p.epi == EPI_DGRAD ? reinterpret_cast<uintptr_t>(p.aux0) : 0);
+    const int64_t a_elems = p.a_mode == OP_PLAIN_K ? (int64_t)p.M * p.lda : (int64_t)(p.M / (p.g.OH * p.g.OW) + 1) * p.g.H * p.g.W * p.g.C;
+    if ((at & 15) || a_elems >= (1ll << 31) || (int64_t)p.N * p.ldb >= (1ll << 31)) return false;
+  }
   if (p.a_mode == OP_PLAIN_K) return p.lda == p.K;
-  if (p.a_mode == OP_CONV_FWD || p.a_mode == OP_CONV_DGRAD) return (p.g.C % bk) == 0 && p.g.KH * p.g.KW <= 32;
+  if (p.a_mode == OP_CONV_FWD || p.a_mode == OP_CONV_DGRAD) return (p.g.C % vec) == 0 && p.g.KH * p.g.KW <= 32;
   return false;
 }
 
@@ -786,20 +813,20 @@ constexpr int conv_gemm_lds_bytes() {
   return oper > stage ? oper : stage;
 }
 
-template <typename T, int BM, int BN, int BK, bool DB>
+template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>
 static hipError_t launch_conv_gemm_inst(const GemmBatch& b, dim3 grid, hipStream_t stream) {
   constexpr int lds = conv_gemm_lds_bytes<T, BM, BN, BK, DB>();
   static_assert(lds <= 64 * 1024, "stays within the default dynamic LDS limit");
-  hipLaunchKernelGGL((conv_gemm_kernel<T, BM, BN, BK, DB>), grid, dim3(256), lds, stream, b);
+  hipLaunchKernelGGL((conv_gemm_kernel<T, BM, BN, BK, DB, RAGGED>), grid, dim3(256), lds, stream, b);
   return hipGetLastError();
 }
 
-template <typename T, int BK>
+template <typename T, int BK, bool RAGGED = false>
 static hipError_t launch_conv_gemm_typed(const GemmBatch& b, int bm, int bn, dim3 grid, hipStream_t stream) {
-  if (bm == 128 && bn == 128) return launch_conv_gemm_inst<T, 128, 128, BK, false>(b, grid, stream);
-  if (bm == 128) return launch_conv_gemm_inst<T, 128, 64, BK, false>(b, grid, stream);
-  if (bn == 128) return launch_conv_gemm_inst<T, 64, 128, BK, true>(b, grid, stream);
-  return launch_conv_gemm_inst<T, 64, 64, BK, true>(b, grid, stream);
+  if (bm == 128 && bn == 128) return launch_conv_gemm_inst<T, 128, 128, BK, false, RAGGED>(b, grid, stream);
+  if (bm == 128) return launch_conv_gemm_inst<T, 128, 64, BK, false, RAGGED>(b, grid, stream);
+  if (bn == 128) return launch_conv_gemm_inst<T, 64, 128, BK, true, RAGGED>(b, grid, stream);
+  return launch_conv_gemm_inst<T, 64, 64, BK, true, RAGGED>(b, grid, stream);
 }
 
 // Tile shape for the forward / data-gradient problems of one launch: the largest of
@@ -835,11 +862,13 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
   int total = 0;
   if (const int dl = conv_dl_tile(b.p, b.n, dtype)) return launch_conv_dl(b, dtype, dl, stream);
   bool deep = true;  // every problem allows the double-depth slab
+  bool ragged = false;
   for (int i = 0; i < b.n; ++i) {
     GemmProb& p = b.p[i];
     if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.epi == EPI_WGRAD || !conv_fast_eligible(p, dtype)) return hipErrorInvalidValue;
     const int C = p.a_mode == OP_PLAIN_K ? p.K : p.g.C;
     if (C % (2 * bk)) deep = false;
+    if (C % bk) ragged = true;
     p.splits = 1;
     p.tiles_n = (p.N + bn - 1) / bn;
     p.tile_begin = total;
@@ -849,7 +878,7 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
   // ranges of at least 4 slabs, at most 8 per tile, while the partial tiles fit the workspace.
   // (64 x 64 tiles only: the partial tile of a larger one costs more than the shorter chain saves)
   if (b.thin_ws && b.thin_cnt && total < 512 && bm == 64 && bn == 64) {
-    const int slab = deep ? 2 * bk : bk, want = (640 + total - 1) / total;
+    const int slab = deep || ragged ? 2 * bk : bk, want = (640 + total - 1) / total;
     int split_total = 0;
     for (int i = 0; i < b.n; ++i) {
       GemmProb& p = b.p[i];
@@ -868,6 +897,8 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
   }
   b.total_tiles = total;
   dim3 grid(total);
+  if (ragged) return dtype == DT_BF16 ? launch_conv_gemm_typed<uint16_t, 64, true>(b, bm, bn, grid, stream)
+                                      : launch_conv_gemm_typed<float, 32, true>(b, bm, bn, grid, stream);
   if (dtype == DT_BF16) return deep ? launch_conv_gemm_typed<uint16_t, 64>(b, bm, bn, grid, stream)
                                     : launch_conv_gemm_typed<uint16_t, 32>(b, bm, bn, grid, stream);
   return deep ? launch_conv_gemm_typed<float, 32>(b, bm, bn, grid, stream)

@@ -374,3 +374,13 @@ def test_conv_short_of_workgroups(rows, out, slabs):
     for red in ((64 * slabs, 32 * slabs) if slabs <= 7 else (64 * slabs,)):
         _conv_1x1_bf16(0, rows, red, out)
         _conv_1x1_bf16(1, rows, out, red)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("case", [(8, 28, 28, 24, 136, 3, 1, 1), (16, 56, 56, 40, 40, 3, 2, 1), (2, 9, 9, 72, 200, 3, 1, 1),
+                                  (1, 1, 3000, 120, 88, 1, 1, 0), (3, 7, 7, 8, 8, 5, 1, 2), (2, 11, 13, 40, 24, 3, 3, 1),
+                                  (4, 1, 5000, 1000, 520, 1, 1, 0)])
+def test_conv_channels_not_whole_slabs(dtype, case):
+    """Channel counts that are whole 16-byte chunks but not whole reduction slabs: slabs across taps, a partial last slab,
+    strides 1 to 3, every tile shape."""
+    test_conv_passes_match_oracle(dtype, case)
