@@ -1,5 +1,5 @@
-// The self-attention core in bf16: one kernel forward, two backward, nothing but the probabilities travelling
-// through memory between the products.
+// The self-attention core: one kernel forward, two backward, nothing but the probabilities (fp32: and the gradient of
+// the scores) travelling through memory between the products.  First bf16, then fp32.
 //
 // What bounds them: 32 samples x 12 heads x 196 tokens of width 64 are 68 MB forward and 97 MB backward (q, k, v, d out,
 // the probabilities, the results) against 3.8 and 7.6 GFLOP, so memory; the contractions are short and the softmax
@@ -451,6 +451,364 @@ __global__ __launch_bounds__(256, KS <= 4 ? 3 : 2) void attn_bwd_dkv_kernel(cons
   }
 }
 
+// ---- fp32 --------------------------------------------------------------------------------------------------------------
+// The same products on 32x32x2, where a wavefront with all keys of its 32 queries would be a chain of a thousand matrix
+// instructions: a workgroup owns 32 queries (or keys) of one head, its two to eight wavefronts take the blocks of 32 keys
+// (or queries) in turn, and maxima, sums and partial results meet in LDS, added in wavefront order.  An accumulator register
+// is an operand as it is (lane half hi holds rows 8 g + 4 hi + i), the other operand's value comes straight from memory,
+// whole rows of the head at a time; row operands are 16-byte pieces whose columns both sides take in one order.  Loads of a
+// block go out together, without a branch between them, and before the wait for the other wavefronts where there is one.
+// The backward keeps the gradient of the scores (contracting it again for dk cost more than its trip through memory).
+// What bounds it: 4 samples x 3 heads x 324 tokens of width 64 are 132 workgroups of three chained blocks, 5 us of matrix
+// time forward under 16 us of loads, products and two waits in turn; the chip is half empty.  As three and five kernels
+// 26.7 us forward and 51 us backward, 16.4 and 25.7 us so; 32 x 12 x 196 of width 64 107 / 182 -> 82 / 163 us (matrix time
+// 36 / 72 us), 64 x 8 x 64 of width 32 24.6 / 29.9 -> 9.6 / 17.7 us.
+struct AttnArgs32 {
+  const float* qkv;   // [B][NT][3 D]
+  float* P;           // [B][heads][NT][NT]: written forward, read backward
+  const float* dout;  // backward: [B][NT][D]
+  float* out;         // forward: [B][NT][D]; backward: d qkv [B][NT][3 D]
+  float* ds;          // backward: [B][heads][NT][NT], gradient of the scores
+  int NT, D, heads, dh;
+  int blocks;         // of 32 tokens
+  int vec;            // rows of P and ds are whole, aligned 16-byte groups
+  float scale;
+};
+__device__ __forceinline__ v16f_t mfma32(float4 a, float4 b, v16f_t c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, c, 0, 0, 0);
+}
+// Rows of the head: row r of `base` (clamped to the last token) as row operand pieces, column 8 s + 4 hi.
+template <int OB>
+__device__ __forceinline__ void load_row32(float4 (&f)[4 * OB], const float* row, int dh, int hi) {
+#pragma unroll
+  for (int s = 0; s < 4 * OB; ++s) {  // a select, no branch: the loads have to be in flight together
+    f[s] = *reinterpret_cast<const float4*>(row + min(8 * s, dh - 8) + 4 * hi);
+    const bool in = 8 * s < dh;
+    f[s].x = in ? f[s].x : 0.f;
+    f[s].y = in ? f[s].y : 0.f;
+    f[s].z = in ? f[s].z : 0.f;
+    f[s].w = in ? f[s].w : 0.f;
+  }
+}
+// The same rows for every wavefront of the workgroup: fetched once, in whole lines, and handed out through LDS (a row operand
+// straight from memory touches 32 lines a load).
+template <int OB, int W32>
+__device__ __forceinline__ void share_rows32(float4 (&f)[4 * OB], float* red, const float* src, int64_t ld, int row0, int NT, int dh) {
+  constexpr int PITCH = 32 * OB + 4;
+  for (int i = threadIdx.x; i < 32 * 8 * OB; i += 64 * W32) {
+    const int r = i / (8 * OB), c = 4 * (i % (8 * OB));
+    float4 x = *reinterpret_cast<const float4*>(src + (int64_t)min(row0 + r, NT - 1) * ld + min(c, dh - 4));
+    if (c >= dh) x = make_float4(0.f, 0.f, 0.f, 0.f);
+    *reinterpret_cast<float4*>(red + r * PITCH + c) = x;
+  }
+  __syncthreads();
+  const int l31 = threadIdx.x & 31, hi = threadIdx.x >> 5 & 1;
+#pragma unroll
+  for (int s = 0; s < 4 * OB; ++s) f[s] = *reinterpret_cast<const float4*>(red + l31 * PITCH + 8 * s + 4 * hi);
+}
+// Products with rows past the last token are none: whatever the last token holds must not reach a sum.
+__device__ __forceinline__ void clear32(v16f_t& s, int row0, int NT, int hi) {
+  if (row0 + 32 <= NT) return;
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    if (row0 + 8 * (v >> 2) + 4 * hi + (v & 3) >= NT) s[v] = 0.f;
+}
+// a . b over the head width for one block of 32 rows (given by the lane's row) against the lane's column.
+template <int OB>
+__device__ __forceinline__ v16f_t rows32(const float* row, const float4 (&col)[4 * OB], int dh, int hi) {
+  float4 f[4 * OB];
+  load_row32<OB>(f, row, dh, hi);
+  v16f_t s = zero16();
+#pragma unroll
+  for (int k = 0; k < 4 * OB; ++k) s = mfma32(f[k], col[k], s);
+  return s;
+}
+// acc[ob][j][.] += sum over 32 rows of src[row][32 ob + j] * x[row]; x as an accumulator holds it.  Loads and products apart,
+// so that the loads can be on their way before a wait that the products need.
+template <int OB>
+__device__ __forceinline__ void cols_load32(float (&f)[OB][16], const float* src, int64_t ld, int row0, int NT, int dh, int lane) {
+  const int l31 = lane & 31, hi = lane >> 5;
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) {
+    const float* p = src + min(32 * ob + l31, dh - 1);  // columns past the head only reach results that are not stored
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = row0 + 8 * (v >> 2) + 4 * hi + (v & 3);
+      f[ob][v] = p[(int64_t)min(r, NT - 1) * ld];
+    }
+  }
+}
+template <int OB>
+__device__ __forceinline__ void cols_mul32(v16f_t (&acc)[OB], const float (&f)[OB][16], const v16f_t& x, int row0, int NT, int hi) {
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) {
+    v16f_t y;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) y[v] = f[ob][v];
+    clear32(y, row0, NT, hi);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(y[v], x[v], acc[ob], 0, 0, 0);
+  }
+}
+// The wavefronts' partial results, added in wavefront order: each finishes some groups of four columns of the lanes' tokens
+// and stores them at dst + column (nullptr: nothing to store).
+template <int OB, int W32>
+__device__ __forceinline__ void finish32(const v16f_t (&acc)[OB], float* red, float* dst, int dh, int wave, int lane) {
+  const int hi = lane >> 5;
+  __syncthreads();  // red is free
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) red[((wave * OB + ob) * 16 + v) * 64 + lane] = acc[ob][v];
+  __syncthreads();
+  for (int g = wave; g < 4 * OB; g += W32) {
+    const int j = 8 * g + 4 * hi;
+    float r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* x = red + (4 * g + i) * 64 + lane;
+      r[i] = x[0];
+#pragma unroll
+      for (int w = 1; w < W32; ++w) r[i] += x[w * OB * 1024];
+    }
+    if (dst != nullptr && j < dh) *reinterpret_cast<float4*>(dst + j) = make_float4(r[0], r[1], r[2], r[3]);
+  }
+}
+// Probabilities of the lane's query (nullptr: none) for one block of keys, as an accumulator holds them; zero past the last.
+__device__ __forceinline__ void load_p32(v16f_t& p, const float* row, int k0, int NT, int vec, int hi) {
+  if (row == nullptr) {
+    p = zero16();
+    return;
+  }
+  if (vec) {  // NT is a multiple of four: a piece is all in or all out
+    float4 f[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) f[g] = *reinterpret_cast<const float4*>(row + min(k0 + 8 * g + 4 * hi, NT - 4));
+#pragma unroll
+    for (int g = 0; g < 4; ++g) { p[4 * g] = f[g].x; p[4 * g + 1] = f[g].y; p[4 * g + 2] = f[g].z; p[4 * g + 3] = f[g].w; }
+  } else {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) p[v] = row[min(k0 + 8 * (v >> 2) + 4 * hi + (v & 3), NT - 1)];
+  }
+  clear32(p, k0, NT, hi);
+}
+__device__ __forceinline__ void store_p32(float* row, const v16f_t& p, int k0, int NT, int vec, int hi) {
+  if (row == nullptr) return;
+  if (vec) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (k0 + 8 * g + 4 * hi < NT)
+        *reinterpret_cast<float4*>(row + k0 + 8 * g + 4 * hi) = make_float4(p[4 * g], p[4 * g + 1], p[4 * g + 2], p[4 * g + 3]);
+    return;
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    if (const int k = k0 + 8 * (v >> 2) + 4 * hi + (v & 3); k < NT) row[k] = p[v];
+}
+// Sum / maximum over the lane pair of a query and the wavefronts; every lane of the query gets it.
+template <bool MAX, int W32>
+__device__ __forceinline__ float across32(float v, float* red, int wave, int lane) {
+  const float o = __shfl_xor(v, 32, 64);
+  v = MAX ? fmaxf(v, o) : v + o;
+  __syncthreads();
+  if (lane < 32) red[wave * 32 + lane] = v;
+  __syncthreads();
+  v = red[lane & 31];
+#pragma unroll
+  for (int w = 1; w < W32; ++w) {
+    const float x = red[w * 32 + (lane & 31)];
+    v = MAX ? fmaxf(v, x) : v + x;
+  }
+  return v;
+}
+
+template <int OB, int W32, int NBW>
+__global__ __launch_bounds__(64 * W32, 2) void attn_fwd32_kernel(const AttnArgs32 a) {
+  __shared__ __attribute__((aligned(16))) float red[W32 * OB * 1024];
+  const int NT = a.NT, dh = a.dh;
+  const int id = xcd_block_cyclic(blockIdx.x, gridDim.x, a.blocks), z = id / a.blocks, sample = z / a.heads, head = z % a.heads;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5;
+  const int q = (id % a.blocks) * 32 + l31;
+  const int64_t tok = 3ll * a.D;
+  const float* base = a.qkv + (int64_t)sample * NT * tok + head * dh;
+  float4 qf[4 * OB];
+  share_rows32<OB, W32>(qf, red, base, tok, q - l31, NT, dh);
+  v16f_t s[NBW];
+  float m = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int k0 = 32 * (wave + W32 * t);
+    if (k0 >= NT) continue;
+    s[t] = rows32<OB>(base + a.D + (int64_t)min(k0 + l31, NT - 1) * tok, qf, dh, hi);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      if (k0 + 8 * (v >> 2) + 4 * hi + (v & 3) >= NT) s[t][v] = -INFINITY;
+      m = fmaxf(m, s[t][v]);
+    }
+  }
+  const float c = a.scale * 1.44269504088896340736f;
+  m = across32<true, W32>(m, red, wave, lane) * c;  // finite: key 0 is always there
+  float sum = 0.f;
+#pragma unroll
+  for (int t = 0; t < NBW; ++t)
+    if (32 * (wave + W32 * t) < NT) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        s[t][v] = exp2f(fmaf(s[t][v], c, -m));
+        sum += s[t][v];
+      }
+    }
+  float f[OB][16];
+  cols_load32<OB>(f, base + 2 * a.D, tok, 32 * wave, NT, dh, lane);
+  const float inv = 1.f / across32<false, W32>(sum, red, wave, lane);
+  float* prow = q < NT ? a.P + ((int64_t)z * NT + q) * NT : nullptr;
+  v16f_t o[OB];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) o[ob] = zero16();
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int k0 = 32 * (wave + W32 * t);
+    if (k0 >= NT) continue;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[t][v] *= inv;
+    store_p32(prow, s[t], k0, NT, a.vec, hi);
+    if (t > 0) cols_load32<OB>(f, base + 2 * a.D, tok, k0, NT, dh, lane);
+    cols_mul32<OB>(o, f, s[t], k0, NT, hi);
+  }
+  finish32<OB, W32>(o, red, q < NT ? a.out + ((int64_t)sample * NT + q) * a.D + head * dh : nullptr, dh, wave, lane);
+}
+
+// dq of 32 queries, leaving the gradient of the scores behind; and dv or dk of 32 keys: the same sum over the queries, of
+// probabilities times output gradient or of score gradient times q.  dv needs nothing of dq and shares its launch.
+template <int OB, int W32, int NBW>
+__device__ __forceinline__ void attn_dq32(const AttnArgs32& a, float* red, int id) {
+  const int NT = a.NT, dh = a.dh, z = id / a.blocks, sample = z / a.heads, head = z % a.heads;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5;
+  const int q = (id % a.blocks) * 32 + l31;
+  const int64_t tok = 3ll * a.D;
+  const float* base = a.qkv + (int64_t)sample * NT * tok + head * dh;
+  const float* prow = q < NT ? a.P + ((int64_t)z * NT + q) * NT : nullptr;
+  float* drow = q < NT ? a.ds + ((int64_t)z * NT + q) * NT : nullptr;
+  float4 df[4 * OB];
+  share_rows32<OB, W32>(df, red, a.dout + (int64_t)sample * NT * a.D + head * dh, a.D, q - l31, NT, dh);
+  v16f_t s[NBW], p[NBW];
+  float delta = 0.f;
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int k0 = 32 * (wave + W32 * t);
+    if (k0 >= NT) continue;
+    load_p32(p[t], prow, k0, NT, a.vec, hi);
+    s[t] = rows32<OB>(base + 2 * a.D + (int64_t)min(k0 + l31, NT - 1) * tok, df, dh, hi);
+    clear32(s[t], k0, NT, hi);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) delta = fmaf(p[t][v], s[t][v], delta);
+  }
+  float f[OB][16];
+  cols_load32<OB>(f, base + a.D, tok, 32 * wave, NT, dh, lane);
+  delta = across32<false, W32>(delta, red, wave, lane);
+  v16f_t o[OB];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) o[ob] = zero16();
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int k0 = 32 * (wave + W32 * t);
+    if (k0 >= NT) continue;
+    if (t > 0) cols_load32<OB>(f, base + a.D, tok, k0, NT, dh, lane);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[t][v] = p[t][v] * (s[t][v] - delta) * a.scale;
+    store_p32(drow, s[t], k0, NT, a.vec, hi);
+    cols_mul32<OB>(o, f, s[t], k0, NT, hi);
+  }
+  finish32<OB, W32>(o, red, q < NT ? a.out + ((int64_t)sample * NT + q) * tok + head * dh : nullptr, dh, wave, lane);
+}
+template <int OB, int W32>
+__device__ __forceinline__ void attn_dkv32(const AttnArgs32& a, float* red, int id, bool dv) {
+  const int NT = a.NT, dh = a.dh, z = id / a.blocks, sample = z / a.heads, head = z % a.heads;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5;
+  const int k = (id % a.blocks) * 32 + l31;
+  const int64_t tok = 3ll * a.D, ld = dv ? a.D : tok;
+  const float* y = (dv ? a.dout : a.qkv) + (int64_t)sample * NT * ld + head * dh;
+  const float* x = (dv ? a.P : a.ds) + (int64_t)z * NT * NT + min(k, NT - 1);
+  auto load = [&](v16f_t& p, float (&f)[OB][16], int q0) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) p[v] = x[(int64_t)min(q0 + 8 * (v >> 2) + 4 * hi + (v & 3), NT - 1) * NT];
+    cols_load32<OB>(f, y, ld, q0, NT, dh, lane);
+  };
+  v16f_t o[OB], p[2];
+  float f0[OB][16], f1[OB][16];
+#pragma unroll
+  for (int ob = 0; ob < OB; ++ob) o[ob] = zero16();
+  constexpr int STEP = 32 * W32;
+  if (32 * wave < NT) {
+    if constexpr (OB < 3) {
+      load(p[0], f0, 32 * wave);
+      for (int q0 = 32 * wave; q0 < NT; q0 += 2 * STEP) {
+        if (q0 + STEP < NT) load(p[1], f1, q0 + STEP);
+        clear32(p[0], q0, NT, hi);
+        cols_mul32<OB>(o, f0, p[0], q0, NT, hi);
+        if (q0 + STEP >= NT) break;
+        if (q0 + 2 * STEP < NT) load(p[0], f0, q0 + 2 * STEP);
+        clear32(p[1], q0 + STEP, NT, hi);
+        cols_mul32<OB>(o, f1, p[1], q0 + STEP, NT, hi);
+      }
+    } else {  // two blocks of a wide head at once do not fit the registers
+      for (int q0 = 32 * wave; q0 < NT; q0 += STEP) {
+        load(p[0], f0, q0);
+        clear32(p[0], q0, NT, hi);
+        cols_mul32<OB>(o, f0, p[0], q0, NT, hi);
+      }
+    }
+  }
+  finish32<OB, W32>(o, red, k < NT ? a.out + ((int64_t)sample * NT + k) * tok + (dv ? 2 : 1) * a.D + head * dh : nullptr, dh, wave, lane);
+}
+template <int OB, int W32, int NBW>
+__global__ __launch_bounds__(64 * W32, 2) void attn_bwd_dq_dv32_kernel(const AttnArgs32 a) {
+  __shared__ __attribute__((aligned(16))) float red[W32 * OB * 1024];
+  const int id = xcd_block_cyclic(blockIdx.x, gridDim.x, a.blocks), n = gridDim.x / 2;
+  if (id < n) attn_dq32<OB, W32, NBW>(a, red, id);
+  else attn_dkv32<OB, W32>(a, red, id - n, true);
+}
+template <int OB, int W32>
+__global__ __launch_bounds__(64 * W32, 2) void attn_bwd_dk32_kernel(const AttnArgs32 a) {
+  __shared__ __attribute__((aligned(16))) float red[W32 * OB * 1024];
+  attn_dkv32<OB, W32>(a, red, xcd_block_cyclic(blockIdx.x, gridDim.x, a.blocks), false);
+}
+
+template <int OB, int W32, int NBW>
+hipError_t launch_attn32_w(const AttnArgs32& a, bool backward, int batch, hipStream_t stream) {
+  const unsigned n = (unsigned)batch * (unsigned)a.blocks;
+  if (!backward) {
+    hipLaunchKernelGGL((attn_fwd32_kernel<OB, W32, NBW>), dim3(n), dim3(64 * W32), 0, stream, a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((attn_bwd_dq_dv32_kernel<OB, W32, NBW>), dim3(2 * n), dim3(64 * W32), 0, stream, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_bwd_dk32_kernel<OB, W32>), dim3(n), dim3(64 * W32), 0, stream, a);
+  return hipGetLastError();
+}
+// As many wavefronts as there are blocks of 32 tokens, up to eight, and then as many blocks for each as it takes; with
+// more than two workgroups per CU to run, two of four wavefronts on a CU rather than one of eight, whose waits the other
+// one fills (32 x 12 x 196 of width 64: 94 / 230 -> 82 / 163 us, 16 x 8 x 512 161 / 333 -> 132 / 281 us).
+template <int OB>
+hipError_t launch_attn32_ob(const AttnArgs32& a, bool backward, int batch, hipStream_t stream) {
+  if (a.blocks <= 2) return launch_attn32_w<OB, 2, 1>(a, backward, batch, stream);
+  if (a.blocks <= 4) return launch_attn32_w<OB, 4, 1>(a, backward, batch, stream);
+  if (a.blocks <= 8 && batch * a.blocks > 512) return launch_attn32_w<OB, 4, 2>(a, backward, batch, stream);
+  if (a.blocks <= 8) return launch_attn32_w<OB, 8, 1>(a, backward, batch, stream);
+  if (a.blocks <= 16 && batch * a.blocks > 512) return launch_attn32_w<OB, 4, 4>(a, backward, batch, stream);
+  if (a.blocks <= 16) return launch_attn32_w<OB, 8, 2>(a, backward, batch, stream);
+  return launch_attn32_w<OB, 8, 4>(a, backward, batch, stream);
+}
+hipError_t launch_attn32(const AttnArgs32& a, bool backward, int batch, hipStream_t stream) {
+  if (batch <= 0 || batch > 65535 || a.blocks > 32) return hipErrorInvalidValue;
+  if (a.dh <= 32) return launch_attn32_ob<1>(a, backward, batch, stream);
+  if (a.dh <= 64) return launch_attn32_ob<2>(a, backward, batch, stream);
+  return launch_attn32_ob<3>(a, backward, batch, stream);
+}
 constexpr size_t ATTN_LDS = 160 * 1024;
 size_t attn_lds(int NT, int dh) {
   const size_t pitch = dh == 64 ? dh : dh + 8;
@@ -499,34 +857,68 @@ AttnArgs attn_args(const void* qkv, const void* P, int B, int NT, int D, int hea
   return a;
 }
 
+AttnArgs32 attn_args32(const void* qkv, const void* P, int NT, int D, int heads) {
+  AttnArgs32 a;
+  a.qkv = static_cast<const float*>(qkv);
+  a.P = static_cast<float*>(const_cast<void*>(P));
+  a.dout = nullptr; a.out = nullptr; a.ds = nullptr;
+  a.NT = NT; a.D = D; a.heads = heads; a.dh = D / heads;
+  a.blocks = (NT + 31) / 32;
+  a.vec = NT % 4 == 0 && aligned(P, 16);
+  a.scale = 1.0f / sqrtf((float)a.dh);
+  return a;
+}
+
 }  // namespace
 
-// Heads whose width is a whole number of 16-wide reduction steps up to 80 (the accumulators of a wider one leave a
+// bf16: heads whose width is a whole number of 16-wide reduction steps up to 80 (the accumulators of a wider one leave a
 // single workgroup per CU), two tiles of all tokens in LDS; the launches below also want aligned rows.
-bool attention_fused(int NT, int D, int heads, int dtype) {
-  if (dtype != DT_BF16 || heads <= 0 || NT <= 0 || D % heads) return false;
+// fp32: three accumulators of 32 columns at most.  Long sequences in many heads run as well as products of whole matrices
+// (16 x 8 x 512 of width 64: 270 us backward against 281 us, 4 x 8 x 1024 271 against 296 us; 16 x 8 x 384 157 against
+// 148 us, 1 x 8 x 1024 134 against 73 us), unless their rows end inside a 16-byte piece (8 x 12 x 577: 495 against 399 us);
+// forward the kernel is the faster one there too (152 against 142 us).
+bool attention_fused(bool backward, int B, int NT, int D, int heads, int dtype) {
+  if (heads <= 0 || NT <= 0 || D % heads) return false;
   const int dh = D / heads;
+  if (dtype == DT_F32) {
+    const int64_t blocks = (NT + 31) / 32;
+    if (dh % 8 || dh > 96 || NT > 1024) return false;
+    return !backward || blocks <= 8 || NT % 4 != 0 || (int64_t)B * heads * blocks * blocks <= 24576;
+  }
   return dh % 16 == 0 && dh <= 80 && attn_lds(NT, dh) <= ATTN_LDS;
 }
-bool attention_fused_fwd_ok(const void* qkv, const void* out, int NT, int D, int heads, int dtype) {
-  return attention_fused(NT, D, heads, dtype) && aligned(qkv, 16) && aligned(out, 8);
+bool attention_fused_fwd_ok(const void* qkv, const void* out, int B, int NT, int D, int heads, int dtype) {
+  return attention_fused(false, B, NT, D, heads, dtype) && aligned(qkv, 16) && aligned(out, dtype == DT_F32 ? 16 : 8);
 }
-bool attention_fused_bwd_ok(const void* qkv, const void* dout, const void* dqkv, int NT, int D, int heads, int dtype) {
-  return attention_fused(NT, D, heads, dtype) && aligned(qkv, 16) && aligned(dout, 16) && aligned(dqkv, 8);
+bool attention_fused_bwd_ok(const void* qkv, const void* dout, const void* dqkv, int B, int NT, int D, int heads, int dtype) {
+  return attention_fused(true, B, NT, D, heads, dtype) && aligned(qkv, 16) && aligned(dout, 16) && aligned(dqkv, dtype == DT_F32 ? 16 : 8);
 }
 
-hipError_t launch_attention_fused_fwd(const void* qkv, void* P, void* out, int B, int NT, int D, int heads, hipStream_t stream) {
+hipError_t launch_attention_fused_fwd(const void* qkv, void* P, void* out, int B, int NT, int D, int heads, int dtype, hipStream_t stream) {
+  if (dtype == DT_F32) {
+    AttnArgs32 f = attn_args32(qkv, P, NT, D, heads);
+    f.out = static_cast<float*>(out);
+    return launch_attn32(f, false, B * heads, stream);
+  }
   AttnArgs a = attn_args(qkv, P, B, NT, D, heads);
   a.out = static_cast<uint16_t*>(out);
   return launch_attn_pass(a, D / heads, 0, B * heads, stream);
 }
-hipError_t launch_attention_fused_bwd(const void* qkv, const void* P, const void* dout, void* dqkv, float* delta, int B, int NT, int D, int heads,
-                                      hipStream_t stream) {
+hipError_t launch_attention_fused_bwd(const void* qkv, const void* P, const void* dout, void* dqkv, float* ws, int B, int NT, int D, int heads,
+                                      int dtype, hipStream_t stream) {
+  if (dtype == DT_F32) {
+    AttnArgs32 f = attn_args32(qkv, P, NT, D, heads);
+    f.dout = static_cast<const float*>(dout);
+    f.out = static_cast<float*>(dqkv);
+    f.ds = ws;
+    f.vec = f.vec && aligned(ws, 16);
+    return launch_attn32(f, true, B * heads, stream);
+  }
   AttnArgs a = attn_args(qkv, P, B, NT, D, heads);
   a.dout = static_cast<const uint16_t*>(dout);
   a.out = static_cast<uint16_t*>(dqkv);
-  a.delta = delta;
-  a.dvec = NT % 4 == 0 && aligned(delta, 16);
+  a.delta = ws;
+  a.dvec = NT % 4 == 0 && aligned(ws, 16);
   hipError_t e = launch_attn_pass(a, D / heads, 1, B * heads, stream);
   return e != hipSuccess ? e : launch_attn_pass(a, D / heads, 2, B * heads, stream);
 }

@@ -308,17 +308,19 @@ hipError_t launch_attention_fwd(const void* qkv, void* P, void* out, float* ws, 
                                 hipStream_t stream);
 hipError_t launch_attention_bwd(const void* qkv, const void* P, const void* dout, void* dqkv, float* ws_dp, void* ws_ds, int B,
                                 int T, int D, int heads, int dtype, hipStream_t stream);
-// The same in one kernel forward and two backward (attention_kernels.hip): bf16, head widths that are multiples of 16 up
-// to 80, as many tokens as fit LDS twice.  _fwd_ok / _bwd_ok also look at the alignment of the operands; delta: fp32
-// [B][heads][T] scratch.
-bool attention_fused(int NT, int D, int heads, int dtype);
-bool attention_fused_fwd_ok(const void* qkv, const void* out, int NT, int D, int heads, int dtype);
-bool attention_fused_bwd_ok(const void* qkv, const void* dout, const void* dqkv, int NT, int D, int heads, int dtype);
-hipError_t launch_attention_fused_fwd(const void* qkv, void* P, void* out, int B, int NT, int D, int heads, hipStream_t stream);
-hipError_t launch_attention_fused_bwd(const void* qkv, const void* P, const void* dout, void* dqkv, float* delta, int B, int NT, int D, int heads,
+// The same in one kernel forward and two backward (attention_kernels.hip): bf16 with head widths that are multiples of 16
+// up to 80 and as many tokens as fit LDS twice, fp32 with head widths that are multiples of 8 up to 96 (backward, long
+// sequences in many heads excepted).  _fwd_ok / _bwd_ok also look at the alignment of the operands; ws: fp32 scratch,
+// [B][heads][T] in bf16, [B][heads][T][T] in fp32.
+bool attention_fused(bool backward, int B, int NT, int D, int heads, int dtype);
+bool attention_fused_fwd_ok(const void* qkv, const void* out, int B, int NT, int D, int heads, int dtype);
+bool attention_fused_bwd_ok(const void* qkv, const void* dout, const void* dqkv, int B, int NT, int D, int heads, int dtype);
+hipError_t launch_attention_fused_fwd(const void* qkv, void* P, void* out, int B, int NT, int D, int heads, int dtype,
                                       hipStream_t stream);
+hipError_t launch_attention_fused_bwd(const void* qkv, const void* P, const void* dout, void* dqkv, float* ws, int B, int NT, int D, int heads,
+                                      int dtype, hipStream_t stream);
 // Kernels one call of launch_attention_fwd / _bwd launches.
-int attention_launches(bool backward, int NT, int D, int heads, int dtype);
+int attention_launches(bool backward, int B, int NT, int D, int heads, int dtype);
 
 // T -> f32 copy (cdp_get_weights of a ring copy).
 hipError_t launch_to_f32(const void* src, float* dst, int64_t n, int dtype, hipStream_t stream);

@@ -899,7 +899,7 @@ hipError_t launch_attention_fwd(const void* qkv, void* P, void* out, float* ws, 
   const char* base = static_cast<const char*>(qkv);
   const int eb = dtype == DT_BF16 ? 2 : 4;
   const int64_t rows = (int64_t)B * heads * NT;
-  if (attention_fused_fwd_ok(qkv, out, NT, D, heads, dtype)) return launch_attention_fused_fwd(qkv, P, out, B, NT, D, heads, stream);
+  if (attention_fused_fwd_ok(qkv, out, B, NT, D, heads, dtype)) return launch_attention_fused_fwd(qkv, P, out, B, NT, D, heads, dtype, stream);
   BmmArgs s;  // S[z][q][key] = scale * sum_j q[q][j] k[key][j]
   s.A = BmmOperand{base, NT * tok, dh, tok, 1};
   s.B = BmmOperand{base + (int64_t)D * eb, NT * tok, dh, tok, 1};
@@ -922,17 +922,17 @@ hipError_t launch_attention_fwd(const void* qkv, void* P, void* out, float* ws, 
   return launch_bmm(o, B * heads, dtype, stream);
 }
 
-int attention_launches(bool backward, int NT, int D, int heads, int dtype) {
+int attention_launches(bool backward, int B, int NT, int D, int heads, int dtype) {
   // (operands the engine passes are 256-byte aligned)
-  const bool fused = attention_fused(NT, D, heads, dtype);
+  const bool fused = attention_fused(backward, B, NT, D, heads, dtype);
   return backward ? (fused ? 2 : 5) : (fused ? 1 : 3);
 }
 
 hipError_t launch_attention_bwd(const void* qkv, const void* P, const void* dout, void* dqkv, float* ws_dp, void* ws_ds, int B,
                                 int NT, int D, int heads, int dtype, hipStream_t stream) {
   if (B <= 0 || NT <= 0 || NT > 64 * LN_MAX_PER_LANE || heads <= 0 || D % heads) return hipErrorInvalidValue;
-  if (attention_fused_bwd_ok(qkv, dout, dqkv, NT, D, heads, dtype))
-    return launch_attention_fused_bwd(qkv, P, dout, dqkv, ws_dp, B, NT, D, heads, stream);
+  if (attention_fused_bwd_ok(qkv, dout, dqkv, B, NT, D, heads, dtype))
+    return launch_attention_fused_bwd(qkv, P, dout, dqkv, ws_dp, B, NT, D, heads, dtype, stream);
   const int dh = D / heads;
   const int64_t tok = 3ll * D, TT = (int64_t)NT * NT;
   const float scale = 1.0f / sqrtf((float)dh);

@@ -323,6 +323,16 @@ def test_attention_fused_edges(B, T, D, heads):
     test_attention_kernels_match_oracle(wl.BF16, B, T, D, heads)
 
 
+@pytest.mark.parametrize("B,T,D,heads", [(1, 1, 8, 1), (2, 31, 40, 5), (1, 33, 96, 1), (1, 128, 72, 1), (1, 129, 64, 2), (1, 385, 32, 1),
+                                         (1, 1021, 96, 2), (1, 1024, 80, 1), (1, 64, 104, 1),
+                                         (26, 129, 32, 4), (29, 257, 16, 2), (76, 260, 32, 4)])
+def test_attention_fused_edges_fp32(B, T, D, heads):
+    """The fp32 kernels: a single token, one block of 32 short of one and one more, one to four blocks per
+    wavefront, rows of probabilities that are not whole pieces, head widths 8 to 96 and one past them; enough workgroups
+    for four wavefronts with two and four blocks each, and for the separate kernels backward."""
+    test_attention_kernels_match_oracle(wl.F32, B, T, D, heads)
+
+
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("rows,C", [(1, 8), (17, 1024), (33, 64), (4100, 520), (8200, 16)])
 def test_layernorm_whole_chunk_edges(dtype, rows, C):
