@@ -813,6 +813,94 @@ constexpr int conv_gemm_lds_bytes() {
   return oper > stage ? oper : stage;
 }
 
+// fp32, few tiles: a workgroup per 32 x 32 tile of the result, its four wavefronts take every fourth slab of 32 of the reduction
+// with both operands straight from memory (16-byte pieces of 32 rows, both sides' columns in the same order, the next slab's on
+// their way during the products), and add their tiles through LDS in wavefront order.  Bound by the address path, 32 bytes
+// of a row per access: 162 tiles, 1152 deep (3x3, stride 2, data gradient of 32 x 9 x 9 x 64) 38.6 us as 41 tiles of 64 x 64,
+// 12.6 us so; 100 tiles, 576 deep 20.6 -> 8.8 us.
+__global__ __launch_bounds__(256, 2) void conv_gemm_few_kernel(const GemmBatch batch) {
+  __shared__ float red[4 * 16 * 64];
+  const int tile = blockIdx.x;
+  const GemmProb& P = batch.p[find_problem(batch, tile)];
+  const int local = tile - P.tile_begin, tn = local % P.tiles_n, tm = local / P.tiles_n;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5;
+  const int r = tm * 32 + l31, col0 = tn * 32;
+  const ConvGeom g = P.g;
+  const int mode = P.a_mode, C = mode == OP_PLAIN_K ? P.K : g.C;
+  int base = 0;
+  unsigned mask = 0;
+  if (r < P.M) {
+    if (mode == OP_PLAIN_K) {
+      base = r * P.lda;
+      mask = 1u;
+    } else {
+      conv_row(g, mode, r, base, mask);
+    }
+  }
+  const float* Ap = static_cast<const float*>(P.A) + 4 * hi;
+  const float* Bp = static_cast<const float*>(P.B) + (int64_t)min(col0 + l31, P.N - 1) * P.ldb + 4 * hi;
+  auto load = [&](float4 (&a)[4], float4 (&b)[4], int k) {
+    const int tap = k / C, c0 = k - tap * C;
+    int delta = c0;
+    if (mode != OP_PLAIN_K) {
+      const int kh = tap / g.KW, kw = tap - kh * g.KW;
+      if (mode == OP_CONV_FWD) delta += (kh * g.W + kw) * g.C;
+      else delta -= ((kh / g.stride) * g.W + (kw / g.stride)) * g.C;
+    }
+    const bool in = (mask >> tap) & 1u;
+    const float* p = Ap + (in ? base + delta : 0);  // a select, no branch: the loads go out together
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      a[s] = *reinterpret_cast<const float4*>(p + 8 * s);
+      b[s] = *reinterpret_cast<const float4*>(Bp + k + 8 * s);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      a[s].x = in ? a[s].x : 0.f;
+      a[s].y = in ? a[s].y : 0.f;
+      a[s].z = in ? a[s].z : 0.f;
+      a[s].w = in ? a[s].w : 0.f;
+    }
+  };
+  v16f_t acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  auto contract = [&](const float4 (&a)[4], const float4 (&b)[4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {  // transposed: see conv_epilogue
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[s].x, a[s].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[s].y, a[s].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[s].z, a[s].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[s].w, a[s].w, acc, 0, 0, 0);
+    }
+  };
+  constexpr int STEP = 4 * 32;
+  float4 a0[4], b0[4], a1[4], b1[4];
+  int k = 32 * wave;
+  if (k < P.K) load(a0, b0, k);
+  for (; k < P.K; k += 2 * STEP) {
+    if (k + STEP < P.K) load(a1, b1, k + STEP);
+    contract(a0, b0);
+    if (k + STEP >= P.K) break;
+    if (k + 2 * STEP < P.K) load(a0, b0, k + 2 * STEP);
+    contract(a1, b1);
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[v];
+  __syncthreads();
+  const int c = col0 + 8 * wave + 4 * hi;  // each wavefront finishes four columns per lane half
+  if (r >= P.M || c >= P.N) return;
+  const int64_t o = (int64_t)r * P.ldo + c;
+  float val[4], bias[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float* x = red + (4 * wave + e) * 64 + lane;
+    val[e] = (x[0] + x[1024]) + (x[2048] + x[3072]);
+    if (P.epi == EPI_FWD && P.aux0) bias[e] = static_cast<const float*>(P.aux0)[c + e];
+  }
+  conv_finish<float>(P, o, val, bias, P.aux1 ? *reinterpret_cast<const uint4*>(static_cast<const float*>(P.aux1) + o) : make_uint4(0, 0, 0, 0));
+}
+
 template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>
 static hipError_t launch_conv_gemm_inst(const GemmBatch& b, dim3 grid, hipStream_t stream) {
   constexpr int lds = conv_gemm_lds_bytes<T, BM, BN, BK, DB>();
@@ -853,6 +941,22 @@ void conv_gemm_tile(const GemmProb* p, int n, int* bm, int* bn) {
   }
 }
 
+// Launches of conv_gemm_few_kernel: fp32, up to three workgroups per CU, and no workspace in which 64 x 64 tiles could share
+// their reductions over workgroups (with it those are the faster ones: a ResNet-18-shaped fp32 step of 4 samples 3.03 against
+// 3.38 ms).  64 x 64 tiles without it against these, us: 256 tiles, 4608 deep 130 / 37; 512 tiles, 2304 deep 68 / 36; 600
+// tiles, 768 deep 27 / 23; 1024 tiles, 1152 deep 39 / 40; 1568 tiles, 64 deep 8.9 / 9.3.
+static bool conv_few_tiles(const GemmBatch& b, int dtype) {
+  if (dtype != DT_F32 || b.thin_ws) return false;
+  const GemmProb* p = b.p;
+  int64_t tiles = 0;
+  for (int i = 0; i < b.n; ++i) {
+    if (p[i].M <= 0 || p[i].N <= 0 || p[i].K <= 0 || p[i].epi == EPI_WGRAD || !conv_fast_eligible(p[i], dtype)) return false;
+    if ((p[i].a_mode == OP_PLAIN_K ? p[i].K : p[i].g.C) % 32) return false;
+    tiles += (int64_t)((p[i].M + 31) / 32) * ((p[i].N + 31) / 32);
+  }
+  return tiles <= 768;
+}
+
 // (bf16 launches short of workgroups run on the direct-to-LDS tiles instead, whatever tile was asked for)
 hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
@@ -861,6 +965,18 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
   const int bk = dtype == DT_BF16 ? 32 : 16;
   int total = 0;
   if (const int dl = conv_dl_tile(b.p, b.n, dtype)) return launch_conv_dl(b, dtype, dl, stream);
+  if (conv_few_tiles(b, dtype)) {
+    for (int i = 0; i < b.n; ++i) {
+      GemmProb& p = b.p[i];
+      p.splits = 1;
+      p.tiles_n = (p.N + 31) / 32;
+      p.tile_begin = total;
+      total += ((p.M + 31) / 32) * p.tiles_n;
+    }
+    b.total_tiles = total;
+    hipLaunchKernelGGL(conv_gemm_few_kernel, dim3(total), dim3(256), 0, stream, b);
+    return hipGetLastError();
+  }
   bool deep = true;  // every problem allows the double-depth slab
   bool ragged = false;
   for (int i = 0; i < b.n; ++i) {

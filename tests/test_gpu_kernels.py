@@ -394,3 +394,12 @@ def test_conv_channels_not_whole_slabs(dtype, case):
     """Channel counts that are whole 16-byte chunks but not whole reduction slabs: slabs across taps, a partial last slab,
     strides 1 to 3, every tile shape."""
     test_conv_passes_match_oracle(dtype, case)
+
+
+@pytest.mark.parametrize("case", [(1, 1, 1, 32, 32, 1, 1, 0), (1, 5, 7, 96, 36, 1, 1, 0), (3, 9, 9, 64, 160, 3, 2, 1), (2, 8, 8, 32, 32, 5, 1, 2),
+                                  (1, 1, 33, 160, 96, 1, 1, 0), (2, 11, 13, 32, 64, 3, 3, 1), (16, 1, 48, 64, 1024, 1, 1, 0),
+                                  (16, 1, 49, 64, 1024, 1, 1, 0)])
+def test_conv_few_tiles_fp32(case):
+    """Tiles of 32 x 32 whose wavefronts share the reduction: one element of a tile, rows and columns past it, fewer slabs than
+    wavefronts and one more, taps off the stride lattice, the last count of tiles that takes it and the first that does not."""
+    test_conv_passes_match_oracle(wl.F32, case)
