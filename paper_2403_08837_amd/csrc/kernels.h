@@ -324,6 +324,5 @@ int attention_launches(bool backward, int B, int NT, int D, int heads, int dtype
 
 // T -> f32 copy (cdp_get_weights of a ring copy).
 hipError_t launch_to_f32(const void* src, float* dst, int64_t n, int dtype, hipStream_t stream);
-hipError_t launch_fill_f32(float* dst, int64_t n, float v, hipStream_t stream);
 
 }  // namespace cdp

@@ -695,13 +695,5 @@ hipError_t launch_to_f32(const void* src, float* dst, int64_t n, int dtype, hipS
                                          static_cast<const T*>(src), dst, n));
   return hipGetLastError();
 }
-__global__ void fill_f32_kernel(float* __restrict__ dst, int64_t n, float v) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) dst[i] = v;
-}
-hipError_t launch_fill_f32(float* dst, int64_t n, float v, hipStream_t stream) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_f32_kernel, dim3(blocks_for(n, 256, 4096)), dim3(256), 0, stream, dst, n, v);
-  return hipGetLastError();
-}
 
 }  // namespace cdp
