@@ -264,9 +264,9 @@ static bool conv_dl_eligible(const GemmProb& p, int dtype, int bk) {
 }
 bool conv_gemm256_eligible(const GemmProb& p, int dtype) { return conv_dl_eligible(p, dtype, 64); }
 
-// Worth it (measured against the 128 x 128 tile of conv_gemm_kernel: 880 vs 720 TFLOP/s on a 3x3 convolution
-// over 512 channels with 25088 rows, 1050 TFLOP/s on an 8192^3 product, but 705 vs 745 on 25088 x 2048 x 2048,
-// where the 784 tiles make 3.06 rounds of one workgroup per CU): long reductions (the tile's prologue and
+// Worth it (against the 256 x 128 tile: 1050 vs 911 TFLOP/s on a 3x3 convolution over 512 channels with 25088 rows, 1154 vs
+// 1077 on an 8192^3 product, but 795-864 vs 888 on 25088 x 2048 x 2048, where the 784 tiles make 3.06 rounds of one
+// workgroup per CU): long reductions (the tile's prologue and
 // epilogue are paid once per 256 x 256 outputs), mostly full tiles, and a tile count that rounds well to the CUs.
 bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype) {
   constexpr int BM = 256, BN = 256, BK = 64;
