@@ -28,15 +28,15 @@ bool HostReader::prepare() {
 }
 
 // Pieces thread, thread + THREADS, ... of the range.
-hipError_t HostReader::work(int thread, char* dst, const char* src, size_t bytes, hipStream_t stream) {
+hipError_t HostReader::work(int thread, char* dst, const char* src, size_t bytes) {
   const size_t pieces = (bytes + PIECE - 1) / PIECE;
   auto len = [&](size_t p) { return std::min(PIECE, bytes - p * PIECE); };
   auto buffer = [&](size_t n) { return pinned_ + ((size_t)thread * DEPTH + n % DEPTH) * PIECE; };
   auto request = [&](size_t n) -> hipError_t {  // the thread's n-th piece
     const size_t p = thread + n * THREADS;
     if (p >= pieces) return hipSuccess;
-    hipError_t e = hipMemcpyAsync(buffer(n), src + p * PIECE, len(p), hipMemcpyDeviceToHost, stream);
-    return e != hipSuccess ? e : hipEventRecord(event_[thread * DEPTH + n % DEPTH], stream);
+    hipError_t e = hipMemcpyAsync(buffer(n), src + p * PIECE, len(p), hipMemcpyDeviceToHost, nullptr);
+    return e != hipSuccess ? e : hipEventRecord(event_[thread * DEPTH + n % DEPTH], nullptr);
   };
   hipError_t e = request(0);
   for (size_t n = 0; e == hipSuccess && thread + n * THREADS < pieces; ++n) {
@@ -49,11 +49,12 @@ hipError_t HostReader::work(int thread, char* dst, const char* src, size_t bytes
 }
 
 hipError_t HostReader::read(void* dst, const void* src, size_t bytes, hipStream_t stream) {
+  // The wait is the calling thread's: a handle may mean another stream in another thread (hipStreamPerThread).  The copies are
+  // the null stream's, as those of a plain hipMemcpy, which every thread means the same by.
+  hipError_t e = hipStreamSynchronize(stream);
+  if (e != hipSuccess) return e;
   int device = 0;
-  if (bytes < WORTH || hipGetDevice(&device) != hipSuccess || !prepare()) {
-    hipError_t e = hipStreamSynchronize(stream);
-    return e != hipSuccess ? e : hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
-  }
+  if (bytes < WORTH || hipGetDevice(&device) != hipSuccess || !prepare()) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
   char* to = static_cast<char*>(dst);
   const char* from = static_cast<const char*>(src);
   std::thread helper[THREADS];
@@ -61,20 +62,19 @@ hipError_t HostReader::read(void* dst, const void* src, size_t bytes, hipStream_
   int started = 1;
   try {
     for (; started < THREADS; ++started)
-      helper[started] = std::thread([this, started, device, to, from, bytes, stream, &result] {
-        hipError_t e = hipSetDevice(device);  // the current device is the thread's own
-        result[started] = e != hipSuccess ? e : work(started, to, from, bytes, stream);
+      helper[started] = std::thread([this, started, device, to, from, bytes, &result] {
+        const hipError_t set = hipSetDevice(device);  // the current device is the thread's own
+        result[started] = set != hipSuccess ? set : work(started, to, from, bytes);
       });
   } catch (const std::system_error&) {  // no more threads to be had: their pieces are this thread's too
   }
-  result[0] = work(0, to, from, bytes, stream);
-  for (int t = started; t < THREADS; ++t) result[t] = work(t, to, from, bytes, stream);
-  hipError_t e = hipSuccess;
+  result[0] = work(0, to, from, bytes);
+  for (int t = started; t < THREADS; ++t) result[t] = work(t, to, from, bytes);
   for (int t = 0; t < THREADS; ++t) {
     if (helper[t].joinable()) helper[t].join();
     if (e == hipSuccess) e = result[t];
   }
-  if (e != hipSuccess) (void)hipStreamSynchronize(stream);  // nothing is left in flight into the pinned buffers
+  if (e != hipSuccess) (void)hipStreamSynchronize(nullptr);  // nothing is left in flight into the pinned buffers
   return e;
 }
 

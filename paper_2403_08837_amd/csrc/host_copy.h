@@ -26,7 +26,7 @@ class HostReader {
   static constexpr size_t WORTH = 16u << 20;
   bool prepare();
   void release();
-  hipError_t work(int thread, char* dst, const char* src, size_t bytes, hipStream_t stream);
+  hipError_t work(int thread, char* dst, const char* src, size_t bytes);
   char* pinned_ = nullptr;
   hipEvent_t event_[THREADS * DEPTH] = {};
 };

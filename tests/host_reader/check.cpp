@@ -1,0 +1,75 @@
+// HostReader (host_copy.cpp) against the HIP stand-in beside this file.  check NAME: exit code 0 when it holds.
+#include "host_copy.h"
+
+#include <cstdio>
+#include <cstring>
+#include <string>
+
+using cdp::HostReader;
+
+namespace {
+
+constexpr size_t BIG = (33u << 20) + 12;  // above the size from which threads copy, and not a whole number of pieces
+std::vector<char> device_memory(BIG), host_memory(BIG);
+
+void fill(std::vector<char>& v, unsigned seed) {
+  for (size_t i = 0; i < v.size(); ++i) v[i] = (char)((i * 2654435761u + seed) >> 13);
+}
+// Work that writes the weights, enqueued on `s`, and what it writes.
+std::vector<char> enqueue_update(hipStream_t s, unsigned seed) {
+  std::vector<char> want(BIG);
+  fill(want, seed);
+  std::lock_guard<std::recursive_mutex> l(stub::mutex);
+  stub::push(s, [want] { std::memcpy(device_memory.data(), want.data(), BIG); });
+  return want;
+}
+bool reads(HostReader& r, hipStream_t s, const std::vector<char>& want, size_t bytes = BIG) {
+  fill(host_memory, 99);
+  const hipError_t e = r.read(host_memory.data(), device_memory.data(), bytes, s);
+  if (e != hipSuccess) { std::printf("read: error %d\n", (int)e); return false; }
+  if (std::memcmp(host_memory.data(), want.data(), bytes)) { std::printf("read: stale or wrong bytes\n"); return false; }
+  return true;
+}
+
+// Every kind of stream handle that a context can be given, twice each, and a size that one plain copy serves.
+bool order() {
+  stub::Stream own;
+  stub::created.push_back(&own);
+  for (hipStream_t s : {(hipStream_t) nullptr, hipStreamPerThread, &own}) {
+    HostReader r;
+    for (unsigned k = 1; k < 3; ++k)
+      if (!reads(r, s, enqueue_update(s, k))) return false;
+    if (!reads(r, s, enqueue_update(s, 7), 4096)) return false;
+  }
+  return stub::pinned_now == 0 && stub::events_now == 0;
+}
+
+// A copy that fails is reported, and nothing writes into the buffers afterwards.
+bool failing_copy() {
+  for (int n : {0, 3, 9}) {
+    HostReader r;
+    auto want = enqueue_update(hipStreamPerThread, 3);
+    stub::fail_copy = stub::async_copies + n;
+    if (r.read(host_memory.data(), device_memory.data(), BIG, hipStreamPerThread) == hipSuccess) return false;
+    stub::fail_copy = -1;
+    for (auto& t : stub::per_thread)
+      if (t.second.done != t.second.work.size()) return false;
+    for (auto& t : stub::legacy)
+      if (t.second.done != t.second.work.size()) return false;
+    if (!reads(r, hipStreamPerThread, want)) return false;
+  }
+  return true;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string name = argc > 1 ? argv[1] : "";
+  bool ok = false;
+  stub::late = std::this_thread::get_id();
+  if (name == "order") ok = order();
+  else if (name == "failing_copy") ok = failing_copy();
+  else std::printf("no such check\n");
+  std::printf("%s: %s\n", name.c_str(), ok ? "holds" : "FAILS");
+  return ok ? 0 : 1;
+}
