@@ -2,7 +2,7 @@
 
 #include <algorithm>
 #include <cstring>
-#include <system_error>
+#include <exception>
 #include <thread>
 
 namespace cdp {
@@ -66,7 +66,7 @@ hipError_t HostReader::read(void* dst, const void* src, size_t bytes, hipStream_
         const hipError_t set = hipSetDevice(device);  // the current device is the thread's own
         result[started] = set != hipSuccess ? set : work(started, to, from, bytes);
       });
-  } catch (const std::system_error&) {  // no more threads to be had: their pieces are this thread's too
+  } catch (const std::exception&) {  // no more threads to be had, or no memory for one: their pieces are this thread's too
   }
   result[0] = work(0, to, from, bytes);
   for (int t = started; t < THREADS; ++t) result[t] = work(t, to, from, bytes);

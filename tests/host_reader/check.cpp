@@ -3,7 +3,18 @@
 
 #include <cstdio>
 #include <cstring>
+#include <new>
 #include <string>
+
+// Allocations of the thread that armed this, outside the stand-in, until one of them fails (-1: none does).
+static thread_local int allocations_left = -1;
+void* operator new(size_t n) {
+  if (!stub::quiet && allocations_left >= 0 && allocations_left-- == 0) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 using cdp::HostReader;
 
@@ -61,6 +72,22 @@ bool failing_copy() {
   return true;
 }
 
+// No memory for the k-th helper thread: the call does without it, and nothing is thrown.
+bool no_memory_for_threads() {
+  for (int k = 0; k < 3; ++k) {
+    HostReader r;
+    if (!reads(r, nullptr, enqueue_update(nullptr, 1))) return false;  // buffers and events are there
+    auto want = enqueue_update(nullptr, 20 + k);
+    fill(host_memory, 99);
+    allocations_left = k;
+    const hipError_t e = r.read(host_memory.data(), device_memory.data(), BIG, nullptr);
+    const bool fired = allocations_left < 0;
+    allocations_left = -1;
+    if (!fired || e != hipSuccess || std::memcmp(host_memory.data(), want.data(), BIG)) return false;
+  }
+  return true;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -69,6 +96,7 @@ int main(int argc, char** argv) {
   stub::late = std::this_thread::get_id();
   if (name == "order") ok = order();
   else if (name == "failing_copy") ok = failing_copy();
+  else if (name == "no_memory_for_threads") ok = no_memory_for_threads();
   else std::printf("no such check\n");
   std::printf("%s: %s\n", name.c_str(), ok ? "holds" : "FAILS");
   return ok ? 0 : 1;
