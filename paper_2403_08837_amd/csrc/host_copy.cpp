@@ -16,8 +16,9 @@ void HostReader::release() {
   pinned_ = nullptr;
 }
 
-bool HostReader::prepare() {
-  if (pinned_) return true;
+bool HostReader::prepare(int device) {
+  if (pinned_) return device == device_;  // events are recorded on streams of the device that was current when they were made
+  device_ = device;
   bool ok = hipHostMalloc(reinterpret_cast<void**>(&pinned_), THREADS * DEPTH * PIECE, hipHostMallocDefault) == hipSuccess;
   for (hipEvent_t& e : event_) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
   if (!ok) {
@@ -54,7 +55,7 @@ hipError_t HostReader::read(void* dst, const void* src, size_t bytes, hipStream_
   hipError_t e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return e;
   int device = 0;
-  if (bytes < WORTH || hipGetDevice(&device) != hipSuccess || !prepare()) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+  if (bytes < WORTH || hipGetDevice(&device) != hipSuccess || !prepare(device)) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
   char* to = static_cast<char*>(dst);
   const char* from = static_cast<const char*>(src);
   std::thread helper[THREADS];

@@ -24,9 +24,10 @@ class HostReader {
   static constexpr size_t PIECE = 2u << 20;
   // From here on the threads and pinned buffers pay (below it one plain copy).
   static constexpr size_t WORTH = 16u << 20;
-  bool prepare();
+  bool prepare(int device);
   void release();
   hipError_t work(int thread, char* dst, const char* src, size_t bytes);
+  int device_ = 0;
   char* pinned_ = nullptr;
   hipEvent_t event_[THREADS * DEPTH] = {};
 };

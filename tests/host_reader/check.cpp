@@ -88,6 +88,20 @@ bool no_memory_for_threads() {
   return true;
 }
 
+// Calling threads whose current device differs from call to call; the context's stream is on device 0.
+bool other_device() {
+  stub::Stream own;
+  stub::created.push_back(&own);
+  HostReader r;
+  bool ok = true;
+  for (int d : {0, 1, 0, 1}) {
+    stub::device = d;
+    ok = ok && reads(r, &own, enqueue_update(&own, 30 + d));
+  }
+  stub::device = 0;
+  return ok;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -97,6 +111,7 @@ int main(int argc, char** argv) {
   if (name == "order") ok = order();
   else if (name == "failing_copy") ok = failing_copy();
   else if (name == "no_memory_for_threads") ok = no_memory_for_threads();
+  else if (name == "other_device") ok = other_device();
   else std::printf("no such check\n");
   std::printf("%s: %s\n", name.c_str(), ok ? "holds" : "FAILS");
   return ok ? 0 : 1;
