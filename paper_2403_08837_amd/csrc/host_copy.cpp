@@ -55,7 +55,8 @@ hipError_t HostReader::read(void* dst, const void* src, size_t bytes, hipStream_
   hipError_t e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return e;
   int device = 0;
-  if (bytes < WORTH || hipGetDevice(&device) != hipSuccess || !prepare(device)) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+  std::unique_lock<std::mutex> mine(in_use_, std::try_to_lock);  // the buffers serve one call at a time
+  if (bytes < WORTH || !mine.owns_lock() || hipGetDevice(&device) != hipSuccess || !prepare(device)) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
   char* to = static_cast<char*>(dst);
   const char* from = static_cast<const char*>(src);
   std::thread helper[THREADS];

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <mutex>
 
 namespace cdp {
 
@@ -16,7 +17,7 @@ class HostReader {
   HostReader(const HostReader&) = delete;
   HostReader& operator=(const HostReader&) = delete;
   ~HostReader();
-  // Copies after everything enqueued on `stream` so far; returns when dst is written.  One call at a time per object.
+  // Copies after everything enqueued on `stream` so far; returns when dst is written.
   hipError_t read(void* dst, const void* src, size_t bytes, hipStream_t stream);
 
  private:
@@ -27,6 +28,7 @@ class HostReader {
   bool prepare(int device);
   void release();
   hipError_t work(int thread, char* dst, const char* src, size_t bytes);
+  std::mutex in_use_;
   int device_ = 0;
   char* pinned_ = nullptr;
   hipEvent_t event_[THREADS * DEPTH] = {};

@@ -102,6 +102,26 @@ bool other_device() {
   return ok;
 }
 
+// Two threads that read different vectors of one context at a time.
+bool two_callers() {
+  std::vector<char> source[2] = {std::vector<char>(BIG), std::vector<char>(BIG)};
+  for (int k = 0; k < 4; ++k) {
+    HostReader r;
+    bool ok[2] = {false, false};
+    std::thread t[2];
+    for (int c = 0; c < 2; ++c) fill(source[c], 40 + 2 * k + c);
+    for (int c = 0; c < 2; ++c) {
+      t[c] = std::thread([&, c] {
+        std::vector<char> host(BIG);
+        ok[c] = r.read(host.data(), source[c].data(), BIG, nullptr) == hipSuccess && host == source[c];
+      });
+    }
+    for (auto& x : t) x.join();
+    if (!ok[0] || !ok[1]) return false;
+  }
+  return true;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -112,6 +132,7 @@ int main(int argc, char** argv) {
   else if (name == "failing_copy") ok = failing_copy();
   else if (name == "no_memory_for_threads") ok = no_memory_for_threads();
   else if (name == "other_device") ok = other_device();
+  else if (name == "two_callers") ok = two_callers();
   else std::printf("no such check\n");
   std::printf("%s: %s\n", name.c_str(), ok ? "holds" : "FAILS");
   return ok ? 0 : 1;

@@ -135,8 +135,11 @@ inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t h) {
 }
 inline hipError_t hipEventSynchronize(hipEvent_t e) {
   stub::Quiet q;
-  std::lock_guard<std::recursive_mutex> l(stub::mutex);
-  if (e->stream) stub::run(e->stream, e->upto);
+  {
+    std::lock_guard<std::recursive_mutex> l(stub::mutex);
+    if (e->stream) stub::run(e->stream, e->upto);
+  }
+  std::this_thread::sleep_for(std::chrono::milliseconds(2));  // the host is slow to see it: others run in between
   return hipSuccess;
 }
 inline hipError_t hipStreamSynchronize(hipStream_t h) {
