@@ -28,6 +28,15 @@ bool HostReader::prepare(int device) {
   return ok;
 }
 
+// Memory that the device writes by itself: a plain copy is one transfer there, and the faster way (16.8 MB 300 us against 530 us
+// through buffers, 67 MB 1186 against 1736 us).
+static bool pinned(const void* p) {
+  hipPointerAttribute_t at;
+  const hipError_t e = hipPointerGetAttributes(&at, p);
+  if (e != hipSuccess) (void)hipGetLastError();  // ordinary memory
+  return e == hipSuccess && at.type != hipMemoryTypeUnregistered;
+}
+
 // Pieces thread, thread + THREADS, ... of the range.
 hipError_t HostReader::work(int thread, char* dst, const char* src, size_t bytes) {
   const size_t pieces = (bytes + PIECE - 1) / PIECE;
@@ -56,7 +65,8 @@ hipError_t HostReader::read(void* dst, const void* src, size_t bytes, hipStream_
   if (e != hipSuccess) return e;
   int device = 0;
   std::unique_lock<std::mutex> mine(in_use_, std::try_to_lock);  // the buffers serve one call at a time
-  if (bytes < WORTH || !mine.owns_lock() || hipGetDevice(&device) != hipSuccess || !prepare(device)) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+  if (bytes < WORTH || !mine.owns_lock() || pinned(dst) || hipGetDevice(&device) != hipSuccess || !prepare(device))
+    return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
   char* to = static_cast<char*>(dst);
   const char* from = static_cast<const char*>(src);
   std::thread helper[THREADS];

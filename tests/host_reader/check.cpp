@@ -122,6 +122,16 @@ bool two_callers() {
   return true;
 }
 
+// Memory that the device reaches by itself needs no help from the host: one copy.
+bool pinned_by_caller() {
+  HostReader r;
+  stub::pinned_by_caller = host_memory.data();
+  const bool ok = reads(r, nullptr, enqueue_update(nullptr, 50));
+  stub::pinned_by_caller = nullptr;
+  if (!ok || stub::async_copies != 0 || stub::plain_copies != 1) return false;
+  return reads(r, nullptr, enqueue_update(nullptr, 51)) && stub::async_copies > 0 && stub::plain_copies == 1;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -133,6 +143,7 @@ int main(int argc, char** argv) {
   else if (name == "no_memory_for_threads") ok = no_memory_for_threads();
   else if (name == "other_device") ok = other_device();
   else if (name == "two_callers") ok = two_callers();
+  else if (name == "pinned_by_caller") ok = pinned_by_caller();
   else std::printf("no such check\n");
   std::printf("%s: %s\n", name.c_str(), ok ? "holds" : "FAILS");
   return ok ? 0 : 1;

@@ -46,6 +46,7 @@ inline std::map<int, Stream> legacy;                                      // per
 inline std::map<std::pair<std::thread::id, int>, Stream> per_thread;      // hipStreamPerThread
 inline std::vector<Stream*> created;
 inline std::thread::id late;                                              // a thread whose copies come last
+inline const void* pinned_by_caller = nullptr;
 inline int pinned_now = 0, events_now = 0, plain_copies = 0, async_copies = 0, fail_copy = -1;
 
 inline Stream* find(hipStream_t s) {
@@ -92,6 +93,16 @@ inline void push(hipStream_t h, std::function<void()> f) {
 
 typedef stub::Event* hipEvent_t;
 
+enum hipMemoryType { hipMemoryTypeUnregistered = 0, hipMemoryTypeHost = 1 };
+struct hipPointerAttribute_t {
+  hipMemoryType type;
+};
+
+inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  if (p != stub::pinned_by_caller) return hipErrorInvalidValue;
+  a->type = hipMemoryTypeHost;
+  return hipSuccess;
+}
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline hipError_t hipGetDevice(int* d) { *d = stub::device; return hipSuccess; }
 inline hipError_t hipSetDevice(int d) { stub::device = d; return hipSuccess; }

@@ -19,12 +19,14 @@ def check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["order", "failing_copy", "no_memory_for_threads", "other_device", "two_callers"])
+@pytest.mark.parametrize("name", ["order", "failing_copy", "no_memory_for_threads", "other_device", "two_callers",
+                                  "pinned_by_caller"])
 def test_host_reader(check, name):
     """order: copies come after the work before them for every kind of stream handle, hipStreamPerThread (every thread's
     own) among them.  failing_copy: an error is reported and leaves nothing in flight.
     no_memory_for_threads: a thread that cannot be had is done without, nothing is thrown.
     other_device: the calling thread's current device may be another one than at the first call.
-    two_callers: two threads reading two stages of one context at a time each get theirs."""
+    two_callers: two threads reading two stages of one context at a time each get theirs.
+    pinned_by_caller: memory that is pinned already is written by one plain copy."""
     p = subprocess.run([check, name], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
