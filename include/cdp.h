@@ -15,7 +15,9 @@
  *     CDP_ESTATE and can only be read and destroyed;
  *   - "dev" pointers are HIP device pointers, "host" pointers are ordinary host memory;
  *   - the caller owns every pointer it passes (inputs, labels, output buffers, the
- *     arena, the stream); the library owns only cdp_ctx and sub-allocates the arena;
+ *     arena, the stream); the library owns only cdp_ctx and sub-allocates the arena.  With the
+ *     context go HIP events and, from the first cdp_get_weights of at least 16 MiB into memory
+ *     that is not pinned, 16 MiB of pinned host memory; cdp_destroy gives both back;
  *   - all device work is enqueued on opts->hip_stream; calls return without waiting
  *     unless stated otherwise;
  *   - indices are 0-based: stage j in [0,S), micro-batch i in [0,N), step t >= 0,
