@@ -14,7 +14,6 @@
 //     into an LDS table.  wgrad_reduce_kernel folds the ranges into G (scaled by gamma) and
 //     produces d gamma and d beta.
 #include <algorithm>
-#include <cmath>
 
 #include "conv_tile.h"
 #include "elem.h"
@@ -752,31 +751,33 @@ int conv_wgrad_splits(const GemmProb& p, int dtype, int wanted) {
   return std::max(1, std::min(nslab, std::max(wanted, min_splits)));
 }
 
-// Ranges of a problem launched on its own, at most `room` of them: the cheapest by what the launch costs.  Fitted to
-// measured launches of 14 shapes with 1 to 256 ranges each (5 to 144 tiles, 13 to 1568 slabs), which it follows within
-// about 15 %:
-//   bf16: a workgroup takes 1.6 us per slab alone on its CU (a chain of latencies), 1.75 us beside one other and 2.2 us
-//         beside two, which fill it; fp32: 3.3 us, matrix cores and all, so a second workgroup on a CU doubles it;
-//   every range writes its partial matrix once and the fold reads it once, at about 3.5 TB/s together.
-// (3072 x 768 over 6272 rows 86 -> 72 us against three ranges or one per 16 slabs, 128 x 1152 over 25088 37 -> 35,
-// 256 x 1024 over 6272 32 -> 27, fp32 128 x 576 over 800 37 -> 26)
+// Ranges of a problem launched on its own, at most `room` of them: the cheapest by what the launch costs.  A workgroup's slab
+// takes a chain of latencies alone on its CU and longer beside others; how much longer is matrix time, which depends on the type
+// and on the height of the tile.  The workgroups run in rounds of as many as a CU holds, and every range writes its partial
+// matrix once and the fold reads it once.  Fitted to 900 launches of 150 shapes (1 to 310 tiles, 1 to 12544 slabs, 1 to 784 ranges), rms
+// 2.5 % in fp32 and 5 % in bf16.  Against three ranges or one per 16 slabs, us:
+//   bf16 3072 x 768 over 6272 rows 86 -> 71, 128 x 1152 over 25088 37 -> 31, 136 x 19800 over 15129 265 -> 265;
+//   fp32 128 x 576 over 800 37 -> 25, 280 x 504 over 40656 178 -> 159, 144 x 936 over 87846 440 -> 431;
+//   104 shapes of 1 to 100 thousand rows 1.33 times as fast by the geometric mean, none slower.
 int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room) {
-  const bool bf16 = dtype == DT_BF16;
-  const int nslab = (p.K + wg_slab(dtype) - 1) / wg_slab(dtype), to = p.M >= 128 ? 128 : 64;
-  const double tiles = (double)((p.M + to - 1) / to) * ((p.N + 127) / 128);
-  const double range_us = 2.0 * 4.0 * p.M * (double)p.N / 3.5e6;
-  int best = 1;
+  // us per slab with 1, 2, .. workgroups on the CU: [fp32, bf16][tiles of 64, 128 rows]
+  static const double SLAB_US[2][2][4] = {{{1.95, 2.9, 3.9, 4.85}, {3.1, 5.15, 7.1, 9.4}}, {{1.25, 1.5, 1.7, 0.0}, {1.45, 1.8, 2.05, 0.0}}};
+  const bool bf16 = dtype == DT_BF16, tall = p.M >= 128;
+  const double* slab_us = SLAB_US[bf16][tall];
+  const int resident = bf16 ? 3 : 4, to = tall ? 128 : 64;
+  const int64_t nslab = ((int64_t)p.K + wg_slab(dtype) - 1) / wg_slab(dtype);
+  const int64_t tiles = (int64_t)((p.M + to - 1) / to) * ((p.N + 127) / 128);
+  const double range_us = 2.0 * 4.0 * p.M * (double)p.N / (bf16 ? 6e6 : 7e6);
+  int64_t best = 1;
   double best_us = 1e30;
-  for (int len = 1; len <= nslab; len += 1 + len / 8) {  // slabs per range
-    const int s = (nslab + len - 1) / len;
+  for (int64_t len = 1; len <= nslab; len += 1 + len / 16) {  // slabs per range
+    const int64_t s = (nslab + len - 1) / len;
     if (s > std::max(1, room)) continue;
-    const double wgs = tiles * s, per_cu = std::ceil(wgs / 256.0);
-    const double rounds = bf16 ? std::ceil(per_cu / 3.0) : 1.0;
-    const double slab_us = bf16 ? (per_cu >= 3 ? 2.2 : per_cu >= 2 ? 1.75 : 1.6) : 3.3 * per_cu;
-    const double us = rounds * len * slab_us + s * range_us;
+    const int64_t rounds = tiles * s / (256 * resident), rest = tiles * s - rounds * 256 * resident;
+    const double us = len * (rounds * slab_us[resident - 1] + (rest ? slab_us[(rest - 1) / 256] : 0.0)) + s * range_us;
     if (us < best_us) { best_us = us; best = s; }
   }
-  return best;
+  return (int)best;
 }
 
 // ---------------------------------------------------------------------------------
