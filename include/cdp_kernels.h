@@ -37,8 +37,9 @@ int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void
  *               channel counts that are multiples of 64
  * in0/in1: (x, w) | (dy, wt) | (dy, x).  `out` must not alias the inputs.
  * workspace (device, may be NULL): scratch for the split weight-gradient kernel.  Where the shape allows and it holds
- * at least one partial sum (4 * Cout*k*k*Cin bytes) the two-phase path is used, with at most
- * B*Ho*Wo / 512 + 4 of them; without, the generic single-pass kernel runs. */
+ * at least one partial sum (4 * Cout*k*k*Cin bytes) the two-phase path is used; without, the generic single-pass kernel
+ * runs.  How many ranges the reduction is cut into, and with it the order of the sums, depends on the shape alone where the
+ * workspace holds B*Ho*Wo / 512 + 4 partial sums; a smaller one may mean fewer ranges (other roundings, slower). */
 int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out, int B, int H, int W,
                int Cin, int Cout, int ksize, int stride, int pad, void* workspace,
                size_t workspace_bytes, void* stream);

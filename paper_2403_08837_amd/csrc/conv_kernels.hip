@@ -15,6 +15,7 @@
 //     produces d gamma and d beta.
 #include <algorithm>
 
+#include "../../include/cdp_kernels.h"
 #include "conv_tile.h"
 #include "elem.h"
 #include "kernels.h"
@@ -759,6 +760,9 @@ int conv_wgrad_splits(const GemmProb& p, int dtype, int wanted) {
 //   bf16 3072 x 768 over 6272 rows 86 -> 71, 128 x 1152 over 25088 37 -> 31, 136 x 19800 over 15129 265 -> 265;
 //   fp32 128 x 576 over 800 37 -> 25, 280 x 504 over 40656 178 -> 159, 144 x 936 over 87846 440 -> 431;
 //   104 shapes of 1 to 100 thousand rows 1.33 times as fast by the geometric mean, none slower.
+// A function of the shape where there is room for what it wants, which is what cdp_k_conv asks of its workspace and no more than
+// the library's own array where one per 16 slabs or three fit that: cdp_k_conv and cdp_k_conv_wgrad_static then add
+// in one order and give the same bits (costs up to 5 %: 128 x 1152 over 25088 in bf16 is 28 ranges, 34.8 us, instead of 49, 31.3 us).
 int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room) {
   // us per slab with 1, 2, .. workgroups on the CU: [fp32, bf16][tiles of 64, 128 rows]
   static const double SLAB_US[2][2][4] = {{{1.95, 2.9, 3.9, 4.85}, {3.1, 5.15, 7.1, 9.4}}, {{1.25, 1.5, 1.7, 0.0}, {1.45, 1.8, 2.05, 0.0}}};
@@ -768,11 +772,14 @@ int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room) {
   const int64_t nslab = ((int64_t)p.K + wg_slab(dtype) - 1) / wg_slab(dtype);
   const int64_t tiles = (int64_t)((p.M + to - 1) / to) * ((p.N + 127) / 128);
   const double range_us = 2.0 * 4.0 * p.M * (double)p.N / (bf16 ? 6e6 : 7e6);
+  int64_t most = std::max<int64_t>(1, std::min<int64_t>(room, (int64_t)p.K / 512 + 4));
+  const int64_t own = (int64_t)CDP_STATIC_SCRATCH_BYTES / (4ll * p.M * p.N);
+  if (conv_wgrad_splits(p, dtype, 3) <= own) most = std::min(most, own);
   int64_t best = 1;
   double best_us = 1e30;
   for (int64_t len = 1; len <= nslab; len += 1 + len / 16) {  // slabs per range
     const int64_t s = (nslab + len - 1) / len;
-    if (s > std::max(1, room)) continue;
+    if (s > most) continue;
     const int64_t rounds = tiles * s / (256 * resident), rest = tiles * s - rounds * 256 * resident;
     const double us = len * (rounds * slab_us[resident - 1] + (rest ? slab_us[(rest - 1) / 256] : 0.0)) + s * range_us;
     if (us < best_us) { best_us = us; best = s; }

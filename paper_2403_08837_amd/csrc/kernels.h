@@ -182,7 +182,7 @@ int conv_dl_tile(const GemmProb* p, int n, int dtype);
 hipError_t launch_conv_dl(GemmBatch& batch, int dtype, int tile, hipStream_t stream);
 // Weight gradient in two phases: launch_conv_wgrad writes per-range partial sums
 // (out = f32 [splits][Cout][Ncol], aux3 = f32 [splits][Cout] or NULL; splits: any number of ranges from 1 to
-// ceil(K / conv_wgrad_slab), conv_wgrad_splits gives what a problem launched on its own wants),
+// ceil(K / conv_wgrad_slab), conv_wgrad_splits gives at least `wanted` and one per 16 slabs while a launch is short of workgroups),
 // launch_wgrad_reduce folds them into the accumulators.
 int conv_wgrad_splits(const GemmProb& p, int dtype, int wanted);
 int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room);  // the same for a single call, at most `room` ranges

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstring>
 
 #include "../../include/cdp.h"
@@ -84,7 +85,7 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
   // same kernel choice as the engine: the fast implicit-GEMM paths where the shape allows
   if (which == 2) {
     const size_t range_bytes = (size_t)p.M * p.N * 4;
-    const int room = (int)std::min<size_t>((size_t)p.K / 512 + 4, workspace ? workspace_bytes / range_bytes : 0);
+    const int room = (int)std::min<size_t>(INT_MAX, workspace ? workspace_bytes / range_bytes : 0);
     if (conv_fast_eligible(p, dtype) && room >= 1) {
       const int splits = conv_wgrad_splits_alone(p, dtype, room);
       // two phases as in the engine: partial sums per reduction range, then the fold

@@ -7,8 +7,8 @@
 // everything after that uses that pointer.
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cstring>
-#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -73,13 +73,11 @@ extern "C" int cdp_k_conv_wgrad_static(int dtype, const void* dy, const void* x,
   if (!conv_fast_eligible(p, dtype))
     return fail(CDP_EINVAL, "cdp_k_conv_wgrad_static: shape not supported by the two-phase weight-gradient kernels "
                             "(channel counts must be whole 16-byte chunks, at most 32 taps)");
-  const int splits = conv_wgrad_splits(p, dtype, 3);
-  const size_t need = (size_t)splits * (size_t)p.M * (size_t)p.N * 4;
+  const int ranges = conv_wgrad_splits_alone(p, dtype, INT_MAX);
+  const size_t need = (size_t)ranges * (size_t)p.M * (size_t)p.N * 4;
   if (need > SCRATCH_BYTES)
     return fail(CDP_ENOMEM, "cdp_k_conv_wgrad_static: needs " + std::to_string(need) + " bytes of partial sums, the static scratch holds " +
                                 std::to_string(SCRATCH_BYTES) + "; use cdp_k_conv with a workspace");
-  const int room = (int)std::min<size_t>((size_t)p.K / 512 + 4, SCRATCH_BYTES / ((size_t)p.M * (size_t)p.N * 4));
-  const int ranges = conv_wgrad_splits_alone(p, dtype, room);
   void* ws = nullptr;
   int rc = scratch_ptr(&ws);
   if (rc) return rc;

@@ -45,6 +45,40 @@ def test_static_scratch_weight_gradient_equals_workspace_variant(dtype):
         assert err <= 1e-5, err     # fp32 accumulation of exactly representable products
 
 
+# bf16 / fp32: more ranges fit the workspace that cdp_k_conv asks for than the array; a 1x1 layer whose ranges only just fit; a
+# matrix of which the array holds a few ranges
+LARGE_CASES = [(32, 28, 28, 128, 128, 3, 1, 1), (8, 1, 196, 1024, 512, 1, 1, 0), (32, 14, 14, 192, 192, 3, 1, 1), (32, 14, 14, 256, 256, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("case", LARGE_CASES)
+def test_static_scratch_weight_gradient_equals_workspace_variant_near_the_limit(dtype, case):
+    """Bit for bit where the array is too small for the number of ranges that a workspace would allow, with the workspace that
+    the header asks for and with a larger one."""
+    import torch
+    B, H, W, Cin, Cout, ks, st, pad = case
+    tdt = torch.bfloat16 if dtype == wl.BF16 else torch.float32
+    Ho, Wo = (H + 2 * pad - ks) // st + 1, (W + 2 * pad - ks) // st + 1
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x = torch.randn((B, H, W, Cin), generator=gen, device="cuda").to(tdt)
+    dy = torch.randn((B, Ho, Wo, Cout), generator=gen, device="cuda").to(tdt)
+    outs = []
+    for sums in (B * Ho * Wo // 512 + 4, B * Ho * Wo // 64 + 4):
+        ws = torch.full((Cout * ks * ks * Cin * sums,), float("nan"), dtype=torch.float32, device="cuda")
+        outs.append(torch.full((Cout, ks, ks, Cin), float("nan"), dtype=torch.float32, device="cuda"))
+        b.cdp_k_conv(dtype, 2, dy.data_ptr(), x.data_ptr(), outs[-1].data_ptr(), B, H, W, Cin, Cout, ks, st, pad, ws.data_ptr(), ws.numel() * 4)
+    got = torch.full((Cout, ks, ks, Cin), float("nan"), dtype=torch.float32, device="cuda")
+    try:
+        b.cdp_k_conv_wgrad_static(dtype, dy.data_ptr(), x.data_ptr(), got.data_ptr(), B, H, W, Cin, Cout, ks, st, pad)
+        outs.append(got)
+    except b.CdpError as e:
+        assert e.code == b.CDP_ENOMEM and dtype == wl.F32 and ks == 3   # one per 16 slabs is already too many there
+    torch.cuda.synchronize()
+    for o in outs:
+        assert torch.isfinite(o).all() and torch.equal(o, outs[0])
+
+
 def test_static_scratch_rejects_what_does_not_fit():
     import torch
     x = torch.zeros(16, dtype=torch.float32, device="cuda")
