@@ -291,17 +291,24 @@ bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype) {
 // and past the line 6272 x 3072 x 768 56 / 53, 25088 x 768 x 768 43 / 51: three register-staged workgroups per CU cover for
 // each other there.  64 x 64: slabs of 64 for long reductions, of 32 (twice the workgroups per CU) for short ones
 // (6272 x 1024 x 256 13.5 against 11.9, 1568 x 512 x 4608 23.8 against 25.5) and for channel counts that are odd multiples of 32.
-int conv_dl_tile(const GemmProb* p, int n, int dtype) {
-  int64_t t128 = 0, narrow = 0, kmax = 0;
+// `shared`: there is a workspace in which workgroups can share a reduction.  A long reduction of few tiles is cut there (64 x 64
+// tiles of conv_gemm_kernel, up to eight workgroups each) where here it is one chain: the longer it is, the more tiles it takes before
+// the chip is busy with chains.  us, shared / here: 49 x 512 x 4608 10.9 / 22.5, 784 x 512 x 4608 17.8 / 22.7, 1568 x 512 x 4608 24.4 / 22.8;
+// 784 x 256 x 2304 11.5 / 13.5, 1568 x 256 x 2304 14.3 / 13.4; 392 x 512 x 2048 10.0 / 11.7, 784 x 512 x 2048 15.0 / 11.7; 1568 x 128 x 1152
+// 8.5 / 8.9, 3136 x 128 x 1152 10.3 / 9.0; 256 x 64 x 576 7.9 / 6.4.
+int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
+  int64_t t128 = 0, t64 = 0, narrow = 0, kmax = 0;
   bool slab64 = true, all_narrow = true;
   for (int i = 0; i < n; ++i) {
     if (!conv_dl_eligible(p[i], dtype, 32)) return 0;
     slab64 = slab64 && conv_dl_eligible(p[i], dtype, 64);
     all_narrow = all_narrow && p[i].N <= 64;
     t128 += (int64_t)((p[i].M + 127) / 128) * ((p[i].N + 127) / 128);
+    t64 += (int64_t)((p[i].M + 63) / 64) * ((p[i].N + 63) / 64);
     narrow += (int64_t)((p[i].M + 127) / 128);
     kmax = std::max<int64_t>(kmax, p[i].K);
   }
+  if (shared && kmax >= 1024 && t64 <= std::min<int64_t>(kmax / 24, 256)) return 0;
   if (all_narrow) return narrow < 384 ? DL_64x64_SHORT : 0;
   if (t128 >= 512) return 0;
   if (slab64 && t128 >= 256) return DL_256x128;

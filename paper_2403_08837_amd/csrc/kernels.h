@@ -178,7 +178,7 @@ hipError_t launch_conv_gemm(GemmBatch& batch, int dtype, int bm, int bn, hipStre
 enum ConvDlTile : int { DL_NONE = 0, DL_256x256, DL_256x128, DL_64x128, DL_64x64, DL_64x64_SHORT };
 bool conv_gemm256_eligible(const GemmProb& p, int dtype);
 bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype);
-int conv_dl_tile(const GemmProb* p, int n, int dtype);
+int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared);  // shared: there is a workspace to share reductions in
 hipError_t launch_conv_dl(GemmBatch& batch, int dtype, int tile, hipStream_t stream);
 // Weight gradient in two phases: launch_conv_wgrad writes per-range partial sums
 // (out = f32 [splits][Cout][Ncol], aux3 = f32 [splits][Cout] or NULL; splits: any number of ranges from 1 to

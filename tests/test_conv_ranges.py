@@ -1,6 +1,7 @@
-"""How many ranges the reduction of a convolution's weight gradient is cut into when it is launched on its own
-(conv_wgrad_splits_alone in csrc/conv_kernels.hip), asked of the built library.  No GPU: the count is host arithmetic, and the
-times it is held against were measured on one."""
+"""Rules by which convolution launches are laid out, asked of the built library: how many ranges the reduction of a weight gradient
+is cut into when it is launched on its own (conv_wgrad_splits_alone in csrc/conv_kernels.hip), and which forward / data-gradient
+launches share their reductions over workgroups (conv_dl_tile in csrc/conv256_kernels.hip).  No GPU: the rules are host
+arithmetic, and the times they are held against were measured on one."""
 import os
 import subprocess
 
@@ -11,20 +12,30 @@ LIB = os.path.join(ROOT, "paper_2403_08837_amd")
 F32, BF16 = 0, 1
 
 
-@pytest.fixture(scope="module")
-def ranges(tmp_path_factory):
+def _asker(tmp_path_factory, name):
+    """A small program that calls a rule of the library for every line of numbers it is given."""
     from paper_2403_08837_amd import binding
     binding.lib()  # fails here when the library has not been built
-    exe = str(tmp_path_factory.mktemp("conv_ranges") / "ranges")
+    exe = str(tmp_path_factory.mktemp("conv_ranges") / name)
     subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(LIB, "csrc"),
-                    os.path.join(ROOT, "tests", "conv_ranges", "ranges.cpp"), "-o", exe, os.path.join(LIB, "libcdp.so"),
+                    os.path.join(ROOT, "tests", "conv_ranges", name + ".cpp"), "-o", exe, os.path.join(LIB, "libcdp.so"),
                     "-Wl,-rpath," + LIB, "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True)
 
     def ask(problems):
-        text = "".join("%d %d %d %d %d\n" % p for p in problems)
+        text = "".join(" ".join("%d" % x for x in p) + "\n" for p in problems)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=60).stdout
         return [int(x) for x in out.split()]
     return ask
+
+
+@pytest.fixture(scope="module")
+def ranges(tmp_path_factory):
+    return _asker(tmp_path_factory, "ranges")
+
+
+@pytest.fixture(scope="module")
+def tiles(tmp_path_factory):
+    return _asker(tmp_path_factory, "tiles")
 
 
 # dtype, M (output channels), N (taps x input channels), K (positions), {ranges: us measured}; one count per 16 slabs or three
@@ -102,3 +113,19 @@ def test_refusal_names_the_bytes_of_the_launch(ranges, dtype):
             b.cdp_k_conv_wgrad_static(dtype, 64, 64, 64, k // width, 1, width, n, m, 1, 1, 0)
         assert e.value.code == b.CDP_ENOMEM and "needs %d bytes" % need in str(e.value), str(e.value)
     assert refused >= 2
+
+
+# M, N, K, us with the reduction shared over workgroups, us as one chain per tile
+SHARED = [(49, 512, 4608, 10.9, 22.5), (392, 512, 4608, 13.4, 22.6), (784, 512, 4608, 17.8, 22.7), (1568, 512, 4608, 24.4, 22.8),
+          (98, 1024, 9216, 15.2, 40.5), (392, 1024, 9216, 26.5, 40.8), (196, 256, 2304, 9.3, 13.4), (784, 256, 2304, 11.5, 13.5),
+          (1568, 256, 2304, 14.3, 13.4), (3136, 256, 2304, 17.5, 14.0), (49, 512, 2048, 8.2, 11.6), (392, 512, 2048, 10.0, 11.7),
+          (784, 512, 2048, 15.0, 11.7), (64, 64, 1024, 7.1, 7.7), (784, 512, 1024, 8.7, 7.7), (784, 128, 1152, 8.4, 8.9),
+          (3136, 128, 1152, 10.3, 9.0), (98, 512, 512, 7.2, 5.9), (256, 64, 576, 7.9, 6.4)]
+
+
+def test_long_reductions_of_few_tiles_are_shared(tiles):
+    """Where a workspace is there, the faster of the two; without one, never."""
+    got = tiles([(m, n, k, 1) for m, n, k, _, _ in SHARED])
+    for (m, n, k, shared_us, chain_us), tile in zip(SHARED, got):
+        assert (shared_us if tile == 0 else chain_us) <= 1.03 * min(shared_us, chain_us), (m, n, k, tile)
+    assert all(t != 0 for t in tiles([(m, n, k, 0) for m, n, k, _, _ in SHARED]))
