@@ -291,6 +291,8 @@ bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype) {
 // and past the line 6272 x 3072 x 768 56 / 53, 25088 x 768 x 768 43 / 51: three register-staged workgroups per CU cover for
 // each other there.  64 x 64: slabs of 64 for long reductions, of 32 (twice the workgroups per CU) for short ones
 // (6272 x 1024 x 256 13.5 against 11.9, 1568 x 512 x 4608 23.8 against 25.5) and for channel counts that are odd multiples of 32.
+// At most 64 output columns: the same two tiles up to 384 rows of 128; past two workgroups per CU very long reductions are
+// conv_gemm_kernel's (us, that / slabs of 64 / of 32: 34848 x 64 x 5184 58 / 55 / 67, 34848 x 64 x 9216 100 / 109 / 123, 45000 x 64 x 576 11.5 / 10.1 / 10.1).
 // `shared`: there is a workspace in which workgroups can share a reduction.  A long reduction of few tiles is cut there (64 x 64
 // tiles of conv_gemm_kernel, up to eight workgroups each) where here it is one chain: the longer it is, the more tiles it takes before
 // the chip is busy with chains.  us, shared / here: 49 x 512 x 4608 10.9 / 22.5, 784 x 512 x 4608 17.8 / 22.7, 1568 x 512 x 4608 24.4 / 22.8;
@@ -309,11 +311,12 @@ int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
     kmax = std::max<int64_t>(kmax, p[i].K);
   }
   if (shared && kmax >= 1024 && t64 <= std::min<int64_t>(kmax / 24, 256)) return 0;
-  if (all_narrow) return narrow < 384 ? DL_64x64_SHORT : 0;
+  const int t6464 = slab64 && kmax >= 1024 ? DL_64x64 : DL_64x64_SHORT;
+  if (all_narrow) return narrow < 384 && !(t64 > 512 && kmax > 7168) ? t6464 : 0;
   if (t128 >= 512) return 0;
   if (slab64 && t128 >= 256) return DL_256x128;
   if (slab64 && t128 >= 150) return DL_64x128;
-  return slab64 && kmax >= 1024 ? DL_64x64 : DL_64x64_SHORT;
+  return t6464;
 }
 
 hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream) {

@@ -129,3 +129,14 @@ def test_long_reductions_of_few_tiles_are_shared(tiles):
     for (m, n, k, shared_us, chain_us), tile in zip(SHARED, got):
         assert (shared_us if tile == 0 else chain_us) <= 1.03 * min(shared_us, chain_us), (m, n, k, tile)
     assert all(t != 0 for t in tiles([(m, n, k, 0) for m, n, k, _, _ in SHARED]))
+
+
+# M, N, K, us: conv_gemm_kernel, direct-to-LDS tiles of 64 x 64 with slabs of 64, of 32
+NARROW = [(34848, 64, 5184, 58.2, 54.9, 67.2), (40328, 64, 5184, 62.5, 57.3, 68.9), (48672, 64, 5184, 71.2, 64.3, 74.5),
+          (28800, 64, 9216, 87.6, 73.0, 81.8), (34848, 64, 9216, 99.8, 108.7, 123.0), (40328, 40, 9216, 103.9, 108.8, 116.9),
+          (12800, 64, 5184, 38.2, 25.4, 27.4), (28800, 64, 576, 9.8, 8.0, 7.9), (45000, 64, 1024, 17.5, 16.9, 18.7)]
+
+
+def test_narrow_launches_take_the_fastest_tile(tiles):
+    for (m, n, k, *us), tile in zip(NARROW, tiles([(m, n, k, 0) for m, n, k, *_ in NARROW])):
+        assert us[{0: 0, 4: 1, 5: 2}[tile]] <= 1.03 * min(us), (m, n, k, tile)
