@@ -316,10 +316,13 @@ def test_attention_kernels_match_oracle(dtype, B, T, D, heads):
 
 
 @pytest.mark.parametrize("B,T,D,heads", [(2, 208, 128, 2), (1, 17, 48, 3), (2, 224, 64, 1), (1, 400, 160, 2), (1, 321, 48, 1),
-                                         (1, 624, 64, 1), (1, 640, 64, 1)])
+                                         (1, 624, 64, 1), (1, 640, 64, 1), (1, 577, 128, 2), (1, 255, 80, 1), (1, 262, 96, 2),
+                                         (2, 364, 96, 2), (2, 368, 96, 2), (1, 384, 160, 2)])
 def test_attention_fused_edges(B, T, D, heads):
     """Edges of the fused kernels: token counts that end on 16 of a block of 32, one token past a step of 16, more than
-    256 tokens (scores contracted twice), the last count that fits LDS and one past it (separate kernels)."""
+    256 tokens (scores contracted twice), the last count that fits LDS and one past it (separate kernels); rows of
+    probabilities that start at any element, in each of the pieces that move at once; both sides of the line from which heads
+    of width 48 and 80 have their backward in separate kernels."""
     test_attention_kernels_match_oracle(wl.BF16, B, T, D, heads)
 
 
