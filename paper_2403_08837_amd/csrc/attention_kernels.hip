@@ -879,6 +879,11 @@ AttnArgs32 attn_args32(const void* qkv, const void* P, int NT, int D, int heads)
 // (16 x 8 x 512 of width 64: 270 us backward against 281 us, 4 x 8 x 1024 271 against 296 us; 16 x 8 x 384 157 against
 // 148 us, 1 x 8 x 1024 134 against 73 us), unless their rows end inside a 16-byte piece (8 x 12 x 577: 495 against 399 us);
 // forward the kernel is the faster one there too (152 against 142 us).
+// bf16 backward of more tokens than leave room for a second workgroup on a CU, in rows of whole 8-byte groups (where separate kernels do
+// not go element by element): heads of width 48, whose products are padded to 64 columns, are faster in separate kernels when the
+// last round of workgroups is not full, and only up to 1.18 times slower when it is (us, separate / here: 72 heads x 416 tokens 88 / 124, 48 x 656
+// 153 / 199, 96 x 500 141 / 156, 96 x 600 215 / 191, 4 x 624 70 / 63); heads of width 80 with a second round of few or a first of very
+// few (72 x 416 124 / 137, 4 x 384 45 / 47; 64 x 416 120 / 72).
 bool attention_fused(bool backward, int B, int NT, int D, int heads, int dtype) {
   if (heads <= 0 || NT <= 0 || D % heads) return false;
   const int dh = D / heads;
@@ -887,7 +892,12 @@ bool attention_fused(bool backward, int B, int NT, int D, int heads, int dtype) 
     if (dh % 8 || dh > 96 || NT > 1024) return false;
     return !backward || blocks <= 8 || NT % 4 != 0 || (int64_t)B * heads * blocks * blocks <= 24576;
   }
-  return dh % 16 == 0 && dh <= 80 && attn_lds(NT, dh) <= ATTN_LDS;
+  if (dh % 16 || dh > 80 || attn_lds(NT, dh) > ATTN_LDS) return false;
+  if (backward && NT % 4 == 0 && attn_lds(NT, dh) > ATTN_LDS / 2) {
+    const int64_t wgs = (int64_t)B * heads * ((NT + 127) / 128);
+    if (dh == 48 || (dh == 80 && NT > 370 && (wgs < 32 || (wgs > 256 && wgs <= 320)))) return false;
+  }
+  return true;
 }
 bool attention_fused_fwd_ok(const void* qkv, const void* out, int B, int NT, int D, int heads, int dtype) {
   return attention_fused(false, B, NT, D, heads, dtype) && aligned(qkv, 16) && aligned(out, dtype == DT_F32 ? 16 : 8);
