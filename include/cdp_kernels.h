@@ -18,7 +18,8 @@ extern "C" {
  * backward computation of a stage on one micro-batch).
  *   dtype      0 fp32, 1 bf16 (operand element type)
  *   tile_shape 0: 128x128, 1: 64x128, 2: 64x64 workgroup tile of the generic kernel (with a_kmajor =
- *              b_kmajor = 0, a weight gradient, all three run the tiles the Linear stages use for it);
+ *              b_kmajor = 0, a weight gradient, all three run the tiles the Linear stages use for it
+ *              where those are faster: in fp32 not for large results in odd layouts or of very few rows);
  *              3: 64x64, 4: 64x128 tile of the weight-streaming kernel the Linear stages
  *              use; 5: what is fastest for a Linear layer on its own: a kernel for one problem of few
  *              rows and 16-byte-chunked operands, else the tiles the engine launches (3..5 need

@@ -154,6 +154,9 @@ hipError_t launch_gemm_batch(GemmBatch& batch, int dtype, int tile_shape, hipStr
 bool gemm_stream_wanted(const void* A, const void* B, int M, int N, int K, int lda, int ldb, int dtype);
 hipError_t launch_gemm_stream(const void* A, const void* B, float* C, int M, int N, int K, int lda, int ldb, int dtype, hipStream_t stream);
 
+// cdp_k_gemm with both operands row-contiguous: on the weight-gradient tiles of the Linear launch, not the generic kernel (kernels_api.cpp).
+bool gemm_wgrad_tiles_wanted(int tile_shape, int M, int N, int K, int lda, int ldb, int dtype);
+
 // HBM-streaming variants for Linear layers with a small batch (plain operands only):
 //   skinny: forward / data gradient, operands both k-contiguous; wide = 128-column tiles.
 //   dw:     weight gradient G (+)= dY^T X with A = dY (OP_PLAIN_R), B = X (OP_PLAIN_R),

@@ -11,6 +11,20 @@
 
 using namespace cdp;
 
+// Both operands run along the output (a weight gradient): the weight-gradient tiles of the Linear launch read them as they lie and
+// transpose on the way out of LDS, where the generic kernel scatters 2- or 4-byte elements into LDS.  Against the generic kernel's
+// best tile over outputs of 64 x 64 to 4096 x 4096, 8 to 4096 rows: fp32 64 x 64 x 8 13 -> 7 us, bf16 4096 x 4096 x 64 52 -> 16 us,
+// 4096^3 1124 -> 271 us.  Not so in fp32 for large results on the generic kernel's 128 x 128 tile, where what counts is how the result
+// leaves: if rows of an operand are not whole 16-byte chunks (us, generic / these: 4001 x 3003 x 16 29 / 40, x 64 55 / 50, x 2000 830 / 945), and for
+// up to one slab of 16 if rows of the result are not whole 128-byte lines (4672 x 2320 x 16 24 / 28, x 17 35 / 28, 4096 x 4096 x 8 40 / 30).  At
+// 512 tiles of 64 x 128 these are 1.5 times as fast, at 1025 they are not.
+bool cdp::gemm_wgrad_tiles_wanted(int tile_shape, int M, int N, int K, int lda, int ldb, int dtype) {
+  if (dtype != DT_F32 || tile_shape != TILE_128x128) return true;
+  if ((int64_t)((M + 63) / 64) * ((N + 127) / 128) < 768) return true;
+  const bool whole = M % 4 == 0 && N % 4 == 0 && lda % 4 == 0 && ldb % 4 == 0;
+  return whole && (K > 16 || N % 32 == 0);
+}
+
 extern "C" {
 
 int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void* A, const void* B, float* C, int M, int N,
@@ -29,11 +43,7 @@ int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void
   p.epi = EPI_FWD;
   p.flags = GF_OUT_F32;
   p.splits = 1;
-  if (!a_kmajor && !b_kmajor) {
-    // Both operands run along the output (a weight gradient): the weight-gradient tiles of the Linear launch read them
-    // as they lie and transpose on the way out of LDS, where the generic kernel scatters 2- or 4-byte elements into
-    // LDS.  Measured against the generic kernel's best tile over outputs of 64 x 64 to 4096 x 4096, 8 to 4096 rows:
-    // faster at every one (fp32 64 x 64 x 8 13 -> 7 us, bf16 4096 x 4096 x 64 52 -> 16 us, 4096^3 1124 -> 271 us).
+  if (!a_kmajor && !b_kmajor && gemm_wgrad_tiles_wanted(tile_shape, M, N, K, lda, ldb, dtype)) {
     p.epi = EPI_WGRAD;
     p.flags = 0;
     return launch_linear_tick(b, dtype, false, false, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;

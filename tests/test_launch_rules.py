@@ -1,7 +1,8 @@
 """Rules by which launches are laid out, asked of the built library: how many ranges the reduction of a weight gradient
 is cut into when it is launched on its own (conv_wgrad_splits_alone in csrc/conv_kernels.hip), which forward / data-gradient
-launches share their reductions over workgroups (conv_dl_tile in csrc/conv256_kernels.hip), and which attention passes run in
-one kernel (attention_fused in csrc/attention_kernels.hip).  No GPU: the rules are host arithmetic, and the times they are held
+launches share their reductions over workgroups (conv_dl_tile in csrc/conv256_kernels.hip), which attention passes run in
+one kernel (attention_fused in csrc/attention_kernels.hip), and which products of row-contiguous operands run on the
+weight-gradient tiles of the Linear launch (gemm_wgrad_tiles_wanted in csrc/kernels_api.cpp).  No GPU: the rules are host arithmetic, and the times they are held
 against were measured on one."""
 import os
 import subprocess
@@ -37,6 +38,11 @@ def ranges(tmp_path_factory):
 @pytest.fixture(scope="module")
 def fused(tmp_path_factory):
     return _asker(tmp_path_factory, "attention")
+
+
+@pytest.fixture(scope="module")
+def wgrad_tiles(tmp_path_factory):
+    return _asker(tmp_path_factory, "gemm")
 
 
 @pytest.fixture(scope="module")
@@ -158,3 +164,19 @@ ATTENTION = [(6, 416, 12, 48, 87.5, 123.8), (4, 656, 12, 48, 152.7, 199.2), (8, 
 def test_attention_backward_takes_the_faster_kernels(fused):
     for (b, t, h, dh, apart, together), one in zip(ATTENTION, fused([(1, BF16, b, t, h * dh, h) for b, t, h, dh, _, _ in ATTENTION])):
         assert (together if one else apart) <= 1.02 * min(apart, together), (b, t, h, dh)
+
+
+# fp32, 128 x 128 tile asked for; M, N, K, us on the generic kernel, us on the weight-gradient tiles
+ROW_CONTIGUOUS = [(4001, 3003, 1, 28.1, 38.1), (4001, 3003, 16, 29.0, 39.6), (4001, 3003, 2000, 830, 945), (4672, 2321, 12, 24.8, 38.4),
+                  (4673, 2320, 32, 35.3, 40.1), (3001, 7001, 200, 219, 238), (2601, 3101, 16, 27.7, 35.0), (4672, 2320, 12, 23.9, 28.2),
+                  (4672, 2320, 17, 34.7, 28.2), (4672, 2320, 64, 45.4, 29.5), (40000, 300, 12, 40.1, 46.7), (20000, 600, 8, 38.6, 42.5),
+                  (20000, 600, 24, 54.2, 42.9), (4096, 4096, 8, 39.5, 30.0), (600, 20000, 8, 41.4, 29.0), (2004, 2004, 8, 19.5, 12.5),
+                  (1001, 2003, 8, 21.0, 10.0), (1000, 2000, 1, 19.5, 11.0), (64, 64, 8, 17.0, 7.0)]
+
+
+def test_row_contiguous_products_take_the_faster_kernel(wgrad_tiles):
+    got = wgrad_tiles([(0, m, n, k, m, n, F32) for m, n, k, _, _ in ROW_CONTIGUOUS])
+    for (m, n, k, generic, tiles_us), on_tiles in zip(ROW_CONTIGUOUS, got):
+        assert (tiles_us if on_tiles else generic) <= 1.02 * min(generic, tiles_us), (m, n, k)
+    # the other tiles of the generic kernel, and bf16, never were faster
+    assert all(wgrad_tiles([(s, m, n, k, m, n, dt) for m, n, k, _, _ in ROW_CONTIGUOUS for s, dt in ((1, F32), (2, F32), (0, BF16))]))
