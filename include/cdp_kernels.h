@@ -22,8 +22,9 @@ extern "C" {
  *              where those are faster: in fp32 not for large results in odd layouts or of very few rows);
  *              3: 64x64, 4: 64x128 tile of the weight-streaming kernel the Linear stages
  *              use; 5: what is fastest for a Linear layer on its own: a kernel for one problem of few
- *              rows and 16-byte-chunked operands, else the tiles the engine launches (3..5 need
- *              a_kmajor = b_kmajor = 1)
+ *              rows and 16-byte-chunked operands, else the tiles the engine launches; 6: those tiles, which for
+ *              at most 32 rows and 16-byte-chunked operands are 32x32 with waves that split the reduction
+ *              (3..6 need a_kmajor = b_kmajor = 1); 7, 8, 9: the generic kernel of 0, 1, 2 in every layout
  *   a_kmajor   1: A[m][k] at A[m*lda + k]   0: A[m][k] at A[k*lda + m]
  *   b_kmajor   1: B[n][k] at B[n*ldb + k]   0: B[n][k] at B[k*ldb + n] */
 int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void* A, const void* B,
@@ -36,11 +37,16 @@ int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void
  *         3, 4: as 0, 1 on the direct-to-LDS kernel's 256 x 256 tile whatever the size (the engine and which =
  *               0, 1 choose by launch size); 5, 6: the same kernel's 256 x 128 tile; CDP_EINVAL unless bf16 with
  *               channel counts that are multiples of 64
+ *         7, 8: as 0, 1 the way the engine launches them, with a workspace in which workgroups share the reductions
+ *               of a launch of few tiles: CDP_CONV_SHARE_BYTES, the last 8192 of them zero before the first call (every
+ *               call leaves them zero); CDP_EINVAL without it or for channel counts that are not whole 16-byte chunks
+ *         9: as 2, but added to dw instead of overwriting it; needs the workspace of the two-phase path
  * in0/in1: (x, w) | (dy, wt) | (dy, x).  `out` must not alias the inputs.
  * workspace (device, may be NULL): scratch for the split weight-gradient kernel.  Where the shape allows and it holds
  * at least one partial sum (4 * Cout*k*k*Cin bytes) the two-phase path is used; without, the generic single-pass kernel
  * runs.  How many ranges the reduction is cut into, and with it the order of the sums, depends on the shape alone where the
  * workspace holds B*Ho*Wo / 512 + 4 partial sums; a smaller one may mean fewer ranges (other roundings, slower). */
+#define CDP_CONV_SHARE_BYTES ((32u << 20) + 8192u)
 int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out, int B, int H, int W,
                int Cin, int Cout, int ksize, int stride, int pad, void* workspace,
                size_t workspace_bytes, void* stream);

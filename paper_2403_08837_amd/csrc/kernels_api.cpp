@@ -25,12 +25,17 @@ bool cdp::gemm_wgrad_tiles_wanted(int tile_shape, int M, int N, int K, int lda, 
   return whole && (K > 16 || N % 32 == 0);
 }
 
+static_assert((int64_t)CDP_CONV_SHARE_BYTES == CONV_SPLIT_WS_BYTES + CONV_SPLIT_SLOTS * 4, "partial tiles, then counters");
+
 extern "C" {
 
 int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void* A, const void* B, float* C, int M, int N,
                int K, int lda, int ldb, void* stream) {
-  if (!A || !B || !C || M <= 0 || N <= 0 || K <= 0 || tile_shape < 0 || tile_shape >= TILE_COUNT + 3) return CDP_EINVAL;
-  if (tile_shape >= TILE_COUNT && !(a_kmajor && b_kmajor)) return CDP_EINVAL;
+  // tile shapes: 0 .. 2 generic kernel, 3, 4 tick launch with 64 / 128 columns, 5 fastest, 6 tick launch as the engine makes it, 7 .. 9 generic
+  // kernel in every layout
+  constexpr int FASTEST = TILE_COUNT + 2, AS_ENGINE = TILE_COUNT + 3, GENERIC = TILE_COUNT + 4;
+  if (!A || !B || !C || M <= 0 || N <= 0 || K <= 0 || tile_shape < 0 || tile_shape >= GENERIC + TILE_COUNT) return CDP_EINVAL;
+  if (tile_shape >= TILE_COUNT && tile_shape < GENERIC && !(a_kmajor && b_kmajor)) return CDP_EINVAL;
   if (dtype != DT_F32 && dtype != DT_BF16) return CDP_EINVAL;
   GemmBatch b;
   memset(&b, 0, sizeof(b));
@@ -43,16 +48,22 @@ int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void
   p.epi = EPI_FWD;
   p.flags = GF_OUT_F32;
   p.splits = 1;
-  if (!a_kmajor && !b_kmajor && gemm_wgrad_tiles_wanted(tile_shape, M, N, K, lda, ldb, dtype)) {
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  hipError_t e;
+  if (tile_shape >= GENERIC) {
+    e = launch_gemm_batch(b, dtype, tile_shape - GENERIC, st);
+  } else if (!a_kmajor && !b_kmajor && gemm_wgrad_tiles_wanted(tile_shape, M, N, K, lda, ldb, dtype)) {
     p.epi = EPI_WGRAD;
     p.flags = 0;
-    return launch_linear_tick(b, dtype, false, false, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
+    e = launch_linear_tick(b, dtype, false, false, st);
+  } else if (tile_shape == FASTEST && gemm_stream_wanted(A, B, M, N, K, lda, ldb, dtype)) {
+    e = launch_gemm_stream(A, B, C, M, N, K, lda, ldb, dtype, st);
+  } else if (tile_shape >= TILE_COUNT) {
+    e = launch_linear_tick(b, dtype, tile_shape == TILE_COUNT + 1, tile_shape == FASTEST || tile_shape == AS_ENGINE, st);
+  } else {
+    e = launch_gemm_batch(b, dtype, tile_shape, st);
   }
-  if (tile_shape == TILE_COUNT + 2 && gemm_stream_wanted(A, B, M, N, K, lda, ldb, dtype))
-    return launch_gemm_stream(A, B, C, M, N, K, lda, ldb, dtype, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
-  if (tile_shape >= TILE_COUNT)
-    return launch_linear_tick(b, dtype, tile_shape == TILE_COUNT + 1, tile_shape == TILE_COUNT + 2, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
-  return launch_gemm_batch(b, dtype, tile_shape, static_cast<hipStream_t>(stream)) == hipSuccess ? CDP_OK : CDP_EHIP;
+  return e == hipSuccess ? CDP_OK : CDP_EHIP;
 }
 
 int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out, int B, int H, int W, int Cin, int Cout,
@@ -72,7 +83,10 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
   g.KH = ks; g.KW = ks; g.stride = stride; g.pad = pad;
   const bool force256 = which >= 3 && which <= 6;  // the direct-to-LDS tile regardless of the launch heuristic
   const int forced_tile = which >= 5 ? DL_256x128 : DL_256x256;
+  const bool shared = which == 7 || which == 8, accumulate = which == 9;
   if (force256) which -= which >= 5 ? 5 : 3;
+  if (shared) which -= 7;
+  if (accumulate) which = 2;
   if (which == 0) {
     p.M = B * Ho * Wo; p.N = Cout; p.K = ks * ks * Cin;
     p.a_mode = OP_CONV_FWD; p.b_mode = OP_PLAIN_K; p.ldb = p.K; p.ldo = Cout;
@@ -92,29 +106,36 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
     return CDP_EINVAL;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // same kernel choice as the engine: the fast implicit-GEMM paths where the shape allows
+  if (shared && (!conv_fast_eligible(p, dtype) || !workspace || workspace_bytes < (size_t)CDP_CONV_SHARE_BYTES)) return CDP_EINVAL;
+  // the fast implicit-GEMM paths where the shape allows, as in the engine; what is different for a call on its own: no workspace to share
+  // reductions in (which = 7, 8 have one), ranges of the weight gradient for a launch of its own, and a fold that overwrites
   if (which == 2) {
     const size_t range_bytes = (size_t)p.M * p.N * 4;
     const int room = (int)std::min<size_t>(INT_MAX, workspace ? workspace_bytes / range_bytes : 0);
     if (conv_fast_eligible(p, dtype) && room >= 1) {
       const int splits = conv_wgrad_splits_alone(p, dtype, room);
-      // two phases as in the engine: partial sums per reduction range, then the fold
+      // two phases: partial sums per reduction range, then the fold
       WReduceBatch rb;
       memset(&rb, 0, sizeof(rb));
       rb.n = 1;
       rb.p[0].part = static_cast<const float*>(workspace);
       rb.p[0].G = static_cast<float*>(out);
       rb.p[0].Cout = p.M; rb.p[0].Ncol = p.N; rb.p[0].splits = splits;
-      rb.p[0].overwrite = 1;
+      rb.p[0].overwrite = !accumulate;
       p.out = workspace;
       p.splits = splits;
       if (launch_conv_wgrad(b, dtype, p.M >= 128, st) != hipSuccess) return CDP_EHIP;
       return launch_wgrad_reduce(rb, dtype, st) == hipSuccess ? CDP_OK : CDP_EHIP;
     }
+    if (accumulate) return CDP_EINVAL;
   } else if (force256) {
     if (!conv_gemm256_eligible(p, dtype)) return CDP_EINVAL;
     return launch_conv_dl(b, dtype, forced_tile, st) == hipSuccess ? CDP_OK : CDP_EHIP;
   } else if (conv_fast_eligible(p, dtype)) {
+    if (shared) {
+      b.thin_ws = static_cast<float*>(workspace);
+      b.thin_cnt = reinterpret_cast<unsigned int*>(static_cast<char*>(workspace) + CONV_SPLIT_WS_BYTES);
+    }
     if (conv_gemm256_wanted(&p, 1, dtype)) return launch_conv_dl(b, dtype, DL_256x256, st) == hipSuccess ? CDP_OK : CDP_EHIP;
     int bm, bn;
     conv_gemm_tile(&p, 1, &bm, &bn);

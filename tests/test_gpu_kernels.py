@@ -28,13 +28,15 @@ def _rnd(a, dtype):
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
-@pytest.mark.parametrize("shape", [0, 1, 2, 3, 4, 5])
+@pytest.mark.parametrize("shape", [0, 1, 2, 3, 4, 5, 6, 7, 8, 9])
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (0, 0), (1, 0), (0, 1)])
 @pytest.mark.parametrize("M,N,K", [(8, 64, 64), (64, 200, 136), (130, 257, 70), (333, 129, 515), (5, 7, 3), (32, 300, 1100),
                                    (32, 1024, 1024), (17, 200, 3072), (32, 96, 136), (1, 40, 8), (9, 33, 2056)])
 def test_gemm_all_layouts(dtype, shape, a_k, b_k, M, N, K):
+    """Every selector of cdp_k_gemm.  6 is the launch of the engine's Linear stages (32 x 32 tiles at up to 32 rows, one slab and
+    several), 7 to 9 the generic kernel, which 0 to 2 are too unless both operands are row-contiguous."""
     torch = _torch()
-    if shape >= 3 and not (a_k and b_k):
+    if 3 <= shape < 7 and not (a_k and b_k):
         pytest.skip("the weight-streaming kernel takes k-contiguous operands only")
     A = wl.random_normal(1, 10 * M + K, M * K).reshape(M, K)
     Bm = wl.random_normal(2, 10 * N + K, N * K).reshape(N, K)
@@ -140,6 +142,65 @@ def test_conv_passes_match_oracle(dtype, case):
         assert np.isfinite(g).all(), name
         err = np.abs(g - ref).max() / max(1e-6, np.abs(ref).max())
         assert err <= tol, (name, err)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("case", [(1, 7, 7, 512, 512, 3, 1, 1),     # 8 tiles of 64 x 64, 72 slabs, eight workgroups a tile
+                                  (2, 5, 5, 256, 136, 3, 1, 1),     # ragged in both directions
+                                  (1, 1, 130, 2048, 64, 1, 1, 0), (3, 9, 7, 192, 96, 3, 2, 1), (1, 3, 3, 1000, 72, 3, 1, 1),
+                                  (4, 8, 8, 32, 40, 3, 1, 1),       # fp32: two slabs of 32 a tap, too short to share
+                                  (2, 14, 14, 64, 256, 3, 1, 1)])
+def test_conv_launches_of_the_engine(dtype, case):
+    """Forward and data gradient as the engine launches them (which = 7, 8): few tiles share their reductions over workgroups in a
+    workspace whose counters are zero again afterwards.  Twice with the same bits."""
+    torch = _torch()
+    B, H, W, Cin, Cout, ks, st, pad = case
+    x = wl.random_normal(3, 1, B * H * W * Cin).reshape(B, H, W, Cin)
+    w = wl.random_normal(3, 2, Cout * ks * ks * Cin).reshape(Cout, ks, ks, Cin) / np.sqrt(ks * ks * Cin)
+    xr, wr = _rnd(x, dtype), _rnd(w, dtype)
+    y = L.conv2d_fwd(xr, wr, st, pad)
+    dy = wl.random_normal(3, 3, y.size).reshape(y.shape)
+    dx, _ = L.conv2d_bwd(xr, wr, st, pad, _rnd(dy, dtype))
+    tol = 2.0 ** -7 if dtype == wl.BF16 else 1e-5
+    share = (32 << 20) + 8192
+    ws = torch.full((share,), 255, dtype=torch.uint8, device="cuda")
+    ws[-8192:] = 0
+    xd, wd, dyd, wtd = _dev(x, dtype), _dev(w, dtype), _dev(dy, dtype), _dev(np.transpose(w, (3, 1, 2, 0)), dtype)
+    for which, a, k, ref in ((7, xd, wd, y), (8, dyd, wtd, dx)):
+        got = []
+        for _ in range(2):
+            got.append(torch.full(ref.shape, float("nan"), dtype=xd.dtype, device="cuda"))
+            b.cdp_k_conv(dtype, which, a.data_ptr(), k.data_ptr(), got[-1].data_ptr(), *case, ws_ptr=ws.data_ptr(), ws_bytes=share)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], got[1])
+        assert int(ws[-8192:].sum()) == 0
+        _close(got[0], ref, tol, which)
+    with pytest.raises(b.CdpError):
+        b.cdp_k_conv(dtype, 7, xd.data_ptr(), wd.data_ptr(), got[0].data_ptr(), *case, ws_ptr=ws.data_ptr(), ws_bytes=share - 1)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("case", [(2, 8, 8, 32, 64, 3, 1, 1), (8, 28, 28, 24, 40, 3, 1, 1), (1, 1, 200, 512, 4104, 1, 1, 0), (4, 20, 20, 16, 16, 3, 1, 1)])
+def test_conv_weight_gradient_added_to_an_accumulator(dtype, case):
+    """which = 9: the fold adds to what dw holds, as in a step of several micro-batches; by rows (4104 of them) and by pieces, with one
+    range and with many."""
+    torch = _torch()
+    B, H, W, Cin, Cout, ks, st, pad = case
+    Ho, Wo = (H + 2 * pad - ks) // st + 1, (W + 2 * pad - ks) // st + 1
+    x = wl.random_normal(6, 1, B * H * W * Cin).reshape(B, H, W, Cin)
+    dy = wl.random_normal(6, 2, B * Ho * Wo * Cout).reshape(B, Ho, Wo, Cout)
+    _, dw = L.conv2d_bwd(_rnd(x, dtype), np.zeros((Cout, ks, ks, Cin)), st, pad, _rnd(dy, dtype))
+    old = wl.random_normal(6, 3, dw.size).reshape(dw.shape) * np.abs(dw).max()
+    xd, dyd = _dev(x, dtype), _dev(dy, dtype)
+    for sums in (1, B * Ho * Wo // 512 + 4):
+        got = _dev(old, wl.F32)
+        ws = torch.full((dw.size * sums,), float("nan"), dtype=torch.float32, device="cuda")
+        b.cdp_k_conv(dtype, 9, dyd.data_ptr(), xd.data_ptr(), got.data_ptr(), *case, ws_ptr=ws.data_ptr(), ws_bytes=ws.numel() * 4)
+        torch.cuda.synchronize()
+        # products of exactly representable inputs, fp32 sums
+        _close(got, _rnd(old, wl.F32) + dw, 1e-5, sums)
+    with pytest.raises(b.CdpError):
+        b.cdp_k_conv(dtype, 9, dyd.data_ptr(), xd.data_ptr(), got.data_ptr(), *case)
 
 
 LARGE_TILE_CASES = [
