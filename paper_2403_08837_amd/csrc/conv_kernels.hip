@@ -965,7 +965,9 @@ static bool conv_few_tiles(const GemmBatch& b, int dtype) {
   return tiles <= 768;
 }
 
-// (bf16 launches short of workgroups run on the direct-to-LDS tiles instead, whatever tile was asked for)
+// The tile is a wish: bf16 launches short of workgroups whose reductions are not shared run on the direct-to-LDS tiles (conv_dl_tile), fp32
+// launches of few tiles without a workspace on conv_gemm_few_kernel.  What is left for 64 x 64 tiles here is shared reductions, ragged
+// channel counts and fp32; for 64 x 128, ragged, fp32, and operands that are not 16-byte aligned or need 64-bit offsets.
 hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
   if (b.n > GEMM_MAX_PROBS) return hipErrorInvalidValue;
@@ -986,6 +988,10 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
     return hipGetLastError();
   }
   bool deep = true;  // every problem allows the double-depth slab
+  // One problem whose channels are not whole slabs takes the whole launch to the RAGGED kernel.  Ragged problems in a launch of their own
+  // (with the others on the direct-to-LDS tiles), ms per step of ResNets on 4 micro-batches, one launch / two: width 16 (one stage in four ragged) of 16
+  // samples 1.51 / 1.60, width 24 (two in four) 1.70 / 1.66, in fp32 2.47 / 2.59, width 40 of 32 samples 2.27 / 2.35, width 80 of 8 3.08 / 2.89, ResNet-50 of width 16
+  // 4.78 / 4.62: a launch fewer per level is worth more on most.  (All on the element-by-element kernel: 2.57, 3.80, 3.86, 7.15, 6.57, 6.73.)
   bool ragged = false;
   for (int i = 0; i < b.n; ++i) {
     GemmProb& p = b.p[i];

@@ -723,8 +723,9 @@ int launch_level(cdp_ctx* c, std::vector<Item>& items) {
   // Forward / data-gradient problems with at most 64 output columns have a launch of their own (128 x 64 tiles).
   // Where the level's wide problems fill a launch of 128 x 128 tiles by themselves, the narrow ones join it
   // instead, half of each of their tiles empty: they are bound by their operand traffic, not by the matrix
-  // cores, and one launch fewer per level is worth more than the idle half (cfg4 22.8 -> 22.0 ms per step; on
-  // the small launches of cfg3, which run on 64 x 64 tiles with shared reductions, the same costs 19 %).
+  // cores, and one launch fewer per level is worth more than the idle half (ResNet-50-shaped, 8 micro-batches of 32: 21.7 -> 20.8 ms
+  // per step; of 4 micro-batches of 32 ResNet-18-shaped, whose launches are short of workgroups and run on 64-column tiles
+  // with shared reductions or a deep prefetch, the same costs 30 %: 2.83 -> 3.68 ms).
   bool narrow_joins_wide = false;
   {
     std::vector<GemmProb> wide;
