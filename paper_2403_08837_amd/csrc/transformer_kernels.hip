@@ -474,8 +474,10 @@ hipError_t launch_layernorm_bwd_batch(const LnBwdBatch& b, int rows, int C, int 
     if (!b.p[i].workspace || !b.p[i].x || !b.p[i].dy || !b.p[i].dx || !b.p[i].Ggamma || !b.p[i].Gbeta ||
         !layernorm_batchable(b.p[i].x, b.p[i].dy, b.p[i].add, b.p[i].dx, C, dtype))
       return hipErrorInvalidValue;
-  // one workgroup per CU in all, and no more partial rows than the workspace has room for
-  const int wgs = std::min((rows + LN_ROWS_PER_WG - 1) / LN_ROWS_PER_WG, std::max(1, 256 / b.n));
+  // at most one workgroup per CU and problem, and no more partial rows than the workspace has room for.  The count looks at the rows
+  // alone: what else is in the launch must not change the order in which a column is summed (sharing the CUs out among the problems
+  // instead was within 2 % either way on ViT-shaped steps).
+  const int wgs = std::min((rows + LN_ROWS_PER_WG - 1) / LN_ROWS_PER_WG, 256);
   const int stats_floats = (int)(ln_stats_bytes(rows) / 4);
   hipError_t e = hipSuccess;
   CDP_TDISPATCH(dtype, e = (launch_layernorm_bwd_vec<T>(b, rows, C, wgs, stats_floats, stream)));

@@ -405,6 +405,43 @@ def test_layernorm_whole_chunk_edges(dtype, rows, C):
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("rows,C", [(6272, 768), (4100, 64), (40, 128)])
+def test_layernorm_backward_does_not_depend_on_its_launch(dtype, rows, C):
+    """A problem's gradients have the same bits whether it is launched alone or with others of its shape, as the engine does."""
+    import ctypes
+    torch = _torch()
+    launch = getattr(b.lib(), "_ZN3cdp26launch_layernorm_bwd_batchERKNS_10LnBwdBatchEiiiP12ihipStream_t")
+
+    class Prob(ctypes.Structure):
+        _fields_ = [(n, ctypes.c_void_p) for n in ("x", "dy", "add", "gamma", "dx", "Ggamma", "Gbeta", "workspace")]
+
+    class Batch(ctypes.Structure):
+        _fields_ = [("p", Prob * 8), ("n", ctypes.c_int)]      # LnBwdBatch of csrc/kernels.h
+
+    def run(n):
+        batch, out = Batch(), []
+        batch.n = n
+        for q in range(n):
+            gen = torch.Generator(device="cuda")
+            gen.manual_seed(q)
+            r = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+            x, dy = (r(rows, C).to(torch.bfloat16 if dtype == wl.BF16 else torch.float32) for _ in range(2))
+            o = dict(x=x, dy=dy, gamma=r(C), dx=torch.empty_like(x), Ggamma=torch.zeros(C, device="cuda"), Gbeta=torch.zeros(C, device="cuda"),
+                     workspace=torch.empty(2 * rows + 2 * C * ((rows + 31) // 32) + 64, device="cuda"))
+            for k, t in o.items():
+                setattr(batch.p[q], k, t.data_ptr())
+            out.append(o)
+        torch.cuda.synchronize()
+        assert launch(ctypes.byref(batch), rows, C, dtype, None) == 0
+        torch.cuda.synchronize()
+        return out
+
+    alone, shared = run(1)[0], run(5)[0]
+    for k in ("dx", "Ggamma", "Gbeta"):
+        assert torch.equal(alone[k], shared[k]), k
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 def test_gelu_over_the_whole_range(dtype):
     """Tails, zeros and infinities: Phi of large negative arguments has to vanish, the derivative too."""
     torch = _torch()
