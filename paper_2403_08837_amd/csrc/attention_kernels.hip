@@ -15,9 +15,11 @@
 // The limit in tokens is LDS (64-wide heads: 624); past 256 tokens the forward contracts the scores twice instead of
 // keeping them (8 x 400 tokens, 8 heads of 64: 43 -> 22 us forward, 84 -> 49 us backward against separate kernels).
 // Measured there (us, forward / backward): score rows and products as kernels of their own 50 / 101; these three
-// 20 / 52 (dq 27, dkv 29 under the profiler).  What is left above the bytes (13 / 28 at the rate of a large copy, the
-// backward reading q, v, d out and P once per kernel) is that the resident workgroups move in step: they stage, contract
-// and store together; 192 workgroups, less than one per CU, take 10 us already.
+// 20 / 52 (dq 27, dkv 29 under the profiler).  What is left above the bytes (13 / 28 at the rate of a large copy, were every tensor
+// read once per kernel) is that the resident workgroups move in step: they stage, contract and store together; 192
+// workgroups, less than one per CU, take 10 us already.  Requested is more: every workgroup of 128 tokens stages k and v (or q and
+// d out) of its head again, twice at 196 tokens, and dq walks the probabilities twice, for the row sums and for the products; the
+// bound above takes those second reads for hits of the XCD's L2, to which the workgroups of a head are dealt together.
 #include "elem.h"
 #include "kernels.h"
 

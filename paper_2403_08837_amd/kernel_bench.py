@@ -81,7 +81,7 @@ def vit_kernels(reps=50):
     res.append(("layernorm fwd 6272x768", us, 2 * 2.0 * rows * D / us / 1e3))
     us = _time(lambda: b.cdp_k_layernorm(1, 1, x.data_ptr(), dy.data_ptr(), 0, gam.data_ptr(), 0, out.data_ptr(), dg.data_ptr(),
                                          db.data_ptr(), ws.data_ptr(), ws.numel() * 4, rows, D), reps)
-    res.append(("layernorm bwd 6272x768 (3 kernels)", us, 5 * 2.0 * rows * D / us / 1e3))
+    res.append(("layernorm bwd 6272x768 (2 kernels)", us, 5 * 2.0 * rows * D / us / 1e3))
     n = rows * 4 * D
     xg, dyg = torch.randn(n, device="cuda").to(bf), torch.randn(n, device="cuda").to(bf)
     og = torch.empty_like(xg)
@@ -98,17 +98,20 @@ def vit_kernels(reps=50):
     wsa = torch.empty(2 * tt + 128, device="cuda")
     us = _time(lambda: b.cdp_k_attention(1, 0, qkv.data_ptr(), P.data_ptr(), 0, o.data_ptr(), wsa.data_ptr(), wsa.numel() * 4,
                                          Bn, T, D, H), reps)
-    res.append(("attention fwd 32x12 heads, 196 tokens (2 kernels)", us, 2.0 * (qkv.numel() + tt + o.numel()) / us / 1e3))
+    res.append(("attention fwd 32x12 heads, 196 tokens (1 kernel)", us, 2.0 * (qkv.numel() + tt + o.numel()) / us / 1e3))
     us = _time(lambda: b.cdp_k_attention(1, 1, qkv.data_ptr(), P.data_ptr(), do.data_ptr(), dq.data_ptr(), wsa.data_ptr(),
                                          wsa.numel() * 4, Bn, T, D, H), reps)
-    res.append(("attention bwd 32x12 heads, 196 tokens (4 kernels)", us, 2.0 * (2 * qkv.numel() + tt + do.numel()) / us / 1e3))
+    res.append(("attention bwd 32x12 heads, 196 tokens (2 kernels)", us, 2.0 * (2 * qkv.numel() + tt + do.numel()) / us / 1e3))
     return res
 
 
 LINEAR_SHAPES = [  # (label, M, N, K, tile_shape)
-    ("cfg2 layer  32x1024x1024 (thin tiles)", 32, 1024, 1024, 5),
-    ("cfg2 stem   32x1024x3072 (thin tiles)", 32, 1024, 3072, 5),
+    ("cfg2 layer  32x1024x1024 (thin tiles)", 32, 1024, 1024, 6),
+    ("cfg2 layer  32x1024x1024 (on its own)", 32, 1024, 1024, 5),
+    ("cfg2 stem   32x1024x3072 (thin tiles)", 32, 1024, 3072, 6),
+    ("cfg2 stem   32x1024x3072 (on its own)", 32, 1024, 3072, 5),
     ("cfg5 layer  64x4096x4096 (64x128 tiles)", 64, 4096, 4096, 4),
+    ("cfg5 layer  64x4096x4096 (on its own)", 64, 4096, 4096, 5),
     ("8 x cfg5    64x32768x4096 (64x128 tiles)", 64, 32768, 4096, 4),
 ]
 CONV_SHAPES = [  # ResNet-50 layers of one micro-batch of 32, and two large compute-bound shapes

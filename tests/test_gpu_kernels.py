@@ -216,11 +216,11 @@ LARGE_TILE_CASES = [
 ]
 
 
-@pytest.mark.parametrize("tile", [256, 128])
+@pytest.mark.parametrize("tile", ["256x256", "256x128"])
 @pytest.mark.parametrize("case", LARGE_TILE_CASES)
 def test_conv_large_tile_matches_oracle(case, tile):
-    """Forward / data gradient on the direct-to-LDS kernel (bf16; swizzled rows, two stages), 256 x 256 and
-    128 x 128 tiles, against the oracle's convolution."""
+    """Forward / data gradient on the direct-to-LDS kernel (bf16; swizzled rows), 256 x 256 tiles with two stages and 256 x 128 tiles
+    with three, against the oracle's convolution."""
     torch = _torch()
     which, B, H, W, Cin, Cout, ks, st, pad = case
     dtype = wl.BF16
@@ -231,14 +231,14 @@ def test_conv_large_tile_matches_oracle(case, tile):
         ref = L.conv2d_fwd(xr, wr, st, pad)
         xd, wd = _dev(x, dtype), _dev(w, dtype)
         got = torch.full(ref.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
-        b.cdp_k_conv(dtype, 3 if tile == 256 else 5, xd.data_ptr(), wd.data_ptr(), got.data_ptr(), B, H, W, Cin, Cout, ks, st, pad)
+        b.cdp_k_conv(dtype, 3 if tile == "256x256" else 5, xd.data_ptr(), wd.data_ptr(), got.data_ptr(), B, H, W, Cin, Cout, ks, st, pad)
     else:
         Ho, Wo = (H + 2 * pad - ks) // st + 1, (W + 2 * pad - ks) // st + 1
         dy = wl.random_normal(7, 3, B * Ho * Wo * Cout).reshape(B, Ho, Wo, Cout)
         ref, _ = L.conv2d_bwd(xr, wr, st, pad, _rnd(dy, dtype))
         dyd, wtd = _dev(dy, dtype), _dev(np.transpose(w, (3, 1, 2, 0)), dtype)
         got = torch.full(x.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
-        b.cdp_k_conv(dtype, 4 if tile == 256 else 6, dyd.data_ptr(), wtd.data_ptr(), got.data_ptr(), B, H, W, Cin, Cout, ks, st, pad)
+        b.cdp_k_conv(dtype, 4 if tile == "256x256" else 6, dyd.data_ptr(), wtd.data_ptr(), got.data_ptr(), B, H, W, Cin, Cout, ks, st, pad)
     torch.cuda.synchronize()
     g = got.float().cpu().numpy().astype(np.float64)
     assert np.isfinite(g).all()
@@ -346,9 +346,9 @@ def test_gelu_kernels_match_oracle(dtype):
 def test_attention_kernels_match_oracle(dtype, B, T, D, heads):
     """Probabilities, output and the gradient with respect to q | k | v: the ViT-B/16 shape,
     a shape where nothing is a multiple of four (element-wise staging, ragged tiles), 324
-    tokens, the reduced test shape, heads of width 32 / 64 with 50, 256 and 33 tokens, and the limits of the
-    one-kernel score rows of the bf16 path (head widths 80, 16 and 96: the last one too wide for it; 129 and 260
-    tokens: a third key block of one key, and one token too many)."""
+    tokens, the reduced test shape, heads of width 32 / 64 with 50, 256 and 33 tokens; in bf16 head widths 80 and 16 (the
+    widest and narrowest of the fused kernels) and 96 (too wide for them), 256 and 260 tokens (scores kept in registers up to 256,
+    contracted twice past that), 129 tokens (a second workgroup of one query)."""
     torch = _torch()
     tdt = torch.bfloat16 if dtype == wl.BF16 else torch.float32
     eb = 2 if dtype == wl.BF16 else 4
@@ -485,6 +485,16 @@ def test_conv_short_of_workgroups(rows, out, slabs):
     for red in ((64 * slabs, 32 * slabs) if slabs <= 7 else (64 * slabs,)):
         _conv_1x1_bf16(0, rows, red, out)
         _conv_1x1_bf16(1, rows, out, red)
+
+
+@pytest.mark.parametrize("case", [(4, 56, 56, 64, 320, 3, 1, 1),       # forward on 256 x 128 tiles, data gradient on 64 x 64
+                                  (8, 41, 41, 64, 136, 3, 1, 1),       # forward on 64 x 128
+                                  (8, 41, 41, 200, 192, 3, 1, 1),      # data gradient on 64 x 128
+                                  (9, 57, 57, 64, 200, 3, 2, 1), (5, 33, 31, 128, 64, 5, 2, 2),
+                                  (3, 13, 11, 192, 128, 3, 1, 1), (2, 15, 15, 128, 192, 3, 3, 1)])   # 64 x 64, long reductions
+def test_conv_short_of_workgroups_taps(case):
+    """The tiles of launches that do not fill the chip, with taps, strides and padding."""
+    test_conv_passes_match_oracle(wl.BF16, case)
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
