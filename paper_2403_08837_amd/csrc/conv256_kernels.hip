@@ -341,6 +341,7 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
     if (total >= (1ll << 31)) return hipErrorInvalidValue;
   }
   b.total_tiles = (int)total;
+  tile_starts_set(b.starts, b.p, b.n);
   const dim3 grid((unsigned)total);
   switch (tile) {
     case DL_256x256: hipLaunchKernelGGL((conv_gemm_dl_kernel<256, 256, 2, 4, 64, 2, 2>), grid, dim3(512), 0, stream, b); break;

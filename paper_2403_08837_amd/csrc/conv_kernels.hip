@@ -505,10 +505,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WReduceBatch batch) {
   using E = Elem<T>;
   __shared__ float4 red[8][32];
-  int pi = 0;
-  for (int q = 1; q < batch.n; ++q)
-    if ((int)blockIdx.x >= batch.p[q].tile_begin) pi = q;
-  const WReduceProb& P = batch.p[pi];
+  const WReduceProb& P = batch.p[tile_starts_find(batch.starts, batch.n, (int)blockIdx.x)];
   const int rg = P.rg, rows_per_wg = 8 / rg;
   const int chunks = (P.Ncol + 127) >> 7;
   const int local = (int)blockIdx.x - P.tile_begin;
@@ -635,10 +632,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WReduceBatch ba
 template <typename T>
 __global__ __launch_bounds__(256) void wgrad_fold_rows_kernel(const WReduceBatch batch) {
   using E = Elem<T>;
-  int pi = 0;
-  for (int q = 1; q < batch.n; ++q)
-    if ((int)blockIdx.x >= batch.p[q].tile_begin) pi = q;
-  const WReduceProb& P = batch.p[pi];
+  const WReduceProb& P = batch.p[tile_starts_find(batch.starts, batch.n, (int)blockIdx.x)];
   const int cl = threadIdx.x & 31, grp = threadIdx.x >> 5;
   const int o = ((int)blockIdx.x - P.tile_begin) * 8 + grp;
   if (o >= P.Cout) return;  // whole 32-lane groups leave: the exchanges below stay inside a group
@@ -717,6 +711,7 @@ hipError_t launch_wgrad_reduce(WReduceBatch& b, int dtype, hipStream_t stream) {
         b.p[i].tile_begin = total;
         total += (b.p[i].Cout + 7) / 8;
       }
+      tile_starts_set(b.starts, b.p, b.n);
       if (dtype == DT_BF16) hipLaunchKernelGGL((wgrad_fold_rows_kernel<uint16_t>), dim3((unsigned)total), dim3(256), 0, stream, b);
       else hipLaunchKernelGGL((wgrad_fold_rows_kernel<float>), dim3((unsigned)total), dim3(256), 0, stream, b);
       return hipGetLastError();
@@ -733,6 +728,7 @@ hipError_t launch_wgrad_reduce(WReduceBatch& b, int dtype, hipStream_t stream) {
     total += (int64_t)((p.Cout + rows_per_wg - 1) / rows_per_wg) * ((p.Ncol + 127) / 128);
     if (total >= (1ll << 31)) return hipErrorInvalidValue;
   }
+  tile_starts_set(b.starts, b.p, b.n);
   dim3 grid((unsigned)total), block(256);
   if (dtype == DT_BF16) hipLaunchKernelGGL((wgrad_reduce_kernel<uint16_t>), grid, block, 0, stream, b);
   else hipLaunchKernelGGL((wgrad_reduce_kernel<float>), grid, block, 0, stream, b);
@@ -984,6 +980,7 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
       total += ((p.M + 31) / 32) * p.tiles_n;
     }
     b.total_tiles = total;
+    tile_starts_set(b.starts, b.p, b.n);
     hipLaunchKernelGGL(conv_gemm_few_kernel, dim3(total), dim3(256), 0, stream, b);
     return hipGetLastError();
   }
@@ -1026,6 +1023,7 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
     }
   }
   b.total_tiles = total;
+  tile_starts_set(b.starts, b.p, b.n);
   dim3 grid(total);
   if (ragged) return dtype == DT_BF16 ? launch_conv_gemm_typed<uint16_t, 64, true>(b, bm, bn, grid, stream)
                                       : launch_conv_gemm_typed<float, 32, true>(b, bm, bn, grid, stream);
@@ -1049,6 +1047,7 @@ hipError_t launch_conv_wgrad_mixed(GemmBatch& b, int dtype, hipStream_t stream) 
     total += ((p.M + to - 1) / to) * p.tiles_n * p.splits;
   }
   b.total_tiles = total;
+  tile_starts_set(b.starts, b.p, b.n);
   if (dtype == DT_BF16) hipLaunchKernelGGL((conv_wgrad_mixed_kernel<uint16_t>), dim3(total), dim3(256), 0, stream, b);
   else hipLaunchKernelGGL((conv_wgrad_mixed_kernel<float>), dim3(total), dim3(256), 0, stream, b);
   return hipGetLastError();
@@ -1068,6 +1067,7 @@ hipError_t launch_conv_wgrad(GemmBatch& b, int dtype, bool wide, hipStream_t str
     total += ((p.M + to - 1) / to) * p.tiles_n * p.splits;
   }
   b.total_tiles = total;
+  tile_starts_set(b.starts, b.p, b.n);
   dim3 grid(total), block(256);
   if (dtype == DT_BF16) {
     if (wide) hipLaunchKernelGGL((conv_wgrad_kernel<uint16_t, 128>), grid, block, 0, stream, b);

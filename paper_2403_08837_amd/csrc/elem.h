@@ -38,13 +38,60 @@ template <typename T> union Chunk16 {
   T e[16 / sizeof(T)];
 };
 
-// Problem of a launch that owns tile number `tile` (problems are listed by ascending tile_begin).
-__device__ __forceinline__ int find_problem(const GemmBatch& batch, int tile) {
+// Problem of a launch of n problems that owns tile number `tile` (problems are listed by ascending tile_begin): compares on
+// scalars that one or two wide reads bring in, no loop whose every step waits for a read.  A launch of one problem reads nothing.
+template <int MAX> __device__ __forceinline__ int tile_starts_find(const TileStarts<MAX>& t, int n, int tile) {
+  auto past = [&](int at) { return (int)((unsigned)(at - 1 - tile) >> 31); };  // tile >= at, without a trip through the vector unit
   int pi = 0;
-  for (int q = 1; q < batch.n; ++q)
-    if (tile >= batch.p[q].tile_begin) pi = q;
+  if (n > 1) {
+#pragma unroll
+    for (int q = 1; q < 8; ++q) pi += past(t.at[q]);
+    if (n > 8) {
+#pragma unroll
+      for (int q = 8; q < MAX; ++q) pi += past(t.at[q]);
+    }
+  }
   return pi;
 }
+// A descriptor of the argument block in registers, all of it in one round of scalar reads (the asm takes every part at once, so none
+// is put off).  Read field by field where they are used, a descriptor is a read of 300 ns at every place
+// the compiler moves one to: a small tile of linear_tick_kernel waits for six of them, of the nine microseconds it takes.
+template <typename S> __device__ __forceinline__ S read_args(const S& src) {
+  typedef uint32_t w16 __attribute__((ext_vector_type(16), aligned(4)));
+  typedef uint32_t w4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef uint32_t w2 __attribute__((ext_vector_type(2), aligned(4)));
+  constexpr int N = sizeof(S) / 4;
+  static_assert(sizeof(S) % 4 == 0 && (N == 38 || N == 24 || N == 20), "sizes this is written for");
+  const uint32_t* const p = reinterpret_cast<const uint32_t*>(&src);
+  struct alignas(alignof(S)) Words { uint32_t w[N]; } words;
+  w16 a = *reinterpret_cast<const w16*>(p);
+  if constexpr (N == 38) {
+    w16 b = *reinterpret_cast<const w16*>(p + 16);
+    w4 c = *reinterpret_cast<const w4*>(p + 32);
+    w2 d = *reinterpret_cast<const w2*>(p + 36);
+    asm volatile("" : "+s"(a), "+s"(b), "+s"(c), "+s"(d));
+#pragma unroll
+    for (int i = 0; i < 16; ++i) words.w[16 + i] = b[i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) words.w[32 + i] = c[i];
+    words.w[36] = d[0];
+    words.w[37] = d[1];
+  } else if constexpr (N == 24) {
+    w4 b = *reinterpret_cast<const w4*>(p + 16), c = *reinterpret_cast<const w4*>(p + 20);
+    asm volatile("" : "+s"(a), "+s"(b), "+s"(c));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { words.w[16 + i] = b[i]; words.w[20 + i] = c[i]; }
+  } else {
+    w4 b = *reinterpret_cast<const w4*>(p + 16);
+    asm volatile("" : "+s"(a), "+s"(b));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) words.w[16 + i] = b[i];
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) words.w[i] = a[i];
+  return __builtin_bit_cast(S, words);
+}
+__device__ __forceinline__ int find_problem(const GemmBatch& batch, int tile) { return tile_starts_find(batch.starts, batch.n, tile); }
 
 // blockIdx -> logical tile so that runs of G consecutive logical tiles (neighbours in a problem's tile grid, which
 // read the same operand rows) execute on one XCD and find each other's rows in its L2: consecutive workgroup ids

@@ -158,10 +158,7 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(const GemmBatch batch
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
-  int pi = 0;
-  for (int q = 1; q < batch.n; ++q)
-    if ((int)blockIdx.x >= batch.p[q].tile_begin) pi = q;
-  const GemmProb& P = batch.p[pi];
+  const GemmProb& P = batch.p[find_problem(batch, (int)blockIdx.x)];
 
   int local = (int)blockIdx.x - P.tile_begin;
   const int split = local % P.splits;
@@ -322,6 +319,7 @@ hipError_t launch_gemm_batch(GemmBatch& b, int dtype, int shape, hipStream_t str
     total += ((p.M + bm - 1) / bm) * p.tiles_n * p.splits;
   }
   b.total_tiles = total;
+  tile_starts_set(b.starts, b.p, b.n);
   if (dtype == DT_BF16) return wgrad ? launch_typed<uint16_t, 1>(b, shape, stream) : launch_typed<uint16_t, 0>(b, shape, stream);
   return wgrad ? launch_typed<float, 1>(b, shape, stream) : launch_typed<float, 0>(b, shape, stream);
 }

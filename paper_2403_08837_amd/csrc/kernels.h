@@ -119,6 +119,15 @@ struct StageCopy {
 };
 constexpr int STAGE_COPY_ELEMS = 8192;  // elements per copy tile
 
+// First tiles of the problems of a launch side by side, for the kernels' search (tile_starts_find): read from the problems
+// themselves it is one read of the argument block after the other, 150 bytes apart, each waited for (a launch of six
+// problems: 2200 cycles of a 9 us kernel, 600 so).  At the end of the argument block: a launch of one problem, which has nothing to
+// search, finds its problem next to the header as before.
+template <int MAX> struct TileStarts { int at[MAX]; };
+template <int MAX, typename Prob> inline void tile_starts_set(TileStarts<MAX>& t, const Prob* p, int n) {
+  for (int i = 0; i < MAX; ++i) t.at[i] = i < n ? p[i].tile_begin : 0x7fffffff;
+}
+
 constexpr int GEMM_MAX_PROBS = 24;
 constexpr int LIN_UPD_MAX = 2;
 struct GemmBatch {
@@ -139,8 +148,9 @@ struct GemmBatch {
   GemmProb p[GEMM_MAX_PROBS];
   LinUpdate upd[LIN_UPD_MAX];
   StageCopy sc;
+  TileStarts<GEMM_MAX_PROBS> starts;  // set by the launch functions
 };
-static_assert(sizeof(GemmBatch) <= 4000, "kernel argument block must stay under 4 KiB");
+static_assert(sizeof(GemmBatch) <= 4032, "kernel argument block must stay under 4 KiB");
 
 // Tile shape variants (rows x cols of C per workgroup).
 enum TileShape : int { TILE_128x128 = 0, TILE_64x128 = 1, TILE_64x64 = 2, TILE_COUNT = 3 };
@@ -210,7 +220,7 @@ struct WReduceProb {
 };
 constexpr int FOLD_COUNTERS = 1 << 16;  // counters the engine keeps for the fold launches
 constexpr int WREDUCE_MAX_PROBS = 32;
-struct WReduceBatch { int n; WReduceProb p[WREDUCE_MAX_PROBS]; };
+struct WReduceBatch { int n; WReduceProb p[WREDUCE_MAX_PROBS]; TileStarts<WREDUCE_MAX_PROBS> starts; };
 hipError_t launch_wgrad_reduce(WReduceBatch& b, int dtype, hipStream_t stream);
 
 // ---------------------------------------------------------------------------------
@@ -261,7 +271,7 @@ struct RepackArgs {
   int tile_begin;  // first workgroup of this matrix in the launch (set by launch_repack_batch)
 };
 constexpr int REPACK_MAX = 12;
-struct RepackBatch { int n; RepackArgs a[REPACK_MAX]; };
+struct RepackBatch { int n; RepackArgs a[REPACK_MAX]; TileStarts<REPACK_MAX> starts; };
 hipError_t launch_repack_batch(RepackBatch& b, int dtype, hipStream_t stream);
 
 // Explicit im2col for layers whose channel count is below one 16-byte chunk (the RGB stem):

@@ -349,6 +349,19 @@ __device__ __forceinline__ void thin_tile(const GemmBatch& batch, const GemmProb
       qb[j] = kin ? *reinterpret_cast<const uint4*>(Bp + offB[j] + k0) : make_uint4(0, 0, 0, 0);
     }
   };
+  // What the epilogue reads is requested ahead of the operands, not a memory round trip after them.
+  const bool ce = (P.flags & GF_CE) != 0;
+  const int c = col0 + r31;
+  const float bias = (P.epi == EPI_FWD && P.aux0 != nullptr) ? static_cast<const float*>(P.aux0)[min(c, P.N - 1)] : 0.f;
+  EpiOperand eo[4];
+  int label[4];
+  if (ce) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) label[q] = static_cast<const int32_t*>(P.aux2)[min(wave * 8 + g * 4 + q, P.M - 1)];
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) eo[q] = load_epilogue_operand<T>(P, min(wave * 8 + g * 4 + q, P.M - 1), min(c, P.N - 1), true);
+  }
   v16f_t acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -398,9 +411,6 @@ __device__ __forceinline__ void thin_tile(const GemmBatch& batch, const GemmProb
 #pragma unroll
   for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[v];
   __syncthreads();
-  const int c = col0 + r31;
-  const float bias = (P.epi == EPI_FWD && P.aux0 != nullptr && c < P.N) ? static_cast<const float*>(P.aux0)[c] : 0.f;
-  const bool ce = (P.flags & GF_CE) != 0;
   float vals[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -442,40 +452,39 @@ __device__ __forceinline__ void thin_tile(const GemmBatch& batch, const GemmProb
       for (int q = 0; q < 4; ++q) vals[q] += part[q];
     }
   }
-  EpiOperand eo[4];
+  if (!ce) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = wave * 8 + g * 4 + q;
-    eo[q] = load_epilogue_operand<T>(P, r, c, !ce && r < P.M && c < P.N);
+    for (int q = 0; q < 4; ++q) {
+      const int r = wave * 8 + g * 4 + q;
+      if (r < P.M && c < P.N) store_result<T>(P, r, c, vals[q], bias, eo[q]);
+    }
+    return;
   }
+  // Loss head on the logits rows this half wavefront holds (one class per lane, N <= 32): softmax cross-entropy, dlogits =
+  // (softmax - onehot) / rows, row loss added to its slot.  out = dlogits T[M][N], aux2 = labels, aux3 = loss slots,
+  // g.H = rows per loss slot.  The four rows go through every step together: one after the other their exchanges, each of
+  // which waits for the one before, were 11900 of the tile's 18400 cycles.
+  const bool cls = c < P.N;
+  float z[4], m[4], e[4], sum[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) m[q] = z[q] = cls ? vals[q] + bias : -INFINITY;
+#pragma unroll
+  for (int off = 16; off >= 1; off >>= 1)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[q] = fmaxf(m[q], __shfl_xor(m[q], off, 64));
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sum[q] = e[q] = cls ? expf(z[q] - m[q]) : 0.f;
+#pragma unroll
+  for (int off = 16; off >= 1; off >>= 1)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[q] += __shfl_xor(sum[q], off, 64);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const float val = vals[q];
-    const int r = wave * 8 + g * 4 + q;
-    if (!ce) {
-      if (r < P.M && c < P.N) store_result<T>(P, r, c, val, bias, eo[q]);
-      continue;
-    }
-    // Loss head on the logits row this half wavefront holds (one class per lane, N <= 32):
-    // softmax cross-entropy, dlogits = (softmax - onehot) / rows, row loss added to its slot.
-    // out = dlogits T[M][N], aux2 = labels, aux3 = loss slots, g.H = rows per loss slot.
-    const bool cls = c < P.N;
-    const float z = cls ? val + bias : -INFINITY;
-    float m = z;
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    const float e = cls ? expf(z - m) : 0.f;
-    float sum = e;
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    const int y = r < P.M ? static_cast<const int32_t*>(P.aux2)[r] : -1;
-    float own = (cls && c == y) ? (m + logf(sum)) - z : 0.f;  // the row's loss sits in the lane of its label
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) own += __shfl_xor(own, off, 64);
-    if (r < P.M) {
-      if (cls) static_cast<T*>(P.out)[(int64_t)r * P.ldo + c] = E::from_f32((e / sum - (c == y ? 1.f : 0.f)) / (float)P.M);
-      if (r31 == 0) atomicAdd(static_cast<int*>(P.aux3) + r / P.g.H, __float2int_rn(own / (float)P.g.H * LOSS_SCALE));  // fixed point: order-independent
-    }
+    const int r = wave * 8 + g * 4 + q, y = label[q];
+    if (r >= P.M) continue;
+    if (cls) static_cast<T*>(P.out)[(int64_t)r * P.ldo + c] = E::from_f32((e[q] / sum[q] - (c == y ? 1.f : 0.f)) / (float)P.M);
+    // the row's loss sits in the lane of its label; fixed point: order-independent
+    if (cls && c == y) atomicAdd(static_cast<int*>(P.aux3) + r / P.g.H, __float2int_rn(((m[q] + logf(sum[q])) - z[q]) / (float)P.g.H * LOSS_SCALE));
   }
 }
 
@@ -487,7 +496,7 @@ __device__ __forceinline__ void thin_tile(const GemmBatch& batch, const GemmProb
 // (ldb = K), out = G [N][K] (ldo = K), P.M = N, P.N = K, P.K = Mb (reduction length);
 // aux2 = bias-gradient vector [N] or NULL.
 template <typename T, int TN>
-__device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& P, int tile, unsigned char* smem) {
+__device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& P, int prob, int tile, unsigned char* smem) {
   using E = LT<T>;
   constexpr int TK = 128, MB = 64, VEC = E::VEC, NI2 = TN / 32;
   // LDS pitches (elements): bf16 fragments are read with the transposing LDS read, which wants
@@ -512,51 +521,84 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
   //   momentum:              v' = [mu*v + Gold/N + wd*w] + acc/N ,  w' = w - lr*v'
   const bool rmw = (flags & GF_ACCUM) != 0;
   const bool upd = P.upd != 0;
-  const LinUpdate& U = batch.upd[upd ? P.upd - 1 : 0];
+  LinUpdate U;
+  if (upd) U = read_args(batch.upd[__builtin_amdgcn_readfirstlane(P.upd - 1)]);
   const bool mom = upd && U.V != nullptr;
   const int gc = k0 + wave * 32 + (lane & 31);
-  float gold[16 * NI2];
-#pragma unroll
-  for (int i = 0; i < NI2; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = n0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-      const bool inb = r < Nn && gc < Kk;
-      const int64_t idx = (int64_t)r * P.ldo + gc;
-      gold[i * 16 + v] = (rmw && inb) ? G[idx] : 0.f;
-    }
-  if (upd) {
-    // All master weights (and velocities) of the tile are requested before the first one is used: read inside
-    // a per-element branch, each was waited for before the next was issued, 32 memory round trips in a row.
-    // Outside the matrix everything reads 0 and combines to 0.
-    float wm[16 * NI2];
+  // Elements outside the matrix read the nearest one inside and are not stored: with a guard on each read every element is a branch of
+  // its own, and a small tile is bound by that chain of branches and not by memory (a 64 x 64 fp32 layer on 8 rows:
+  // 3000 cycles of a tile that reads no old values, 7800 of one with the step, 900 and 2900 so).
+  const int gcc = min(gc, Kk - 1);
+  const bool rows_in = n0 + TN <= Nn;  // (uniform)
+  auto elem = [&](int i, int v) { return n0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3); };
+  auto load_tile = [&](const float* base, float* t) {
+    int ldo = P.ldo;
+    asm("" : "+s"(ldo));  // offsets are computed again for every array: kept, they are 64 registers
 #pragma unroll
     for (int i = 0; i < NI2; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = n0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        wm[i * 16 + v] = (r < Nn && gc < Kk) ? U.master[(int64_t)r * P.ldo + gc] : 0.f;
-      }
+      for (int v = 0; v < 16; ++v) t[i * 16 + v] = base[(int64_t)min(elem(i, v), Nn - 1) * ldo + gcc];
+  };
+  float gold[16 * NI2];
+  if (rmw) load_tile(G, gold);
+  else {
+#pragma unroll
+    for (int e = 0; e < 16 * NI2; ++e) gold[e] = 0.f;
+  }
+  const bool dvec = (P.lda % VEC) == 0, xvec = (P.ldb % VEC) == 0;
+  const bool whole = dvec && xvec && (Nn % VEC) == 0 && (Kk % VEC) == 0;  // every operand chunk is inside or outside the matrices
+  // the reduction runs over the rows of one micro-batch, or (GF_GROUP) of several micro-batches whose dY / X
+  // lie in buffers of their own
+  const bool grouped = (flags & GF_GROUP) != 0;
+  const int rows = grouped ? P.g.pad : Mb, nmem = grouped ? Mb / P.g.pad : 1;
+  constexpr int DCH = TN / VEC, XCH = TK / VEC;  // chunks per row
+  constexpr int ND = MB * DCH / 256, NX = MB * XCH / 256;
+  static_assert(ND * 256 == MB * DCH && NX * 256 == MB * XCH, "whole chunks per thread");
+  uint4 rd[ND], rx[NX];
+  const int per = (rows + MB - 1) / MB, nit = nmem * per;  // slabs of 64 rows of a member, of all members
+  auto fetch = [&](int it) {
+    const int mem = it / per, m0 = (it - mem * per) * MB;
+    const T* __restrict__ Dp = static_cast<const T*>(dw_member(batch.p[prob], mem, 0));
+    const T* __restrict__ Xp = static_cast<const T*>(dw_member(batch.p[prob], mem, 1));
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int id = tid + 256 * i, m = id / DCH, c = (id % DCH) * VEC;
+      rd[i] = (m0 + m < rows && n0 + c < Nn) ? *reinterpret_cast<const uint4*>(Dp + (int64_t)(m0 + m) * P.lda + n0 + c)
+                                            : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int id = tid + 256 * i, m = id / XCH, c = (id % XCH) * VEC;
+      rx[i] = (m0 + m < rows && k0 + c < Kk) ? *reinterpret_cast<const uint4*>(Xp + (int64_t)(m0 + m) * P.ldb + k0 + c)
+                                            : make_uint4(0, 0, 0, 0);
+    }
+  };
+  // A tile 32 rows high requests its operands with the old values still on their way and keeps its master weights for a step with
+  // momentum; one of 64 rows has no registers for either.
+  constexpr bool EARLY = NI2 == 1;
+  if (EARLY && whole) fetch(0);
+  // the bias: old sum, master, velocity of column n0 + tid
+  const bool bias_here = tk == 0 && P.aux2 != nullptr && tid < TN && n0 + tid < Nn, bias_step = bias_here && upd && U.bmaster != nullptr;
+  const float b_sum = bias_here && rmw ? static_cast<const float*>(P.aux2)[n0 + tid] : 0.f;
+  const float b_old = bias_step ? U.bmaster[n0 + tid] : 0.f;
+  float b_vel = bias_step && U.bV ? U.bV[n0 + tid] : 0.f;
+  float wm[16 * NI2];
+  if (upd) {
+    float vm[16 * NI2];
+    load_tile(U.master, wm);
+    if (EARLY && mom) load_tile(U.V, vm);
+#pragma unroll
+    for (int e = 0; e < 16 * NI2; ++e) {
+      const float gw = gold[e] * U.sgd.inv_n + U.sgd.wd * wm[e];
+      gold[e] = mom ? gw : wm[e] - U.sgd.lr * gw;
+    }
     if (mom) {
-      float vm[16 * NI2];
-#pragma unroll
-      for (int i = 0; i < NI2; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = n0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-          vm[i * 16 + v] = (r < Nn && gc < Kk) ? U.V[(int64_t)r * P.ldo + gc] : 0.f;
-        }
-#pragma unroll
-      for (int e = 0; e < 16 * NI2; ++e) {
-        const float gw = gold[e] * U.sgd.inv_n + U.sgd.wd * wm[e];
-        gold[e] = U.sgd.momentum * vm[e] + gw;
+      if (!EARLY) {
+        asm volatile("" ::: "memory");  // (three arrays at a time are more registers than there are)
+        load_tile(U.V, vm);
       }
-    } else {
 #pragma unroll
-      for (int e = 0; e < 16 * NI2; ++e) {
-        const float gw = gold[e] * U.sgd.inv_n + U.sgd.wd * wm[e];
-        gold[e] = wm[e] - U.sgd.lr * gw;
-      }
+      for (int e = 0; e < 16 * NI2; ++e) gold[e] = U.sgd.momentum * vm[e] + gold[e];
     }
   }
 
@@ -567,64 +609,54 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
     for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
   float bsum = 0.f;  // bias gradient of column n0 + tid (threads 0..63 of the first column tile)
 
-  const bool dvec = (P.lda % VEC) == 0, xvec = (P.ldb % VEC) == 0;
-  // the reduction runs over the rows of one micro-batch, or (GF_GROUP) of several micro-batches whose dY / X
-  // lie in buffers of their own
-  const bool grouped = (flags & GF_GROUP) != 0;
-  const int rows = grouped ? P.g.pad : Mb, nmem = grouped ? Mb / P.g.pad : 1;
-  constexpr int DCH = TN / VEC, XCH = TK / VEC;  // chunks per row
-  constexpr int ND = MB * DCH / 256, NX = MB * XCH / 256;
-  static_assert(ND * 256 == MB * DCH && NX * 256 == MB * XCH, "whole chunks per thread");
   // 3. contraction over the batch rows of the staged slab; fragments are read transposed out of LDS
-  auto contract = [&]() {
+  // (mr: rows of the slab that exist; the rest of it is zeros and only the last group of rows is contracted with some)
+  auto contract = [&](int mr) {
     const int g = lane >> 5, l31 = lane & 31;
     if constexpr (sizeof(T) == 2) {
+      if (mr > MB - 16) {
 #pragma unroll
-      for (int kk = 0; kk < MB; kk += 16) {
-        const uint4 bv = frag_tr_bf16(Xs, PX, kk, wave * 32, lane);
+        for (int kk = 0; kk < MB; kk += 16) {
+          const uint4 bv = frag_tr_bf16(Xs, PX, kk, wave * 32, lane);
 #pragma unroll
-        for (int i = 0; i < NI2; ++i) acc[i] = mfma_bf16(frag_tr_bf16(Ds, PD, kk, i * 32, lane), bv, acc[i]);
+          for (int i = 0; i < NI2; ++i) acc[i] = mfma_bf16(frag_tr_bf16(Ds, PD, kk, i * 32, lane), bv, acc[i]);
+        }
+      } else {
+        for (int kk = 0; kk < mr; kk += 16) {
+          const uint4 bv = frag_tr_bf16(Xs, PX, kk, wave * 32, lane);
+#pragma unroll
+          for (int i = 0; i < NI2; ++i) acc[i] = mfma_bf16(frag_tr_bf16(Ds, PD, kk, i * 32, lane), bv, acc[i]);
+        }
       }
     } else {
-#pragma unroll 8
-      for (int kk = 0; kk < MB; kk += 2) {
+      auto step = [&](int kk) {
         const float bv = Xs[(kk + g) * PX + wave * 32 + l31];
 #pragma unroll
         for (int i = 0; i < NI2; ++i)
           acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(Ds[(kk + g) * PD + i * 32 + l31], bv, acc[i], 0, 0, 0);
+      };
+      if (mr > MB - 8) {
+#pragma unroll 8
+        for (int kk = 0; kk < MB; kk += 2) step(kk);
+      } else {
+        for (int k8 = 0; k8 < mr; k8 += 8)
+#pragma unroll
+          for (int kk = k8; kk < k8 + 8; kk += 2) step(kk);
       }
     }
     if (tk == 0 && P.aux2 != nullptr && tid < TN) {
-      for (int m = 0; m < MB; ++m) bsum += E::to_f32(Ds[m * PD + tid]);
+      for (int m8 = 0; m8 < mr; m8 += 8)
+#pragma unroll
+        for (int m = m8; m < m8 + 8; ++m) bsum += E::to_f32(Ds[m * PD + tid]);
     }
   };
-  if (dvec && xvec && (Nn % VEC) == 0 && (Kk % VEC) == 0) {
-    // 2. every chunk is whole (inside or outside the matrices): slabs of 64 batch rows of dY[.., n0..n0+TN-1] and
-    // X[.., k0..k0+127] are staged as they lie in memory, one slab ahead: the next slab (of this member or of the
-    // next one of the group) is requested before the current one is contracted, so a reduction over several
-    // slabs is not one memory round trip per slab.  All of a thread's chunks are requested before the first one
+  if (whole) {
+    if (!EARLY) fetch(0);
+    // 2. slabs of 64 batch rows of dY[.., n0..n0+TN-1] and X[.., k0..k0+127] are staged as they lie in memory, one slab ahead: the next
+    // slab (of this member or of the next one of the group) is requested before the current one is contracted, so a reduction over
+    // several slabs is not one memory round trip per slab.  All of a thread's chunks are requested before the first one
     // is written to LDS (requested one by one, the six round trips of a bf16 tile cost 30 us of a 280 us launch
     // of 16384 tiles).
-    const int per = (rows + MB - 1) / MB, nit = nmem * per;
-    uint4 rd[ND], rx[NX];
-    auto fetch = [&](int it) {
-      const int mem = it / per, m0 = (it - mem * per) * MB;
-      const T* __restrict__ Dp = static_cast<const T*>(dw_member(P, mem, 0));
-      const T* __restrict__ Xp = static_cast<const T*>(dw_member(P, mem, 1));
-#pragma unroll
-      for (int i = 0; i < ND; ++i) {
-        const int id = tid + 256 * i, m = id / DCH, c = (id % DCH) * VEC;
-        rd[i] = (m0 + m < rows && n0 + c < Nn) ? *reinterpret_cast<const uint4*>(Dp + (int64_t)(m0 + m) * P.lda + n0 + c)
-                                              : make_uint4(0, 0, 0, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < NX; ++i) {
-        const int id = tid + 256 * i, m = id / XCH, c = (id % XCH) * VEC;
-        rx[i] = (m0 + m < rows && k0 + c < Kk) ? *reinterpret_cast<const uint4*>(Xp + (int64_t)(m0 + m) * P.ldb + k0 + c)
-                                              : make_uint4(0, 0, 0, 0);
-      }
-    };
-    fetch(0);
     for (int it = 0; it < nit; ++it) {
       if (it > 0) __syncthreads();
 #pragma unroll
@@ -647,12 +679,12 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
       }
       __syncthreads();
       if (it + 1 < nit) fetch(it + 1);
-      contract();
+      contract(min(MB, rows - it % per * MB));
     }
   } else {
   for (int mem = 0; mem < nmem; ++mem) {
-  const T* __restrict__ Dp = static_cast<const T*>(dw_member(P, mem, 0));
-  const T* __restrict__ Xp = static_cast<const T*>(dw_member(P, mem, 1));
+  const T* __restrict__ Dp = static_cast<const T*>(dw_member(batch.p[prob], mem, 0));
+  const T* __restrict__ Xp = static_cast<const T*>(dw_member(batch.p[prob], mem, 1));
   for (int m0 = 0; m0 < rows; m0 += MB) {
     if (mem > 0 || m0 > 0) __syncthreads();
     {
@@ -694,24 +726,31 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
       }
     }
     __syncthreads();
-    contract();
+    contract(min(MB, rows - m0));
   }
   }
   }
 
   if (!upd) {
     // 4. accumulate and write back
+    int ldo32 = P.ldo;
+    asm("" : "+s"(ldo32));
+    const int64_t ldo = ldo32;
+    if (gc < Kk) {
+      if (rows_in) {
 #pragma unroll
-    for (int i = 0; i < NI2; ++i)
+        for (int i = 0; i < NI2; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = n0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        if (r < Nn && gc < Kk) G[(int64_t)r * P.ldo + gc] = gold[i * 16 + v] + acc[i][v];
+          for (int v = 0; v < 16; ++v) G[elem(i, v) * ldo + gc] = gold[i * 16 + v] + acc[i][v];
+      } else {
+#pragma unroll
+        for (int i = 0; i < NI2; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            if (elem(i, v) < Nn) G[elem(i, v) * ldo + gc] = gold[i * 16 + v] + acc[i][v];
       }
-    if (tk == 0 && P.aux2 != nullptr && tid < TN && n0 + tid < Nn) {
-      float* gb = static_cast<float*>(P.aux2) + n0 + tid;
-      *gb = rmw ? (*gb + bsum) : bsum;
     }
+    if (bias_here) static_cast<float*>(P.aux2)[n0 + tid] = rmw ? b_sum + bsum : bsum;
     return;
   }
 
@@ -724,83 +763,93 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
   const float lr = U.sgd.lr, inv_n = U.sgd.inv_n, step = U.sgd.lr * U.sgd.inv_n;
   float* const master = U.master;
   float* const Vel = U.V;
-  float wm[16 * NI2];
-  if (mom) {  // the master weights again, all requested before the first store
-#pragma unroll
-    for (int i = 0; i < NI2; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = n0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        wm[i * 16 + v] = (r < Nn && gc < Kk) ? master[(int64_t)r * P.ldo + gc] : 0.f;
-      }
-  }
+  float late[16 * NI2];
+  if (!EARLY && mom) load_tile(master, late);  // the master weights again, all requested before the first store
+  int ldo32 = P.ldo;
+  asm("" : "+s"(ldo32));
+  const int64_t ldo = ldo32;
+  float wn[16 * NI2];
 #pragma unroll
   for (int i = 0; i < NI2; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int rl = i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-      const int r = n0 + rl;
-      float w = 0.f;
-      if (r < Nn && gc < Kk) {
-        const int64_t idx = (int64_t)r * P.ldo + gc;
-        if (mom) {
-          const float vel = gold[i * 16 + v] + acc[i][v] * inv_n;
-          Vel[idx] = vel;
-          w = wm[i * 16 + v] - lr * vel;
-        } else {
-          w = gold[i * 16 + v] - step * acc[i][v];
-        }
-        master[idx] = w;
+      const int e = i * 16 + v;
+      if (mom) {
+        gold[e] = gold[e] + acc[i][v] * inv_n;  // the new velocity
+        wn[e] = (EARLY ? wm[e] : late[e]) - lr * gold[e];
+      } else {
+        wn[e] = gold[e] - step * acc[i][v];
       }
-      Ws[rl * PW + wave * 32 + (lane & 31)] = E::from_f32(w);
+      Ws[(elem(i, v) - n0) * PW + wave * 32 + (lane & 31)] = E::from_f32(wn[e]);  // (what lies outside the matrix is not copied out)
     }
+  if (gc < Kk) {
+#pragma unroll
+    for (int i = 0; i < NI2; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (rows_in || elem(i, v) < Nn) master[elem(i, v) * ldo + gc] = wn[i * 16 + v];
+    if (mom) {
+#pragma unroll
+      for (int i = 0; i < NI2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (rows_in || elem(i, v) < Nn) Vel[elem(i, v) * ldo + gc] = gold[i * 16 + v];
+    }
+  }
   __syncthreads();
+  // Both compute copies: forward layout, rows n in 16-byte chunks along k; data-gradient layout, rows k in chunks along n (read
+  // transposed out of LDS).  All of a thread's chunks leave LDS before the first store.
   T* __restrict__ wf = static_cast<T*>(U.wf);
   T* __restrict__ wt = static_cast<T*>(U.wt);
-  {  // forward layout: rows n, 16-byte chunks along k
-    constexpr int CPR = TK / VEC;
-    const bool al = (Kk % VEC) == 0;
-    for (int id = tid; id < TN * CPR; id += 256) {
-      const int n = id / CPR, ck = (id % CPR) * VEC;
-      if (n0 + n >= Nn || k0 + ck >= Kk) continue;
-      Chunk16<T> tmp;
+  constexpr int CF = TK / VEC, CT = TN / VEC, NF = TN * CF / 256, NT = TK * CT / 256;
+  static_assert(NF * 256 == TN * CF && NT * 256 == TK * CT, "whole chunks per thread");
+  const bool al = (Kk % VEC) == 0 && (Nn % VEC) == 0;
+  Chunk16<T> cf[NF], ct[NT];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) tmp.e[e] = Ws[n * PW + ck + e];
-      T* dst = wf + (int64_t)(n0 + n) * Kk + k0 + ck;
-      if (al) {
-        *reinterpret_cast<uint4*>(dst) = tmp.v;
-      } else {
+  for (int i = 0; i < NF; ++i) {
+    const int id = tid + 256 * i, n = id / CF, ck = (id % CF) * VEC;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e)
-          if (k0 + ck + e < Kk) dst[e] = tmp.e[e];
-      }
+    for (int e = 0; e < VEC; ++e) cf[i].e[e] = Ws[n * PW + ck + e];
+  }
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const int id = tid + 256 * i, k = id / CT, cn = (id % CT) * VEC;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) ct[i].e[e] = Ws[(cn + e) * PW + k];
+  }
+  if (al) {  // every chunk is inside or outside
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const int id = tid + 256 * i, n = n0 + id / CF, k = k0 + (id % CF) * VEC;
+      if (n < Nn && k < Kk) *reinterpret_cast<uint4*>(wf + (int64_t)n * Kk + k) = cf[i].v;
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;
+      if (k < Kk && n < Nn) *reinterpret_cast<uint4*>(wt + (int64_t)k * Nn + n) = ct[i].v;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const int id = tid + 256 * i, n = n0 + id / CF, k = k0 + (id % CF) * VEC;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        if (n < Nn && k + e < Kk) wf[(int64_t)n * Kk + k + e] = cf[i].e[e];
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        if (k < Kk && n + e < Nn) wt[(int64_t)k * Nn + n + e] = ct[i].e[e];
     }
   }
-  {  // data-gradient layout: rows k, 16-byte chunks along n (read transposed out of LDS)
-    constexpr int CPR = TN / VEC;
-    const bool al = (Nn % VEC) == 0;
-    for (int id = tid; id < TK * CPR; id += 256) {
-      const int k = id / CPR, cn = (id % CPR) * VEC;
-      if (k0 + k >= Kk || n0 + cn >= Nn) continue;
-      Chunk16<T> tmp;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) tmp.e[e] = Ws[(cn + e) * PW + k];
-      T* dst = wt + (int64_t)(k0 + k) * Nn + n0 + cn;
-      if (al) {
-        *reinterpret_cast<uint4*>(dst) = tmp.v;
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e)
-          if (n0 + cn + e < Nn) dst[e] = tmp.e[e];
-      }
-    }
-  }
-  if (tk == 0 && U.bmaster != nullptr && tid < TN && n0 + tid < Nn) {
+  if (bias_step) {
     const int n = n0 + tid;
-    const float gb = (rmw ? static_cast<const float*>(P.aux2)[n] : 0.f) + bsum;
-    const float b = sgd_step(U.bmaster[n], gb, U.bV ? U.bV + n : nullptr, U.sgd);
+    const float b = sgd_step(b_old, b_sum + bsum, U.bV ? &b_vel : nullptr, U.sgd);
     U.bmaster[n] = b;
     U.bcopy[n] = b;
+    if (U.bV) U.bV[n] = b_vel;
   }
 }
 
@@ -1057,6 +1106,7 @@ __device__ __forceinline__ void linear_tick_body(const GemmBatch& batch) {
   // separately (each XCD gets a contiguous share of both, so a problem's activations sit in
   // one L2); the longer update tiles stay in launch order, which deals them round-robin to
   // all XCDs.
+  const TileStarts<GEMM_MAX_PROBS> starts = read_args(batch.starts);
   const int head8 = (batch.head_tiles + 7) & ~7, upd8 = (batch.upd_tiles + 7) & ~7;
   const int bid = (int)blockIdx.x;
   int tile;
@@ -1086,28 +1136,32 @@ __device__ __forceinline__ void linear_tick_body(const GemmBatch& batch) {
     tile = first + xcd_remap(bid - head8 - upd8, batch.total_tiles - first);
     if (tile >= batch.total_tiles) return;
   }
-  const GemmProb& P = batch.p[find_problem(batch, tile)];
-  if (P.epi == EPI_WGRAD) {
+  const int prob = __builtin_amdgcn_readfirstlane(tile_starts_find(starts, batch.n, tile));
+  const GemmProb& Q = batch.p[prob];
+  if (Q.epi == EPI_WGRAD) {
     constexpr bool RUN_UPD = BN == 128 && sizeof(T) == 2;  // the new-weight tile has LDS of its own only there
-    const bool upd_ok = RUN_UPD && P.upd != 0 && batch.upd[P.upd - 1].V == nullptr;
-    if (dw_run_length(P, E::VEC, upd_ok) > 1) {
+    const bool upd_ok = RUN_UPD && Q.upd != 0 && batch.upd[Q.upd - 1].V == nullptr;
+    if (dw_run_length(Q, E::VEC, upd_ok) > 1) {
       if constexpr (RUN_UPD) {
-        if (P.upd) {
-          dw_run<T, true>(batch, P, tile, smem);
+        if (Q.upd) {
+          dw_run<T, true>(batch, Q, tile, smem);
           return;
         }
       }
-      dw_run<T, false>(batch, P, tile, smem);
-    } else if (dw_tile_rows(P) == 32) dw_tile<T, 32>(batch, P, tile, smem);
-    else dw_tile<T, 64>(batch, P, tile, smem);
+      dw_run<T, false>(batch, Q, tile, smem);
+    } else {
+      const GemmProb P = read_args(Q);
+      if (dw_tile_rows(P) == 32) dw_tile<T, 32>(batch, P, prob, tile, smem);
+      else dw_tile<T, 64>(batch, P, prob, tile, smem);
+    }
   } else {
     if constexpr (THIN) {
-      if (P.flags & GF_THIN) {
-        thin_tile<T>(batch, P, tile, smem);
+      if (Q.flags & GF_THIN) {
+        thin_tile<T>(batch, read_args(Q), tile, smem);
         return;
       }
     }
-    skinny_tile<T, BN>(batch, P, tile, smem);
+    skinny_tile<T, BN>(batch, Q, tile, smem);
   }
 }
 
@@ -1220,6 +1274,7 @@ hipError_t launch_linear_tick(GemmBatch& b, int dtype, bool wide, bool allow_thi
     total += tiles;
   }
   b.total_tiles = total;
+  tile_starts_set(b.starts, b.p, b.n);
   // partial tiles are addressed by tile number: one slot size per launch
   b.slot_floats = skinny_split ? 64 * 64 : 32 * 32;
   if ((int64_t)b.head_tiles * b.slot_floats > (int64_t)THIN_WS_SLOTS * 1024 && split_ok) {

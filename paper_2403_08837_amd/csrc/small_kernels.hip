@@ -186,10 +186,7 @@ hipError_t launch_update_vec_batch(const VecUpdateBatch& b, SgdParams sgd, hipSt
 template <typename T>
 __global__ __launch_bounds__(256) void repack_kernel(const RepackBatch batch) {
   __shared__ float tile[64][65];
-  int pi = 0;
-  for (int q = 1; q < batch.n; ++q)
-    if ((int)blockIdx.x >= batch.a[q].tile_begin) pi = q;
-  const RepackArgs& a = batch.a[pi];
+  const RepackArgs& a = batch.a[tile_starts_find(batch.starts, batch.n, (int)blockIdx.x)];
   int local = (int)blockIdx.x - a.tile_begin;
   const int tiles_c = (a.C + 63) / 64, tiles_o = (a.O + 63) / 64;
   const int c0 = (local % tiles_c) * 64;
@@ -255,6 +252,7 @@ hipError_t launch_repack_batch(RepackBatch& b, int dtype, hipStream_t stream) {
     total += (int64_t)((a.C + 63) / 64) * ((a.O + 63) / 64) * a.T;
     if (total >= (1ll << 31)) return hipErrorInvalidValue;
   }
+  tile_starts_set(b.starts, b.a, b.n);
   CDP_DISPATCH(dtype, hipLaunchKernelGGL((repack_kernel<T>), dim3((unsigned)total), dim3(256), 0, stream, b));
   return hipGetLastError();
 }

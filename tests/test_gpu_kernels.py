@@ -76,6 +76,27 @@ def test_gemm_weight_gradient_tiles(dtype, M, N, K, lda, ldb):
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("K", [1, 7, 8, 9, 16, 17, 48, 49, 56, 57, 64, 72])
+@pytest.mark.parametrize("M,N", [(64, 64), (33, 130), (72, 200), (2080, 2056)])
+def test_gemm_weight_gradient_rows(dtype, K, M, N):
+    """C = A^T B over few rows: the last slab is contracted by groups of 8 (fp32) or 16 rows, and elements outside the matrix
+    read its edge; 2080 x 2056 has tiles 64 rows high, the others of 32."""
+    torch = _torch()
+    A = wl.random_normal(1, 10 * M + K, K * M).reshape(K, M)
+    Bm = wl.random_normal(2, 10 * N + K, K * N).reshape(K, N)
+    ref = _rnd(A, dtype).T @ _rnd(Bm, dtype)
+    Ad, Bd = _dev(A, dtype), _dev(Bm, dtype)
+    Cd = torch.full((M * N + 256,), float("nan"), dtype=torch.float32, device="cuda")
+    b.cdp_k_gemm(dtype, 0, 0, 0, Ad.data_ptr(), Bd.data_ptr(), Cd.data_ptr(), M, N, K, M, N)
+    torch.cuda.synchronize()
+    got = Cd.cpu().numpy().astype(np.float64)
+    assert np.isnan(got[M * N:]).all(), "written past the matrix"
+    got = got[:M * N].reshape(M, N)
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= 2e-5 * np.sqrt(K) * max(1.0, np.abs(ref).max())  # as above
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("M", [1, 16, 17, 32, 33, 64, 65, 128, 129])
 def test_gemm_few_rows(dtype, M):
     """The kernel for one problem of few rows: edges of its row blocks (129: the tick launch's tiles), ragged columns, and
