@@ -299,10 +299,8 @@ __device__ __forceinline__ void conv_wgrad_body(const GemmProb& P, int tile, T* 
   constexpr int WAVES_C = 4 / WAVES_O;         // 4 or 2
   constexpr int WTC = TC / WAVES_C;            // 32 or 64 columns per wave
   constexpr int NI = WTC / 32;                 // 1 or 2
-  int local = tile - P.tile_begin;
-  const int split = local % P.splits;
-  local /= P.splits;
-  const int tc = local % P.tiles_n, to = local / P.tiles_n;
+  const int row_tiles = (P.M + TO - 1) / TO, local = tile - P.tile_begin;
+  const int tc = local % P.tiles_n, to = local / P.tiles_n % row_tiles, split = local / P.tiles_n / row_tiles;  // tiles of a range are neighbours
   const int o0 = to * TO, col0 = tc * TC;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wo = wave / WAVES_C, wc = wave % WAVES_C;
@@ -365,8 +363,8 @@ __device__ __forceinline__ void conv_wgrad_body(const GemmProb& P, int tile, T* 
     for (int j = 0; j < NI; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  float bsum = 0.f;
-  const bool do_beta = (tc == 0) && P.aux3 != nullptr && tid < TO;
+  const bool do_beta = tc == 0 && P.aux3 != nullptr && wc == 0;
+  float bsum[2] = {0.f, 0.f};  // column sums of dy out of the fragments that are multiplied anyway
 
   // The range is walked in chunks of at most WG_MAX_SLABS slabs; per chunk the positions are
   // decoded once into the LDS table.
@@ -425,6 +423,13 @@ __device__ __forceinline__ void conv_wgrad_body(const GemmProb& P, int tile, T* 
         for (int i = 0; i < 2; ++i) a[i] = frag_tr_bf16(Ds, PD, kk, wo * 64 + i * 32, lane);
 #pragma unroll
         for (int j = 0; j < NI; ++j) b[j] = frag_tr_bf16(Xs, PX, kk, wc * WTC + j * 32, lane);
+        if (do_beta) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            auto pair = [&](uint32_t w) { return __uint_as_float(w << 16) + __uint_as_float(w & 0xffff0000u); };
+            bsum[i] += (pair(a[i].x) + pair(a[i].y)) + (pair(a[i].z) + pair(a[i].w));
+          }
+        }
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -438,14 +443,16 @@ __device__ __forceinline__ void conv_wgrad_body(const GemmProb& P, int tile, T* 
         for (int i = 0; i < 2; ++i) a[i] = Ds[(kk + gq) * PD + wo * 64 + i * 32 + l31];
 #pragma unroll
         for (int j = 0; j < NI; ++j) b[j] = Xs[(kk + gq) * PX + wc * WTC + j * 32 + l31];
+        if (do_beta) {
+          bsum[0] += a[0];
+          bsum[1] += a[1];
+        }
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
       }
     }
-    if (do_beta)
-      for (int m = 0; m < MB; ++m) bsum += E::to_f32(Ds[m * PD + tid]);
   }
   }
 
@@ -463,7 +470,14 @@ __device__ __forceinline__ void conv_wgrad_body(const GemmProb& P, int tile, T* 
         if (c < Ncol) part[(int64_t)r * Ncol + c] = acc[i][j][v];
       }
     }
-  if (do_beta && o0 + tid < Cout) static_cast<float*>(P.aux3)[(int64_t)split * Cout + o0 + tid] = bsum;
+  if (do_beta) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float sum = bsum[i] + __shfl_xor(bsum[i], 32, 64);
+      const int r = o0 + wo * 64 + i * 32 + (lane & 31);
+      if (lane < 32 && r < Cout) static_cast<float*>(P.aux3)[(int64_t)split * Cout + r] = sum;
+    }
+  }
 }
 
 template <typename T, int TO>
@@ -473,7 +487,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(const GemmBatch batch) 
   __shared__ __attribute__((aligned(16))) T Xs[MB * (128 + PAD)];
   __shared__ int pos_base[WG_MAX_SLABS * MB];
   __shared__ int pos_hw[WG_MAX_SLABS * MB];
-  const int tile = (int)blockIdx.x;
+  const int tile = xcd_block_cyclic((int)blockIdx.x, batch.total_tiles, batch.xcd_run);
   conv_wgrad_body<T, TO>(batch.p[find_problem(batch, tile)], tile, Ds, Xs, pos_base, pos_hw);
 }
 // Tiles of both heights in one launch (the height is the problem's: 128 rows for matrices of 128 rows and more, 64
@@ -487,7 +501,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_mixed_kernel(const GemmBatch b
   __shared__ __attribute__((aligned(16))) T Xs[MB * (128 + PAD)];
   __shared__ int pos_base[WG_MAX_SLABS * MB];
   __shared__ int pos_hw[WG_MAX_SLABS * MB];
-  const int tile = (int)blockIdx.x;
+  const int tile = xcd_block_cyclic((int)blockIdx.x, batch.total_tiles, batch.xcd_run);
   const GemmProb& P = batch.p[find_problem(batch, tile)];
   if (conv_wgrad_rows(P) == 128) conv_wgrad_body<T, 128>(P, tile, Ds, Xs, pos_base, pos_hw);
   else conv_wgrad_body<T, 64>(P, tile, Ds, Xs, pos_base, pos_hw);
@@ -1033,6 +1047,17 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
               : launch_conv_gemm_typed<float, 16>(b, bm, bn, grid, stream);
 }
 
+// Neighbouring weight-gradient tiles that go to one XCD.  The tiles of a range read the same rows of dy and x, so an XCD that holds
+// many of them finds those rows in its L2; dealt one by one every XCD reads every row.  Launches of several shapes take shorter runs:
+// their tiles are of different lengths and long runs leave an XCD with the longest ones.  us with 1 / 8 / 16 / 32 / 64:
+//   six ResNet stages, 11 layers (about 1400 tiles)     145.5 / 141.6 / 141.5 / 143.4 / 165.8
+//   16 ViT layers of 6272 rows, two ranges (3456)       556.6 / 547.8 / 543.1 / 538.1 / 531.0
+//   3072 x 768 over 6272 rows, five ranges (720)         57.9 /  54.8 /  53.6 /  53.1 /  52.2
+//   128 x 1152 over 25088 positions, 28 ranges (252)     29.1 /  28.1 /  27.8 /  27.6 /  27.6
+// (ranges as neighbours instead of tiles, as before: 170, 589, 58.1, 29.8; part of that is the column sums of dy, then read
+// back out of LDS row by row.)
+static int wgrad_xcd_run(const GemmBatch& b) { return b.n == 1 || b.total_tiles >= 2048 ? 32 : 16; }
+
 hipError_t launch_conv_wgrad_mixed(GemmBatch& b, int dtype, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
   if (b.n > GEMM_MAX_PROBS) return hipErrorInvalidValue;
@@ -1048,6 +1073,7 @@ hipError_t launch_conv_wgrad_mixed(GemmBatch& b, int dtype, hipStream_t stream) 
   }
   b.total_tiles = total;
   tile_starts_set(b.starts, b.p, b.n);
+  b.xcd_run = wgrad_xcd_run(b);
   if (dtype == DT_BF16) hipLaunchKernelGGL((conv_wgrad_mixed_kernel<uint16_t>), dim3(total), dim3(256), 0, stream, b);
   else hipLaunchKernelGGL((conv_wgrad_mixed_kernel<float>), dim3(total), dim3(256), 0, stream, b);
   return hipGetLastError();
@@ -1068,6 +1094,8 @@ hipError_t launch_conv_wgrad(GemmBatch& b, int dtype, bool wide, hipStream_t str
   }
   b.total_tiles = total;
   tile_starts_set(b.starts, b.p, b.n);
+  b.xcd_run = wgrad_xcd_run(b);
+  b.xcd_run = wgrad_xcd_run(b);
   dim3 grid(total), block(256);
   if (dtype == DT_BF16) {
     if (wide) hipLaunchKernelGGL((conv_wgrad_kernel<uint16_t, 128>), grid, block, 0, stream, b);
