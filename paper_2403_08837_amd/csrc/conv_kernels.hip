@@ -1056,7 +1056,7 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
 //   128 x 1152 over 25088 positions, 28 ranges (252)     29.1 /  28.1 /  27.8 /  27.6 /  27.6
 // (ranges as neighbours instead of tiles, as before: 170, 589, 58.1, 29.8; part of that is the column sums of dy, then read
 // back out of LDS row by row.)
-static int wgrad_xcd_run(const GemmBatch& b) { return b.n == 1 || b.total_tiles >= 2048 ? 32 : 16; }
+int conv_wgrad_xcd_run(const GemmBatch& b) { return b.n == 1 || b.total_tiles >= 2048 ? 32 : 16; }
 
 hipError_t launch_conv_wgrad_mixed(GemmBatch& b, int dtype, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
@@ -1066,6 +1066,10 @@ hipError_t launch_conv_wgrad_mixed(GemmBatch& b, int dtype, hipStream_t stream) 
     GemmProb& p = b.p[i];
     if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.epi != EPI_WGRAD || !conv_fast_eligible(p, dtype)) return hipErrorInvalidValue;
     if (p.splits < 1 || p.splits > (p.K + wg_slab(dtype) - 1) / wg_slab(dtype)) return hipErrorInvalidValue;  // the caller sized the partial buffer
+  }
+  if (conv_wgrad_small_wanted(b, dtype)) return launch_conv_wgrad_small(b, dtype, stream);
+  for (int i = 0; i < b.n; ++i) {
+    GemmProb& p = b.p[i];
     const int to = conv_wgrad_rows(p);
     p.tiles_n = (p.N + 127) / 128;
     p.tile_begin = total;
@@ -1073,7 +1077,7 @@ hipError_t launch_conv_wgrad_mixed(GemmBatch& b, int dtype, hipStream_t stream) 
   }
   b.total_tiles = total;
   tile_starts_set(b.starts, b.p, b.n);
-  b.xcd_run = wgrad_xcd_run(b);
+  b.xcd_run = conv_wgrad_xcd_run(b);
   if (dtype == DT_BF16) hipLaunchKernelGGL((conv_wgrad_mixed_kernel<uint16_t>), dim3(total), dim3(256), 0, stream, b);
   else hipLaunchKernelGGL((conv_wgrad_mixed_kernel<float>), dim3(total), dim3(256), 0, stream, b);
   return hipGetLastError();
@@ -1088,14 +1092,18 @@ hipError_t launch_conv_wgrad(GemmBatch& b, int dtype, bool wide, hipStream_t str
     GemmProb& p = b.p[i];
     if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.epi != EPI_WGRAD || !conv_fast_eligible(p, dtype)) return hipErrorInvalidValue;
     if (p.splits < 1 || p.splits > (p.K + wg_slab(dtype) - 1) / wg_slab(dtype)) return hipErrorInvalidValue;  // the caller sized the partial buffer
+  }
+  if (conv_wgrad_small_wanted(b, dtype)) return launch_conv_wgrad_small(b, dtype, stream);
+  for (int i = 0; i < b.n; ++i) {
+    GemmProb& p = b.p[i];
     p.tiles_n = (p.N + 127) / 128;
     p.tile_begin = total;
     total += ((p.M + to - 1) / to) * p.tiles_n * p.splits;
   }
   b.total_tiles = total;
   tile_starts_set(b.starts, b.p, b.n);
-  b.xcd_run = wgrad_xcd_run(b);
-  b.xcd_run = wgrad_xcd_run(b);
+  b.xcd_run = conv_wgrad_xcd_run(b);
+  b.xcd_run = conv_wgrad_xcd_run(b);
   dim3 grid(total), block(256);
   if (dtype == DT_BF16) {
     if (wide) hipLaunchKernelGGL((conv_wgrad_kernel<uint16_t, 128>), grid, block, 0, stream, b);

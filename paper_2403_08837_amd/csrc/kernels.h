@@ -204,6 +204,10 @@ int conv_wgrad_slab(int dtype);  // output positions per reduction slab; a probl
 hipError_t launch_conv_wgrad(GemmBatch& batch, int dtype, bool wide, hipStream_t stream);
 // the same with the tile height chosen per problem (128 rows for matrices of 128 rows and more, 64 below)
 hipError_t launch_conv_wgrad_mixed(GemmBatch& batch, int dtype, hipStream_t stream);
+// Launches of either kind that are short of workgroups (conv_wgrad_small.hip); same partial sums.
+bool conv_wgrad_small_wanted(const GemmBatch& b, int dtype);
+hipError_t launch_conv_wgrad_small(GemmBatch& b, int dtype, hipStream_t stream);
+int conv_wgrad_xcd_run(const GemmBatch& b);  // neighbouring tiles that go to one XCD (total_tiles is set)
 struct WReduceProb {
   const float* part; const float* part_beta;  // partial sums [splits][Cout][Ncol], [splits][Cout]
   float* G; float* Ggamma; float* Gbeta;      // accumulators (Ggamma / Gbeta may be NULL)

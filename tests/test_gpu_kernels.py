@@ -224,6 +224,39 @@ def test_conv_weight_gradient_added_to_an_accumulator(dtype, case):
         b.cdp_k_conv(dtype, 9, dyd.data_ptr(), xd.data_ptr(), got.data_ptr(), *case)
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("sums", [1, 2, 5, 12])
+@pytest.mark.parametrize("case", [(1, 1, 1, 8, 8, 1, 1, 0),       # one position
+                                  (3, 5, 7, 24, 40, 3, 1, 1),     # 105 positions: a group (or slab) and a part of one
+                                  (2, 8, 8, 8, 72, 3, 1, 1),      # 128 positions: whole slabs; a second row of tiles with 8 rows
+                                  (3, 8, 8, 16, 64, 5, 1, 2),     # 25 taps, 400 columns
+                                  (5, 9, 9, 40, 136, 3, 2, 1),    # stride 2 on an odd map
+                                  (4, 11, 13, 48, 24, 1, 2, 0),   # 1x1, stride 2: gathered
+                                  (2, 1, 321, 136, 200, 1, 1, 0), # plain rows, 642 positions: every remainder of the three stages
+                                  (1, 1, 961, 32, 32, 1, 1, 0)])
+def test_conv_weight_gradient_short_of_workgroups(dtype, case, sums):
+    """The tiles of launches short of workgroups, from one range to several (some of them empty), operands 16-byte aligned and not,
+    against the oracle; nothing is written past the result."""
+    torch = _torch()
+    B, H, W, Cin, Cout, ks, st, pad = case
+    Ho, Wo = (H + 2 * pad - ks) // st + 1, (W + 2 * pad - ks) // st + 1
+    x = wl.random_normal(6, 1, B * H * W * Cin).reshape(B, H, W, Cin)
+    dy = wl.random_normal(6, 2, B * Ho * Wo * Cout).reshape(B, Ho, Wo, Cout)
+    _, dw = L.conv2d_bwd(_rnd(x, dtype), np.zeros((Cout, ks, ks, Cin)), st, pad, _rnd(dy, dtype))
+    xd = _dev(x, dtype)
+    for shift in (0, 4):
+        room = torch.empty(dy.size + 8, dtype=xd.dtype, device="cuda")
+        dyd = room[shift:shift + dy.size]
+        dyd.copy_(_dev(dy, dtype).reshape(-1))
+        got = torch.full((dw.size + 64,), float("nan"), dtype=torch.float32, device="cuda")
+        ws = torch.full((dw.size * sums + 64,), float("nan"), dtype=torch.float32, device="cuda")
+        b.cdp_k_conv(dtype, 2, dyd.data_ptr(), xd.data_ptr(), got.data_ptr(), *case, ws_ptr=ws.data_ptr(), ws_bytes=dw.size * sums * 4)
+        torch.cuda.synchronize()
+        assert torch.isnan(got[dw.size:]).all() and torch.isnan(ws[dw.size * sums:]).all(), "written past the end"
+        # products of exactly representable inputs, fp32 sums
+        _close(got[:dw.size].reshape(dw.shape), dw, 1e-5, (sums, shift))
+
+
 LARGE_TILE_CASES = [
     # pass, B, H, W, Cin, Cout, ks, stride, pad: shapes that fill the chip with 256 x 256 tiles
     ("fwd", 16, 56, 56, 64, 256, 3, 1, 1),
