@@ -48,8 +48,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // BM x BN outputs per workgroup of WAVES_M x WAVES_N wavefronts, slabs of BK, STAGES of them in LDS; WPS: wavefronts per SIMD
 // that LDS allows (said to the compiler, which otherwise copies the accumulators between the two register files).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WPS) void conv_gemm_dl_kernel(const GemmBatch batch) {
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool GELU>
+__device__ __forceinline__ void conv_gemm_dl_body(const GemmBatch& batch) {
   constexpr int NWAVE = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;  // wave tile
   constexpr int MI = WTM / 32, NI = WTN / 32;            // MFMA tiles per wave
@@ -247,7 +247,20 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WPS) void conv_gemm_dl_kern
       }
     });
   }
-  conv_epilogue<uint16_t, MI, NI>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane);
+  conv_epilogue<uint16_t, MI, NI, GELU>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane);
+}
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WPS) void conv_gemm_dl_kernel(const GemmBatch batch) {
+  conv_gemm_dl_body<BM, BN, WAVES_M, WAVES_N, BK, STAGES, false>(batch);
+}
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WPS) void conv_gelu_dl_kernel(const GemmBatch batch) {
+  conv_gemm_dl_body<BM, BN, WAVES_M, WAVES_N, BK, STAGES, true>(batch);
+}
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
+static void launch_dl(const GemmBatch& b, dim3 grid, hipStream_t stream) {
+  if (conv_has_gelu(b)) hipLaunchKernelGGL((conv_gelu_dl_kernel<BM, BN, WAVES_M, WAVES_N, BK, STAGES, WPS>), grid, dim3(WAVES_M * WAVES_N * 64), 0, stream, b);
+  else hipLaunchKernelGGL((conv_gemm_dl_kernel<BM, BN, WAVES_M, WAVES_N, BK, STAGES, WPS>), grid, dim3(WAVES_M * WAVES_N * 64), 0, stream, b);
 }
 
 // A forward / data-gradient problem these tiles take: bf16, every reduction slab of `bk` inside one tap, 16-byte aligned
@@ -344,11 +357,11 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
   tile_starts_set(b.starts, b.p, b.n);
   const dim3 grid((unsigned)total);
   switch (tile) {
-    case DL_256x256: hipLaunchKernelGGL((conv_gemm_dl_kernel<256, 256, 2, 4, 64, 2, 2>), grid, dim3(512), 0, stream, b); break;
-    case DL_256x128: hipLaunchKernelGGL((conv_gemm_dl_kernel<256, 128, 4, 2, 64, 3, 2>), grid, dim3(512), 0, stream, b); break;
-    case DL_64x128: hipLaunchKernelGGL((conv_gemm_dl_kernel<64, 128, 2, 2, 64, 3, 2>), grid, dim3(256), 0, stream, b); break;
-    case DL_64x64: hipLaunchKernelGGL((conv_gemm_dl_kernel<64, 64, 2, 2, 64, 3, 3>), grid, dim3(256), 0, stream, b); break;
-    default: hipLaunchKernelGGL((conv_gemm_dl_kernel<64, 64, 2, 2, 32, 4, 4>), grid, dim3(256), 0, stream, b); break;
+    case DL_256x256: launch_dl<256, 256, 2, 4, 64, 2, 2>(b, grid, stream); break;
+    case DL_256x128: launch_dl<256, 128, 4, 2, 64, 3, 2>(b, grid, stream); break;
+    case DL_64x128: launch_dl<64, 128, 2, 2, 64, 3, 2>(b, grid, stream); break;
+    case DL_64x64: launch_dl<64, 64, 2, 2, 64, 3, 3>(b, grid, stream); break;
+    default: launch_dl<64, 64, 2, 2, 32, 4, 4>(b, grid, stream); break;
   }
   return hipGetLastError();
 }

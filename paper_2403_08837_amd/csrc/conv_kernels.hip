@@ -35,8 +35,9 @@ constexpr int XCD_RUN = 8;
 // RAGGED: channel counts that are whole 16-byte chunks but not whole slabs.  A chunk still lies inside one tap, but a slab
 // does not, so tap and address delta are the lane's own (all its rows load the same chunk column), found with a division
 // per slab; the last slab may be partial.
-template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>
-__global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gemm_kernel(const GemmBatch batch) {
+// GELU: problems of the launch may have GF_GELU (conv_gelu_kernel).
+template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED, bool GELU>
+__device__ __forceinline__ void conv_gemm_body(const GemmBatch& batch) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC, LDP = BK + VEC;
   constexpr int WTM = BM / 2, MI = WTM / 32;   // wave tile WTM x WTN
@@ -271,7 +272,17 @@ __global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gemm
   }
 
   __syncthreads();  // the operand tiles are consumed
-  conv_epilogue_rows<T, MI, NI>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane, reinterpret_cast<float*>(smem) + wave * conv_stage_floats(NI));
+  conv_epilogue_rows<T, MI, NI, GELU>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane, reinterpret_cast<float*>(smem) + wave * conv_stage_floats(NI));
+}
+template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>
+__global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gemm_kernel(const GemmBatch batch) {
+  conv_gemm_body<T, BM, BN, BK, DB, RAGGED, false>(batch);
+}
+// A kernel of its own: with the second epilogue in conv_gemm_kernel its launches without a GELU lose 2 % (3x3 over 128 channels, three passes, 60.3 ->
+// 62.6 us).
+template <int BM, int BN, int BK, bool DB, bool RAGGED>
+__global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gelu_kernel(const GemmBatch batch) {
+  conv_gemm_body<uint16_t, BM, BN, BK, DB, RAGGED, true>(batch);
 }
 
 // ---------------------------------------------------------------------------------
@@ -923,6 +934,12 @@ template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>
 static hipError_t launch_conv_gemm_inst(const GemmBatch& b, dim3 grid, hipStream_t stream) {
   constexpr int lds = conv_gemm_lds_bytes<T, BM, BN, BK, DB>();
   static_assert(lds <= 64 * 1024, "stays within the default dynamic LDS limit");
+  if constexpr (sizeof(T) == 2 && !(BM == 128 && BN == 64)) {  // (a GELU's contractions are more than 64 columns wide)
+    if (conv_has_gelu(b)) {
+      hipLaunchKernelGGL((conv_gelu_kernel<BM, BN, BK, DB, RAGGED>), grid, dim3(256), lds, stream, b);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((conv_gemm_kernel<T, BM, BN, BK, DB, RAGGED>), grid, dim3(256), lds, stream, b);
   return hipGetLastError();
 }
@@ -984,6 +1001,7 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
   if ((bm != 64 && bm != 128) || (bn != 64 && bn != 128)) return hipErrorInvalidValue;
   const int bk = dtype == DT_BF16 ? 32 : 16;
   int total = 0;
+  if (conv_has_gelu(b) && (dtype != DT_BF16 || (bm == 128 && bn == 64))) return hipErrorInvalidValue;
   if (const int dl = conv_dl_tile(b.p, b.n, dtype, b.thin_ws && b.thin_cnt)) return launch_conv_dl(b, dtype, dl, stream);
   if (conv_few_tiles(b, dtype)) {
     for (int i = 0; i < b.n; ++i) {

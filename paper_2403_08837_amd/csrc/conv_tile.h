@@ -2,6 +2,7 @@
 // the epilogue.
 #pragma once
 #include "elem.h"
+#include "gelu.h"
 #include "kernels.h"
 
 namespace cdp {
@@ -37,8 +38,9 @@ __device__ __forceinline__ void conv_row(const ConvGeom& g, int mode, int r, int
 }
 
 // Arithmetic of one 16-byte piece of the result: forward act(acc + bias + residual), data gradient mask(acc + addend (+ old)).
-// x1: the piece's residual / mask.
-template <typename T>
+// x1: the piece's residual / mask.  GF_GELU (bf16): forward also stores GELU of the stored result in aux2, the data gradient is
+// that of the GELU's input, x1.  Both round where the kernels of their own round, so the bits are theirs.
+template <typename T, bool GELU = false>
 __device__ __forceinline__ void conv_finish(const GemmProb& P, int64_t o, float* val, const float* bias, uint4 x1v) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC;
@@ -69,11 +71,26 @@ __device__ __forceinline__ void conv_finish(const GemmProb& P, int64_t o, float*
 #pragma unroll
       for (int e = 0; e < VEC; ++e) val[e] += E::to_f32(x2.e[e]);
     }
-    if (P.aux1) {
+    if (!GELU && P.aux1) {
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
         if (!(E::to_f32(x1.e[e]) > 0.f)) val[e] = 0.f;
     }
+  }
+  if constexpr (GELU) {
+    if (P.epi == EPI_FWD) {
+      Chunk16<T> act;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        res.e[e] = E::from_f32(val[e]);
+        act.e[e] = E::from_f32(gelu_f<T>(E::to_f32(res.e[e])));
+      }
+      *reinterpret_cast<uint4*>(outp + o) = res.v;
+      *reinterpret_cast<uint4*>(static_cast<T*>(P.aux2) + o) = act.v;
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) val[e] = E::to_f32(E::from_f32(val[e])) * gelu_df<T>(E::to_f32(x1.e[e]));
   }
 #pragma unroll
   for (int e = 0; e < VEC; ++e) res.e[e] = E::from_f32(val[e]);
@@ -87,8 +104,8 @@ __device__ __forceinline__ void conv_finish(const GemmProb& P, int64_t o, float*
 // Out of the registers: four columns are 16 bytes of an fp32 result; for bf16 one exchange between the lane halves makes
 // eight of them.  No LDS traffic and no barrier, but an instruction touches 32 rows, which the address path of the CU
 // takes at less than half the rate of whole rows.
-template <typename T, int MI, int NI>
-__device__ __forceinline__ void conv_epilogue(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
+template <typename T, int MI, int NI, bool GELU>
+__device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
   constexpr int VEC = Elem<T>::VEC, NS = 32 * NI / (2 * VEC);  // pieces of 2 VEC columns, VEC per lane half
   const int l31 = lane & 31, hi = lane >> 5;
   const T* aux1 = static_cast<const T*>(P.aux1);
@@ -132,17 +149,24 @@ __device__ __forceinline__ void conv_epilogue(const GemmProb& P, const v16f_t (&
       const int r = row(i);
       if (r >= P.M || c >= P.N) continue;  // N is a multiple of VEC on these paths
       const int64_t o = (int64_t)r * P.ldo + c;
-      conv_finish<T>(P, o, val, bias, !aux1 ? make_uint4(0, 0, 0, 0) : AHEAD ? pa[AHEAD ? i : 0][AHEAD ? s : 0] : *reinterpret_cast<const uint4*>(aux1 + o));
+      conv_finish<T, GELU>(P, o, val, bias, !aux1 ? make_uint4(0, 0, 0, 0) : AHEAD ? pa[AHEAD ? i : 0][AHEAD ? s : 0] : *reinterpret_cast<const uint4*>(aux1 + o));
     }
   }
+}
+template <typename T, int MI, int NI, bool GELU>  // GELU: the launch may hold problems with GF_GELU
+__device__ __forceinline__ void conv_epilogue(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
+  if constexpr (GELU) {
+    if (P.flags & GF_GELU) return conv_epilogue_as<T, MI, NI, true>(P, acc, row0, col0, lane);
+  }
+  conv_epilogue_as<T, MI, NI, false>(P, acc, row0, col0, lane);
 }
 
 // Through LDS, 32 rows at a time and in fp32: every instruction then moves whole rows.  `stage`: conv_stage_floats(NI) floats of
 // the wave's own, which no wave reads any more.  The residual / mask of all passes is requested in one go before the
 // first, into the registers the operand prefetch no longer needs (once per pass it is a memory round trip per pass).
 constexpr int conv_stage_floats(int NI) { return 32 * (32 * NI + 4); }
-template <typename T, int MI, int NI>
-__device__ __forceinline__ void conv_epilogue_rows(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane, float* stage) {
+template <typename T, int MI, int NI, bool GELU>
+__device__ __forceinline__ void conv_epilogue_rows_as(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane, float* stage) {
   constexpr int VEC = Elem<T>::VEC, SP = 32 * NI + 4;          // pitch: rows 4 banks apart
   constexpr int CPS = 32 * NI / VEC, NCH = 32 * CPS / 64;      // chunks per staged row, per lane and pass
   static_assert(64 % CPS == 0, "a lane keeps its columns from chunk to chunk");
@@ -183,9 +207,16 @@ __device__ __forceinline__ void conv_epilogue_rows(const GemmProb& P, const v16f
       float val[VEC];
 #pragma unroll
       for (int e = 0; e < VEC; ++e) val[e] = stage[sr * SP + (lane % CPS) * VEC + e];
-      conv_finish<T>(P, (int64_t)r * P.ldo + c, val, bias, aux1 ? pa[i][t] : make_uint4(0, 0, 0, 0));
+      conv_finish<T, GELU>(P, (int64_t)r * P.ldo + c, val, bias, aux1 ? pa[i][t] : make_uint4(0, 0, 0, 0));
     }
   }
+}
+template <typename T, int MI, int NI, bool GELU>
+__device__ __forceinline__ void conv_epilogue_rows(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane, float* stage) {
+  if constexpr (GELU) {
+    if (P.flags & GF_GELU) return conv_epilogue_rows_as<T, MI, NI, true>(P, acc, row0, col0, lane, stage);
+  }
+  conv_epilogue_rows_as<T, MI, NI, false>(P, acc, row0, col0, lane, stage);
 }
 
 }  // namespace cdp

@@ -86,6 +86,7 @@ enum : int {
   GF_THIN = 16,  // set by launch_linear_tick
   GF_A_F32 = 32, // linear_tick_kernel, forward: A holds fp32 values, rounded to the compute type on load
   GF_GROUP = 128, // linear_tick_kernel, WGRAD: operands of several micro-batches (DwGroupView)
+  GF_GELU = 256, // convolution kernels, bf16: forward, aux2 = GELU of the result; data gradient, times the GELU's derivative at aux1
   GF_CE = 64     // linear_tick_kernel, thin forward tile with N <= 32 classes: softmax cross-entropy in the epilogue
                  // (out = dlogits T[M][N], aux2 = int32 labels, aux3 = loss slots, g.H = rows per loss slot)
 };
@@ -184,6 +185,11 @@ constexpr int64_t THIN_WS_BYTES = (int64_t)THIN_WS_SLOTS * (32 * 32 * 4 + 4);  /
 
 // Implicit-GEMM convolution fast paths (channel counts that are multiples of the slab).
 bool conv_fast_eligible(const GemmProb& p, int dtype);
+inline bool conv_has_gelu(const GemmBatch& b) {
+  for (int i = 0; i < b.n; ++i)
+    if (b.p[i].flags & GF_GELU) return true;
+  return false;
+}
 void conv_gemm_tile(const GemmProb* p, int n, int* bm, int* bn);  // tile shape that keeps the chip busy for these problems
 hipError_t launch_conv_gemm(GemmBatch& batch, int dtype, int bm, int bn, hipStream_t stream);  // forward / data gradient
 // Direct-to-LDS variant for bf16 problems whose reduction slabs lie inside one tap: 256 x 256 tiles for large launches with

@@ -389,6 +389,18 @@ def test_vit_odd_shapes(name, rule):
     check(cfg, rule, cfg.steps)
 
 
+@pytest.mark.parametrize("dim,heads,B,rule", [(64, 4, 3, wl.RULE_V2),     # 192 rows, hidden width 256: the smallest tiles
+                                              (40, 5, 3, wl.RULE_V1),     # channel counts that are not whole slabs
+                                              (64, 2, 13, wl.RULE_V2),    # 832 rows, a ragged last tile
+                                              (32, 2, 40, wl.RULE_DP)])   # 2560 rows, hidden width 128
+def test_vit_gelu_in_the_contractions(dim, heads, B, rule):
+    """More than 128 token rows in bf16: the block's GELU is computed by the contractions before and after it (fewer rows, and
+    fp32, have kernels of its own)."""
+    cfg = wl.Config("vit_gelu", wl._vit(32, 4, dim, heads, 2, 5), (32, 32, 3), 5, N=2, B=B, dtype=wl.BF16, lr=0.02, steps=3,
+                    init_gain_last_affine=0.25, init_gain_head=0.2)
+    check(cfg, rule, cfg.steps)
+
+
 def test_vit_b16_full_shapes_single_microbatch(capfd):
     """Every stage of the ViT-B/16-shaped workload at its real shape (B = 32, 196 tokens of width
     768, 12 heads, 12 block stages, 1000 classes) with one micro-batch per step, where CDP-v2 is
