@@ -295,15 +295,22 @@ bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype) {
   return useful / ((double)rounds * 256 * BM * BN) >= 0.75;
 }
 
-// Launches that do not fill the chip twice over with 128 x 128 tiles: there the reduction is a chain of memory latencies per
-// workgroup, which the deeper prefetch hides, and conv_gemm_kernel, one slab ahead, does not.  The largest tile that still
-// gives every CU a workgroup, or, for 256 x 128 (eight wavefronts), half of them.  us, conv_gemm_kernel / here:
-//   256 x 128  6272 x 768 x 3072        84 / 49      6272 x 768 x 768       25 / 17
-//   64 x 128   25088 x 128 x 1152       19 / 16      data gradient          22 / 18
-//   64 x 64    6272 x 256 x 2304        23 / 17      1568 x 512 x 4608      40 / 24     6272 x 256 x 1024  12.9 / 9.5
-// and past the line 6272 x 3072 x 768 56 / 53, 25088 x 768 x 768 43 / 51: three register-staged workgroups per CU cover for
-// each other there.  64 x 64: slabs of 64 for long reductions, of 32 (twice the workgroups per CU) for short ones
+// Launches of one round or two, and long reductions.  conv_gemm_kernel is one slab ahead and needs its three workgroups per CU to
+// cover for each other; the tiles here, one workgroup of eight wavefronts per CU with two slabs on their way, do not, so what counts is how
+// full the rounds of 256 tiles are: the largest tile whose count fits one round.  us, conv_gemm_kernel / 256 x 128 / 192 x 128 / 128 x 128
+// (64 x 128 with four wavefronts, the tile of one round before):
+//   25088 x 128 x 1152   24.9 / 21.9 / 18.0 / 14.6 (17.1)     8503 x 344 x 3072    45.1 / 43.7 / 34.5 / 27.5 (31.3)
+//   2725 x 928 x 128      7.8 /  8.3 /  7.3 /  6.2 (6.4)      3457 x 984 x 1536    26.3 / 25.8 / 21.3 / 17.7 (19.2)
+//   6272 x 768 x 3072    54.2 / 44.3 / 37.3 / 53.2            6272 x 768 x 768     19.9 / 17.1 / 14.2 / 19.4
+//   20091 x 256 x 128     9.8 /  9.2 /  8.1 / 10.4            5684 x 768 x 2304    43.4 / 36.0 / 29.7 / 42.1
+//   12544 x 512 x 1024   24.5 / 21.3 / 30.8 / 23.3 (264 tiles of 192 x 128: two rounds)
+// Past one round of 256 x 128 conv_gemm_kernel's finer tiles round better, but it multiplies at two thirds of their rate, which decides
+// for reductions of 1024 and more.  In rounds of 256 x 128 it costs 0.0027 per 128 x 128 tile and at least 2, a round of 192 x 128 0.885:
+//   us, conv_gemm_kernel / 192 x 128  9673 x 1024 x 1024 35.5 / 31.2, 14518 x 768 x 2304 72.9 / 62.8, 9209 x 1024 x 4608 127 / 106; x 768 30.4 / 30.9;
+//   eight problems of 6272 x 768 x 3072 306 / 278 (256 x 128); four of 6272 x 768 x 2304 110 / 111, left where they are.
+// 64 x 64 (below 150 tiles of 128 x 128): slabs of 64 for long reductions, of 32 (twice the workgroups per CU) for short ones
 // (6272 x 1024 x 256 13.5 against 11.9, 1568 x 512 x 4608 23.8 against 25.5) and for channel counts that are odd multiples of 32.
+//   6272 x 256 x 2304 23 / 17 (conv_gemm_kernel / here)     1568 x 512 x 4608 40 / 24     6272 x 256 x 1024  12.9 / 9.5
 // At most 64 output columns: the same two tiles up to 384 rows of 128; past two workgroups per CU very long reductions are
 // conv_gemm_kernel's (us, that / slabs of 64 / of 32: 34848 x 64 x 5184 58 / 55 / 67, 34848 x 64 x 9216 100 / 109 / 123, 45000 x 64 x 576 11.5 / 10.1 / 10.1).
 // `shared`: there is a workspace in which workgroups can share a reduction.  A long reduction of few tiles is cut there (64 x 64
@@ -312,24 +319,30 @@ bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype) {
 // 784 x 256 x 2304 11.5 / 13.5, 1568 x 256 x 2304 14.3 / 13.4; 392 x 512 x 2048 10.0 / 11.7, 784 x 512 x 2048 15.0 / 11.7; 1568 x 128 x 1152
 // 8.5 / 8.9, 3136 x 128 x 1152 10.3 / 9.0; 256 x 64 x 576 7.9 / 6.4.
 int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
-  int64_t t128 = 0, t64 = 0, narrow = 0, kmax = 0;
+  int64_t t256 = 0, t192 = 0, t128 = 0, t64 = 0, narrow = 0, kmax = 0, kmin = INT64_MAX;
   bool slab64 = true, all_narrow = true;
   for (int i = 0; i < n; ++i) {
     if (!conv_dl_eligible(p[i], dtype, 32)) return 0;
     slab64 = slab64 && conv_dl_eligible(p[i], dtype, 64);
     all_narrow = all_narrow && p[i].N <= 64;
     t128 += (int64_t)((p[i].M + 127) / 128) * ((p[i].N + 127) / 128);
+    t192 += (int64_t)((p[i].M + 191) / 192) * ((p[i].N + 127) / 128);
+    t256 += (int64_t)((p[i].M + 255) / 256) * ((p[i].N + 127) / 128);
     t64 += (int64_t)((p[i].M + 63) / 64) * ((p[i].N + 63) / 64);
     narrow += (int64_t)((p[i].M + 127) / 128);
     kmax = std::max<int64_t>(kmax, p[i].K);
+    kmin = std::min<int64_t>(kmin, p[i].K);
   }
   if (shared && kmax >= 1024 && t64 <= std::min<int64_t>(kmax / 24, 256)) return 0;
   const int t6464 = slab64 && kmax >= 1024 ? DL_64x64 : DL_64x64_SHORT;
   if (all_narrow) return narrow < 384 && !(t64 > 512 && kmax > 7168) ? t6464 : 0;
-  if (t128 >= 512) return 0;
-  if (slab64 && t128 >= 256) return DL_256x128;
-  if (slab64 && t128 >= 150) return DL_64x128;
-  return t6464;
+  if (!slab64) return t128 >= 512 ? 0 : t6464;
+  if (t128 < 150) return t6464;
+  if (t128 <= 256) return DL_128x128;
+  if (t128 < 512) return t192 <= 256 ? DL_192x128 : DL_256x128;
+  if (kmin < 1024) return 0;
+  const double by256 = (double)((t256 + 255) / 256), by192 = 0.885 * ((t192 + 255) / 256), other = std::max(2.0, 0.0027 * t128);
+  return std::min(by256, by192) >= 0.93 * other ? 0 : by192 < by256 ? DL_192x128 : DL_256x128;
 }
 
 hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream) {
@@ -339,7 +352,8 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
   switch (tile) {
     case DL_256x256: bm = 256; bn = 256; break;
     case DL_256x128: bm = 256; bn = 128; break;
-    case DL_64x128: bm = 64; bn = 128; break;
+    case DL_192x128: bm = 192; bn = 128; break;
+    case DL_128x128: bm = 128; bn = 128; break;
     case DL_64x64: case DL_64x64_SHORT: bm = 64; bn = 64; break;
     default: return hipErrorInvalidValue;
   }
@@ -359,7 +373,8 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
   switch (tile) {
     case DL_256x256: launch_dl<256, 256, 2, 4, 64, 2, 2>(b, grid, stream); break;
     case DL_256x128: launch_dl<256, 128, 4, 2, 64, 3, 2>(b, grid, stream); break;
-    case DL_64x128: launch_dl<64, 128, 2, 2, 64, 3, 2>(b, grid, stream); break;
+    case DL_192x128: launch_dl<192, 128, 2, 4, 64, 3, 2>(b, grid, stream); break;
+    case DL_128x128: launch_dl<128, 128, 4, 2, 64, 3, 2>(b, grid, stream); break;
     case DL_64x64: launch_dl<64, 64, 2, 2, 64, 3, 3>(b, grid, stream); break;
     default: launch_dl<64, 64, 2, 2, 32, 4, 4>(b, grid, stream); break;
   }

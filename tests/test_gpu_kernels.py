@@ -534,16 +534,24 @@ def _conv_1x1_bf16(which, rows, cin, cout, seed=3):
 @pytest.mark.parametrize("rows,out", [(4100, 1032), (19300, 120), (700, 200), (190, 72), (513, 40)])
 @pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 6, 7, 16, 17, 18])
 def test_conv_short_of_workgroups(rows, out, slabs):
-    """Every tile of the launches that do not fill the chip (256 x 128, 64 x 128, 64 x 64 with slabs of 64 and of 32), ragged
+    """The tiles of the launches that do not fill the chip (192 x 128, 128 x 128, 64 x 64 with slabs of 64 and of 32), ragged
     in both directions, with every number of slabs that the unrolled pipeline can end on; forward and data gradient."""
     for red in ((64 * slabs, 32 * slabs) if slabs <= 7 else (64 * slabs,)):
         _conv_1x1_bf16(0, rows, red, out)
         _conv_1x1_bf16(1, rows, out, red)
 
 
-@pytest.mark.parametrize("case", [(4, 56, 56, 64, 320, 3, 1, 1),       # forward on 256 x 128 tiles, data gradient on 64 x 64
-                                  (8, 41, 41, 64, 136, 3, 1, 1),       # forward on 64 x 128
-                                  (8, 41, 41, 200, 192, 3, 1, 1),      # data gradient on 64 x 128
+@pytest.mark.parametrize("rows,out,slabs", [(13000, 500, 1), (13000, 500, 2), (13000, 500, 5),    # 256 x 128: 272 tiles of 192 x 128
+                                            (9310, 1032, 16), (9310, 1032, 17),                    # 192 x 128, 441 tiles in two rounds
+                                            (16330, 128, 3), (16390, 256, 3)])                     # 128 x 128, just below and above a full round
+def test_conv_rounds_of_tiles(rows, out, slabs):
+    """One round of tiles or two, at the lines of the rule."""
+    _conv_1x1_bf16(0, rows, 64 * slabs, out)
+
+
+@pytest.mark.parametrize("case", [(4, 56, 56, 64, 320, 3, 1, 1),       # forward on 192 x 128 tiles, data gradient on 64 x 64
+                                  (8, 41, 41, 64, 136, 3, 1, 1),       # forward on 128 x 128
+                                  (8, 41, 41, 200, 192, 3, 1, 1),      # data gradient on 128 x 128
                                   (9, 57, 57, 64, 200, 3, 2, 1), (5, 33, 31, 128, 64, 5, 2, 2),
                                   (3, 13, 11, 192, 128, 3, 1, 1), (2, 15, 15, 128, 192, 3, 3, 1)])   # 64 x 64, long reductions
 def test_conv_short_of_workgroups_taps(case):
