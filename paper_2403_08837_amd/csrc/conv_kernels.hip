@@ -375,7 +375,7 @@ __device__ __forceinline__ void conv_wgrad_body(const GemmProb& P, int tile, T* 
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   const bool do_beta = tc == 0 && P.aux3 != nullptr && wc == 0;
-  float bsum[2] = {0.f, 0.f};  // column sums of dy out of the fragments that are multiplied anyway
+  float bsum[2] = {0.f, 0.f};  // column sums of dy (bf16: out of the fragments that are multiplied anyway)
 
   // The range is walked in chunks of at most WG_MAX_SLABS slabs; per chunk the positions are
   // decoded once into the LDS table.
@@ -454,14 +454,18 @@ __device__ __forceinline__ void conv_wgrad_body(const GemmProb& P, int tile, T* 
         for (int i = 0; i < 2; ++i) a[i] = Ds[(kk + gq) * PD + wo * 64 + i * 32 + l31];
 #pragma unroll
         for (int j = 0; j < NI; ++j) b[j] = Xs[(kk + gq) * PX + wc * WTC + j * 32 + l31];
-        if (do_beta) {
-          bsum[0] += a[0];
-          bsum[1] += a[1];
-        }
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+      // The column sums have a pass of their own: an addition per fragment between the products keeps the compiler from requesting the
+      // x fragments of eight steps ahead, and every step then waits for its own (64 rows: 40 x 688 over 16530 positions 37.6 -> 42.2 us).
+      if (do_beta) {
+#pragma unroll 8
+        for (int kk = 0; kk < MB; kk += 2)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) bsum[i] += Ds[(kk + gq) * PD + wo * 64 + i * 32 + l31];
       }
     }
   }
