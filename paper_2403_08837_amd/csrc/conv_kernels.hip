@@ -1069,16 +1069,25 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
               : launch_conv_gemm_typed<float, 16>(b, bm, bn, grid, stream);
 }
 
-// Neighbouring weight-gradient tiles that go to one XCD.  The tiles of a range read the same rows of dy and x, so an XCD that holds
-// many of them finds those rows in its L2; dealt one by one every XCD reads every row.  Launches of several shapes take shorter runs:
-// their tiles are of different lengths and long runs leave an XCD with the longest ones.  us with 1 / 8 / 16 / 32 / 64:
+// Neighbouring weight-gradient tiles that go to one XCD (xcd_block_cyclic: whole blocks of eight such runs, what is left keeps its place).  The
+// tiles of a range read the same rows of dy and x, so an XCD that holds many of them finds those rows in its L2; dealt one by one every
+// XCD reads every row.  Launches of several shapes take shorter runs: their tiles are of different lengths and long runs leave an
+// XCD with the longest ones.  us with 1 / 8 / 16 / 32 / 64:
 //   six ResNet stages, 11 layers (about 1400 tiles)     145.5 / 141.6 / 141.5 / 143.4 / 165.8
 //   16 ViT layers of 6272 rows, two ranges (3456)       556.6 / 547.8 / 543.1 / 538.1 / 531.0
 //   3072 x 768 over 6272 rows, five ranges (720)         57.9 /  54.8 /  53.6 /  53.1 /  52.2
-//   128 x 1152 over 25088 positions, 28 ranges (252)     29.1 /  28.1 /  27.8 /  27.6 /  27.6
-// (ranges as neighbours instead of tiles, as before: 170, 589, 58.1, 29.8; part of that is the column sums of dy, then read
-// back out of LDS row by row.)
-int conv_wgrad_xcd_run(const GemmBatch& b) { return b.n == 1 || b.total_tiles >= 2048 ? 32 : 16; }
+// Short ranges of many tiles in one round (bf16: 768 workgroups are resident) have little to share, and there what counts is that the work
+// starts spread out: us with 1 / 4 / 32, bf16,
+//   648 x 576 over 3200, ten ranges (300 tiles)     22.6 / 25.4 / 25.9      1984 x 648 over 1088, three (288)    24.5 / 26.1 / 27.7
+//   104 x 5688 over 2048, seven (630)               21.9 / 22.0 / 24.3      40 x 8424 over 2448, eight (528)     18.6 / 18.6 / 20.8
+//   776 x 120 over 85050, 103 (721: long ranges)    78.8 / 54.4 / 54.1      272 x 368 over 18432, 36 (324: few tiles) 29.7 / 27.4 / 27.5
+// 411 launches of 250 to 2000 tiles: 6.3 % faster than ranges as neighbours, 5.9 % with runs of 32 throughout (the slowest 0.95 and 0.87).
+int conv_wgrad_xcd_run(const GemmBatch& b) {
+  if (b.n > 1) return b.total_tiles >= 2048 ? 32 : 16;
+  const int ranges = b.p[0].splits, tiles = b.total_tiles / ranges;
+  if (b.total_tiles <= 768 && b.p[0].K / ranges <= 600 && tiles >= (b.total_tiles <= 512 ? 28 : 40)) return b.total_tiles <= 512 ? 1 : 4;
+  return 32;
+}
 
 hipError_t launch_conv_wgrad_mixed(GemmBatch& b, int dtype, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
@@ -1124,7 +1133,6 @@ hipError_t launch_conv_wgrad(GemmBatch& b, int dtype, bool wide, hipStream_t str
   }
   b.total_tiles = total;
   tile_starts_set(b.starts, b.p, b.n);
-  b.xcd_run = conv_wgrad_xcd_run(b);
   b.xcd_run = conv_wgrad_xcd_run(b);
   dim3 grid(total), block(256);
   if (dtype == DT_BF16) {

@@ -384,7 +384,7 @@ hipError_t launch_conv_wgrad_small(GemmBatch& b, int dtype, hipStream_t stream) 
   }
   b.total_tiles = total;
   tile_starts_set(b.starts, b.p, b.n);
-  b.xcd_run = conv_wgrad_xcd_run(b);
+  b.xcd_run = b.n == 1 ? 32 : 16;  // (below 256 or 128 workgroups the order is as listed)
   if (bf16) hipLaunchKernelGGL(conv_wgrad_dl_kernel, dim3(total), dim3(256), 0, stream, b);
   else hipLaunchKernelGGL(conv_wgrad_few_kernel, dim3(total), dim3(256), 0, stream, b);
   return hipGetLastError();

@@ -213,7 +213,7 @@ hipError_t launch_conv_wgrad_mixed(GemmBatch& batch, int dtype, hipStream_t stre
 // Launches of either kind that are short of workgroups (conv_wgrad_small.hip); same partial sums.
 bool conv_wgrad_small_wanted(const GemmBatch& b, int dtype);
 hipError_t launch_conv_wgrad_small(GemmBatch& b, int dtype, hipStream_t stream);
-int conv_wgrad_xcd_run(const GemmBatch& b);  // neighbouring tiles that go to one XCD (total_tiles is set)
+int conv_wgrad_xcd_run(const GemmBatch& b);  // the two above: neighbouring tiles that go to one XCD (splits and total_tiles are set)
 struct WReduceProb {
   const float* part; const float* part_beta;  // partial sums [splits][Cout][Ncol], [splits][Cout]
   float* G; float* Ggamma; float* Gbeta;      // accumulators (Ggamma / Gbeta may be NULL)

@@ -1,5 +1,6 @@
 """Rules by which launches are laid out, asked of the built library: how many ranges the reduction of a weight gradient
-is cut into when it is launched on its own (conv_wgrad_splits_alone in csrc/conv_kernels.hip), which forward / data-gradient
+is cut into when it is launched on its own (conv_wgrad_splits_alone in csrc/conv_kernels.hip) and how many neighbouring tiles of it
+go to one XCD (conv_wgrad_xcd_run there), which forward / data-gradient
 launches share their reductions over workgroups (conv_dl_tile in csrc/conv256_kernels.hip), which attention passes run in
 one kernel (attention_fused in csrc/attention_kernels.hip), and which products of row-contiguous operands run on the
 weight-gradient tiles of the Linear launch (gemm_wgrad_tiles_wanted in csrc/kernels_api.cpp).  No GPU: the rules are host arithmetic, and the times they are held
@@ -33,6 +34,11 @@ def _asker(tmp_path_factory, name):
 @pytest.fixture(scope="module")
 def ranges(tmp_path_factory):
     return _asker(tmp_path_factory, "ranges")
+
+
+@pytest.fixture(scope="module")
+def runs(tmp_path_factory):
+    return _asker(tmp_path_factory, "runs")
 
 
 @pytest.fixture(scope="module")
@@ -86,6 +92,22 @@ def test_count_stays_within_bounds(ranges):
     for p, got in zip(problems, ranges(problems)):
         slabs = -(-p[3] // (64 if p[0] else 32))
         assert 1 <= got <= max(1, min(slabs, p[4])), (p, got)
+
+
+# M, N, K, ranges, us before tiles of a range were neighbours, {neighbouring tiles on one XCD: us}; bf16 but the last
+ORDER = [(648, 576, 3200, 10, 24.0, {1: 22.6, 4: 25.4, 32: 25.9}), (1984, 648, 1088, 3, 25.8, {1: 24.5, 4: 26.1, 32: 27.7}),
+         (280, 1224, 4800, 11, 25.5, {1: 26.3, 4: 27.2, 32: 29.2}), (784, 7128, 300, 1, 29.6, {1: 29.6, 4: 32.0, 32: 31.0}),
+         (1664, 792, 2200, 3, 36.2, {1: 34.6, 4: 35.5, 32: 37.7}), (1832, 896, 1104, 3, 26.6, {1: 26.2, 4: 26.1, 32: 28.4}),
+         (104, 5688, 2048, 7, 21.8, {1: 21.9, 4: 22.0, 32: 24.3}), (104, 1368, 15552, 27, 28.0, {1: 27.9, 4: 27.7, 32: 29.4}),
+         (40, 8424, 2448, 8, 22.0, {1: 18.6, 4: 18.6, 32: 20.8}), (80, 2400, 13950, 20, 33.3, {1: 30.3, 4: 30.4, 32: 31.9}),
+         (776, 120, 85050, 103, 82.3, {1: 78.8, 4: 54.4, 32: 54.1}), (272, 368, 18432, 36, 26.5, {1: 29.7, 4: 27.4, 32: 27.5}),
+         (928, 18400, 98, 1, 48.5, {1: 48.4, 4: 51.3, 32: 49.3}), (96, 6192, 1331, 5, 37.9, {1: 38.1, 4: 38.1, 32: 39.4})]
+
+
+def test_order_of_weight_gradient_tiles(runs):
+    """Within 6 % of the order before (two launches of one order differ by up to 3 %)."""
+    for (m, n, k, s, before, us), run in zip(ORDER, runs([c[:4] for c in ORDER])):
+        assert us[run] <= 1.06 * before, (m, n, k, run)
 
 
 # Cout, taps x Cin, positions: what the library's own array holds at one range per 16 slabs or three, some of it only just
