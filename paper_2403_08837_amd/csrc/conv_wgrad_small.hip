@@ -357,19 +357,24 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_few_kernel(const GemmBatch 
     static_cast<float*>(P.aux3)[(int64_t)split * Cout + o0 + l31] = (bred[l31] + bred[32 + l31]) + (bred[64 + l31] + bred[96 + l31]);
 }
 
-// As many workgroups as are resident at once (bf16: 72 KB of LDS, two per CU), a third more in fp32.  us past the line, conv_wgrad_kernel
-// / here: bf16 1008 workgroups (256 x 2304 over 6272 [14]) 30.2 / 32.3, 980 (64 x 576 over 100352 [196]) 31.9 / 34.0; fp32 2304 (512 x 4608 over 98 [1])
-// 26.6 / 27.6, 2048 (1024 x 512 over 200 [4]) 17.3 / 17.8, 7632 (128 x 1152 over 25088 [53]) 90 / 147.
+// As many workgroups as are resident at once (bf16: 72 KB of LDS, two per CU; fp32 three), and in fp32 a third more, but where the
+// other kernel has tiles of 64 rows and ranges are one or two groups of positions, so that two or three of the four wavefronts here have nothing to
+// do.  us past the line, conv_wgrad_kernel / here: bf16 1008 workgroups (256 x 2304 over 6272 [14]) 30.2 / 32.3, 980 (64 x 576 over 100352 [196])
+// 31.9 / 34.0; fp32 2304 (512 x 4608 over 98 [1]) 26.6 / 27.6, 2048 (1024 x 512 over 200 [4]) 17.3 / 17.8, 7632 (128 x 1152 over 25088 [53]) 90 / 147.
+// Short ranges: 884 (104 x 7056 over 25 [1]) 10.6 / 13.7, 832 (40 x 3312 over 98 [4]) 10.5 / 12.2, 640 (64 x 5112 over 49 [2]) 10.4 / 10.2, of 128 rows 952
+// (216 x 1080 over 200 [4]) 17.1 / 13.4; longer ones 832 (64 x 1656 over 2450 [8]) 31.7 / 21.7.
 bool conv_wgrad_small_wanted(const GemmBatch& b, int dtype) {
   const bool bf16 = dtype == DT_BF16;
   const int to = bf16 ? 64 : 32, tc = bf16 ? 128 : 32;
   int64_t total = 0;
+  bool idle = !bf16;  // every problem leaves wavefronts idle
   for (int i = 0; i < b.n; ++i) {
     const GemmProb& p = b.p[i];
     if (bf16 && ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B)) & 15)) return false;  // 16 bytes per request
     total += (int64_t)((p.M + to - 1) / to) * ((p.N + tc - 1) / tc) * p.splits;
+    idle = idle && p.M < 128 && ((int64_t)p.K + 31) / 32 <= 2 * (int64_t)p.splits;
   }
-  return total <= (bf16 ? 512 : 1024);
+  return total <= (bf16 ? 512 : idle ? 768 : 1024);
 }
 
 hipError_t launch_conv_wgrad_small(GemmBatch& b, int dtype, hipStream_t stream) {

@@ -1,6 +1,7 @@
 """Rules by which launches are laid out, asked of the built library: how many ranges the reduction of a weight gradient
 is cut into when it is launched on its own (conv_wgrad_splits_alone in csrc/conv_kernels.hip) and how many neighbouring tiles of it
-go to one XCD (conv_wgrad_xcd_run there), which forward / data-gradient
+go to one XCD (conv_wgrad_xcd_run there), which weight gradients run on the tiles of launches short of workgroups
+(conv_wgrad_small_wanted in csrc/conv_wgrad_small.hip), which forward / data-gradient
 launches share their reductions over workgroups (conv_dl_tile in csrc/conv256_kernels.hip), which attention passes run in
 one kernel (attention_fused in csrc/attention_kernels.hip), and which products of row-contiguous operands run on the
 weight-gradient tiles of the Linear launch (gemm_wgrad_tiles_wanted in csrc/kernels_api.cpp).  No GPU: the rules are host arithmetic, and the times they are held
@@ -39,6 +40,11 @@ def ranges(tmp_path_factory):
 @pytest.fixture(scope="module")
 def runs(tmp_path_factory):
     return _asker(tmp_path_factory, "runs")
+
+
+@pytest.fixture(scope="module")
+def few(tmp_path_factory):
+    return _asker(tmp_path_factory, "few")
 
 
 @pytest.fixture(scope="module")
@@ -108,6 +114,22 @@ def test_order_of_weight_gradient_tiles(runs):
     """Within 6 % of the order before (two launches of one order differ by up to 3 %)."""
     for (m, n, k, s, before, us), run in zip(ORDER, runs([c[:4] for c in ORDER])):
         assert us[run] <= 1.06 * before, (m, n, k, run)
+
+
+# dtype, M, N, K, ranges, us on conv_wgrad_kernel, us on the tiles of launches short of workgroups
+FEW = [(F32, 104, 7056, 25, 1, 10.6, 13.7), (F32, 32, 7128, 98, 4, 10.3, 13.7), (F32, 112, 2016, 128, 4, 9.8, 13.1), (F32, 48, 4032, 243, 4, 11.5, 13.1),
+       (F32, 104, 1584, 200, 4, 12.7, 13.1), (F32, 40, 3312, 98, 4, 10.5, 12.2), (F32, 64, 5112, 49, 2, 10.4, 10.2), (F32, 48, 2808, 128, 4, 10.2, 9.7),
+       (F32, 728, 504, 49, 2, 13.5, 10.4), (F32, 880, 1008, 32, 1, 13.6, 13.8), (F32, 216, 1080, 200, 4, 17.1, 13.4), (F32, 256, 1296, 169, 3, 17.6, 14.2),
+       (F32, 64, 1656, 2450, 8, 31.7, 21.7), (F32, 40, 2600, 1250, 6, 24.7, 18.7), (F32, 512, 4608, 98, 1, 26.6, 27.6), (F32, 128, 1152, 25088, 53, 90, 147),
+       (BF16, 744, 5112, 25, 1, 18.3, 18.8), (BF16, 56, 5688, 2800, 9, 20.9, 19.5), (BF16, 232, 1400, 6845, 11, 27.4, 25.1), (BF16, 24, 2880, 10368, 21, 21.0, 19.1),
+       (BF16, 256, 2304, 6272, 14, 30.2, 32.3), (BF16, 64, 576, 100352, 196, 31.9, 34.0)]
+
+
+def test_launches_short_of_workgroups(few):
+    """The faster of the two kernels; in bf16 only where both operands are 16-byte aligned."""
+    for (dt, m, n, k, s, other, here), on in zip(FEW, few([c[:5] + (0,) for c in FEW])):
+        assert (here if on else other) <= 1.03 * min(here, other), (dt, m, n, k, s, on)
+    assert not any(few([c[:5] + (1,) for c in FEW if c[0] == BF16]))
 
 
 # Cout, taps x Cin, positions: what the library's own array holds at one range per 16 slabs or three, some of it only just
