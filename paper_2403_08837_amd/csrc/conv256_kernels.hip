@@ -297,17 +297,21 @@ bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype) {
 
 // Launches of one round or two, and long reductions.  conv_gemm_kernel is one slab ahead and needs its three workgroups per CU to
 // cover for each other; the tiles here, one workgroup of eight wavefronts per CU with two slabs on their way, do not, so what counts is how
-// full the rounds of 256 tiles are: the largest tile whose count fits one round.  us, conv_gemm_kernel / 256 x 128 / 192 x 128 / 128 x 128
+// full the rounds of 256 tiles are: the smallest of the three whose count fits one round.  us, conv_gemm_kernel / 256 x 128 / 192 x 128 / 128 x 128
 // (64 x 128 with four wavefronts, the tile of one round before):
 //   25088 x 128 x 1152   24.9 / 21.9 / 18.0 / 14.6 (17.1)     8503 x 344 x 3072    45.1 / 43.7 / 34.5 / 27.5 (31.3)
 //   2725 x 928 x 128      7.8 /  8.3 /  7.3 /  6.2 (6.4)      3457 x 984 x 1536    26.3 / 25.8 / 21.3 / 17.7 (19.2)
 //   6272 x 768 x 3072    54.2 / 44.3 / 37.3 / 53.2            6272 x 768 x 768     19.9 / 17.1 / 14.2 / 19.4
 //   20091 x 256 x 128     9.8 /  9.2 /  8.1 / 10.4            5684 x 768 x 2304    43.4 / 36.0 / 29.7 / 42.1
 //   12544 x 512 x 1024   24.5 / 21.3 / 30.8 / 23.3 (264 tiles of 192 x 128: two rounds)
-// Past one round of 256 x 128 conv_gemm_kernel's finer tiles round better, but it multiplies at two thirds of their rate, which decides
-// for reductions of 1024 and more.  In rounds of 256 x 128 it costs 0.0027 per 128 x 128 tile and at least 2, a round of 192 x 128 0.885:
-//   us, conv_gemm_kernel / 192 x 128  9673 x 1024 x 1024 35.5 / 31.2, 14518 x 768 x 2304 72.9 / 62.8, 9209 x 1024 x 4608 127 / 106; x 768 30.4 / 30.9;
-//   eight problems of 6272 x 768 x 3072 306 / 278 (256 x 128); four of 6272 x 768 x 2304 110 / 111, left where they are.
+// Past two rounds of 128 x 128 and for reductions of 1024 and more the time is counted in rounds of 256 x 128: one of 192 x 128 is 0.835 of it;
+// conv_gemm_kernel, whose workgroups are not in rounds but pile up on the CUs, takes 0.562 - 100 / K for each tile of 128 x 128 that a CU gets, and 0.34.
+// (Fitted to 238 products of 512 to 4970 tiles, K 1024 to 4032, rms 3.4 %.  Counted as 0.0027 per tile whatever K and the rounding, 17 of
+// them were 2 to 9 % slower than conv_gemm_kernel, now 3, the slowest 0.95; all of them 8.1 % faster than it, 7.1 % with that count.)
+//   us, conv_gemm_kernel / 256 x 128 / 192 x 128: 66517 x 824 x 1024 164 / 176 / 176, 68436 x 360 x 1216 94 / 101 / 101, 23232 x 2088 x 1152 159 / 170 / 175,
+//   16735 x 1944 x 1344 126 / 132 / 127; 800 tiles of K 2944 121 / 96 / 112, 518 of 3456 101 / 104 / 85, 1524 of 3456 205 / 175 / 184.
+//   9673 x 1024 x 1024 35.5 / - / 31.2, 14518 x 768 x 2304 72.9 / - / 62.8, 9209 x 1024 x 4608 127 / - / 106; x 768 30.4 / - / 30.9;
+//   eight problems of 6272 x 768 x 3072 306 / 278 / -; four of 6272 x 768 x 2304 110 / 111 / -, left where they are.
 // 64 x 64 (below 150 tiles of 128 x 128): slabs of 64 for long reductions, of 32 (twice the workgroups per CU) for short ones
 // (6272 x 1024 x 256 13.5 against 11.9, 1568 x 512 x 4608 23.8 against 25.5) and for channel counts that are odd multiples of 32.
 //   6272 x 256 x 2304 23 / 17 (conv_gemm_kernel / here)     1568 x 512 x 4608 40 / 24     6272 x 256 x 1024  12.9 / 9.5
@@ -341,8 +345,9 @@ int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
   if (t128 <= 256) return DL_128x128;
   if (t128 < 512) return t192 <= 256 ? DL_192x128 : DL_256x128;
   if (kmin < 1024) return 0;
-  const double by256 = (double)((t256 + 255) / 256), by192 = 0.885 * ((t192 + 255) / 256), other = std::max(2.0, 0.0027 * t128);
-  return std::min(by256, by192) >= 0.93 * other ? 0 : by192 < by256 ? DL_192x128 : DL_256x128;
+  const double by256 = (double)((t256 + 255) / 256), by192 = 0.835 * ((t192 + 255) / 256);
+  const double other = ((t128 + 255) / 256) * (0.562 - 100.0 / kmin) + 0.34;
+  return std::min(by256, by192) >= 0.97 * other ? 0 : by192 < by256 ? DL_192x128 : DL_256x128;
 }
 
 hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream) {

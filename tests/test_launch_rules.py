@@ -198,6 +198,27 @@ def test_narrow_launches_take_the_fastest_tile(tiles):
         assert us[{0: 0, 4: 1, 5: 2}[tile]] <= 1.03 * min(us), (m, n, k, tile)
 
 
+# M, N, K, us: conv_gemm_kernel, tiles of 256 x 128, 192 x 128, 128 x 128 (None: not measured)
+ROUNDS = [(25088, 128, 1152, 24.9, 21.9, 18.0, 14.6), (8503, 344, 3072, 45.1, 43.7, 34.5, 27.5), (2725, 928, 128, 7.8, 8.3, 7.3, 6.2),
+          (3457, 984, 1536, 26.3, 25.8, 21.3, 17.7), (6272, 768, 3072, 54.2, 44.3, 37.3, 53.2), (6272, 768, 768, 19.9, 17.1, 14.2, 19.4),
+          (20091, 256, 128, 9.8, 9.2, 8.1, 10.4), (5684, 768, 2304, 43.4, 36.0, 29.7, 42.1), (12544, 512, 1024, 24.5, 21.3, 30.8, 23.3),
+          (161728, 120, 1152, 68.2, 74.5, 78.2, None), (66517, 824, 1024, 162.5, 176.0, 176.3, None), (23232, 2088, 1152, 157.1, 170.1, 175.1, None),
+          (68436, 360, 1216, 93.7, 100.7, 100.7, None), (103394, 200, 1088, 85.7, 91.7, 92.1, None), (80515, 248, 1664, 102.3, 109.0, 115.2, None),
+          (38108, 1984, 1024, 205.8, 216.6, 226.1, None), (92500, 616, 1152, 179.0, 188.2, 189.7, None), (16735, 1944, 1344, 126.5, 132.1, 127.4, None)]
+
+
+def test_launches_in_rounds_take_the_fastest_tile(tiles):
+    """One round, two, and long reductions past that; lines at 150, 256 and 512 tiles of 128 x 128, 256 of 192 x 128, and K = 1024."""
+    for (m, n, k, *us), tile in zip(ROUNDS, tiles([c[:3] + (0,) for c in ROUNDS])):
+        assert us[{0: 0, 2: 1, 6: 2, 3: 3}[tile]] <= 1.03 * min(u for u in us if u), (m, n, k, tile)
+    #  256 x 128: 2, 128 x 128: 3, 64 x 64: 4, 192 x 128: 6, conv_gemm_kernel: 0
+    lines = {(149 * 128, 128, 1024): 4, (150 * 128, 128, 1024): 3, (128 * 128, 256, 1024): 3, (128 * 128 + 1, 256, 1024): 6,
+             (128 * 192, 256, 1024): 6, (128 * 192 + 1, 256, 1024): 2, (511 * 128, 128, 512): 2, (512 * 128, 128, 512): 0,
+             (512 * 128, 128, 1024): 2, (512 * 128, 128, 960): 0, (512 * 192, 128, 4096): 6, (512 * 192 + 1, 128, 4096): 2,
+             (4001 * 128, 128, 1024): 0, (4000 * 128, 128, 4096): 2}
+    assert {c: t for c, t in zip(lines, tiles([c + (0,) for c in lines]))} == lines
+
+
 # bf16 backward; samples, tokens, heads, width of a head, us in separate kernels, us in the fused ones
 ATTENTION = [(6, 416, 12, 48, 87.5, 123.8), (4, 656, 12, 48, 152.7, 199.2), (8, 500, 12, 48, 140.8, 156.1), (64, 416, 8, 48, 518.3, 598.0),
              (8, 624, 8, 48, 156.4, 191.8), (1, 656, 12, 48, 78.1, 85.8), (6, 416, 12, 80, 123.6, 137.3), (1, 384, 4, 80, 45.2, 46.9),
