@@ -803,7 +803,6 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
   T* __restrict__ wt = static_cast<T*>(U.wt);
   constexpr int CF = TK / VEC, CT = TN / VEC, NF = TN * CF / 256, NT = TK * CT / 256;
   static_assert(NF * 256 == TN * CF && NT * 256 == TK * CT, "whole chunks per thread");
-  const bool al = (Kk % VEC) == 0 && (Nn % VEC) == 0;
   Chunk16<T> cf[NF], ct[NT];
 #pragma unroll
   for (int i = 0; i < NF; ++i) {
@@ -817,16 +816,13 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
 #pragma unroll
     for (int e = 0; e < VEC; ++e) ct[i].e[e] = Ws[(cn + e) * PW + k];
   }
-  if (al) {  // every chunk is inside or outside
+  // A copy whose own rows are whole chunks leaves in chunks, whatever the other's are (a classifier of 10 classes: the forward copy).  With one
+  // test for both, steps of one micro-batch with a layer of 2048 -> 4001 took 3.7 % longer (bf16 145 -> 150 us, fp32 154 -> 158).
+  if ((Kk % VEC) == 0) {
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
       const int id = tid + 256 * i, n = n0 + id / CF, k = k0 + (id % CF) * VEC;
       if (n < Nn && k < Kk) *reinterpret_cast<uint4*>(wf + (int64_t)n * Kk + k) = cf[i].v;
-    }
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;
-      if (k < Kk && n < Nn) *reinterpret_cast<uint4*>(wt + (int64_t)k * Nn + n) = ct[i].v;
     }
   } else {
 #pragma unroll
@@ -836,6 +832,14 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
       for (int e = 0; e < VEC; ++e)
         if (n < Nn && k + e < Kk) wf[(int64_t)n * Kk + k + e] = cf[i].e[e];
     }
+  }
+  if ((Nn % VEC) == 0) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;
+      if (k < Kk && n < Nn) *reinterpret_cast<uint4*>(wt + (int64_t)k * Nn + n) = ct[i].v;
+    }
+  } else {
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;

@@ -277,6 +277,19 @@ def test_momentum_and_weight_decay(name, rule):
     check(cfg, rule, cfg.steps, momentum=0.9, weight_decay=5e-4)
 
 
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+@pytest.mark.parametrize("dtype,inputs,width,classes", [(wl.F32, 70, 132, 10), (wl.F32, 64, 130, 12), (wl.BF16, 70, 136, 10),
+                                                        (wl.BF16, 72, 132, 16), (wl.BF16, 264, 72, 33)])
+def test_layers_with_one_width_that_is_not_whole_pieces(dtype, inputs, width, classes, momentum):
+    """The update writes a forward and a transposed copy of the new weights, each in 16-byte pieces where its own rows are whole ones:
+    input widths, output widths, both or neither."""
+    # bf16: an update is 5.4e-2 off in its worst tensor, the storage stand-in by as much, and the gate is 2e-2 of the largest weight, so the
+    # steps together have to stay below 0.37 of it; momentum 0.9 adds up to 2.7 times as much in three steps and takes a fifth of the rate
+    cfg = wl.Config("mlp_one_odd", wl._mlp(inputs, width, 2, classes, stem=False), (inputs,), classes, N=2, B=5, dtype=dtype,
+                    lr=0.004 if momentum else 0.02, steps=3)
+    check(cfg, wl.RULE_V2, cfg.steps, momentum=momentum, weight_decay=5e-4 if momentum else 0.0)
+
+
 def test_ring_copy_of_previous_version():
     """cdp_get_weights(version = freshest-1) returns the compute copy still in the ring."""
     import torch
