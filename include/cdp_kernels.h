@@ -41,6 +41,9 @@ int cdp_k_gemm(int dtype, int tile_shape, int a_kmajor, int b_kmajor, const void
  *               of a launch of few tiles: CDP_CONV_SHARE_BYTES, the last 8192 of them zero before the first call (every
  *               call leaves them zero); CDP_EINVAL without it or for channel counts that are not whole 16-byte chunks
  *         9: as 2, but added to dw instead of overwriting it; needs the workspace of the two-phase path
+ *         10, 11: as 0, 1 before and after a GELU, as the engine launches them: 10 also stores the GELU of y, 11 multiplies dx by the GELU's
+ *               derivative at its input; that other tensor, of the size and type of the result and 16-byte aligned, is
+ *               `workspace`; CDP_EINVAL unless bf16, more than 64 columns and channel counts that are whole 16-byte chunks
  * in0/in1: (x, w) | (dy, wt) | (dy, x).  `out` must not alias the inputs.
  * workspace (device, may be NULL): scratch for the split weight-gradient kernel.  Where the shape allows and it holds
  * at least one partial sum (4 * Cout*k*k*Cin bytes) the two-phase path is used; without, the generic single-pass kernel

@@ -352,7 +352,7 @@ int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
 
 hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
-  if (b.n > GEMM_MAX_PROBS) return hipErrorInvalidValue;
+  if (b.n > GEMM_MAX_PROBS || !conv_gelu_valid(b, dtype)) return hipErrorInvalidValue;
   int bm, bn;
   switch (tile) {
     case DL_256x256: bm = 256; bn = 256; break;

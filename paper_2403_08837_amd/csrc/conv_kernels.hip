@@ -1005,7 +1005,7 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
   if ((bm != 64 && bm != 128) || (bn != 64 && bn != 128)) return hipErrorInvalidValue;
   const int bk = dtype == DT_BF16 ? 32 : 16;
   int total = 0;
-  if (conv_has_gelu(b) && (dtype != DT_BF16 || (bm == 128 && bn == 64))) return hipErrorInvalidValue;
+  if (!conv_gelu_valid(b, dtype) || (conv_has_gelu(b) && bm == 128 && bn == 64)) return hipErrorInvalidValue;
   if (const int dl = conv_dl_tile(b.p, b.n, dtype, b.thin_ws && b.thin_cnt)) return launch_conv_dl(b, dtype, dl, stream);
   if (conv_few_tiles(b, dtype)) {
     for (int i = 0; i < b.n; ++i) {

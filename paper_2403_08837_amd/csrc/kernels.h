@@ -185,6 +185,16 @@ constexpr int64_t THIN_WS_BYTES = (int64_t)THIN_WS_SLOTS * (32 * 32 * 4 + 4);  /
 
 // Implicit-GEMM convolution fast paths (channel counts that are multiples of the slab).
 bool conv_fast_eligible(const GemmProb& p, int dtype);
+// What a problem with GF_GELU has to bring: its second tensor moves in 16-byte pieces, and the tiles for 64 columns have no such epilogue.
+inline bool conv_gelu_valid(const GemmBatch& b, int dtype) {
+  for (int i = 0; i < b.n; ++i) {
+    const GemmProb& p = b.p[i];
+    if (!(p.flags & GF_GELU)) continue;
+    const void* second = p.epi == EPI_FWD ? p.aux2 : p.aux1;
+    if (dtype != DT_BF16 || p.N <= 64 || !second || (reinterpret_cast<uintptr_t>(second) & 15)) return false;
+  }
+  return true;
+}
 inline bool conv_has_gelu(const GemmBatch& b) {
   for (int i = 0; i < b.n; ++i)
     if (b.p[i].flags & GF_GELU) return true;

@@ -83,10 +83,11 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
   g.KH = ks; g.KW = ks; g.stride = stride; g.pad = pad;
   const bool force256 = which >= 3 && which <= 6;  // the direct-to-LDS tile regardless of the launch heuristic
   const int forced_tile = which >= 5 ? DL_256x128 : DL_256x256;
-  const bool shared = which == 7 || which == 8, accumulate = which == 9;
+  const bool shared = which == 7 || which == 8, accumulate = which == 9, gelu = which == 10 || which == 11;
   if (force256) which -= which >= 5 ? 5 : 3;
   if (shared) which -= 7;
   if (accumulate) which = 2;
+  if (gelu) which -= 10;
   if (which == 0) {
     p.M = B * Ho * Wo; p.N = Cout; p.K = ks * ks * Cin;
     p.a_mode = OP_CONV_FWD; p.b_mode = OP_PLAIN_K; p.ldb = p.K; p.ldo = Cout;
@@ -107,6 +108,13 @@ int cdp_k_conv(int dtype, int which, const void* in0, const void* in1, void* out
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (shared && (!conv_fast_eligible(p, dtype) || !workspace || workspace_bytes < (size_t)CDP_CONV_SHARE_BYTES)) return CDP_EINVAL;
+  if (gelu) {
+    if (dtype != DT_BF16 || p.N <= 64 || !conv_fast_eligible(p, dtype) || !workspace || workspace_bytes / 2 < (size_t)p.M * p.N) return CDP_EINVAL;
+    if (which == 0) p.aux2 = workspace;
+    else p.aux1 = workspace;
+    p.flags |= GF_GELU;
+    if (!conv_gelu_valid(b, dtype)) return CDP_EINVAL;
+  }
   // the fast implicit-GEMM paths where the shape allows, as in the engine; what is different for a call on its own: no workspace to share
   // reductions in (which = 7, 8 have one), ranges of the weight gradient for a launch of its own, and a fold that overwrites
   if (which == 2) {

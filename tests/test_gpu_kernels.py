@@ -543,10 +543,46 @@ def test_conv_short_of_workgroups(rows, out, slabs):
 
 @pytest.mark.parametrize("rows,out,slabs", [(13000, 500, 1), (13000, 500, 2), (13000, 500, 5),    # 256 x 128: 272 tiles of 192 x 128
                                             (9310, 1032, 16), (9310, 1032, 17),                    # 192 x 128, 441 tiles in two rounds
-                                            (16330, 128, 3), (16390, 256, 3)])                     # 128 x 128, just below and above a full round
+                                            (16330, 256, 3),                                       # 128 x 128, a full round (256 tiles)
+                                            (16390, 256, 3)])                                      # a tile row more: 192 x 128
 def test_conv_rounds_of_tiles(rows, out, slabs):
     """One round of tiles or two, at the lines of the rule."""
     _conv_1x1_bf16(0, rows, 64 * slabs, out)
+
+
+# rows, width beside the GELU, reduction: every tile that a contraction before or after a GELU can run on, ragged in both directions
+GELU_CASES = [(700, 200, 64, "64 x 64, slabs of 32"), (700, 200, 1088, "64 x 64, slabs of 64"), (700, 200, 96, "64 x 64, odd multiple of 32"),
+              (9700, 200, 128, "128 x 128 in one round"), (13000, 264, 192, "192 x 128"), (16500, 376, 128, "256 x 128"),
+              (9310, 1032, 1088, "192 x 128, two rounds"), (12540, 1016, 2048, "256 x 256"), (22000, 376, 128, "conv 128 x 128"),
+              (22000, 376, 96, "conv 128 x 128, slabs of 32"), (700, 200, 72, "ragged 64 x 64"), (12000, 264, 72, "ragged 64 x 128"),
+              (22000, 376, 40, "ragged 128 x 128")]
+
+
+@pytest.mark.parametrize("rows,width,red,tile", GELU_CASES, ids=[c[3] for c in GELU_CASES])
+def test_gelu_in_the_epilogue_has_the_bits_of_its_own_kernels(rows, width, red, tile):
+    """Forward: the contraction and the GELU of it; data gradient: times the GELU's derivative.  Bit for bit what the plain contraction
+    followed by cdp_k_gelu gives, nothing written past the end, and the contraction itself within rounding of float64."""
+    torch = _torch()
+    n = rows * width
+    x = _dev(wl.random_normal(8, 1, rows * red).reshape(rows, red), wl.BF16)
+    w = _dev(wl.random_normal(8, 2, width * red).reshape(width, red) / np.sqrt(red), wl.BF16)
+    h = _dev(wl.random_normal(8, 3, n), wl.BF16)
+    new = lambda: torch.full((n + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    y, act, y0, act0, dx, dx0, plain = (new() for _ in range(7))
+    fwd, bwd = (1, 1, rows, red, width, 1, 1, 0), (1, 1, rows, width, red, 1, 1, 0)
+    b.cdp_k_conv(wl.BF16, 10, x.data_ptr(), w.data_ptr(), y.data_ptr(), *fwd, ws_ptr=act.data_ptr(), ws_bytes=2 * n)
+    b.cdp_k_conv(wl.BF16, 0, x.data_ptr(), w.data_ptr(), y0.data_ptr(), *fwd)
+    b.cdp_k_gelu(wl.BF16, 0, y0.data_ptr(), 0, act0.data_ptr(), n)
+    b.cdp_k_conv(wl.BF16, 11, x.data_ptr(), w.data_ptr(), dx.data_ptr(), *bwd, ws_ptr=h.data_ptr(), ws_bytes=2 * n)
+    b.cdp_k_conv(wl.BF16, 1, x.data_ptr(), w.data_ptr(), plain.data_ptr(), *bwd)
+    b.cdp_k_gelu(wl.BF16, 1, h.data_ptr(), plain.data_ptr(), dx0.data_ptr(), n)
+    torch.cuda.synchronize()
+    for got, ref in ((y, y0), (act, act0), (dx, dx0)):
+        assert torch.isnan(got[n:]).all()
+        assert torch.equal(got[:n].view(torch.int16), ref[:n].view(torch.int16))
+    exact = x.double() @ w.double().t()
+    err = (y[:n].reshape(rows, width).double() - exact).norm() / exact.norm()
+    assert err < 2.0 ** -8, float(err)  # one rounding to bf16: at most half a unit of 2^-7
 
 
 @pytest.mark.parametrize("case", [(4, 56, 56, 64, 320, 3, 1, 1),       # forward on 192 x 128 tiles, data gradient on 64 x 64

@@ -219,6 +219,23 @@ def test_launches_in_rounds_take_the_fastest_tile(tiles):
     assert {c: t for c, t in zip(lines, tiles([c + (0,) for c in lines]))} == lines
 
 
+def test_gelu_epilogue_refuses_what_it_cannot_store():
+    """The second tensor moves in 16-byte pieces: misaligned, missing or short ones are refused before anything is launched, and so are
+    fp32, 64 columns and fewer, and channel counts that are not whole pieces (made-up addresses, every call is refused)."""
+    from paper_2403_08837_amd import binding as b
+    ok = dict(dtype=BF16, rows=512, cin=128, cout=128, ws=4096, bytes=512 * 128 * 2)
+    for which in (10, 11):
+        for bad in (dict(ws=4104), dict(ws=4098), dict(ws=0), dict(bytes=512 * 128 * 2 - 1), dict(bytes=0), dict(dtype=F32), dict(cin=64, cout=64),
+                    dict(cin=100, cout=100)):
+            c = dict(ok, **bad)
+            with pytest.raises(b.CdpError) as e:
+                b.cdp_k_conv(c["dtype"], which, 256, 256, 256, 1, 1, c["rows"], c["cin"], c["cout"], 1, 1, 0, ws_ptr=c["ws"], ws_bytes=c["bytes"])
+            assert e.value.code == b.CDP_EINVAL, bad
+    with pytest.raises(b.CdpError) as e:
+        b.cdp_k_conv(BF16, 12, 256, 256, 256, 1, 1, 512, 128, 128, 1, 1, 0)
+    assert e.value.code == b.CDP_EINVAL
+
+
 # bf16 backward; samples, tokens, heads, width of a head, us in separate kernels, us in the fused ones
 ATTENTION = [(6, 416, 12, 48, 87.5, 123.8), (4, 656, 12, 48, 152.7, 199.2), (8, 500, 12, 48, 140.8, 156.1), (64, 416, 8, 48, 518.3, 598.0),
              (8, 624, 8, 48, 156.4, 191.8), (1, 656, 12, 48, 78.1, 85.8), (6, 416, 12, 80, 123.6, 137.3), (1, 384, 4, 80, 45.2, 46.9),
