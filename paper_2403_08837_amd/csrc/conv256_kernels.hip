@@ -36,14 +36,6 @@ __device__ uint4 g_zero_chunk[4];  // zero-initialised; source of structural zer
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
 }  // namespace
 
 // BM x BN outputs per workgroup of WAVES_M x WAVES_N wavefronts, slabs of BK, STAGES of them in LDS; WPS: wavefronts per SIMD
@@ -277,10 +269,10 @@ static bool conv_dl_eligible(const GemmProb& p, int dtype, int bk) {
 }
 bool conv_gemm256_eligible(const GemmProb& p, int dtype) { return conv_dl_eligible(p, dtype, 64); }
 
-// Worth it (against the 256 x 128 tile: 1050 vs 911 TFLOP/s on a 3x3 convolution over 512 channels with 25088 rows, 1154 vs
-// 1077 on an 8192^3 product, but 795-864 vs 888 on 25088 x 2048 x 2048, where the 784 tiles make 3.06 rounds of one
-// workgroup per CU): long reductions (the tile's prologue and
-// epilogue are paid once per 256 x 256 outputs), mostly full tiles, and a tile count that rounds well to the CUs.
+// Worth it for long reductions (the tile's prologue and epilogue are paid once per 256 x 256 outputs), mostly full tiles, and a tile count
+// that rounds well to the CUs.  us, conv_gemm_kernel / 256 x 256 / 256 x 128 / 192 x 128: 8192^3 1206 / 926 / 1024 / 1092, 3x3 over 512 channels with 25088
+// rows 173 / 114 / 133 / 162, 25088 x 1024 x 2304 151 / 128 / 150 / 149; nothing lost where three rounds are not full: 25088 x 2048 x 2048 (784 tiles, 3.06
+// rounds) 249 / 246 / 245 / 248, 50176 x 1024 x 2048 257 / 261 / 255 / 261, 100352 x 512 x 2304 277 / 266 / 266 / 269.
 bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype) {
   constexpr int BM = 256, BN = 256, BK = 64;
   int64_t tiles = 0;

@@ -777,17 +777,19 @@ int conv_wgrad_splits(const GemmProb& p, int dtype, int wanted) {
   return std::max(1, std::min(nslab, std::max(wanted, min_splits)));
 }
 
-// Ranges of a problem launched on its own, at most `room` of them: the cheapest by what the launch costs.  A workgroup's slab
-// takes a chain of latencies alone on its CU and longer beside others; how much longer is matrix time, which depends on the type
+// Ranges of a problem launched on its own, at most `room` of them: the cheapest by what the launch costs on conv_wgrad_kernel.  A workgroup's
+// slab takes a chain of latencies alone on its CU and longer beside others; how much longer is matrix time, which depends on the type
 // and on the height of the tile.  The workgroups run in rounds of as many as a CU holds, and every range writes its partial
-// matrix once and the fold reads it once.  Fitted to 900 launches of 150 shapes (1 to 310 tiles, 1 to 12544 slabs, 1 to 784 ranges), rms
-// 2.5 % in fp32 and 5 % in bf16.  Against three ranges or one per 16 slabs, us:
-//   bf16 3072 x 768 over 6272 rows 86 -> 71, 128 x 1152 over 25088 37 -> 31, 136 x 19800 over 15129 265 -> 265;
-//   fp32 128 x 576 over 800 37 -> 25, 280 x 504 over 40656 178 -> 159, 144 x 936 over 87846 440 -> 431;
-//   104 shapes of 1 to 100 thousand rows 1.33 times as fast by the geometric mean, none slower.
+// matrix once and the fold reads it once.  Fitted to 900 launches of that kernel (150 shapes of 1 to 310 tiles, 1 to 12544 slabs, 1 to 784
+// ranges, rms 2.5 % in fp32 and 5 % in bf16) with the reduction ranges listed side by side.  It does not know the kernels that launches short
+// of workgroups run on (conv_wgrad_small.hip), but its counts serve them: of 13 shapes timed with 3 to 11 counts, each on the kernel that it runs
+// on, the chosen count is the fastest or within 4 % of it, but for fp32 128 x 576 over 800 (five ranges 11.9 us, four 11.1).  Against three
+// ranges or one per 16 slabs, us:
+//   bf16 3072 x 768 over 6272 rows 75.5 -> 68.7, 128 x 1152 over 25088 30.7 -> 29.5, 136 x 19800 over 15129 251 -> 252;
+//   fp32 128 x 576 over 800 12.5 -> 11.9, 280 x 504 over 40656 175 -> 160, 56 x 792 over 39546 76.9 -> 64.7.
 // A function of the shape where there is room for what it wants, which is what cdp_k_conv asks of its workspace and no more than
 // the library's own array where one per 16 slabs or three fit that: cdp_k_conv and cdp_k_conv_wgrad_static then add
-// in one order and give the same bits (costs up to 5 %: 128 x 1152 over 25088 in bf16 is 28 ranges, 34.8 us, instead of 49, 31.3 us).
+// in one order and give the same bits (128 x 1152 over 25088 in bf16 is 28 ranges so, 29.5 us; 49, 30.6 us, would not fit).
 int conv_wgrad_splits_alone(const GemmProb& p, int dtype, int room) {
   // us per slab with 1, 2, .. workgroups on the CU: [fp32, bf16][tiles of 64, 128 rows]
   static const double SLAB_US[2][2][4] = {{{1.95, 2.9, 3.9, 4.85}, {3.1, 5.15, 7.1, 9.4}}, {{1.25, 1.5, 1.7, 0.0}, {1.45, 1.8, 2.05, 0.0}}};
@@ -1076,6 +1078,8 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
 //   six ResNet stages, 11 layers (about 1400 tiles)     145.5 / 141.6 / 141.5 / 143.4 / 165.8
 //   16 ViT layers of 6272 rows, two ranges (3456)       556.6 / 547.8 / 543.1 / 538.1 / 531.0
 //   3072 x 768 over 6272 rows, five ranges (720)         57.9 /  54.8 /  53.6 /  53.1 /  52.2
+// (170, 589 and 58.1 with the ranges as neighbours and the column sums of dy read back out of LDS row by row: what the first column is better is
+// those two together, the rest the XCDs.)
 // Short ranges of many tiles in one round (bf16: 768 workgroups are resident) have little to share, and there what counts is that the work
 // starts spread out: us with 1 / 4 / 32, bf16,
 //   648 x 576 over 3200, ten ranges (300 tiles)     22.6 / 25.4 / 25.9      1984 x 648 over 1088, three (288)    24.5 / 26.1 / 27.7

@@ -23,14 +23,6 @@ __device__ uint4 g_wgrad_zero[4];  // zero-initialised; source of structural zer
 typedef __attribute__((address_space(3))) void* lds_void;
 typedef __attribute__((address_space(3))) frag_v4s* lds_v4s;
 
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
 }  // namespace
 
 // bf16: tiles of 64 x 128 of the weight matrix, operands straight into LDS (rows of a slab as they lie in memory, read back transposed), three

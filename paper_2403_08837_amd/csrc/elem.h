@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace cdp {
@@ -39,7 +41,8 @@ template <typename T> union Chunk16 {
 };
 
 // Problem of a launch of n problems that owns tile number `tile` (problems are listed by ascending tile_begin): compares on
-// scalars that one or two wide reads bring in, no loop whose every step waits for a read.  A launch of one problem reads nothing.
+// scalars that one or two wide reads bring in, no loop whose every step waits for a read.  A launch of one problem reads none of them
+// (linear_tick_body does: it has the whole table read ahead, in one round with what it needs anyway).
 template <int MAX> __device__ __forceinline__ int tile_starts_find(const TileStarts<MAX>& t, int n, int tile) {
   auto past = [&](int at) { return (int)((unsigned)(at - 1 - tile) >> 31); };  // tile >= at, without a trip through the vector unit
   int pi = 0;
@@ -106,6 +109,14 @@ __device__ __forceinline__ int xcd_block_cyclic(int bid, int total, int G) {
 
 __device__ __forceinline__ v16f_t mfma_bf16(uint4 a, uint4 b, v16f_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf16_t, a), __builtin_bit_cast(v8bf16_t, b), c, 0, 0, 0);
+}
+
+// f(0), f(1), .. f(N - 1) with the index as a constant: code that has to be straight-line, whatever the unroller thinks of it.
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
 }
 
 }  // namespace cdp

@@ -123,7 +123,7 @@ constexpr int STAGE_COPY_ELEMS = 8192;  // elements per copy tile
 // First tiles of the problems of a launch side by side, for the kernels' search (tile_starts_find): read from the problems
 // themselves it is one read of the argument block after the other, 150 bytes apart, each waited for (a launch of six
 // problems: 2200 cycles of a 9 us kernel, 600 so).  At the end of the argument block: a launch of one problem, which has nothing to
-// search, finds its problem next to the header as before.
+// search, finds its problem next to the header (and does not read the table, linear_tick_kernel apart).
 template <int MAX> struct TileStarts { int at[MAX]; };
 template <int MAX, typename Prob> inline void tile_starts_set(TileStarts<MAX>& t, const Prob* p, int n) {
   for (int i = 0; i < MAX; ++i) t.at[i] = i < n ? p[i].tile_begin : 0x7fffffff;

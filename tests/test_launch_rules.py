@@ -62,33 +62,33 @@ def tiles(tmp_path_factory):
     return _asker(tmp_path_factory, "tiles")
 
 
-# dtype, M (output channels), N (taps x input channels), K (positions), {ranges: us measured}; one count per 16 slabs or three
-# was the rule before there was a model of the cost, and comes first
+# dtype, M (output channels), N (taps x input channels), K (positions), {ranges: us measured, on the kernel that a launch of so many runs on};
+# one count per 16 slabs or three was the rule before there was a model of the cost, and comes first
 MEASURED = [
-    (F32, 64, 576, 401408, {205: 329, 28: 895, 49: 514, 64: 576, 98: 384, 128: 404, 196: 338, 256: 316, 392: 336, 784: 352}),
-    (F32, 40, 2880, 20577, {41: 93, 6: 220, 10: 136, 16: 129, 20: 107, 28: 103, 32: 95, 44: 88}),
-    (F32, 120, 432, 107632, {128: 151, 20: 342, 32: 217, 49: 212, 64: 166, 80: 184, 98: 190, 112: 170, 160: 150, 196: 175}),
-    (F32, 64, 3024, 10140, {20: 59, 5: 134, 10: 72, 12: 90, 14: 78, 16: 72, 23: 68}),
-    (F32, 280, 504, 40656, {80: 176, 14: 297, 20: 213, 28: 250, 40: 180, 49: 203, 56: 181, 64: 161, 83: 197}),
-    (F32, 56, 792, 39546, {78: 76, 16: 161, 32: 86, 40: 101, 49: 87, 56: 79, 64: 70, 81: 76}),
-    (F32, 920, 1800, 2645, {6: 119, 1: 271, 2: 144, 3: 159, 4: 125, 5: 139, 8: 132, 9: 131}),
-    (F32, 128, 576, 800, {3: 37, 4: 31, 5: 25}),
-    (BF16, 3072, 768, 6272, {7: 86, 1: 160, 2: 106, 3: 79, 4: 77, 5: 71, 6: 83, 8: 78, 12: 86, 16: 90}),
-    (BF16, 128, 1152, 25088, {25: 37, 6: 108, 12: 61, 20: 43, 28: 35, 32: 41, 40: 37, 49: 31, 53: 31}),
-    (BF16, 64, 576, 100352, {98: 35, 20: 104, 32: 68, 49: 49, 64: 47, 80: 41, 112: 37, 128: 35, 160: 34, 196: 31, 200: 32}),
-    (BF16, 256, 2304, 6272, {7: 34, 2: 83, 4: 50, 6: 41, 8: 41, 10: 35, 12: 36, 14: 31, 16: 36}),
-    (BF16, 136, 19800, 15129, {4: 256, 1: 449, 2: 288, 3: 291, 6: 265, 7: 268, 8: 257, 12: 261, 16: 269, 24: 298, 33: 461}),
+    (F32, 64, 576, 401408, {205: 329, 28: 549, 49: 502, 64: 574, 98: 389, 128: 402, 196: 340, 203: 330, 256: 317, 392: 332, 784: 339}),
+    (F32, 40, 2880, 20577, {41: 93.9, 6: 216, 10: 134, 16: 127, 20: 106, 28: 103, 32: 95.4, 43: 89.8, 44: 89.4}),
+    (F32, 120, 432, 107632, {128: 155, 20: 332, 32: 216, 49: 211, 64: 168, 80: 184, 98: 157, 112: 173, 121: 159, 160: 154, 196: 159}),
+    (F32, 64, 3024, 10140, {20: 59.5, 5: 88.9, 10: 72.2, 12: 88.1, 14: 77.3, 16: 69.1, 23: 69.8}),
+    (F32, 280, 504, 40656, {80: 175, 14: 287, 20: 208, 28: 232, 40: 168, 49: 197, 56: 178, 64: 160, 83: 176}),
+    (F32, 56, 792, 39546, {78: 76.9, 16: 99.2, 32: 85.3, 40: 99.1, 49: 85.6, 56: 77.6, 64: 69.8, 69: 64.7, 81: 77.0}),
+    (F32, 920, 1800, 2645, {6: 120, 1: 263, 2: 144, 3: 148, 4: 120, 5: 132, 8: 131, 9: 133}),
+    (F32, 128, 576, 800, {3: 12.5, 4: 11.1, 5: 11.9}),
+    (BF16, 3072, 768, 6272, {7: 75.5, 1: 120, 2: 104, 3: 78.1, 4: 74.0, 5: 68.7, 6: 76.9, 8: 73.1, 12: 83.0, 16: 86.5}),
+    (BF16, 128, 1152, 25088, {25: 30.7, 6: 74.8, 12: 43.4, 20: 34.2, 28: 29.5, 32: 38.6, 40: 33.1, 49: 30.6, 53: 30.9}),
+    (BF16, 64, 576, 100352, {98: 30.9, 20: 88.1, 32: 58.9, 49: 42.7, 64: 39.4, 80: 34.5, 112: 37.0, 128: 35.4, 160: 34.5, 196: 31.8, 200: 31.8}),
+    (BF16, 256, 2304, 6272, {7: 29.3, 2: 54.6, 4: 36.9, 6: 32.0, 8: 36.3, 10: 34.6, 12: 32.4, 14: 29.9, 16: 32.3}),
+    (BF16, 136, 19800, 15129, {4: 251, 1: 284, 2: 282, 3: 287, 6: 260, 7: 252, 8: 252, 12: 258, 16: 266, 24: 299, 33: 321}),
 ]
 
 
 @pytest.mark.parametrize("case", MEASURED, ids=lambda c: "%s-%dx%dx%d" % ("bf16" if c[0] else "f32", *c[1:4]))
 def test_count_is_no_slower_than_one_per_sixteen_slabs(ranges, case):
-    """The measured count nearest to the one chosen is within 6 % of the old rule's time (two launches of one count differ by up to
-    3 %)."""
+    """The measured count nearest to the one chosen is within 6 % of the old rule's time and 8 % of the best measured (two launches of one
+    count differ by up to 3 %)."""
     dtype, m, n, k, us = case
     got = ranges([(dtype, m, n, k, k // 512 + 4)])[0]
     near = min(us, key=lambda c: abs(c - got))
-    assert us[near] <= 1.06 * next(iter(us.values())), (got, near, us[near])
+    assert us[near] <= 1.06 * next(iter(us.values())) and us[near] <= 1.08 * min(us.values()), (got, near, us[near])
 
 
 def test_count_stays_within_bounds(ranges):
