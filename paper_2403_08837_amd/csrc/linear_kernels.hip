@@ -817,35 +817,48 @@ __device__ __forceinline__ void dw_tile(const GemmBatch& batch, const GemmProb& 
     for (int e = 0; e < VEC; ++e) ct[i].e[e] = Ws[(cn + e) * PW + k];
   }
   // A copy whose own rows are whole chunks leaves in chunks, whatever the other's are (a classifier of 10 classes: the forward copy).  With one
-  // test for both, steps of one micro-batch with a layer of 2048 -> 4001 took 3.7 % longer (bf16 145 -> 150 us, fp32 154 -> 158).
-  if ((Kk % VEC) == 0) {
+  // test for both, steps of one micro-batch with a layer of 2048 -> 4001 took 3.7 % longer (bf16 145 -> 150 us, fp32 154 -> 158).  Where both are
+  // whole they stay under one branch: under two, 20 steps of the 4-stage fp32 MLP of width 64 take 0.8 % longer (2467 -> 2488 us).
+  const bool fwd_whole = (Kk % VEC) == 0, tr_whole = (Nn % VEC) == 0;
+  auto forward_pieces = [&]() {
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
       const int id = tid + 256 * i, n = n0 + id / CF, k = k0 + (id % CF) * VEC;
       if (n < Nn && k < Kk) *reinterpret_cast<uint4*>(wf + (int64_t)n * Kk + k) = cf[i].v;
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const int id = tid + 256 * i, n = n0 + id / CF, k = k0 + (id % CF) * VEC;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e)
-        if (n < Nn && k + e < Kk) wf[(int64_t)n * Kk + k + e] = cf[i].e[e];
-    }
-  }
-  if ((Nn % VEC) == 0) {
+  };
+  auto transposed_pieces = [&]() {
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;
       if (k < Kk && n < Nn) *reinterpret_cast<uint4*>(wt + (int64_t)k * Nn + n) = ct[i].v;
     }
+  };
+  if (fwd_whole && tr_whole) {
+    forward_pieces();
+    transposed_pieces();
   } else {
+    if (fwd_whole) {
+      forward_pieces();
+    } else {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;
+      for (int i = 0; i < NF; ++i) {
+        const int id = tid + 256 * i, n = n0 + id / CF, k = k0 + (id % CF) * VEC;
 #pragma unroll
-      for (int e = 0; e < VEC; ++e)
-        if (k < Kk && n + e < Nn) wt[(int64_t)k * Nn + n + e] = ct[i].e[e];
+        for (int e = 0; e < VEC; ++e)
+          if (n < Nn && k + e < Kk) wf[(int64_t)n * Kk + k + e] = cf[i].e[e];
+      }
+    }
+    if (tr_whole) {
+      transposed_pieces();
+    } else {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const int id = tid + 256 * i, k = k0 + id / CT, n = n0 + (id % CT) * VEC;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+          if (k < Kk && n + e < Nn) wt[(int64_t)k * Nn + n + e] = ct[i].e[e];
+      }
     }
   }
   if (bias_step) {
