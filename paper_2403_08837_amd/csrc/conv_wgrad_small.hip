@@ -2,10 +2,10 @@
 // ahead and three or four of them to a CU, cover for each other; where a CU has one of them, every slab is a chain of memory
 // round trip, LDS write, barrier, read and product.  Here: smaller tiles, and more requests on their way per workgroup.
 // Same reduction ranges, same partial sums (kernels.h).  us with the fold, conv_wgrad_kernel / here, at the number of ranges in brackets:
-//   bf16  128 x 1152 over 25088 positions [28]  36.6 / 28.0      64 x 576 over 100352 [98]  36.9 / 29.4     256 x 2304 over 6272 [7]  36.1 / 27.9
-//         128 x 1152 over 1568 [7]              17.7 / 13.1      512 x 256 over 784 [5]     14.0 / 10.6     24 x 144 over 6272 [14]   17.7 / 13.7
-//   fp32  128 x 576 over 800 [5]                25.5 / 12.0      128 x 1152 over 1568 [7]   33.5 / 21.3     64 x 576 over 12544 [28]  41.4 / 29.0
-//         24 x 144 over 6272 [16]               38.2 / 14.0      512 x 256 over 784 [5]     24.7 / 12.6     32 x 288 over 3136 [10]   30.9 / 12.2
+//   bf16  128 x 1152 over 25088 positions [28]  35.3 / 30.7      64 x 576 over 100352 [98]  34.7 / 30.9     256 x 2304 over 6272 [7]  33.4 / 28.5
+//         128 x 1152 over 1568 [7]              16.9 / 13.1      512 x 256 over 784 [5]     14.1 / 10.9     24 x 144 over 6272 [14]   16.7 / 14.0
+//   fp32  128 x 576 over 800 [5]                24.9 / 11.8      128 x 1152 over 1568 [7]   32.5 / 20.2     64 x 576 over 12544 [28]  36.0 / 27.9
+//         24 x 144 over 6272 [16]               33.9 / 13.9      512 x 256 over 784 [5]     25.1 / 13.9     32 x 288 over 3136 [10]   27.6 / 12.2
 // Errors against 64 bits: bf16 the same, fp32 half (four partial sums per range).
 #include <algorithm>
 #include <type_traits>
@@ -353,8 +353,8 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_few_kernel(const GemmBatch 
 // other kernel has tiles of 64 rows and ranges are one or two groups of positions, so that two or three of the four wavefronts here have nothing to
 // do.  us past the line, conv_wgrad_kernel / here: bf16 1008 workgroups (256 x 2304 over 6272 [14]) 30.2 / 32.3, 980 (64 x 576 over 100352 [196])
 // 31.9 / 34.0; fp32 2304 (512 x 4608 over 98 [1]) 26.6 / 27.6, 2048 (1024 x 512 over 200 [4]) 17.3 / 17.8, 7632 (128 x 1152 over 25088 [53]) 90 / 147.
-// Short ranges: 884 (104 x 7056 over 25 [1]) 10.6 / 13.7, 832 (40 x 3312 over 98 [4]) 10.5 / 12.2, 640 (64 x 5112 over 49 [2]) 10.4 / 10.2, of 128 rows 952
-// (216 x 1080 over 200 [4]) 17.1 / 13.4; longer ones 832 (64 x 1656 over 2450 [8]) 31.7 / 21.7.
+// Short ranges: 884 (104 x 7056 over 25 [1]) 10.6 / 13.7, 832 (40 x 3312 over 98 [4]) 10.0 / 12.2, 640 (64 x 5112 over 49 [2]) 10.4 / 10.2, of 128 rows 952
+// (216 x 1080 over 200 [4]) 16.9 / 13.3; longer ones 832 (64 x 1656 over 2450 [8]) 28.5 / 21.8.
 bool conv_wgrad_small_wanted(const GemmBatch& b, int dtype) {
   const bool bf16 = dtype == DT_BF16;
   const int to = bf16 ? 64 : 32, tc = bf16 ? 128 : 32;

@@ -118,9 +118,9 @@ def test_order_of_weight_gradient_tiles(runs):
 
 # dtype, M, N, K, ranges, us on conv_wgrad_kernel, us on the tiles of launches short of workgroups
 FEW = [(F32, 104, 7056, 25, 1, 10.6, 13.7), (F32, 32, 7128, 98, 4, 10.3, 13.7), (F32, 112, 2016, 128, 4, 9.8, 13.1), (F32, 48, 4032, 243, 4, 11.5, 13.1),
-       (F32, 104, 1584, 200, 4, 12.7, 13.1), (F32, 40, 3312, 98, 4, 10.5, 12.2), (F32, 64, 5112, 49, 2, 10.4, 10.2), (F32, 48, 2808, 128, 4, 10.2, 9.7),
-       (F32, 728, 504, 49, 2, 13.5, 10.4), (F32, 880, 1008, 32, 1, 13.6, 13.8), (F32, 216, 1080, 200, 4, 17.1, 13.4), (F32, 256, 1296, 169, 3, 17.6, 14.2),
-       (F32, 64, 1656, 2450, 8, 31.7, 21.7), (F32, 40, 2600, 1250, 6, 24.7, 18.7), (F32, 512, 4608, 98, 1, 26.6, 27.6), (F32, 128, 1152, 25088, 53, 90, 147),
+       (F32, 104, 1584, 200, 4, 12.7, 13.1), (F32, 40, 3312, 98, 4, 10.0, 12.2), (F32, 64, 5112, 49, 2, 10.4, 10.2), (F32, 48, 2808, 128, 4, 10.2, 9.7),
+       (F32, 728, 504, 49, 2, 13.3, 10.3), (F32, 880, 1008, 32, 1, 13.6, 13.8), (F32, 216, 1080, 200, 4, 16.9, 13.3), (F32, 256, 1296, 169, 3, 17.3, 14.2),
+       (F32, 64, 1656, 2450, 8, 28.5, 21.8), (F32, 40, 2600, 1250, 6, 22.3, 18.8), (F32, 512, 4608, 98, 1, 26.6, 27.6), (F32, 128, 1152, 25088, 53, 90, 147),
        (BF16, 744, 5112, 25, 1, 18.3, 18.8), (BF16, 56, 5688, 2800, 9, 20.9, 19.5), (BF16, 232, 1400, 6845, 11, 27.4, 25.1), (BF16, 24, 2880, 10368, 21, 21.0, 19.1),
        (BF16, 256, 2304, 6272, 14, 30.2, 32.3), (BF16, 64, 576, 100352, 196, 31.9, 34.0)]
 
