@@ -3,23 +3,26 @@
 // of workgroups (conv_dl_tile).
 //
 // What is different from conv_gemm_kernel (128 x 128, four wavefronts):
-//   * operands go from global memory straight into LDS (global_load_lds_dwordx4, 16 bytes per lane, no
-//     register round trip and no LDS store instructions); a lane whose chunk is a structural zero (a tap
-//     outside the image, a row past the matrix) reads 16 zero bytes from a small device array instead;
+//   * operands go from global memory straight into LDS (16 bytes per lane, no register round trip and no LDS store
+//     instructions), as buffer loads: a lane whose chunk is a structural zero (a tap outside the image) asks for an offset past the
+//     buffer and gets zeros, so that a slab costs no address arithmetic in the vector unit: the offsets change with the tap,
+//     the scalar base with the slab;
 //   * one such instruction fills 1 KB of LDS lane by lane, so a tile row is BK unpadded elements and bank
 //     conflicts are avoided by an XOR swizzle: 16-byte chunk c of tile row r sits in slot c ^ ((r >> 1) & 7) (slabs of 64;
 //     c ^ ((r >> 2) & 3) for slabs of 32; the loading lane picks the global chunk that belongs in its slot); a fragment
 //     read of 16 rows x 16 bytes then covers all 64 banks once;
-//   * two to four LDS stages: the loads of the next STAGES - 1 slabs are in flight while one is contracted, one
-//     barrier per slab.  The stages are separate __shared__ arrays on purpose: the compiler orders an
-//     LDS read after every outstanding LDS-writing load it cannot prove disjoint, and a single array would
-//     make it wait for the prefetch before the first fragment read;
-//   * the fragments of the next 16-deep step are read between the products of the current one (a fixed schedule: left to
-//     itself the compiler reads, waits, multiplies);
+//   * two to four LDS stages: the loads of the next STAGES - 1 slabs are in flight while one is contracted, one barrier per slab.  The
+//     loads are assembly without outputs: the compiler keeps an account of loads that write LDS and waits for all of them at fragment
+//     reads it cannot tell apart from them (every second slab waited for the one just requested); here the waits are
+//     those written down, and the barrier's fences keep the fragment reads between the barriers they belong to;
+//   * the barrier stands before the last 16-deep step of a slab, whose fragments are in registers by then: the first fragments of the next
+//     slab are read, and the loads into the stage just freed requested, between the products of that step.  With the barrier between two
+//     slabs all eight wavefronts waited for their first fragments at once;
+//   * fragments of the next 16-deep step are read between the products of the current one, in the order of the source (sched_barrier);
 //   * results leave out of the registers (conv_epilogue).
-// Fixed schedule and register epilogue, 256 x 256 tiles: 8192^3 1057 -> 950 us (1160 TFLOP/s), 3x3 over 512 channels,
-// 25088 rows, 132 -> 115 us.  LDS bandwidth is the next wall there: wave tiles of 128 x 64 read and the loads write about what
-// the LDS of a CU moves in the cycles of their products.
+// us, with compiler-ordered loads, the barrier between slabs and an epilogue whose stores waited for each other / so: 8192^3 985 / 859 (1279 TFLOP/s),
+// 3x3 over 512 channels with 25088 rows 116 / 101 (256 x 256); 6272 x 768 x 3072 38.0 / 33.4 (192 x 128); 25088 x 128 x 1152 13.9 / 12.3 (128 x 128);
+// 1568 x 512 x 4608 22.5 / 19.8, 6272 x 256 x 1024 9.4 / 8.1 (64 x 64).  Outputs bit for bit the same.
 // Same problem descriptors, same epilogues (bias, residual, ReLU; data gradient: addend, accumulate, mask).
 #include <algorithm>
 #include <type_traits>
@@ -32,96 +35,126 @@ namespace cdp {
 
 namespace {
 
-__device__ uint4 g_zero_chunk[4];  // zero-initialised; source of structural zeros
-
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
 }  // namespace
 
-// BM x BN outputs per workgroup of WAVES_M x WAVES_N wavefronts, slabs of BK, STAGES of them in LDS; WPS: wavefronts per SIMD
-// that LDS allows (said to the compiler, which otherwise copies the accumulators between the two register files).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool GELU>
-__device__ __forceinline__ void conv_gemm_dl_body(const GemmBatch& batch) {
-  constexpr int NWAVE = WAVES_M * WAVES_N;
-  constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;  // wave tile
-  constexpr int MI = WTM / 32, NI = WTN / 32;            // MFMA tiles per wave
-  constexpr int ROW = BK * 2, CPR = ROW / 16, RPB = 1024 / ROW;  // bytes and chunks of a tile row, rows per 1 KB block
-  constexpr int STAGE_BYTES = (BM + BN) * ROW;           // one LDS stage
-  constexpr int LPA = BM / RPB / NWAVE, LPB = BN / RPB / NWAVE;  // 1 KB blocks a wave loads per operand and slab
+// Slabs of one tile on their way into LDS: what conv_gemm_dl_kernel loads, and where it stands.  A wavefront fills LPA blocks of 1 KB of
+// the gathered operand and LPB of the weights per slab.
+template <int BM, int BN, int NWAVE, int BK>
+struct SlabLoads {
+  static constexpr int ROW = BK * 2, CPR = ROW / 16, RPB = 1024 / ROW;  // bytes and chunks of a tile row, rows per 1 KB block
+  static constexpr int LPA = BM / RPB / NWAVE, LPB = BN / RPB / NWAVE, N = LPA + LPB;
   static_assert(LPA * RPB * NWAVE == BM && LPB * RPB * NWAVE == BN, "tile rows are dealt to the waves in 1 KB blocks");
-  static_assert(STAGES >= 2 && STAGES <= 4, "");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem0[STAGE_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char smem1[STAGE_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char smem2[STAGES > 2 ? STAGE_BYTES : 1];
-  __shared__ __attribute__((aligned(1024))) unsigned char smem3[STAGES > 3 ? STAGE_BYTES : 1];
-  constexpr int VEC = 8;
   // 16-byte chunk c of tile row r sits in slot c ^ swz(r) of the row
-  auto swz = [](int r) { return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3; };
-  const int tile = xcd_block_cyclic((int)blockIdx.x, batch.total_tiles, 8);
-  const GemmProb& P = batch.p[find_problem(batch, tile)];
-  const int local = tile - P.tile_begin;
-  const int tn = local % P.tiles_n, tm = local / P.tiles_n;
-  const int row0 = tm * BM, col0 = tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const uint16_t* __restrict__ Ap = static_cast<const uint16_t*>(P.A);
-  const uint16_t* __restrict__ Bp = static_cast<const uint16_t*>(P.B);
-  const uint16_t* const zero = reinterpret_cast<const uint16_t*>(g_zero_chunk);
-  const ConvGeom g = P.g;
-  const int mode = P.a_mode;
-  const int C = (mode == OP_PLAIN_K) ? P.K : g.C;  // channels per tap of the gathered tensor
+  static __device__ __forceinline__ int swz(int r) { return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3; }
 
-  // rows this lane loads: block (wave * LPA + i) of RPB rows, row lane / CPR of it, slot lane % CPR
-  const int lr = lane / CPR, ls = lane % CPR;
-  int abase[LPA], boff[LPB];
-  unsigned amask[LPA];
-#pragma unroll
-  for (int i = 0; i < LPA; ++i) {
-    const int tr = (wave * LPA + i) * RPB + lr;   // tile row
-    const int chunk = ls ^ swz(tr);               // the global chunk whose place is slot ls
-    const int r = row0 + tr;
-    abase[i] = 0;
-    amask[i] = 0;
-    if (r < P.M) {
-      if (mode == OP_PLAIN_K) {
-        abase[i] = r * P.lda + chunk * VEC;
-        amask[i] = 1u;
-      } else {
-        conv_row(g, mode, r, abase[i], amask[i]);
-        abase[i] += chunk * VEC;
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < LPB; ++i) {
-    const int tr = (wave * LPB + i) * RPB + lr, c = col0 + tr;
-    boff[i] = c < P.N ? c * P.ldb + (ls ^ swz(tr)) * VEC : -1;
-  }
+  ConvGeom g;
+  int mode, C;                    // C: channels per tap of the gathered tensor
+  int left, tap, c0, kh, kw;      // slabs left; position of the next one: tap, channel offset inside it
+  const char *first, *pa, *pb;    // of the next slab, for offset 0; first: of tap (0, 0)
+  unsigned records;               // bytes of either buffer: 0 once nothing is left
+  unsigned abase[LPA], amask[LPA], aoff[LPA], boff[LPB];  // byte offsets; valid taps of a row, bit kh * KW + kw
 
-  // wavefront-uniform position of the next slab to load: tap index, its address delta, channel offset inside the tap
-  int tap = 0, tdelta = 0, c0 = 0, kh = 0, kw = 0, kload = 0;
-  auto issue = [&](unsigned char* stage) {
-    const int delta = tdelta + c0;
+  __device__ __forceinline__ void at_tap() {
+#pragma unroll
+    for (int i = 0; i < LPA; ++i) aoff[i] = (amask[i] >> tap) & 1u ? abase[i] : ~0u;
+  }
+  __device__ __forceinline__ void start(const GemmProb& P, int row0, int col0, int wave, int lane) {
+    g = P.g;
+    mode = P.a_mode;
+    C = mode == OP_PLAIN_K ? P.K : g.C;
+    left = P.K / BK;
+    tap = c0 = kh = kw = 0;
+    records = 0xfffffff0u;
+    // a row's base is negative in the padding before the first image: offsets count from the lowest one
+    const int shift = mode == OP_CONV_FWD ? (g.pad * g.W + g.pad) * g.C : 0;
+    pa = first = static_cast<const char*>(P.A) - 2 * (int64_t)shift;
+    pb = static_cast<const char*>(P.B);
+    // block (wave * LPA + i) of RPB rows, row lane / CPR of it, slot lane % CPR; rows past the matrix repeat the last one: they only
+    // reach results that are not stored
+    const int lr = lane / CPR, ls = lane % CPR;
 #pragma unroll
     for (int i = 0; i < LPA; ++i) {
-      const uint16_t* pa = ((amask[i] >> tap) & 1u) ? Ap + abase[i] + delta : zero;
-      __builtin_amdgcn_global_load_lds(pa, (lds_ptr)(stage + (wave * LPA + i) * 1024), 16, 0, 0);
+      const int tr = (wave * LPA + i) * RPB + lr, r = min(row0 + tr, P.M - 1);
+      int base;
+      amask[i] = 1u;
+      if (mode == OP_PLAIN_K) base = r * P.lda;
+      else conv_row(g, mode, r, base, amask[i]);
+      abase[i] = 2u * (unsigned)(base + shift + (ls ^ swz(tr)) * 8);
     }
+    at_tap();
 #pragma unroll
     for (int i = 0; i < LPB; ++i) {
-      const uint16_t* pb = boff[i] >= 0 ? Bp + boff[i] + kload : zero;
-      __builtin_amdgcn_global_load_lds(pb, (lds_ptr)(stage + BM * ROW + (wave * LPB + i) * 1024), 16, 0, 0);
+      const int tr = (wave * LPB + i) * RPB + lr, c = min(col0 + tr, P.N - 1);
+      boff[i] = 2u * (unsigned)(c * P.ldb + (ls ^ swz(tr)) * 8);
     }
-    kload += BK;
+  }
+  // Load e of the next slab into the stage whose rows of the gathered operand begin at LDS address `at` (those of the weights behind them).
+  __device__ __forceinline__ void issue(unsigned at, int wave, int e) const {
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    const uintptr_t p = (uintptr_t)(e < LPA ? pa : pb);
+    const v4u buffer = {(unsigned)p, (unsigned)(p >> 32), records, 0x00020000u};
+    const unsigned lds = at + (e < LPA ? (wave * LPA + e) * 1024 : BM * ROW + (wave * LPB + e - LPA) * 1024);
+    // nothing is written to registers; the nop is the wait state between the two
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(e < LPA ? aoff[e] : boff[e - LPA]), "s"(buffer));
+  }
+  __device__ __forceinline__ void advance() {
+    if (--left <= 0) {
+      records = 0;  // the loads past the last slab, which the counted waits expect, read nothing
+      return;
+    }
+    pa += 2 * BK;
+    pb += 2 * BK;
     c0 += BK;
     if (c0 == C) {
       c0 = 0;
       ++tap;
       if (++kw == g.KW) { kw = 0; ++kh; }
-      tdelta = mode == OP_CONV_FWD ? (kh * g.W + kw) * g.C : -((kh / g.stride) * g.W + (kw / g.stride)) * g.C;
+      pa = first + 2 * (int64_t)(mode == OP_CONV_FWD ? (kh * g.W + kw) * g.C : -((kh / g.stride) * g.W + (kw / g.stride)) * g.C);
+      at_tap();
     }
-  };
+  }
+};
 
+// All but the newest N of this wave's loads and stores are done, and its LDS reads.
+template <int N> __device__ __forceinline__ void wait_newest() {
+  static_assert(N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+}
+__device__ __forceinline__ void slab_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// BM x BN outputs per workgroup of WAVES_M x WAVES_N wavefronts, slabs of BK, STAGES of them in LDS; WPS: wavefronts per SIMD
+// that LDS allows (said to the compiler, which otherwise copies the accumulators between the two register files).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool GELU>
+__device__ __forceinline__ void conv_gemm_dl_body(const GemmBatch& batch) {
+  using Loads = SlabLoads<BM, BN, WAVES_M * WAVES_N, BK>;
+  constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;  // wave tile
+  constexpr int MI = WTM / 32, NI = WTN / 32;            // MFMA tiles per wave
+  constexpr int ROW = Loads::ROW, STAGE_BYTES = (BM + BN) * ROW, KK = BK / 16, LP = Loads::N;
+  static_assert(STAGES >= 2 && STAGES <= 4, "");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE_BYTES];
+  const int tile = xcd_block_cyclic((int)blockIdx.x, batch.total_tiles, 8);
+  const GemmProb& P = batch.p[__builtin_amdgcn_readfirstlane(find_problem(batch, tile))];
+  const int local = tile - P.tile_begin;
+  const int tn = local % P.tiles_n, tm = local / P.tiles_n;
+  const int row0 = tm * BM, col0 = tn * BN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const unsigned lds = (unsigned)(uintptr_t)(lds_ptr)smem;
+
+  Loads loads;
+  loads.start(P, row0, col0, wave, lane);
+  static_for<STAGES>([&](auto q) {
+#pragma unroll
+    for (int e = 0; e < LP; ++e) loads.issue(lds + decltype(q)::value * STAGE_BYTES, wave, e);
+    loads.advance();
+  });
   v16f_t acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -131,115 +164,59 @@ __device__ __forceinline__ void conv_gemm_dl_body(const GemmBatch& batch) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
   // fragments: row = base + lane % 32, chunk = 2 * kk + lane / 32
-  const int l31 = lane & 31, hi = lane >> 5;
-  int offa[MI], offb[NI], swa[MI], swb[NI];
+  const int l31 = lane & 31, hi = lane >> 5, swa = Loads::swz(l31);  // rows 32 apart swizzle alike
+  const unsigned char* const ra = smem + (wm * WTM + l31) * ROW;
+  const unsigned char* const rb = smem + BM * ROW + (wn * WTN + l31) * ROW;
+  uint4 fa[2][MI], fb[2][NI];
+  auto frag = [&](int q, int kk, int buf, int e) {  // fragment e of MI + NI
+    const int x = q * STAGE_BYTES + (((kk * 2 + hi) ^ swa) << 4);
+    if (e < MI) fa[buf][e] = *reinterpret_cast<const uint4*>(ra + x + e * 32 * ROW);
+    else fb[buf][e - MI] = *reinterpret_cast<const uint4*>(rb + x + (e - MI) * 32 * ROW);
+  };
+  wait_newest<(STAGES - 1) * LP>();
+  slab_barrier();
 #pragma unroll
-  for (int i = 0; i < MI; ++i) { const int r = wm * WTM + i * 32 + l31; offa[i] = r * ROW; swa[i] = swz(r); }
-#pragma unroll
-  for (int j = 0; j < NI; ++j) { const int r = wn * WTN + j * 32 + l31; offb[j] = BM * ROW + r * ROW; swb[j] = swz(r); }
-  auto contract = [&](const unsigned char* stage) {
-    constexpr int KK = BK / 16;
-    uint4 a[2][MI], b[2][NI];
-    auto frags = [&](int kk, int buf) {
-#pragma unroll
-      for (int i = 0; i < MI; ++i) a[buf][i] = *reinterpret_cast<const uint4*>(stage + offa[i] + (((kk * 2 + hi) ^ swa[i]) << 4));
-#pragma unroll
-      for (int j = 0; j < NI; ++j) b[buf][j] = *reinterpret_cast<const uint4*>(stage + offb[j] + (((kk * 2 + hi) ^ swb[j]) << 4));
-    };
-    frags(0, 0);
+  for (int e = 0; e < MI + NI; ++e) frag(0, 0, 0, e);
+  auto step = [&](auto qc) {
+    constexpr int q = decltype(qc)::value, next = (q + 1) % STAGES;
+    constexpr int MN = MI * NI, RP = (MI + NI + MN - 1) / MN, IP = (LP + MN - 1) / MN;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      if (kk + 1 < KK) frags(kk + 1, (kk + 1) & 1);
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j) acc[i][j] = mfma_bf16(b[kk & 1][j], a[kk & 1][i], acc[i][j]);  // transposed: see the epilogue
-    }
-    {  // fragments of the next 16-deep step between the products of the current one
-      __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
-#pragma unroll
-      for (int kk = 0; kk + 1 < KK; ++kk) {
-#pragma unroll
-        for (int e = 0; e < MI * NI; ++e) {
-          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-          if (e < MI + NI) __builtin_amdgcn_sched_group_barrier(0x100, (MI + NI + MI * NI - 1) / (MI * NI), 0);
-        }
+      const bool last = kk == KK - 1;
+      if (last) {  // the next slab is whole, and every wave has read this one
+        wait_newest<(STAGES - 2) * LP>();
+        slab_barrier();
       }
-      __builtin_amdgcn_sched_group_barrier(0x8, MI * NI, 0);
-    }
-  };
-
-  // Slab t is waited for (every load of this wave but those of the slabs requested after it), the barrier makes it whole
-  // and says that every wave is done with slab t - 1, whose stage slab t + STAGES - 1 is then requested into.
-  // The compiler keeps its own account of loads that write LDS and of the waits it sees, and merges it over branches in
-  // the most careful way: with the wait in assembly, or with a guarded request anywhere before it, it waits for every
-  // load at the first fragment read and the deeper prefetch gains nothing.  Hence builtins, and straight-line code for
-  // every number of slabs that the unrolled loop leaves.
-  const int nslab = P.K / BK;
-  unsigned char* const st[4] = {smem0, smem1, smem2, smem3};
-  auto wait_slabs = [&](auto n) {  // all but the newest n slabs
-    constexpr int N = decltype(n)::value * (LPA + LPB);
-    static_assert(N < 64, "vmcnt");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));  // vmcnt(N) lgkmcnt(0)
-  };
-  auto barrier = [&]() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
-  // slabs 0 .. R - 1 of a row of slabs that starts in stage 0, the first min(R, STAGES - 1) requested already
-  auto finish = [&](auto rem) {
-    constexpr int R = decltype(rem)::value;
-    static_for<R>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      wait_slabs(std::integral_constant<int, (STAGES - 2 < R - 1 - j ? STAGES - 2 : R - 1 - j)>{});
-      barrier();
-      if constexpr (j + STAGES - 1 < R) issue(st[(j + STAGES - 1) % STAGES]);
-      contract(st[j % STAGES]);
-    });
-  };
-  if constexpr (STAGES == 2) {
-    issue(smem0);
-    __builtin_amdgcn_s_waitcnt(0);
-    barrier();
-    for (int t = 0; t < nslab; t += 2) {
-      if (t + 1 < nslab) issue(smem1);
-      contract(smem0);
-      __builtin_amdgcn_s_waitcnt(0);
-      barrier();
-      if (t + 1 >= nslab) break;
-      if (t + 2 < nslab) issue(smem0);
-      contract(smem1);
-      __builtin_amdgcn_s_waitcnt(0);
-      barrier();
-    }
-  } else if (nslab >= STAGES - 1) {
 #pragma unroll
-    for (int q = 0; q < STAGES - 1; ++q) issue(st[q]);
-    int t = 0;
-    for (; t + 2 * STAGES - 2 < nslab; t += STAGES) {
+      for (int e = 0; e < MN; ++e) {
+        acc[e / NI][e % NI] = mfma_bf16(fb[kk & 1][e % NI], fa[kk & 1][e / NI], acc[e / NI][e % NI]);  // transposed: see the epilogue
 #pragma unroll
-      for (int q = 0; q < STAGES; ++q) {
-        wait_slabs(std::integral_constant<int, STAGES - 2>{});
-        barrier();
-        issue(st[(q + STAGES - 1) % STAGES]);
-        contract(st[q]);
+        for (int r = 0; r < RP; ++r)
+          if (e * RP + r < MI + NI) frag(last ? next : q, last ? 0 : kk + 1, (kk + 1) & 1, e * RP + r);
+#pragma unroll
+        for (int r = 0; r < IP; ++r)
+          if (last && e * IP + r < LP) loads.issue(lds + q * STAGE_BYTES, wave, e * IP + r);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    static_for<STAGES>([&](auto k) {  // STAGES - 1 .. 2 STAGES - 2 slabs are left
-      if (nslab - t == STAGES - 1 + decltype(k)::value) finish(std::integral_constant<int, STAGES - 1 + decltype(k)::value>{});
-    });
-  } else {
-    static_for<STAGES - 2>([&](auto k) {
-      constexpr int R = 1 + decltype(k)::value;
-      if (nslab == R) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) issue(st[q]);
-        finish(std::integral_constant<int, R>{});
-      }
-    });
+    loads.advance();
+  };
+  for (int t = P.K / BK;;) {
+    step(std::integral_constant<int, 0>{});
+    if (--t == 0) break;
+    step(std::integral_constant<int, 1>{});
+    if (--t == 0) break;
+    if constexpr (STAGES > 2) {
+      step(std::integral_constant<int, 2>{});
+      if (--t == 0) break;
+    }
+    if constexpr (STAGES > 3) {
+      step(std::integral_constant<int, 3>{});
+      if (--t == 0) break;
+    }
   }
-  conv_epilogue<uint16_t, MI, NI, GELU>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane);
+  wait_newest<0>();  // no load is left that writes LDS when this workgroup gives it back
+  conv_epilogue<MI, NI, GELU>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane);
 }
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WPS) void conv_gemm_dl_kernel(const GemmBatch batch) {
@@ -264,8 +241,9 @@ static bool conv_dl_eligible(const GemmProb& p, int dtype, int bk) {
   if ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B) | reinterpret_cast<uintptr_t>(p.out)) & 15) return false;
   if ((p.aux1 && (reinterpret_cast<uintptr_t>(p.aux1) & 15)) || (p.epi == EPI_DGRAD && p.aux0 && (reinterpret_cast<uintptr_t>(p.aux0) & 15)))
     return false;
-  const int64_t a_elems = p.a_mode == OP_PLAIN_K ? (int64_t)p.M * p.lda : (int64_t)(p.M / (p.g.OH * p.g.OW) + 1) * p.g.H * p.g.W * p.g.C;
-  return a_elems < (1ll << 31) && (int64_t)p.N * p.ldb < (1ll << 31);
+  // 32-bit byte offsets: of the operands below 2^32 - 16, the padding in front of the first row included, of results below 2^31
+  const int64_t a_elems = p.a_mode == OP_PLAIN_K ? (int64_t)p.M * p.lda : (int64_t)(p.M / (p.g.OH * p.g.OW) + 1) * p.g.H * p.g.W * p.g.C + (int64_t)(p.g.pad * p.g.W + p.g.pad) * p.g.C;
+  return a_elems < (1ll << 31) - 1024 && (int64_t)p.N * p.ldb < (1ll << 31) - 1024 && (int64_t)p.M * p.ldo < (1ll << 30) && p.ldo <= (1 << 20);
 }
 bool conv_gemm256_eligible(const GemmProb& p, int dtype) { return conv_dl_eligible(p, dtype, 64); }
 

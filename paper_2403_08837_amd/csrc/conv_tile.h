@@ -101,64 +101,137 @@ __device__ __forceinline__ void conv_finish(const GemmProb& P, int64_t o, float*
 // operand): a lane holds one tile row (its lane % 32) and, per group of four accumulator registers, four neighbouring
 // columns of it.
 //
-// Out of the registers: four columns are 16 bytes of an fp32 result; for bf16 one exchange between the lane halves makes
-// eight of them.  No LDS traffic and no barrier, but an instruction touches 32 rows, which the address path of the CU
-// takes at less than half the rate of whole rows.
-template <typename T, int MI, int NI, bool GELU>
-__device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
-  constexpr int VEC = Elem<T>::VEC, NS = 32 * NI / (2 * VEC);  // pieces of 2 VEC columns, VEC per lane half
+// Out of the registers (bf16): one exchange between the lane halves makes eight columns, a 16-byte piece, of them.  No LDS traffic
+// and no barrier, but an instruction touches 32 rows, which the address path of the CU takes at less than half the rate of
+// whole rows.  Stores count with the loads here, and a load on some path between two stores makes the compiler wait for every
+// store before the next one (sixteen round trips one after the other: 10 of the 30 us of a 256 x 256 x 768 tile).  So everything is chosen per
+// tile, outside the loops: NSUM tensors are added (forward: the residual; data gradient: addend, old result), MASK: aux1 is a mask or the
+// GELU's input, GELU: the forward also stores GELU of the stored result in aux2, the data gradient is that of the GELU's
+// input, aux1.  Operands of the row block after this one are requested before this one's results leave.  Loads and stores
+// are buffer instructions: what lies outside the matrix is outside the buffer, no branch, and every tile stores the same number of
+// times (conv_gemm_run_kernel counts them).  Operations and roundings are those of conv_finish.
+template <int MI, int NI, int NSUM, bool MASK, bool GELU>
+__device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
+  using E = Elem<uint16_t>;
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  constexpr int VEC = 8, NS = 2 * NI, NT = NSUM + (MASK ? 1 : 0), AHEAD = MI * NI > 4 ? 1 : 2;
   const int l31 = lane & 31, hi = lane >> 5;
-  const T* aux1 = static_cast<const T*>(P.aux1);
-  auto column = [&](int s) { return col0 + 2 * VEC * s + VEC * hi; };
-  auto row = [&](int i) { return row0 + 32 * i + l31; };
-  // The residual / mask of the whole tile is requested before the first store (a store may alias the next load for all
-  // the compiler knows), where it fits the registers that the operand fragments no longer need.
-  constexpr bool AHEAD = MI * NS <= 8;
-  uint4 pa[AHEAD ? MI : 1][AHEAD ? NS : 1];
-  if (AHEAD && aux1) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-        pa[AHEAD ? i : 0][AHEAD ? s : 0] = row(i) < P.M && column(s) < P.N ? *reinterpret_cast<const uint4*>(aux1 + (int64_t)row(i) * P.ldo + column(s))
-                                                                          : make_uint4(0, 0, 0, 0);
-  }
+  const bool fwd = P.epi == EPI_FWD, relu = fwd && (P.flags & GF_RELU);
+  const unsigned ldo = P.ldo, bytes = (unsigned)P.M * ldo * 2u;  // below 2^31 (conv_dl_eligible)
+  auto buffer = [&](const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000); };
+  const auto out = buffer(P.out), out2 = buffer(GELU && !MASK ? P.aux2 : P.out);
+  const auto t0 = buffer(NSUM == 0 ? P.aux1 : fwd ? P.aux1 : P.aux0 ? P.aux0 : P.out), t1 = buffer(NSUM == 2 ? P.out : P.aux1), t2 = buffer(P.aux1);
+  unsigned off[NS];  // byte offset of the piece of the first row block; columns past the matrix are sent past the buffer
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    const int c = column(s);
-    float bias[VEC];
-    if (P.epi == EPI_FWD && P.aux0) {
+    const int c = col0 + 2 * VEC * s + VEC * hi;
+    off[s] = c < P.N ? ((unsigned)(row0 + l31) * ldo + c) * 2u : 0x80000000u;
+  }
+  const unsigned block = 64u * ldo;
+  v4u x[NT ? AHEAD : 1][NT ? NT : 1][NS];
+  auto request = [&](int i) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) bias[e] = c < P.N ? static_cast<const float*>(P.aux0)[c + e] : 0.f;
+    for (int s = 0; s < NS; ++s) {
+      if constexpr (NT > 0) x[i % AHEAD][0][s] = __builtin_amdgcn_raw_buffer_load_b128(t0, off[s] + i * block, 0, 0);
+      if constexpr (NT > 1) x[i % AHEAD][1][s] = __builtin_amdgcn_raw_buffer_load_b128(t1, off[s] + i * block, 0, 0);
+      if constexpr (NT > 2) x[i % AHEAD][2][s] = __builtin_amdgcn_raw_buffer_load_b128(t2, off[s] + i * block, 0, 0);
+    }
+  };
+  if constexpr (NT > 0 && AHEAD == 2) request(0);
+  if (fwd && P.aux0) {
+    const float* const bias = static_cast<const float*>(P.aux0);
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b[e] = bias[min(col0 + 32 * j + 8 * q + 4 * hi, P.N - 4) + e];  // N is a multiple of VEC on these paths
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += b[e];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if constexpr (NT > 0) {
+      if (AHEAD == 1) request(i);
+      else if (i + 1 < MI) request(i + 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
+    for (int s = 0; s < NS; ++s) {
       float val[VEC];
-      if constexpr (sizeof(T) == 2) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][s >> 1][8 * (s & 1) + e]),
-                                                          __float_as_uint(acc[i][s >> 1][8 * (s & 1) + 4 + e]), false, false);
-          val[e] = __uint_as_float(x[0]);
-          val[VEC - 4 + e] = __uint_as_float(x[1]);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) val[e] = acc[i][s >> 2][4 * (s & 3) + e];
+      for (int e = 0; e < 4; ++e) {
+        const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][s >> 1][8 * (s & 1) + e]),
+                                                        __float_as_uint(acc[i][s >> 1][8 * (s & 1) + 4 + e]), false, false);
+        val[e] = __uint_as_float(y[0]);
+        val[4 + e] = __uint_as_float(y[1]);
       }
-      const int r = row(i);
-      if (r >= P.M || c >= P.N) continue;  // N is a multiple of VEC on these paths
-      const int64_t o = (int64_t)r * P.ldo + c;
-      conv_finish<T, GELU>(P, o, val, bias, !aux1 ? make_uint4(0, 0, 0, 0) : AHEAD ? pa[AHEAD ? i : 0][AHEAD ? s : 0] : *reinterpret_cast<const uint4*>(aux1 + o));
+      Chunk16<uint16_t> a, b, c, res, act;
+      if constexpr (NT > 0) a.v = __builtin_bit_cast(uint4, x[i % AHEAD][0][s]);
+      if constexpr (NT > 1) b.v = __builtin_bit_cast(uint4, x[i % AHEAD][1][s]);
+      if constexpr (NT > 2) c.v = __builtin_bit_cast(uint4, x[i % AHEAD][2][s]);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        if constexpr (NSUM > 0) val[e] += E::to_f32(a.e[e]);
+        if constexpr (NSUM > 1) val[e] += E::to_f32(b.e[e]);
+      }
+      if (relu) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) val[e] = fmaxf(val[e], 0.f);
+      }
+      if constexpr (MASK) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const float m = E::to_f32(NSUM == 0 ? a.e[e] : NSUM == 1 ? b.e[e] : c.e[e]);
+          if constexpr (GELU) val[e] = E::to_f32(E::from_f32(val[e])) * gelu_df<uint16_t>(m);
+          else if (!(m > 0.f)) val[e] = 0.f;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) res.e[e] = E::from_f32(val[e]);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, res.v), out, off[s] + i * block, 0, 0);
+      if constexpr (GELU && !MASK) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) act.e[e] = E::from_f32(gelu_f<uint16_t>(E::to_f32(res.e[e])));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, act.v), out2, off[s] + i * block, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
-template <typename T, int MI, int NI, bool GELU>  // GELU: the launch may hold problems with GF_GELU
-__device__ __forceinline__ void conv_epilogue(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
-  if constexpr (GELU) {
-    if (P.flags & GF_GELU) return conv_epilogue_as<T, MI, NI, true>(P, acc, row0, col0, lane);
+template <int MI, int NI, bool GELU>  // GELU: the launch may hold problems with GF_GELU
+__device__ __forceinline__ void conv_epilogue(const GemmProb& P, v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
+  if (P.epi == EPI_FWD) {
+    if constexpr (GELU) {
+      if (P.flags & GF_GELU) {
+        if (P.aux1) return conv_epilogue_as<MI, NI, 1, false, true>(P, acc, row0, col0, lane);
+        return conv_epilogue_as<MI, NI, 0, false, true>(P, acc, row0, col0, lane);
+      }
+    }
+    if (P.aux1) return conv_epilogue_as<MI, NI, 1, false, false>(P, acc, row0, col0, lane);
+    return conv_epilogue_as<MI, NI, 0, false, false>(P, acc, row0, col0, lane);
   }
-  conv_epilogue_as<T, MI, NI, false>(P, acc, row0, col0, lane);
+  const int nsum = (P.aux0 != nullptr) + ((P.flags & GF_ACCUM) != 0);
+  if constexpr (GELU) {
+    if (P.flags & GF_GELU) {
+      if (nsum == 2) return conv_epilogue_as<MI, NI, 2, true, true>(P, acc, row0, col0, lane);
+      if (nsum == 1) return conv_epilogue_as<MI, NI, 1, true, true>(P, acc, row0, col0, lane);
+      return conv_epilogue_as<MI, NI, 0, true, true>(P, acc, row0, col0, lane);
+    }
+  }
+  if (P.aux1) {
+    if (nsum == 2) return conv_epilogue_as<MI, NI, 2, true, false>(P, acc, row0, col0, lane);
+    if (nsum == 1) return conv_epilogue_as<MI, NI, 1, true, false>(P, acc, row0, col0, lane);
+    return conv_epilogue_as<MI, NI, 0, true, false>(P, acc, row0, col0, lane);
+  }
+  if (nsum == 2) return conv_epilogue_as<MI, NI, 2, false, false>(P, acc, row0, col0, lane);
+  if (nsum == 1) return conv_epilogue_as<MI, NI, 1, false, false>(P, acc, row0, col0, lane);
+  return conv_epilogue_as<MI, NI, 0, false, false>(P, acc, row0, col0, lane);
 }
 
 // Through LDS, 32 rows at a time and in fp32: every instruction then moves whole rows.  `stage`: conv_stage_floats(NI) floats of
