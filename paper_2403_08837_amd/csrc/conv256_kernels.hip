@@ -25,6 +25,7 @@
 // 1568 x 512 x 4608 22.5 / 19.8, 6272 x 256 x 1024 9.4 / 8.1 (64 x 64).  Outputs bit for bit the same.
 // Same problem descriptors, same epilogues (bias, residual, ReLU; data gradient: addend, accumulate, mask).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "conv_tile.h"
@@ -94,7 +95,9 @@ struct SlabLoads {
   __device__ __forceinline__ void issue(unsigned at, int wave, int e) const {
     typedef unsigned v4u __attribute__((ext_vector_type(4)));
     const uintptr_t p = (uintptr_t)(e < LPA ? pa : pb);
-    const v4u buffer = {(unsigned)p, (unsigned)(p >> 32), records, 0x00020000u};
+    // (uniform; said so because the compiler at times keeps them in vector registers, which the instruction does not take)
+    auto uniform = [](unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); };
+    const v4u buffer = {uniform((unsigned)p), uniform((unsigned)(p >> 32)), uniform(records), 0x00020000u};
     const unsigned lds = at + (e < LPA ? (wave * LPA + e) * 1024 : BM * ROW + (wave * LPB + e - LPA) * 1024);
     // nothing is written to registers; the nop is the wait state between the two
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(e < LPA ? aoff[e] : boff[e - LPA]), "s"(buffer));
@@ -226,6 +229,253 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WPS) void conv_gelu_dl_kernel(const GemmBatch batch) {
   conv_gemm_dl_body<BM, BN, WAVES_M, WAVES_N, BK, STAGES, true>(batch);
 }
+
+// Launches of many tiles: 512 workgroups of four wavefronts, two per CU, walk tiles of 128 x 128 (wave tiles of 64 x 64, slabs of 64,
+// two stages of 32 KB).  The loads run through the tiles without a break: behind the last slab of a tile the first ones of the next
+// are requested, so that its descriptor, its rows' addresses and its first operands arrive under the products, and the results of one tile
+// leave under the products of the next.  What a tile costs beside its products (10 to 15 us for a 256 x 256 tile, of 30 at a
+// reduction of 768) is hidden, in short reductions it was most of the time; two workgroups per CU cover for each other's barriers and epilogues.
+//   Who takes what: the 64 workgroups of an XCD (blockIdx modulo 8) share an eighth of the tiles of every problem, so that rows are found in the
+// XCD's L2, the problems with the longest reductions first.  Every wavefront works the sharing out for itself (RunPlan).
+//   Waits: a step needs the slab after it.  Loads and stores count together and in order, and a tile stores the same number of times in
+// every wavefront (conv_epilogue), so the one wait in which the results are newer than the slab leaves them out.
+// us, conv_gemm_kernel / here: see conv_many_tile.
+constexpr int RUN_PER_XCD = 64;
+constexpr int RUN_SLOT_BITS = 26;  // a tile of an XCD: problem << RUN_SLOT_BITS | number in the XCD's share of it
+
+__device__ __forceinline__ int wave_scan(int v) {  // inclusive sum over the lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast 15, 31
+  return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+}
+__device__ __forceinline__ int wave_max(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// The tiles a workgroup of conv_gemm_run_kernel takes, in order.  Lane w stands for workgroup w of the XCD and knows how much it has been
+// given; problem by problem the workgroups that have less catch up first, the rest is dealt in rounds, what is left over to those that are
+// behind.  A tile is worth its reduction and a fixed part.  (Dealt in rounds throughout, whoever has a long tile more gets as many short ones: a
+// step of the ResNet-50 shape 22.0 -> 24.7 ms.  Drawn from a counter per XCD, the draws waited in line with the slabs: four of
+// 6272 x 768 x 3072 with a residual 134 -> 167 us.)
+struct RunPlan {
+  int first, caught, base, rounds, extra;  // lane i, problem i: own tiles caught up with (first, how many), start of the rounds, rounds, one of the rest or -1
+  int whole, rest;                         // blocks of 64 tiles of the problem, and what is left: a block is eight runs of eight neighbours, one per XCD
+  int n, xcd, own, at, pos;                // place in the order
+
+  __device__ __forceinline__ void start(const GemmBatch& batch, int lane) {
+    n = batch.n;
+    xcd = (int)blockIdx.x & 7;
+    own = (int)blockIdx.x >> 3;
+    at = pos = 0;
+    first = caught = base = rounds = extra = whole = rest = 0;
+    int size = 0, cost = 1;
+    if (lane < n) {
+      const int tiles = (lane + 1 < n ? batch.starts.at[lane + 1] : batch.total_tiles) - batch.starts.at[lane];
+      whole = tiles >> 6;
+      rest = tiles & 63;
+      size = whole * 8 + (rest * (xcd + 1) >> 3) - (rest * xcd >> 3);
+      if (n > 1) cost = (min(batch.p[lane].K, 1 << 14) >> 6) + 4;
+    }
+    if (n == 1) {  // in rounds (100352 x 256 x 64 21.9 -> 20.9 us without the rest)
+      rounds = size >> 6;
+      extra = own < (size & 63) ? 64 * rounds + own : -1;
+      return;
+    }
+    int given = 0;
+    for (int i = 0; i < n; ++i) {
+      int m = __builtin_amdgcn_readlane(size, i);
+      const int c = __builtin_amdgcn_readlane(cost, i);
+      const int most = wave_max(given);
+      int take = (int)((float)(most - given) * __builtin_amdgcn_rcpf((float)c));
+      const int upto = wave_scan(take), from = upto - take;
+      take = max(0, min(take, m - from));
+      const int spent = min(m, __builtin_amdgcn_readlane(upto, 63));
+      given += take * c;
+      m -= spent;
+      const int q = m >> 6, r = m & 63;
+      const unsigned long long behind = __builtin_amdgcn_ballot_w64(2 * (most - given) >= c);
+      auto below = [&](unsigned long long set) { return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(set >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)set, 0u)); };
+      const int rank = (behind >> lane) & 1 ? below(behind) : __builtin_popcountll(behind) + below(~behind);
+      given += (q + (rank < r)) * c;
+      const int f = __builtin_amdgcn_readlane(from, own), t = __builtin_amdgcn_readlane(take, own), k = __builtin_amdgcn_readlane(rank, own);
+      if (lane == i) {
+        first = f;
+        caught = t;
+        base = spent;
+        rounds = q;
+        extra = k < r ? spent + 64 * q + k : -1;
+      }
+    }
+  }
+  __device__ __forceinline__ int next() {  // or -1
+    for (; at < n; ++at, pos = 0) {
+      const int t = __builtin_amdgcn_readlane(caught, at), q = __builtin_amdgcn_readlane(rounds, at), e = __builtin_amdgcn_readlane(extra, at);
+      int slot = -1;
+      if (pos < t) slot = __builtin_amdgcn_readlane(first, at) + pos;
+      else if (pos < t + q) slot = __builtin_amdgcn_readlane(base, at) + (pos - t) * RUN_PER_XCD + own;
+      else if (pos == t + q) slot = e;
+      if (slot < 0) continue;
+      ++pos;
+      return at << RUN_SLOT_BITS | slot;
+    }
+    return -1;
+  }
+  // Tile of the problem, in the order of its share.
+  __device__ __forceinline__ int tile(int pi, int slot) const {
+    const int w = __builtin_amdgcn_readlane(whole, pi);
+    return slot < 8 * w ? (slot >> 3) * 64 + xcd * 8 + (slot & 7) : w * 56 + slot + (__builtin_amdgcn_readlane(rest, pi) * xcd >> 3);
+  }
+};
+
+template <bool GELU>
+__device__ __forceinline__ void conv_gemm_run_body(const GemmBatch& batch) {
+  constexpr int BM = 128, BN = 128, WAVES_N = 2, BK = 64, MI = 2, NI = 2, WT = 64;
+  using Loads = SlabLoads<BM, BN, 4, BK>;
+  constexpr int ROW = Loads::ROW, STAGE_BYTES = (BM + BN) * ROW, KK = BK / 16, LP = Loads::N, STORES = MI * NI * 2;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE_BYTES];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const unsigned lds = (unsigned)(uintptr_t)(lds_ptr)smem;
+  RunPlan plan;
+  plan.start(batch, lane);
+  // Tiles of a problem in panels of about eight columns, row by row inside a panel: the 64 tiles of an XCD in one round then share
+  // few rows of either operand (8192^3 1209 -> 1041 us).
+  auto place = [&](const GemmProb& P, int j, int& row0, int& col0) {
+    const int local = plan.tile(j >> RUN_SLOT_BITS, j & ((1 << RUN_SLOT_BITS) - 1));
+    const int tiles_m = (P.M + BM - 1) / BM, panels = (P.tiles_n + 7) >> 3, w = (P.tiles_n + panels - 1) / panels;
+    const int panel = local / (tiles_m * w), in = local - panel * tiles_m * w, pw = min(w, P.tiles_n - panel * w), tm = in / pw;
+    row0 = tm * BM;
+    col0 = (panel * w + in - tm * pw) * BN;
+  };
+  Loads loads;
+  bool more = true;
+  int cur = plan.next(), ahead[3] = {-1, -1, -1}, known = 0;  // the tile contracted, those after it whose loads have begun
+  if (cur < 0) return;
+  auto start = [&](int j) {
+    const GemmProb& P = batch.p[j >> RUN_SLOT_BITS];
+    int row0, col0;
+    place(P, j, row0, col0);
+    loads.start(P, row0, col0, wave, lane);
+  };
+  auto advance = [&]() {
+    if (loads.left != 1 || !more) return loads.advance();
+    const int j = plan.next();
+    if (j < 0) {
+      more = false;
+      return loads.advance();
+    }
+    if (known == 0) ahead[0] = j;
+    else if (known == 1) ahead[1] = j;
+    else ahead[2] = j;
+    ++known;
+    start(j);
+  };
+  start(cur);
+#pragma unroll
+  for (int e = 0; e < LP; ++e) loads.issue(lds, wave, e);
+  advance();
+#pragma unroll
+  for (int e = 0; e < LP; ++e) loads.issue(lds + STAGE_BYTES, wave, e);
+  // Addresses of the two stages and of the fragments in them; exchanged behind a tile of an odd number of slabs, so that the loop has
+  // constant indices.
+  const int l31 = lane & 31, hi = lane >> 5, swa = Loads::swz(l31);
+  unsigned at[2], xa[2][KK], xb[2][KK];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    at[q] = lds + q * STAGE_BYTES;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const unsigned x = q * STAGE_BYTES + l31 * ROW + (((kk * 2 + hi) ^ swa) << 4);
+      xa[q][kk] = x + wm * WT * ROW;
+      xb[q][kk] = x + BM * ROW + wn * WT * ROW;
+    }
+  }
+  uint4 fa[2][MI], fb[2][NI];
+  auto frag = [&](int q, int kk, int buf, int e) {
+    if (e < MI) fa[buf][e] = *reinterpret_cast<const uint4*>(smem + xa[q][kk] + e * 32 * ROW);
+    else fb[buf][e - MI] = *reinterpret_cast<const uint4*>(smem + xb[q][kk] + (e - MI) * 32 * ROW);
+  };
+  wait_newest<LP>();
+  slab_barrier();
+  advance();
+#pragma unroll
+  for (int e = 0; e < MI + NI; ++e) frag(0, 0, 0, e);
+  v16f_t acc[MI][NI];
+  int stored = 0;  // stores of the tile before that are newer than the slab the next wait is for
+  auto step = [&](auto qc) {
+    constexpr int q = decltype(qc)::value;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const bool last = kk == KK - 1;
+      if (last) {
+        if (stored == 0) wait_newest<0>();
+        else if (stored == STORES) wait_newest<STORES>();
+        else wait_newest<2 * STORES>();
+        stored = 0;
+        slab_barrier();
+      }
+#pragma unroll
+      for (int e = 0; e < MI * NI; ++e) {
+        acc[e / NI][e % NI] = mfma_bf16(fb[kk & 1][e % NI], fa[kk & 1][e / NI], acc[e / NI][e % NI]);  // transposed: see the epilogue
+        frag(last ? 1 - q : q, last ? 0 : kk + 1, (kk + 1) & 1, e);
+        if (last) {
+#pragma unroll
+          for (int r = 0; r < LP / (MI * NI); ++r) loads.issue(at[q], wave, e * (LP / (MI * NI)) + r);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    advance();
+  };
+  static_assert(MI + NI == MI * NI && LP % (MI * NI) == 0, "one fragment and the same number of loads beside each product");
+  for (;;) {
+    const GemmProb& P = batch.p[cur >> RUN_SLOT_BITS];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    bool odd = false;
+    for (int t = P.K / BK;;) {
+      step(std::integral_constant<int, 0>{});
+      if (--t == 0) { odd = true; break; }
+      step(std::integral_constant<int, 1>{});
+      if (--t == 0) break;
+    }
+    if (odd) {
+      auto exchange = [](unsigned& x, unsigned& y) { const unsigned z = x; x = y; y = z; };
+      exchange(at[0], at[1]);
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        exchange(xa[0][kk], xa[1][kk]);
+        exchange(xb[0][kk], xb[1][kk]);
+      }
+    }
+    int row0, col0;
+    place(P, cur, row0, col0);
+    conv_epilogue<MI, NI, GELU>(P, acc, row0 + wm * WT, col0 + wn * WT, lane);
+    stored = GELU && (P.flags & GF_GELU) && P.epi == EPI_FWD ? 2 * STORES : STORES;
+    if (known == 0) break;
+    cur = ahead[0];
+    ahead[0] = ahead[1];
+    ahead[1] = ahead[2];
+    --known;
+  }
+  wait_newest<0>();  // no load is left that writes LDS when this workgroup gives it back
+}
+__global__ __launch_bounds__(256, 2) void conv_gemm_run_kernel(const GemmBatch batch) { conv_gemm_run_body<false>(batch); }
+__global__ __launch_bounds__(256, 2) void conv_gelu_run_kernel(const GemmBatch batch) { conv_gemm_run_body<true>(batch); }
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
 static void launch_dl(const GemmBatch& b, dim3 grid, hipStream_t stream) {
   if (conv_has_gelu(b)) hipLaunchKernelGGL((conv_gelu_dl_kernel<BM, BN, WAVES_M, WAVES_N, BK, STAGES, WPS>), grid, dim3(WAVES_M * WAVES_N * 64), 0, stream, b);
@@ -320,6 +570,56 @@ int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
   return std::min(by256, by192) >= 0.97 * other ? 0 : by192 < by256 ? DL_192x128 : DL_256x128;
 }
 
+// Launches of 512 tiles of 128 x 128 and more: conv_gemm_run_kernel, 256 x 256, or `named`, the tile conv_dl_tile names, by the time each takes:
+// full rounds (of 512 tiles for the first, of 256 for the others) times what a tile costs, fixed and per 1000 of the reduction, and the same for
+// the tiles themselves, whose last round has the memory to itself.  Coefficients (us) fitted to 176 products of 512 to 5720 tiles, N 72 to 3200,
+// K 64 to 3008, one to eight problems, rms 7 to 10 %.  What it takes is 7.6 % faster than conv_gemm_kernel and the tiles of conv_dl_tile on
+// average, 1.0 % slower than the best of the four (the slowest 1.15), conv_gemm_run_kernel alone 4.9 %.  us, conv_gemm_kernel / 256 x 256 / 256 x 128 / 192 x 128 / walked:
+//   6272 x 3072 x 768     45.8 / 45.7 / 46.3 / 49.4 / 40.0       18848 x 2768 x 192   41.1 / 43.4 / 48.6 / 49.0 / 37.7
+//   143204 x 168 x 192    30.3 / 32.3 / 36.5 / 35.5 / 26.1       7163 x 2384 x 2560   115 / 112 / 107 / 87 / 101
+//   36029 x 1672 x 2304   336 / 238 / 283 / 288 / 298            113066 x 496 x 1600  235 / 187 / 203 / 228 / 219
+// Below 640 walked, where 256 x 256 gains little and loses up to 15 %, but for one round of those (25088 x 512 x 128 16.7 / 12.6 / - / - / 16.6);
+// one slab of 64 is nothing to walk with (100352 x 256 x 64 21.0 / - / - / - / 21.7).  A GELU in the epilogue is hidden under the products of the other tiles where they are walked (four
+// of 6272 x 3072 x 768 201 us, on 256 x 256 220).  With residuals, masks or addends (their reads wait in line with the slabs requested ahead) walked or
+// named: four of 6272 x 768 x 3072 with a residual 149 / 173 / 146 / 148 / 135, of 6272 x 3072 x 768 with a mask 177 / 187 / 196 / 212 / 172; short
+// reductions, which are all epilogue, stay with conv_gemm_kernel, whose three workgroups per CU read whole rows: 100352 x 256 x 64 with a residual 31.3 / 54 / 40 / 41 / 33.4,
+// launches of a ResNet-50 tick with a mean reduction below 512 65 to 135 us, up to 17 % more when walked; above it 79 -> 71, 98 -> 89, 88 -> 79.
+static int conv_many_tile(const GemmProb* p, int n, int named) {
+  double t128 = 0, t256 = 0, wide = 0, t192 = 0, deep = 0, operands = 0;
+  bool gelu = false;
+  for (int i = 0; i < n; ++i) {
+    auto count = [&](int bm, int bn) { return (double)((p[i].M + bm - 1) / bm) * ((p[i].N + bn - 1) / bn); };
+    gelu = gelu || (p[i].flags & GF_GELU);
+    t128 += count(128, 128);
+    wide += count(256, 256);
+    t256 += count(256, 128);
+    t192 += count(192, 128);
+    deep += count(128, 128) * p[i].K;
+    if (p[i].aux1 || (p[i].epi == EPI_DGRAD && (p[i].aux0 || (p[i].flags & GF_ACCUM)))) operands += count(128, 128);
+  }
+  if (gelu) return DL_RUN;
+  const double k = 1e-3 * deep / t128;
+  auto us = [&](double tiles, int slots, double a, double b, double c, double d, double e) {
+    return a + std::ceil(tiles / slots) * (b + c * k) + tiles / slots * (d + e * k);
+  };
+  if (operands > 0) return k < 0.512 ? named : DL_RUN;
+  if (k < 0.64 && wide > 256) return k < 0.1 ? named : DL_RUN;
+  const double walked = us(t128, 512, 6.7, -1.3, 4.4, 3.8, 10.8), square = us(wide, 256, 3.7, 2.8, 10.3, 3.1, 13.7);
+  const double other = named == DL_256x128 ? us(t256, 256, 4.3, 2.4, 7.0, 1.5, 7.0) : named == DL_192x128 ? us(t192, 256, 3.7, 3.9, 2.3, -0.7, 8.5) : 1e30;
+  return other < std::min(walked, square) ? named : square < walked ? DL_256x256 : DL_RUN;
+}
+int conv_launch_tile(const GemmProb* p, int n, int dtype, bool shared) {
+  const int named = conv_dl_tile(p, n, dtype, shared);
+  int64_t t128 = 0;
+  bool wide = false;
+  for (int i = 0; i < n; ++i) {
+    if (!conv_dl_eligible(p[i], dtype, 64)) return named;
+    t128 += (int64_t)((p[i].M + 127) / 128) * ((p[i].N + 127) / 128);
+    wide = wide || p[i].N > 64;
+  }
+  return wide && t128 >= 512 && t128 < (1 << 28) ? conv_many_tile(p, n, named) : named;
+}
+
 hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream) {
   if (b.n <= 0) return hipSuccess;
   if (b.n > GEMM_MAX_PROBS || !conv_gelu_valid(b, dtype)) return hipErrorInvalidValue;
@@ -328,10 +628,12 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
     case DL_256x256: bm = 256; bn = 256; break;
     case DL_256x128: bm = 256; bn = 128; break;
     case DL_192x128: bm = 192; bn = 128; break;
-    case DL_128x128: bm = 128; bn = 128; break;
+    case DL_128x128: case DL_RUN: bm = 128; bn = 128; break;
     case DL_64x64: case DL_64x64_SHORT: bm = 64; bn = 64; break;
     default: return hipErrorInvalidValue;
   }
+  // tiles that take the same time are walked in the same rounds, the longest first
+  if (tile == DL_RUN) std::stable_sort(b.p, b.p + b.n, [](const GemmProb& x, const GemmProb& y) { return x.K > y.K; });
   int64_t total = 0;
   for (int i = 0; i < b.n; ++i) {
     GemmProb& p = b.p[i];
@@ -340,12 +642,16 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
     p.tiles_n = (p.N + bn - 1) / bn;
     p.tile_begin = (int)total;
     total += (int64_t)((p.M + bm - 1) / bm) * p.tiles_n;
-    if (total >= (1ll << 31)) return hipErrorInvalidValue;
+    if (total >= (tile == DL_RUN ? 1ll << 28 : 1ll << 31)) return hipErrorInvalidValue;
   }
   b.total_tiles = (int)total;
   tile_starts_set(b.starts, b.p, b.n);
   const dim3 grid((unsigned)total);
   switch (tile) {
+    case DL_RUN:
+      if (conv_has_gelu(b)) hipLaunchKernelGGL(conv_gelu_run_kernel, dim3(8 * RUN_PER_XCD), dim3(256), 0, stream, b);
+      else hipLaunchKernelGGL(conv_gemm_run_kernel, dim3(8 * RUN_PER_XCD), dim3(256), 0, stream, b);
+      break;
     case DL_256x256: launch_dl<256, 256, 2, 4, 64, 2, 2>(b, grid, stream); break;
     case DL_256x128: launch_dl<256, 128, 4, 2, 64, 3, 2>(b, grid, stream); break;
     case DL_192x128: launch_dl<192, 128, 2, 4, 64, 3, 2>(b, grid, stream); break;

@@ -998,7 +998,8 @@ static bool conv_few_tiles(const GemmBatch& b, int dtype) {
   return tiles <= 768;
 }
 
-// The tile is a wish: bf16 launches short of workgroups whose reductions are not shared run on the direct-to-LDS tiles (conv_dl_tile), fp32
+// The tile is a wish: bf16 launches whose channels are whole slabs run on the direct-to-LDS tiles (conv_launch_tile) unless they share reductions or have
+// many tiles of at most 64 columns, fp32
 // launches of few tiles without a workspace on conv_gemm_few_kernel.  What is left for 64 x 64 tiles here is shared reductions, ragged
 // channel counts and fp32; for 64 x 128, ragged, fp32, and operands that are not 16-byte aligned or need 64-bit offsets.
 hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t stream) {
@@ -1008,7 +1009,7 @@ hipError_t launch_conv_gemm(GemmBatch& b, int dtype, int bm, int bn, hipStream_t
   const int bk = dtype == DT_BF16 ? 32 : 16;
   int total = 0;
   if (!conv_gelu_valid(b, dtype) || (conv_has_gelu(b) && bm == 128 && bn == 64)) return hipErrorInvalidValue;
-  if (const int dl = conv_dl_tile(b.p, b.n, dtype, b.thin_ws && b.thin_cnt)) return launch_conv_dl(b, dtype, dl, stream);
+  if (const int dl = conv_launch_tile(b.p, b.n, dtype, b.thin_ws && b.thin_cnt)) return launch_conv_dl(b, dtype, dl, stream);
   if (conv_few_tiles(b, dtype)) {
     for (int i = 0; i < b.n; ++i) {
       GemmProb& p = b.p[i];

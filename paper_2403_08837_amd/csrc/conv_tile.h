@@ -138,21 +138,25 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
     }
   };
   if constexpr (NT > 0 && AHEAD == 2) request(0);
-  if (fwd && P.aux0) {
-    const float* const bias = static_cast<const float*>(P.aux0);
+  if (fwd && P.aux0) {  // all of it in one round: 32 j + 8 q + 4 hi are the columns of this lane as the products leave them
+    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+    v4f b[NI][4];
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)  // N is a multiple of VEC on these paths
+        b[j][q] = *reinterpret_cast<const v4f*>(static_cast<const float*>(P.aux0) + min(col0 + 32 * j + 8 * q + 4 * hi, P.N - 4));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        float b[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) b[e] = bias[min(col0 + 32 * j + 8 * q + 4 * hi, P.N - 4) + e];  // N is a multiple of VEC on these paths
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += b[e];
-        __builtin_amdgcn_sched_barrier(0);
+          for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += b[j][q][e];
       }
+    __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int i = 0; i < MI; ++i) {

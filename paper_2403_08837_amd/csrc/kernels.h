@@ -205,10 +205,11 @@ hipError_t launch_conv_gemm(GemmBatch& batch, int dtype, int bm, int bn, hipStre
 // Direct-to-LDS variant for bf16 problems whose reduction slabs lie inside one tap: 256 x 256 tiles for large launches with
 // long reductions (_wanted: enough mostly-full tiles to fill the chip), smaller ones with a deeper prefetch for
 // launches short of workgroups (conv_dl_tile, 0: neither).
-enum ConvDlTile : int { DL_NONE = 0, DL_256x256, DL_256x128, DL_128x128, DL_64x64, DL_64x64_SHORT, DL_192x128 };
+enum ConvDlTile : int { DL_NONE = 0, DL_256x256, DL_256x128, DL_128x128, DL_64x64, DL_64x64_SHORT, DL_192x128, DL_RUN };
 bool conv_gemm256_eligible(const GemmProb& p, int dtype);
 bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype);
 int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared);  // shared: there is a workspace to share reductions in
+int conv_launch_tile(const GemmProb* p, int n, int dtype, bool shared);  // that, and the tiles of launches of many (DL_RUN: walked by resident workgroups)
 hipError_t launch_conv_dl(GemmBatch& batch, int dtype, int tile, hipStream_t stream);
 // Weight gradient in two phases: launch_conv_wgrad writes per-range partial sums
 // (out = f32 [splits][Cout][Ncol], aux3 = f32 [splits][Cout] or NULL; splits: any number of ranges from 1 to

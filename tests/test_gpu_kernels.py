@@ -550,6 +550,20 @@ def test_conv_rounds_of_tiles(rows, out, slabs):
     _conv_1x1_bf16(0, rows, 64 * slabs, out)
 
 
+@pytest.mark.parametrize("rows,out,slabs", [(21800, 376, 1), (21800, 376, 2), (21800, 376, 3), (33000, 600, 5),   # walked: 513 tiles and 1290, odd numbers of
+                                            (65500, 136, 9), (8200, 1992, 4), (140100, 72, 1),                    # slabs and even, columns past a tile
+                                            (21800, 376, 17), (24000, 760, 34)])                                  # 256 x 256 or the tile of one round
+def test_conv_many_tiles(rows, out, slabs):
+    """Launches of 512 tiles of 128 x 128 and more."""
+    _conv_1x1_bf16(0, rows, 64 * slabs, out)
+
+
+@pytest.mark.parametrize("case", [(16, 57, 57, 64, 136, 3, 1, 1), (24, 57, 57, 136, 64, 3, 2, 1), (24, 115, 113, 64, 136, 3, 2, 1)])
+def test_conv_many_tiles_taps(case):
+    """The same with taps, a stride and padding, forward and data gradient (814, 1220 and 1200 tiles)."""
+    test_conv_passes_match_oracle(wl.BF16, case)
+
+
 # rows, width beside the GELU, reduction: every tile that a contraction before or after a GELU can run on, ragged in both directions
 GELU_CASES = [(700, 200, 64, "64 x 64, slabs of 32"), (700, 200, 1088, "64 x 64, slabs of 64"), (700, 200, 96, "64 x 64, odd multiple of 32"),
               (9700, 200, 128, "128 x 128 in one round"), (13000, 264, 192, "192 x 128"), (16500, 376, 128, "256 x 128"),
@@ -583,6 +597,11 @@ def test_gelu_in_the_epilogue_has_the_bits_of_its_own_kernels(rows, width, red, 
     exact = x.double() @ w.double().t()
     err = (y[:n].reshape(rows, width).double() - exact).norm() / exact.norm()
     assert err < 2.0 ** -8, float(err)  # one rounding to bf16: at most half a unit of 2^-7
+
+
+@pytest.mark.parametrize("rows,width,red", [(22000, 376, 192), (22000, 376, 704), (33000, 520, 128)])
+def test_gelu_in_the_epilogue_of_walked_tiles(rows, width, red):
+    test_gelu_in_the_epilogue_has_the_bits_of_its_own_kernels(rows, width, red, "walked")
 
 
 @pytest.mark.parametrize("case", [(4, 56, 56, 64, 320, 3, 1, 1),       # forward on 192 x 128 tiles, data gradient on 64 x 64
