@@ -238,7 +238,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, WPS) void conv_gelu_dl_kern
 //   Who takes what: the 64 workgroups of an XCD (blockIdx modulo 8) share an eighth of the tiles of every problem, so that rows are found in the
 // XCD's L2, the problems with the longest reductions first.  Every wavefront works the sharing out for itself (RunPlan).
 //   Waits: a step needs the slab after it.  Loads and stores count together and in order, and a tile stores the same number of times in
-// every wavefront (conv_epilogue), so the one wait in which the results are newer than the slab leaves them out.
+// every wavefront (conv_epilogue_as), so the one wait in which the results are newer than the slab leaves them out.
 // us, conv_gemm_kernel / here: see conv_many_tile.
 constexpr int RUN_PER_XCD = 64;
 constexpr int RUN_SLOT_BITS = 26;  // a tile of an XCD: problem << RUN_SLOT_BITS | number in the XCD's share of it
@@ -336,8 +336,7 @@ struct RunPlan {
   }
 };
 
-template <bool GELU>
-__device__ __forceinline__ void conv_gemm_run_body(const GemmBatch& batch) {
+__global__ __launch_bounds__(256, 2) void conv_gemm_run_kernel(const GemmBatch batch) {
   constexpr int BM = 128, BN = 128, WAVES_N = 2, BK = 64, MI = 2, NI = 2, WT = 64;
   using Loads = SlabLoads<BM, BN, 4, BK>;
   constexpr int ROW = Loads::ROW, STAGE_BYTES = (BM + BN) * ROW, KK = BK / 16, LP = Loads::N, STORES = MI * NI * 2;
@@ -410,17 +409,16 @@ __device__ __forceinline__ void conv_gemm_run_body(const GemmBatch& batch) {
 #pragma unroll
   for (int e = 0; e < MI + NI; ++e) frag(0, 0, 0, e);
   v16f_t acc[MI][NI];
-  int stored = 0;  // stores of the tile before that are newer than the slab the next wait is for
+  bool stored = false;  // the results of the tile before are newer than the slab the next wait is for
   auto step = [&](auto qc) {
     constexpr int q = decltype(qc)::value;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       const bool last = kk == KK - 1;
       if (last) {
-        if (stored == 0) wait_newest<0>();
-        else if (stored == STORES) wait_newest<STORES>();
-        else wait_newest<2 * STORES>();
-        stored = 0;
+        if (stored) wait_newest<STORES>();
+        else wait_newest<0>();
+        stored = false;
         slab_barrier();
       }
 #pragma unroll
@@ -463,8 +461,8 @@ __device__ __forceinline__ void conv_gemm_run_body(const GemmBatch& batch) {
     }
     int row0, col0;
     place(P, cur, row0, col0);
-    conv_epilogue<MI, NI, GELU>(P, acc, row0 + wm * WT, col0 + wn * WT, lane);
-    stored = GELU && (P.flags & GF_GELU) && P.epi == EPI_FWD ? 2 * STORES : STORES;
+    conv_epilogue_as<MI, NI, 0, false, false>(P, acc, row0 + wm * WT, col0 + wn * WT, lane);
+    stored = true;
     if (known == 0) break;
     cur = ahead[0];
     ahead[0] = ahead[1];
@@ -473,8 +471,6 @@ __device__ __forceinline__ void conv_gemm_run_body(const GemmBatch& batch) {
   }
   wait_newest<0>();  // no load is left that writes LDS when this workgroup gives it back
 }
-__global__ __launch_bounds__(256, 2) void conv_gemm_run_kernel(const GemmBatch batch) { conv_gemm_run_body<false>(batch); }
-__global__ __launch_bounds__(256, 2) void conv_gelu_run_kernel(const GemmBatch batch) { conv_gemm_run_body<true>(batch); }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, int WPS>
 static void launch_dl(const GemmBatch& b, dim3 grid, hipStream_t stream) {
@@ -579,30 +575,28 @@ int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
 //   143204 x 168 x 192    30.3 / 32.3 / 36.5 / 35.5 / 26.1       7163 x 2384 x 2560   115 / 112 / 107 / 87 / 101
 //   36029 x 1672 x 2304   336 / 238 / 283 / 288 / 298            113066 x 496 x 1600  235 / 187 / 203 / 228 / 219
 // Below 640 walked, where 256 x 256 gains little and loses up to 15 %, but for one round of those (25088 x 512 x 128 16.7 / 12.6 / - / - / 16.6);
-// one slab of 64 is nothing to walk with (100352 x 256 x 64 21.0 / - / - / - / 21.7).  A GELU in the epilogue is hidden under the products of the other tiles where they are walked (four
-// of 6272 x 3072 x 768 201 us, on 256 x 256 220).  With residuals, masks or addends (their reads wait in line with the slabs requested ahead) walked or
-// named: four of 6272 x 768 x 3072 with a residual 149 / 173 / 146 / 148 / 135, of 6272 x 3072 x 768 with a mask 177 / 187 / 196 / 212 / 172; short
-// reductions, which are all epilogue, stay with conv_gemm_kernel, whose three workgroups per CU read whole rows: 100352 x 256 x 64 with a residual 31.3 / 54 / 40 / 41 / 33.4,
-// launches of a ResNet-50 tick with a mean reduction below 512 65 to 135 us, up to 17 % more when walked; above it 79 -> 71, 98 -> 89, 88 -> 79.
+// one slab of 64 is nothing to walk with (100352 x 256 x 64 17.1 / - / - / - / 21.7).
+// Residuals, masks, addends and GELUs leave a launch where it was: their reads wait in line with the slabs requested ahead, and conv_gemm_kernel's
+// three workgroups per CU read whole rows.  Steps of ResNet-50 and ViT-B/16 shapes, ms per four, with all such launches walked / those of a mean
+// reduction of 512 and more / none / no launch walked at all: - / 78.2 / 77.4 / 77.5 and 206.2 / 206.2 / 204.9 / 208.6.
+static bool conv_reads_beside(const GemmProb& p) {  // its epilogue reads a tensor, or is a GELU
+  return p.aux1 || (p.flags & GF_GELU) || (p.epi == EPI_DGRAD && (p.aux0 || (p.flags & GF_ACCUM)));
+}
 static int conv_many_tile(const GemmProb* p, int n, int named) {
-  double t128 = 0, t256 = 0, wide = 0, t192 = 0, deep = 0, operands = 0;
-  bool gelu = false;
+  double t128 = 0, t256 = 0, wide = 0, t192 = 0, deep = 0;
   for (int i = 0; i < n; ++i) {
     auto count = [&](int bm, int bn) { return (double)((p[i].M + bm - 1) / bm) * ((p[i].N + bn - 1) / bn); };
-    gelu = gelu || (p[i].flags & GF_GELU);
+    if (conv_reads_beside(p[i])) return named;
     t128 += count(128, 128);
     wide += count(256, 256);
     t256 += count(256, 128);
     t192 += count(192, 128);
     deep += count(128, 128) * p[i].K;
-    if (p[i].aux1 || (p[i].epi == EPI_DGRAD && (p[i].aux0 || (p[i].flags & GF_ACCUM)))) operands += count(128, 128);
   }
-  if (gelu) return DL_RUN;
   const double k = 1e-3 * deep / t128;
   auto us = [&](double tiles, int slots, double a, double b, double c, double d, double e) {
     return a + std::ceil(tiles / slots) * (b + c * k) + tiles / slots * (d + e * k);
   };
-  if (operands > 0) return k < 0.512 ? named : DL_RUN;
   if (k < 0.64 && wide > 256) return k < 0.1 ? named : DL_RUN;
   const double walked = us(t128, 512, 6.7, -1.3, 4.4, 3.8, 10.8), square = us(wide, 256, 3.7, 2.8, 10.3, 3.1, 13.7);
   const double other = named == DL_256x128 ? us(t256, 256, 4.3, 2.4, 7.0, 1.5, 7.0) : named == DL_192x128 ? us(t192, 256, 3.7, 3.9, 2.3, -0.7, 8.5) : 1e30;
@@ -638,6 +632,7 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
   for (int i = 0; i < b.n; ++i) {
     GemmProb& p = b.p[i];
     if (p.M <= 0 || p.N <= 0 || p.K <= 0 || !conv_dl_eligible(p, dtype, tile == DL_64x64_SHORT ? 32 : 64)) return hipErrorInvalidValue;
+    if (tile == DL_RUN && conv_reads_beside(p)) return hipErrorInvalidValue;
     p.splits = 1;
     p.tiles_n = (p.N + bn - 1) / bn;
     p.tile_begin = (int)total;
@@ -649,8 +644,7 @@ hipError_t launch_conv_dl(GemmBatch& b, int dtype, int tile, hipStream_t stream)
   const dim3 grid((unsigned)total);
   switch (tile) {
     case DL_RUN:
-      if (conv_has_gelu(b)) hipLaunchKernelGGL(conv_gelu_run_kernel, dim3(8 * RUN_PER_XCD), dim3(256), 0, stream, b);
-      else hipLaunchKernelGGL(conv_gemm_run_kernel, dim3(8 * RUN_PER_XCD), dim3(256), 0, stream, b);
+      hipLaunchKernelGGL(conv_gemm_run_kernel, dim3(8 * RUN_PER_XCD), dim3(256), 0, stream, b);
       break;
     case DL_256x256: launch_dl<256, 256, 2, 4, 64, 2, 2>(b, grid, stream); break;
     case DL_256x128: launch_dl<256, 128, 4, 2, 64, 3, 2>(b, grid, stream); break;

@@ -926,14 +926,27 @@ __global__ __launch_bounds__(256, 2) void conv_gemm_few_kernel(const GemmBatch b
   const int c = col0 + 8 * wave + 4 * hi;  // each wavefront finishes four columns per lane half
   if (r >= P.M || c >= P.N) return;
   const int64_t o = (int64_t)r * P.ldo + c;
-  float val[4], bias[4] = {0.f, 0.f, 0.f, 0.f};
+  const bool fwd = P.epi == EPI_FWD, biased = fwd && P.aux0, added = !fwd && P.aux0, accum = !fwd && (P.flags & GF_ACCUM);
+  float* const out = static_cast<float*>(P.out) + o;
+  typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+  const v4f none = {0.f, 0.f, 0.f, 0.f};  // all that is read, in one round
+  const v4f bias = biased ? *reinterpret_cast<const v4f*>(static_cast<const float*>(P.aux0) + c) : none;
+  const v4f x1 = P.aux1 ? *reinterpret_cast<const v4f*>(static_cast<const float*>(P.aux1) + o) : none;
+  const v4f x0 = added ? *reinterpret_cast<const v4f*>(static_cast<const float*>(P.aux0) + o) : none;
+  const v4f old = accum ? *reinterpret_cast<const v4f*>(out) : none;
+  v4f val;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float* x = red + (4 * wave + e) * 64 + lane;
     val[e] = (x[0] + x[1024]) + (x[2048] + x[3072]);
-    if (P.epi == EPI_FWD && P.aux0) bias[e] = static_cast<const float*>(P.aux0)[c + e];
+    if (biased) val[e] += bias[e];
+    if (fwd && P.aux1) val[e] += x1[e];
+    if (fwd && (P.flags & GF_RELU)) val[e] = fmaxf(val[e], 0.f);
+    if (added) val[e] += x0[e];
+    if (accum) val[e] += old[e];
+    if (!fwd && P.aux1 && !(x1[e] > 0.f)) val[e] = 0.f;
   }
-  conv_finish<float>(P, o, val, bias, P.aux1 ? *reinterpret_cast<const uint4*>(static_cast<const float*>(P.aux1) + o) : make_uint4(0, 0, 0, 0));
+  *reinterpret_cast<v4f*>(out) = val;
 }
 
 template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>

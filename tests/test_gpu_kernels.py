@@ -599,11 +599,6 @@ def test_gelu_in_the_epilogue_has_the_bits_of_its_own_kernels(rows, width, red, 
     assert err < 2.0 ** -8, float(err)  # one rounding to bf16: at most half a unit of 2^-7
 
 
-@pytest.mark.parametrize("rows,width,red", [(22000, 376, 192), (22000, 376, 704), (33000, 520, 128)])
-def test_gelu_in_the_epilogue_of_walked_tiles(rows, width, red):
-    test_gelu_in_the_epilogue_has_the_bits_of_its_own_kernels(rows, width, red, "walked")
-
-
 @pytest.mark.parametrize("case", [(4, 56, 56, 64, 320, 3, 1, 1),       # forward on 192 x 128 tiles, data gradient on 64 x 64
                                   (8, 41, 41, 64, 136, 3, 1, 1),       # forward on 128 x 128
                                   (8, 41, 41, 200, 192, 3, 1, 1),      # data gradient on 128 x 128
