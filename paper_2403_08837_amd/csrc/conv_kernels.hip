@@ -939,12 +939,22 @@ __global__ __launch_bounds__(256, 2) void conv_gemm_few_kernel(const GemmBatch b
   for (int e = 0; e < 4; ++e) {
     const float* x = red + (4 * wave + e) * 64 + lane;
     val[e] = (x[0] + x[1024]) + (x[2048] + x[3072]);
-    if (biased) val[e] += bias[e];
-    if (fwd && P.aux1) val[e] += x1[e];
-    if (fwd && (P.flags & GF_RELU)) val[e] = fmaxf(val[e], 0.f);
-    if (added) val[e] += x0[e];
-    if (accum) val[e] += old[e];
-    if (!fwd && P.aux1 && !(x1[e] > 0.f)) val[e] = 0.f;
+  }
+  if (fwd) {
+    if (biased) val += bias;
+    if (P.aux1) val += x1;
+    if (P.flags & GF_RELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) val[e] = fmaxf(val[e], 0.f);
+    }
+  } else {
+    if (added) val += x0;
+    if (accum) val += old;
+    if (P.aux1) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (!(x1[e] > 0.f)) val[e] = 0.f;
+    }
   }
   *reinterpret_cast<v4f*>(out) = val;
 }
