@@ -15,7 +15,7 @@
 // The limit in tokens is LDS (64-wide heads: 624); past 256 tokens the forward contracts the scores twice instead of
 // keeping them (8 x 400 tokens, 8 heads of 64: 43 -> 22 us forward, 84 -> 49 us backward against separate kernels).
 // Measured there (us, forward / backward): score rows and products as kernels of their own 50 / 101; these three
-// 20 / 52 (dq 27, dkv 29 under the profiler).  What is left above the bytes (13 / 28 at the rate of a large copy, were every tensor
+// 20 / 48.  What is left above the bytes (13 / 28 at the rate of a large copy, were every tensor
 // read once per kernel) is that the resident workgroups move in step: they stage, contract and store together; 192
 // workgroups, less than one per CU, take 10 us already.  Requested is more: every workgroup of 128 tokens stages k and v (or q and
 // d out) of its head again, twice at 196 tokens, and dq walks the probabilities twice, for the row sums and for the products; the
@@ -299,10 +299,18 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const AttnArgs a) {
   for (int ks = 0; ks < KS; ++ks) df[ks] = *reinterpret_cast<const uint4*>(drow + 16 * ks + 8 * hi);
   stage_two<KS>(Vs, Ks, base + 2 * a.D, base + a.D, tok, tok, NT, rows);
   __syncthreads();
-  const uint16_t* prow = q < NT ? a.P + ((int64_t)z * NT + q) * NT : nullptr;
-  auto load_block = [&](int b, uint2 (&w)[2][2]) {  // as they lie in memory: swap_halves where they are used
+  // Probabilities as they lie in memory (swap_halves where they are used).  Blocks of 32 whole keys are read without a branch, one block ahead:
+  // a read inside one is waited for inside it, and every block then cost a round trip in either pass.  Queries past the last repeat it
+  // (their lanes are not stored); the block that the keys end in is read once, ahead of everything.
+  const int whole = NT >> 5;
+  const uint16_t* prow = a.P + ((int64_t)z * NT + min(q, NT - 1)) * NT;
+  auto load_block = [&](int b, uint2 (&w)[2][2]) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) load_p16(prow, 32 * b + 16 * t, hi, NT, a.vec, w[t]);
+    for (int t = 0; t < 2; ++t) {
+      const P8 p = *reinterpret_cast<const P8*>(prow + 32 * b + 16 * t + 8 * hi);
+      w[t][0] = make_uint2(p.u[0], p.u[1]);
+      w[t][1] = make_uint2(p.u[2], p.u[3]);
+    }
   };
   auto dp_block = [&](int b) {
     v16f_t s = zero16();
@@ -311,10 +319,7 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const AttnArgs a) {
     return s;
   };
   float delta = 0.f;
-  uint2 w[2][2], nw[2][2];
-  load_block(0, w);
-  for (int b = 0; b < nblk; ++b) {
-    load_block(b + 1 < nblk ? b + 1 : 0, nw);  // the next block's probabilities (at the end: the first's, for the second pass)
+  auto sum_block = [&](int b, uint2 (&w)[2][2]) {
     const v16f_t s = dp_block(b);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -324,17 +329,13 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const AttnArgs a) {
         const int v = 8 * t + 4 * g;
         delta += lo16(w[t][g].x) * s[v] + hi16(w[t][g].x) * s[v + 1];
         delta += lo16(w[t][g].y) * s[v + 2] + hi16(w[t][g].y) * s[v + 3];
-        w[t][g] = nw[t][g];
       }
     }
-  }
-  delta += __shfl_xor(delta, 32, 64);
-  if (q < NT && hi == 0) a.delta[(int64_t)z * NT + q] = delta;
+  };
   v16f_t o[OB];
 #pragma unroll
   for (int ob = 0; ob < OB; ++ob) o[ob] = zero16();
-  for (int b = 0; b < nblk; ++b) {
-    if (b + 1 < nblk) load_block(b + 1, nw);
+  auto mul_block = [&](int b, uint2 (&w)[2][2]) {
     const v16f_t s = dp_block(b);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -345,14 +346,41 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const AttnArgs a) {
         const int v = 8 * t + 4 * g;
         d[g].x = pack2(lo16(w[t][g].x) * (s[v] - delta) * a.scale, hi16(w[t][g].x) * (s[v + 1] - delta) * a.scale);
         d[g].y = pack2(lo16(w[t][g].y) * (s[v + 2] - delta) * a.scale, hi16(w[t][g].y) * (s[v + 3] - delta) * a.scale);
-        w[t][g] = nw[t][g];
       }
       if (32 * b + 16 * t < rows)
 #pragma unroll
         for (int ob = 0; ob < OB; ++ob)
           o[ob] = mfma_bf16(frag_cols<KS>(Ks, 32 * b + 16 * t, 32 * ob, lane), make_uint4(d[0].x, d[0].y, d[1].x, d[1].y), o[ob]);
     }
+  };
+  uint2 w[2][2], nw[2][2], last[2][2];
+  if (nblk > whole) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) load_p16(prow, 32 * whole + 16 * t, hi, NT, a.vec, last[t]);
   }
+  if (whole > 0) load_block(0, w);
+  auto walk = [&](auto block) {
+    for (int b = 0; b < whole; ++b) {
+      load_block(b + 1 < whole ? b + 1 : 0, nw);  // (at the end: the first for the second pass)
+      block(b, w);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) w[t][g] = nw[t][g];
+    }
+    if (nblk > whole) {
+      uint2 e[2][2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) e[t][g] = last[t][g];
+      block(whole, e);
+    }
+  };
+  walk(sum_block);
+  delta += __shfl_xor(delta, 32, 64);
+  if (q < NT && hi == 0) a.delta[(int64_t)z * NT + q] = delta;
+  walk(mul_block);
   if (q < NT) {
     uint16_t* dst = a.out + ((int64_t)sample * NT + q) * tok + head * DH;
 #pragma unroll
@@ -416,12 +444,20 @@ __global__ __launch_bounds__(256, KS <= 4 ? 3 : 2) void attn_bwd_dkv_kernel(cons
 #pragma unroll
   for (int ob = 0; ob < OB; ++ob) { dv[ob] = zero16(); dk[ob] = zero16(); }
   uint16_t p[16], np[16];
+  // delta a block ahead where there are registers for it: for heads of width 48 and 80 the compiler else waits for the next
+  // probabilities with it (333 tokens, 72 heads of 80, both kernels 58.0 -> 45.3 us).  At 64 the two registers too many cost more than the
+  // round trip to cached lines (400 tokens, 64 heads 38.2 -> 40.8 us).
+  constexpr bool DELTA_AHEAD = KS == 3 || KS == 5;
+  float dl[16], ndl[16];
   load_p(0, p);
+  if (DELTA_AHEAD) load_delta(0, dl);
   __syncthreads();
   for (int b = 0; b < nblk; ++b) {
-    float dl[16];
-    load_delta(b, dl);  // a few lines that the whole workgroup reads: cache hits
-    if (b + 1 < nblk) load_p(b + 1, np);
+    if (!DELTA_AHEAD) load_delta(b, dl);
+    if (b + 1 < nblk) {
+      load_p(b + 1, np);
+      if (DELTA_AHEAD) load_delta(b + 1, ndl);
+    }
     v16f_t s = zero16();
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) s = mfma_bf16(frag_rows<KS>(Os, 32 * b, ks, lane, rows), vf[ks], s);
@@ -443,7 +479,10 @@ __global__ __launch_bounds__(256, KS <= 4 ? 3 : 2) void attn_bwd_dkv_kernel(cons
       }
     }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) p[v] = np[v];
+    for (int v = 0; v < 16; ++v) {
+      p[v] = np[v];
+      if (DELTA_AHEAD) dl[v] = ndl[v];
+    }
   }
   if (k < NT) {
     uint16_t* dst = a.out + ((int64_t)sample * NT + k) * tok + head * DH;
