@@ -7,6 +7,7 @@ CPU fallback: loading fails loudly when libcdp.so has not been built.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import List, Optional, Sequence
 
@@ -103,6 +104,25 @@ def lib() -> C.CDLL:
                 getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
+
+
+def _entry(name: str):
+    """Kernel-level entry point `name` of _calls.so (csrc/pycalls.cpp): a call whose arguments are plain integers costs 0.3 us there and
+    one to two through ctypes.  None: an argument is something else, or there is no _calls.so; the caller goes through ctypes then.
+    Loaded with the first call."""
+    def first(*args):
+        lib()
+        path, fast = os.path.join(_HERE, "_calls.so"), None
+        if os.path.exists(path):
+            spec = importlib.util.spec_from_file_location(__package__ + "._calls", path)
+            fast = getattr(importlib.util.module_from_spec(spec), name)
+        globals()["_" + name] = fast or (lambda *a: None)
+        return globals()["_" + name](*args)
+    return first
+
+
+_cdp_k_gemm, _cdp_k_conv, _cdp_k_conv_wgrad_static, _cdp_k_layernorm, _cdp_k_gelu, _cdp_k_attention = (
+    _entry(n) for n in ("cdp_k_gemm", "cdp_k_conv", "cdp_k_conv_wgrad_static", "cdp_k_layernorm", "cdp_k_gelu", "cdp_k_attention"))
 
 
 def _check(rc: int, ctx=None) -> None:
@@ -245,42 +265,60 @@ def cdp_destroy(ctx) -> None:
 
 
 def cdp_k_gemm(dtype, tile_shape, a_kmajor, b_kmajor, A_ptr, B_ptr, C_ptr, M, N, K, lda, ldb, stream=0) -> None:
-    rc = lib().cdp_k_gemm(dtype, tile_shape, a_kmajor, b_kmajor, A_ptr, B_ptr, C_ptr, M, N, K, lda, ldb, stream or None)
+    args = (dtype, tile_shape, a_kmajor, b_kmajor, A_ptr, B_ptr, C_ptr, M, N, K, lda, ldb, stream or None)
+    rc = _cdp_k_gemm(*args)
+    if rc is None:
+        rc = lib().cdp_k_gemm(*args)
     if rc != CDP_OK:
         raise CdpError(rc, "cdp_k_gemm")
 
 
 def cdp_k_conv(dtype, which, in0_ptr, in1_ptr, out_ptr, B, H, W, Cin, Cout, ks, stride, pad, ws_ptr=0, ws_bytes=0,
                stream=0) -> None:
-    rc = lib().cdp_k_conv(dtype, which, in0_ptr, in1_ptr, out_ptr, B, H, W, Cin, Cout, ks, stride, pad, ws_ptr or None,
-                          ws_bytes, stream or None)
+    args = (dtype, which, in0_ptr, in1_ptr, out_ptr, B, H, W, Cin, Cout, ks, stride, pad, ws_ptr or None,
+            ws_bytes, stream or None)
+    rc = _cdp_k_conv(*args)
+    if rc is None:
+        rc = lib().cdp_k_conv(*args)
     if rc != CDP_OK:
         raise CdpError(rc, "cdp_k_conv")
 
 
 def cdp_k_conv_wgrad_static(dtype, dy_ptr, x_ptr, dw_ptr, B, H, W, Cin, Cout, ks, stride, pad, stream=0) -> None:
-    rc = lib().cdp_k_conv_wgrad_static(dtype, dy_ptr, x_ptr, dw_ptr, B, H, W, Cin, Cout, ks, stride, pad, stream or None)
+    args = (dtype, dy_ptr, x_ptr, dw_ptr, B, H, W, Cin, Cout, ks, stride, pad, stream or None)
+    rc = _cdp_k_conv_wgrad_static(*args)
+    if rc is None:
+        rc = lib().cdp_k_conv_wgrad_static(*args)
     if rc != CDP_OK:
         raise CdpError(rc, "cdp_k_conv_wgrad_static: " + lib().cdp_last_error(None).decode())
 
 
 def cdp_k_layernorm(dtype, backward, x_ptr, dy_ptr, add_ptr, gamma_ptr, beta_ptr, out_ptr, dgamma_ptr, dbeta_ptr, ws_ptr,
                     ws_bytes, rows, C_, stream=0) -> None:
-    rc = lib().cdp_k_layernorm(dtype, backward, x_ptr, dy_ptr or None, add_ptr or None, gamma_ptr, beta_ptr or None, out_ptr,
-                               dgamma_ptr or None, dbeta_ptr or None, ws_ptr or None, ws_bytes, rows, C_, stream or None)
+    args = (dtype, backward, x_ptr, dy_ptr or None, add_ptr or None, gamma_ptr, beta_ptr or None, out_ptr,
+            dgamma_ptr or None, dbeta_ptr or None, ws_ptr or None, ws_bytes, rows, C_, stream or None)
+    rc = _cdp_k_layernorm(*args)
+    if rc is None:
+        rc = lib().cdp_k_layernorm(*args)
     if rc != CDP_OK:
         raise CdpError(rc, "cdp_k_layernorm")
 
 
 def cdp_k_gelu(dtype, backward, x_ptr, dy_ptr, out_ptr, n, stream=0) -> None:
-    rc = lib().cdp_k_gelu(dtype, backward, x_ptr, dy_ptr or None, out_ptr, n, stream or None)
+    args = (dtype, backward, x_ptr, dy_ptr or None, out_ptr, n, stream or None)
+    rc = _cdp_k_gelu(*args)
+    if rc is None:
+        rc = lib().cdp_k_gelu(*args)
     if rc != CDP_OK:
         raise CdpError(rc, "cdp_k_gelu")
 
 
 def cdp_k_attention(dtype, backward, qkv_ptr, P_ptr, dout_ptr, out_ptr, ws_ptr, ws_bytes, B, T, D, heads, stream=0) -> None:
-    rc = lib().cdp_k_attention(dtype, backward, qkv_ptr, P_ptr, dout_ptr or None, out_ptr, ws_ptr, ws_bytes, B, T, D, heads,
-                               stream or None)
+    args = (dtype, backward, qkv_ptr, P_ptr, dout_ptr or None, out_ptr, ws_ptr, ws_bytes, B, T, D, heads,
+            stream or None)
+    rc = _cdp_k_attention(*args)
+    if rc is None:
+        rc = lib().cdp_k_attention(*args)
     if rc != CDP_OK:
         raise CdpError(rc, "cdp_k_attention")
 

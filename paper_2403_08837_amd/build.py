@@ -1,13 +1,15 @@
-"""Builds libcdp.so (HIP kernels + host engine + C ABI) in-tree for gfx950."""
+"""Builds libcdp.so (HIP kernels + host engine + C ABI) in-tree for gfx950, and _calls.so, its kernel-level entry points as Python calls."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcdp.so")
+CALLS = os.path.join(HERE, "_calls.so")
 SOURCES = ["gemm.hip", "linear_kernels.hip", "gemm_stream.hip", "conv_kernels.hip", "conv256_kernels.hip", "conv_wgrad_small.hip", "small_kernels.hip", "transformer_kernels.hip", "attention_kernels.hip", "static_scratch.hip", "engine.cpp", "host_copy.cpp", "plan.cpp", "kernels_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 VALU forms are switched off for all device code: the compiler then emits scalar fp32 ops only
@@ -42,6 +44,11 @@ def build(verbose: bool = False) -> str:
     if failed:
         raise RuntimeError("libcdp build failed")
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "pycalls.cpp"), "-o", CALLS, LIB, "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
