@@ -9,7 +9,7 @@
 // back out of a staging block of the wavefront's own in LDS (no barrier); loaded in fragment layout, 16 rows x 64 bytes,
 // the address path of the CU bounds the kernel at 14 bytes per cycle (64 rows, 4096 x 4096: 20.3 us).  The partial tiles
 // meet in LDS and are added in wavefront order.
-// 64 rows, 4096 x 4096, bf16: 26.9 us on the tick launch's tiles, 12.4 us so; 32 rows 15.6 -> 8.3; fp32 97 -> 32 us.
+// 64 rows, 4096 x 4096, bf16: 26.9 us on the tick launch's tiles, 11.9 us so; 32 rows 15.6 -> 7.6; fp32 97 -> 28 us.
 #include "elem.h"
 #include "kernels.h"
 
@@ -50,25 +50,32 @@ __global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const Str
   constexpr int STAGE = 8 * NL * PITCH * (int)sizeof(T), PART = MT * 16 * 17 * 4;
   static_assert(PART <= STAGE, "the partial tile takes the place of the staged piece");
   __shared__ __attribute__((aligned(16))) unsigned char smem[GS_WAVES * STAGE];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, q = lane >> 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l15 = lane & 15, q = lane >> 4;
   const int col0 = blockIdx.x * 16, row0 = blockIdx.y * (16 * MT);
   T* const st = reinterpret_cast<T*>(smem + wave * STAGE);
   const int lr = lane >> 3, lk = (lane & 7) * VEC;
-  // rows and columns past the end repeat the last one: they only reach outputs that are not stored
-  const T* src[NL];
+  // Buffer loads, all of them unconditional: the wait for a piece counts the loads behind it, and with requests under a condition
+  // the compiler waits as if the last had not been made, one piece ahead instead of two.  Pieces past the last read nothing (a
+  // buffer of no bytes), nor do chunks past the end of a row; rows and columns past the end repeat the last one: they only
+  // reach outputs that are not stored.  A wave with a single piece asks for no other.  us, under conditions / so:
+  //   bf16 64 x 4096 x 4096 12.1 / 11.9, 64 x 512 x 512 3.7 / 3.1, 33 x 8192 x 512 5.6 / 5.0, 100 x 1000 x 3000 8.8 / 8.1
+  //   fp32 64 x 4096 x 4096 30.5 / 27.9, 30 x 500 x 2004 9.3 / 8.2, 8 x 64 x 64 3.5 / 2.9
+  constexpr int ES = (int)sizeof(T);
+  const char* const pa = static_cast<const char*>(g.A) + (int64_t)row0 * g.lda * ES;
+  const char* const pb = static_cast<const char*>(g.B) + (int64_t)col0 * g.ldb * ES;
+  unsigned off[NL];
 #pragma unroll
   for (int j = 0; j < NL; ++j)
-    src[j] = j < 2 * MT ? static_cast<const T*>(g.A) + (int64_t)min(row0 + 8 * j + lr, g.M - 1) * g.lda + lk
-                        : static_cast<const T*>(g.B) + (int64_t)min(col0 + 8 * (j - 2 * MT) + lr, g.N - 1) * g.ldb + lk;
-  const int step = GS_WAVES * PIECE;
-  auto load = [&](uint4 (&r)[NL], int k) {
-    if (k + PIECE <= g.K) {
+    off[j] = (unsigned)((j < 2 * MT ? min(8 * j + lr, g.M - 1 - row0) * g.lda : min(8 * (j - 2 * MT) + lr, g.N - 1 - col0) * g.ldb) + lk) * ES;
+  const int step = GS_WAVES * PIECE, first = wave * PIECE;
+  const int pieces = first < g.K ? (g.K - first + step - 1) / step : 0;
+  auto load = [&](uint4 (&r)[NL], int i) {
+    const int k = first + i * step;
+    const unsigned records = i < pieces ? 0xfffffff0u : 0u;
+    const auto ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pa), (short)0, records, 0x00020000);
+    const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pb), (short)0, records, 0x00020000);
 #pragma unroll
-      for (int j = 0; j < NL; ++j) r[j] = *reinterpret_cast<const uint4*>(src[j] + k);
-    } else {  // past the last whole piece (K is whole chunks)
-#pragma unroll
-      for (int j = 0; j < NL; ++j) r[j] = k + lk < g.K ? *reinterpret_cast<const uint4*>(src[j] + k) : make_uint4(0, 0, 0, 0);
-    }
+    for (int j = 0; j < NL; ++j) r[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(j < 2 * MT ? ra : rb, k + lk < g.K ? off[j] + (unsigned)k * ES : 0xfffffff0u, 0, 0));
   };
   v4f_t acc[MT];
 #pragma unroll
@@ -91,18 +98,23 @@ __global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const Str
     __builtin_amdgcn_wave_barrier();
   };
   uint4 r0[NL], r1[NL], r2[NL];
-  int k = wave * PIECE;
-  if (k < g.K) load(r0, k);
-  if (k + step < g.K) load(r1, k + step);
-  for (; k < g.K; k += 3 * step) {  // two pieces ahead
-    if (k + 2 * step < g.K) load(r2, k + 2 * step);
+  if (pieces == 1) {
+    load(r0, 0);
     product(r0);
-    if (k + step >= g.K) break;
-    if (k + 3 * step < g.K) load(r0, k + 3 * step);
-    product(r1);
-    if (k + 2 * step >= g.K) break;
-    if (k + 4 * step < g.K) load(r1, k + 4 * step);
-    product(r2);
+  } else if (pieces > 1) {
+    load(r0, 0);
+    load(r1, 1);
+    for (int i = 0;;) {  // two pieces ahead
+      load(r2, i + 2);
+      product(r0);
+      if (++i == pieces) break;
+      load(r0, i + 2);
+      product(r1);
+      if (++i == pieces) break;
+      load(r1, i + 2);
+      product(r2);
+      if (++i == pieces) break;
+    }
   }
   float (*part)[17] = reinterpret_cast<float (*)[17]>(smem + wave * STAGE);
   // acc[i][v]: row 16 i + 4 q + v, column l15
@@ -136,6 +148,7 @@ void launch_stream(const StreamArgs& g, hipStream_t stream) {
 bool gemm_stream_wanted(const void* A, const void* B, int M, int N, int K, int lda, int ldb, int dtype) {
   const int vec = dtype == DT_BF16 ? 8 : 4;
   if (K % vec || lda % vec || ldb % vec || ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15)) return false;
+  if (lda > (1 << 22) || ldb > (1 << 22)) return false;  // 32-bit byte offsets inside 64 rows
   return M <= 128 && (int64_t)((N + 15) / 16) * (M <= 64 ? 1 : 2) <= 512;
 }
 
