@@ -225,6 +225,31 @@ def test_conv_weight_gradient_added_to_an_accumulator(dtype, case):
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("case", [(4, 40, 40, 8, 20, 3, 1, 1), (4, 40, 40, 16, 24, 3, 1, 1)])
+def test_conv_weight_gradient_fold_of_many_ranges(dtype, case):
+    """Folds at every number of 32-lane groups to a weight row, rows that end inside a chunk of 128 columns; nothing around the
+    accumulator is touched."""
+    torch = _torch()
+    B, H, W, Cin, Cout, ks, st, pad = case
+    x = wl.random_normal(8, 1, B * H * W * Cin).reshape(B, H, W, Cin)
+    dy = wl.random_normal(8, 2, B * H * W * Cout).reshape(B, H, W, Cout)
+    _, dw = L.conv2d_bwd(_rnd(x, dtype), np.zeros((Cout, ks, ks, Cin)), st, pad, _rnd(dy, dtype))
+    old = wl.random_normal(8, 3, dw.size).reshape(dw.shape) * np.abs(dw).max()
+    xd, dyd = _dev(x, dtype), _dev(dy, dtype)
+    for sums in (1, 7, 9, 30, 60):
+        for which in (2, 9):
+            mem = torch.full((dw.size + 16,), 7.0, dtype=torch.float32, device="cuda")
+            mem[8:8 + dw.size] = _dev(old, wl.F32).flatten()
+            ws = torch.full((dw.size * sums,), float("nan"), dtype=torch.float32, device="cuda")
+            b.cdp_k_conv(dtype, which, dyd.data_ptr(), xd.data_ptr(), mem.data_ptr() + 32, *case, ws_ptr=ws.data_ptr(), ws_bytes=ws.numel() * 4)
+            torch.cuda.synchronize()
+            got = mem[8:8 + dw.size].reshape(dw.shape)
+            # products of exactly representable inputs, fp32 sums
+            _close(got, dw if which == 2 else _rnd(old, wl.F32) + dw, 1e-5, (sums, which))
+            assert bool((mem[:8] == 7).all()) and bool((mem[8 + dw.size:] == 7).all())
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("sums", [1, 2, 5, 12])
 @pytest.mark.parametrize("case", [(1, 1, 1, 8, 8, 1, 1, 0),       # one position
                                   (3, 5, 7, 24, 40, 3, 1, 1),     # 105 positions: a group (or slab) and a part of one
