@@ -214,6 +214,9 @@ __global__ __launch_bounds__(256) void repack_kernel(const RepackBatch batch) {
       if (a.gamma) gam[i] = a.gamma[o];
     }
   }
+  // vmcnt(0), here and for all of them: waited for under the condition of its own stores, every row would wait again, and for
+  // the stores of the rows before it (17 tiles 14.2 us so / 11.2 us, 1472 tiles 33.0 / 26.6)
+  __builtin_amdgcn_s_waitcnt(0x0f70);
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int o = o0 + ty + i * 4, c = c0 + tx;
