@@ -11,6 +11,10 @@ namespace cdp {
 namespace {
 
 template <typename T> __device__ __forceinline__ float tld(const T* p, int64_t i) { return ld_f32<T>(p, i); }
+// the bits of a value as a register holds them after the load, and the value: a conversion is a use, which waits for the load
+__device__ __forceinline__ uint32_t tbits(const uint16_t* p, int64_t i) { return p[i]; }
+__device__ __forceinline__ uint32_t tbits(const float* p, int64_t i) { return __float_as_uint(p[i]); }
+template <typename T> __device__ __forceinline__ float tval(uint32_t b) { return __uint_as_float(sizeof(T) == 2 ? b << 16 : b); }
 template <typename T> __device__ __forceinline__ void tst(T* p, int64_t i, float v) { st_f32<T>(p, i, v); }
 
 #define CDP_TDISPATCH(dtype, CALL)                        \
@@ -87,12 +91,26 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const T* __restrict_
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const T* xr = x + (int64_t)row * C;
+  // Every read in one round, as the bits in memory and at an address that is always there; a read under its lane's condition, or
+  // converted under it, would be waited for there: a round trip per 64 channels, and one per store for gamma and beta
+  // (us: 6272 rows of 1001 in bf16 10.1 / 7.1 so, 800 rows of 770 in fp32 4.1 / 3.1).
+  uint32_t xb[LN_MAX_PER_LANE] = {};
+  float ga[LN_MAX_PER_LANE] = {}, be[LN_MAX_PER_LANE] = {};
+#pragma unroll
+  for (int q = 0; q < LN_MAX_PER_LANE; ++q)
+    if (q == 0 || 64 * q < C) {
+      const int c = min(lane + 64 * q, C - 1);
+      xb[q] = tbits(xr, c);
+      ga[q] = gamma[c];
+      be[q] = beta[c];
+    }
   float v[LN_MAX_PER_LANE];
   float s = 0.f;
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 #pragma unroll
   for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
     const int c = lane + 64 * q;
-    v[q] = c < C ? tld<T>(xr, c) : 0.f;
+    v[q] = c < C ? tval<T>(xb[q]) : 0.f;
     s += v[q];
   }
   const float mean = wsum(s) / (float)C;
@@ -107,7 +125,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const T* __restrict_
 #pragma unroll
   for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
     const int c = lane + 64 * q;
-    if (c < C) tst<T>(y, (int64_t)row * C + c, (v[q] - mean) * rstd * gamma[c] + beta[c]);
+    if (c < C) tst<T>(y, (int64_t)row * C + c, (v[q] - mean) * rstd * ga[q] + be[q]);
   }
 }
 
@@ -277,13 +295,27 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __rest
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const int64_t base = (int64_t)row * C;
+  // every read in one round, as in layernorm_fwd_kernel (us, with the kernels behind it: 6272 rows of 1001 in bf16
+  // 33.7 / 24.3 so, of 500 21.4 / 17.0, 800 rows of 770 in fp32 15.0 / 12.5)
+  uint32_t xb[LN_MAX_PER_LANE] = {}, db[LN_MAX_PER_LANE] = {}, ab[LN_MAX_PER_LANE] = {};
+  float ga[LN_MAX_PER_LANE] = {};
+#pragma unroll
+  for (int q = 0; q < LN_MAX_PER_LANE; ++q)
+    if (q == 0 || 64 * q < C) {
+      const int c = min(lane + 64 * q, C - 1);
+      xb[q] = tbits(x, base + c);
+      db[q] = tbits(dy, base + c);
+      ga[q] = gamma[c];
+      if (add) ab[q] = tbits(add, base + c);
+    }
   float v[LN_MAX_PER_LANE], g[LN_MAX_PER_LANE];
   float s = 0.f;
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 #pragma unroll
   for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
     const int c = lane + 64 * q;
-    v[q] = c < C ? tld<T>(x, base + c) : 0.f;
-    g[q] = c < C ? tld<T>(dy, base + c) * gamma[c] : 0.f;
+    v[q] = c < C ? tval<T>(xb[q]) : 0.f;
+    g[q] = c < C ? tval<T>(db[q]) * ga[q] : 0.f;
     s += v[q];
   }
   const float mean = wsum(s) / (float)C;
@@ -309,7 +341,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __rest
     const int c = lane + 64 * q;
     if (c < C) {
       float r = rstd * (g[q] - mg - v[q] * mgx);
-      if (add) r += tld<T>(add, base + c);
+      if (add) r += tval<T>(ab[q]);
       tst<T>(dx, base + c, r);
     }
   }

@@ -225,7 +225,7 @@ def test_conv_weight_gradient_added_to_an_accumulator(dtype, case):
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
-@pytest.mark.parametrize("case", [(4, 40, 40, 8, 20, 3, 1, 1), (4, 40, 40, 16, 24, 3, 1, 1)])
+@pytest.mark.parametrize("case", [(4, 40, 40, 8, 40, 3, 1, 1), (4, 40, 40, 16, 24, 3, 1, 1)])
 def test_conv_weight_gradient_fold_of_many_ranges(dtype, case):
     """Folds at every number of 32-lane groups to a weight row, rows that end inside a chunk of 128 columns; nothing around the
     accumulator is touched."""
