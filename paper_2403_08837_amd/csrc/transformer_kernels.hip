@@ -48,6 +48,8 @@ __device__ __forceinline__ float wmax(float v) {
 
 constexpr float LN_EPS = 1e-5f;
 constexpr int LN_MAX_PER_LANE = 16;  // channels <= 1024
+constexpr int LN_FEW_PER_LANE = 4;   // channels <= 256 of rows that are not whole 16-byte pieces: fewer registers and reads to skip
+// (us, sixteen / four per lane: 6272 rows of 20 in bf16 3.5 / 3.2 forward and 11.2 / 9.8 backward; of 250 4.4 / 3.3 and 13.3 / 11.1 before both)
 
 // 16-byte chunks of a row: 8 bf16 or 4 fp32 values.
 template <typename T> struct RowChunk;
@@ -85,7 +87,7 @@ template <> struct RowChunk<float> {
 // ---------------------------------------------------------------------------------
 // LayerNorm over the channels of every row: one wavefront per row, lane l owns channels
 // l, l+64, ...  y = (x - mean) * rstd * gamma + beta (biased variance, eps = 1e-5).
-template <typename T>
+template <typename T, int PER_LANE>
 __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const T* __restrict__ x, const float* __restrict__ gamma,
                                                             const float* __restrict__ beta, T* __restrict__ y, int rows, int C) {
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -94,21 +96,21 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const T* __restrict_
   // Every read in one round, as the bits in memory and at an address that is always there; a read under its lane's condition, or
   // converted under it, would be waited for there: a round trip per 64 channels, and one per store for gamma and beta
   // (us: 6272 rows of 1001 in bf16 10.1 / 7.1 so, 800 rows of 770 in fp32 4.1 / 3.1).
-  uint32_t xb[LN_MAX_PER_LANE] = {};
-  float ga[LN_MAX_PER_LANE] = {}, be[LN_MAX_PER_LANE] = {};
+  uint32_t xb[PER_LANE] = {};
+  float ga[PER_LANE] = {}, be[PER_LANE] = {};
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q)
+  for (int q = 0; q < PER_LANE; ++q)
     if (q == 0 || 64 * q < C) {
       const int c = min(lane + 64 * q, C - 1);
       xb[q] = tbits(xr, c);
       ga[q] = gamma[c];
       be[q] = beta[c];
     }
-  float v[LN_MAX_PER_LANE];
+  float v[PER_LANE];
   float s = 0.f;
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
+  for (int q = 0; q < PER_LANE; ++q) {
     const int c = lane + 64 * q;
     v[q] = c < C ? tval<T>(xb[q]) : 0.f;
     s += v[q];
@@ -116,14 +118,14 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const T* __restrict_
   const float mean = wsum(s) / (float)C;
   float ss = 0.f;
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
+  for (int q = 0; q < PER_LANE; ++q) {
     const int c = lane + 64 * q;
     const float d = c < C ? v[q] - mean : 0.f;
     ss += d * d;
   }
   const float rstd = rsqrtf(wsum(ss) / (float)C + LN_EPS);
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
+  for (int q = 0; q < PER_LANE; ++q) {
     const int c = lane + 64 * q;
     if (c < C) tst<T>(y, (int64_t)row * C + c, (v[q] - mean) * rstd * ga[q] + be[q]);
   }
@@ -288,7 +290,7 @@ __device__ __forceinline__ void layernorm_bwd_vec_body(const T* __restrict__ x, 
     part[(int64_t)blockIdx.x * 2 * C + c] = s;
   }
 }
-template <typename T>
+template <typename T, int PER_LANE>
 __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __restrict__ x, const T* __restrict__ dy,
                                                                  const T* __restrict__ add, const float* __restrict__ gamma,
                                                                  T* __restrict__ dx, float* __restrict__ stats, int rows, int C) {
@@ -297,10 +299,10 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __rest
   const int64_t base = (int64_t)row * C;
   // every read in one round, as in layernorm_fwd_kernel (us, with the kernels behind it: 6272 rows of 1001 in bf16
   // 33.7 / 24.3 so, of 500 21.4 / 17.0, 800 rows of 770 in fp32 15.0 / 12.5)
-  uint32_t xb[LN_MAX_PER_LANE] = {}, db[LN_MAX_PER_LANE] = {}, ab[LN_MAX_PER_LANE] = {};
-  float ga[LN_MAX_PER_LANE] = {};
+  uint32_t xb[PER_LANE] = {}, db[PER_LANE] = {}, ab[PER_LANE] = {};
+  float ga[PER_LANE] = {};
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q)
+  for (int q = 0; q < PER_LANE; ++q)
     if (q == 0 || 64 * q < C) {
       const int c = min(lane + 64 * q, C - 1);
       xb[q] = tbits(x, base + c);
@@ -308,11 +310,11 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __rest
       ga[q] = gamma[c];
       if (add) ab[q] = tbits(add, base + c);
     }
-  float v[LN_MAX_PER_LANE], g[LN_MAX_PER_LANE];
+  float v[PER_LANE], g[PER_LANE];
   float s = 0.f;
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
+  for (int q = 0; q < PER_LANE; ++q) {
     const int c = lane + 64 * q;
     v[q] = c < C ? tval<T>(xb[q]) : 0.f;
     g[q] = c < C ? tval<T>(db[q]) * ga[q] : 0.f;
@@ -321,7 +323,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __rest
   const float mean = wsum(s) / (float)C;
   float ss = 0.f;
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
+  for (int q = 0; q < PER_LANE; ++q) {
     const int c = lane + 64 * q;
     const float t = c < C ? v[q] - mean : 0.f;
     ss += t * t;
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __rest
   const float rstd = rsqrtf(wsum(ss) / (float)C + LN_EPS);
   float sg = 0.f, sgx = 0.f;
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
+  for (int q = 0; q < PER_LANE; ++q) {
     const int c = lane + 64 * q;
     v[q] = c < C ? (v[q] - mean) * rstd : 0.f;
     sg += g[q];
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __rest
   }
   const float mg = wsum(sg) / (float)C, mgx = wsum(sgx) / (float)C;
 #pragma unroll
-  for (int q = 0; q < LN_MAX_PER_LANE; ++q) {
+  for (int q = 0; q < PER_LANE; ++q) {
     const int c = lane + 64 * q;
     if (c < C) {
       float r = rstd * (g[q] - mg - v[q] * mgx);
@@ -447,8 +449,11 @@ hipError_t launch_layernorm_fwd(const void* x, const float* gamma, const float* 
   if (ln_vec_ok(x, C, eb) && ln_vec_ok(y, C, eb))
     CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_fwd_vec_kernel<T>), dim3((rows + 3) / 4), dim3(256), 0, stream,
                                             static_cast<const T*>(x), gamma, beta, static_cast<T*>(y), rows, C));
+  else if (C <= 64 * LN_FEW_PER_LANE)
+    CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_fwd_kernel<T, LN_FEW_PER_LANE>), dim3((rows + 3) / 4), dim3(256), 0, stream,
+                                            static_cast<const T*>(x), gamma, beta, static_cast<T*>(y), rows, C));
   else
-    CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_fwd_kernel<T>), dim3((rows + 3) / 4), dim3(256), 0, stream,
+    CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_fwd_kernel<T, LN_MAX_PER_LANE>), dim3((rows + 3) / 4), dim3(256), 0, stream,
                                             static_cast<const T*>(x), gamma, beta, static_cast<T*>(y), rows, C));
   return hipGetLastError();
 }
@@ -468,9 +473,14 @@ hipError_t launch_layernorm_bwd(const void* x, const void* dy, const void* add, 
   const int wgs = (rows + LN_ROWS_PER_WG - 1) / LN_ROWS_PER_WG;
   float* stats = workspace;
   float* part = workspace + ln_stats_bytes(rows) / 4;
-  CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_bwd_rows_kernel<T>), dim3((rows + 3) / 4), dim3(256), 0, stream,
-                                          static_cast<const T*>(x), static_cast<const T*>(dy), static_cast<const T*>(add), gamma,
-                                          static_cast<T*>(dx), stats, rows, C));
+  if (C <= 64 * LN_FEW_PER_LANE)
+    CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_bwd_rows_kernel<T, LN_FEW_PER_LANE>), dim3((rows + 3) / 4), dim3(256), 0, stream,
+                                            static_cast<const T*>(x), static_cast<const T*>(dy), static_cast<const T*>(add), gamma,
+                                            static_cast<T*>(dx), stats, rows, C));
+  else
+    CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_bwd_rows_kernel<T, LN_MAX_PER_LANE>), dim3((rows + 3) / 4), dim3(256), 0, stream,
+                                            static_cast<const T*>(x), static_cast<const T*>(dy), static_cast<const T*>(add), gamma,
+                                            static_cast<T*>(dx), stats, rows, C));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   CDP_TDISPATCH(dtype, hipLaunchKernelGGL((layernorm_bwd_cols_kernel<T>), dim3(wgs), dim3(256), 0, stream, static_cast<const T*>(x),

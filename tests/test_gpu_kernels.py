@@ -484,6 +484,13 @@ def test_layernorm_whole_chunk_edges(dtype, rows, C):
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("rows,C", [(1, 1), (6, 63), (9, 65), (300, 255), (13, 257), (7, 1021), (5, 1023)])
+def test_layernorm_ragged_edges(dtype, rows, C):
+    """Rows that are not whole 16-byte pieces: around one value per lane, the widths where a lane holds four and sixteen, the widest."""
+    test_layernorm_kernels_match_oracle(dtype, rows, C)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("rows,C", [(6272, 768), (4100, 64), (40, 128)])
 def test_layernorm_backward_does_not_depend_on_its_launch(dtype, rows, C):
     """A problem's gradients have the same bits whether it is launched alone or with others of its shape, as the engine does."""
