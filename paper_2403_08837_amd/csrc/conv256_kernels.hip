@@ -99,8 +99,16 @@ struct SlabLoads {
     auto uniform = [](unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); };
     const v4u buffer = {uniform((unsigned)p), uniform((unsigned)(p >> 32)), uniform(records), 0x00020000u};
     const unsigned lds = at + (e < LPA ? (wave * LPA + e) * 1024 : BM * ROW + (wave * LPB + e - LPA) * 1024);
-    // nothing is written to registers; the nop is the wait state between the two
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(e < LPA ? aoff[e] : boff[e - LPA]), "s"(buffer));
+    // The wait states of this are ours, the compiler does not look into assembly: one between the write of m0 and the load, five between a
+    // write of a descriptor word by the vector unit (the readfirstlane above may be the instruction before) and the load that reads it.  The
+    // s_mov_b32 is one and s_nop 3 four, whatever stands before.  (us so / with the words pinned in scalar registers a slab
+    // ahead: 8192^3 801 / 806, 6272 x 3072 x 768 41.1 / 41.0, 25088 x 128 x 1152 14.0 / 13.8.)
+    // Nothing is written to registers but m0, which the compiler reserves for itself and warns about: it is said so that no use of its own
+    // is scheduled across.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(e < LPA ? aoff[e] : boff[e - LPA]), "s"(buffer) : "m0");
+#pragma clang diagnostic pop
   }
   __device__ __forceinline__ void advance() {
     if (--left <= 0) {
