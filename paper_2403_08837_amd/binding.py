@@ -106,23 +106,32 @@ def lib() -> C.CDLL:
     return _lib
 
 
+_CALLS = ("cdp_k_gemm", "cdp_k_conv", "cdp_k_conv_wgrad_static", "cdp_k_layernorm", "cdp_k_gelu", "cdp_k_attention")
+
+
+def _calls():
+    """_calls.so (csrc/pycalls.cpp) on the library that this package loaded, or None: it is not built, or not for this interpreter."""
+    try:
+        spec = importlib.util.spec_from_file_location(__package__ + "._calls", os.path.join(_HERE, "_calls.so"))
+        module = importlib.util.module_from_spec(spec)
+        module.use(*(C.cast(getattr(lib(), n), C.c_void_p).value for n in _CALLS))
+        return module
+    except (ImportError, OSError, AttributeError, TypeError):
+        return None
+
+
 def _entry(name: str):
-    """Kernel-level entry point `name` of _calls.so (csrc/pycalls.cpp): a call whose arguments are plain integers costs 0.3 us there and
+    """Kernel-level entry point `name` of _calls.so: a call whose arguments are plain integers costs 0.3 us there and
     one to two through ctypes.  None: an argument is something else, or there is no _calls.so; the caller goes through ctypes then.
     Loaded with the first call."""
     def first(*args):
         lib()
-        path, fast = os.path.join(_HERE, "_calls.so"), None
-        if os.path.exists(path):
-            spec = importlib.util.spec_from_file_location(__package__ + "._calls", path)
-            fast = getattr(importlib.util.module_from_spec(spec), name)
-        globals()["_" + name] = fast or (lambda *a: None)
+        globals()["_" + name] = getattr(_calls(), name, None) or (lambda *a: None)
         return globals()["_" + name](*args)
     return first
 
 
-_cdp_k_gemm, _cdp_k_conv, _cdp_k_conv_wgrad_static, _cdp_k_layernorm, _cdp_k_gelu, _cdp_k_attention = (
-    _entry(n) for n in ("cdp_k_gemm", "cdp_k_conv", "cdp_k_conv_wgrad_static", "cdp_k_layernorm", "cdp_k_gelu", "cdp_k_attention"))
+_cdp_k_gemm, _cdp_k_conv, _cdp_k_conv_wgrad_static, _cdp_k_layernorm, _cdp_k_gelu, _cdp_k_attention = map(_entry, _CALLS)
 
 
 def _check(rc: int, ctx=None) -> None:
