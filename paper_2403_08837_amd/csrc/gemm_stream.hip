@@ -10,6 +10,8 @@
 // the address path of the CU bounds the kernel at 14 bytes per cycle (64 rows, 4096 x 4096: 20.3 us).  The partial tiles
 // meet in LDS and are added in wavefront order.
 // 64 rows, 4096 x 4096, bf16: 26.9 us on the tick launch's tiles, 11.9 us so; 32 rows 15.6 -> 7.6; fp32 97 -> 28 us.
+#include <algorithm>
+
 #include "elem.h"
 #include "kernels.h"
 
@@ -41,8 +43,8 @@ template <typename T> __device__ __forceinline__ v4f_t stream_mfma(uint4 a, uint
   }
 }
 
-// MT: blocks of 16 rows.
-template <typename T, int MT>
+// MT: blocks of 16 rows.  FAR: rows so long that byte offsets inside a workgroup's rows may not fit 32 bits (gemm_stream_far).
+template <typename T, int MT, bool FAR>
 __global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const StreamArgs g) {
   constexpr int VEC = Elem<T>::VEC, PIECE = 8 * VEC;   // elements of a 128-byte piece
   constexpr int NL = 2 * MT + 2;                       // loads per piece: 8 rows x 128 bytes each, A's then B's
@@ -60,16 +62,28 @@ __global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const Str
   // reach outputs that are not stored.  A wave with a single piece asks for no other.  us, under conditions / so:
   //   bf16 64 x 4096 x 4096 12.1 / 11.9, 64 x 512 x 512 3.7 / 3.1, 33 x 8192 x 512 5.6 / 5.0, 100 x 1000 x 3000 8.8 / 8.1
   //   fp32 64 x 4096 x 4096 30.5 / 27.9, 30 x 500 x 2004 9.3 / 8.2, 8 x 64 x 64 3.5 / 2.9
+  // Far rows are read at 64-bit addresses, just as unconditionally: chunks past the end of a row read its last one and become zeros on
+  // their way into LDS.
   constexpr int ES = (int)sizeof(T);
   const char* const pa = static_cast<const char*>(g.A) + (int64_t)row0 * g.lda * ES;
   const char* const pb = static_cast<const char*>(g.B) + (int64_t)col0 * g.ldb * ES;
   unsigned off[NL];
+  const char* far[NL];
 #pragma unroll
-  for (int j = 0; j < NL; ++j)
-    off[j] = (unsigned)((j < 2 * MT ? min(8 * j + lr, g.M - 1 - row0) * g.lda : min(8 * (j - 2 * MT) + lr, g.N - 1 - col0) * g.ldb) + lk) * ES;
+  for (int j = 0; j < NL; ++j) {
+    const int r = j < 2 * MT ? min(8 * j + lr, g.M - 1 - row0) : min(8 * (j - 2 * MT) + lr, g.N - 1 - col0), ld = j < 2 * MT ? g.lda : g.ldb;
+    if constexpr (FAR) far[j] = (j < 2 * MT ? pa : pb) + (int64_t)r * ld * ES;
+    else off[j] = (unsigned)(r * ld + lk) * ES;
+  }
   const int step = GS_WAVES * PIECE, first = wave * PIECE;
   const int pieces = first < g.K ? (g.K - first + step - 1) / step : 0;
   auto load = [&](uint4 (&r)[NL], int i) {
+    if constexpr (FAR) {
+      const unsigned k = min((unsigned)first + (unsigned)i * step + lk, (unsigned)(g.K - VEC));
+#pragma unroll
+      for (int j = 0; j < NL; ++j) r[j] = *reinterpret_cast<const uint4*>(far[j] + (uint64_t)k * ES);
+      return;
+    }
     const int k = first + i * step;
     const unsigned records = i < pieces ? 0xfffffff0u : 0u;
     const auto ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pa), (short)0, records, 0x00020000);
@@ -81,9 +95,12 @@ __global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const Str
 #pragma unroll
   for (int i = 0; i < MT; ++i) acc[i] = v4f_t{0.f, 0.f, 0.f, 0.f};
   // The staged piece is the wavefront's own, whose LDS instructions execute in order: no barrier.
-  auto product = [&](const uint4 (&r)[NL]) {
+  auto product = [&](const uint4 (&r)[NL], int i) {
+    // (by bits: of `past ? zeros : r[j]` the compiler made a branch that left 12 of the 16 registers of the last four chunks as they were)
+    const unsigned in = FAR && (unsigned)first + (unsigned)i * step + lk >= (unsigned)g.K ? 0u : ~0u;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) *reinterpret_cast<uint4*>(st + (8 * j + lr) * PITCH + lk) = r[j];
+    for (int j = 0; j < NL; ++j)
+      *reinterpret_cast<uint4*>(st + (8 * j + lr) * PITCH + lk) = FAR ? make_uint4(r[j].x & in, r[j].y & in, r[j].z & in, r[j].w & in) : r[j];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -100,19 +117,19 @@ __global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const Str
   uint4 r0[NL], r1[NL], r2[NL];
   if (pieces == 1) {
     load(r0, 0);
-    product(r0);
+    product(r0, 0);
   } else if (pieces > 1) {
     load(r0, 0);
     load(r1, 1);
     for (int i = 0;;) {  // two pieces ahead
       load(r2, i + 2);
-      product(r0);
+      product(r0, i);
       if (++i == pieces) break;
       load(r0, i + 2);
-      product(r1);
+      product(r1, i);
       if (++i == pieces) break;
       load(r1, i + 2);
-      product(r2);
+      product(r2, i);
       if (++i == pieces) break;
     }
   }
@@ -132,13 +149,16 @@ __global__ __launch_bounds__(64 * GS_WAVES, 2) void gemm_stream_kernel(const Str
   }
 }
 
-template <typename T>
+template <typename T, bool FAR>
 void launch_stream(const StreamArgs& g, hipStream_t stream) {
   const dim3 cols((g.N + 15) / 16, 1), block(64 * GS_WAVES);
-  if (g.M <= 16) hipLaunchKernelGGL((gemm_stream_kernel<T, 1>), cols, block, 0, stream, g);
-  else if (g.M <= 32) hipLaunchKernelGGL((gemm_stream_kernel<T, 2>), cols, block, 0, stream, g);
-  else hipLaunchKernelGGL((gemm_stream_kernel<T, 4>), dim3(cols.x, (g.M + 63) / 64), block, 0, stream, g);
+  if (g.M <= 16) hipLaunchKernelGGL((gemm_stream_kernel<T, 1, FAR>), cols, block, 0, stream, g);
+  else if (g.M <= 32) hipLaunchKernelGGL((gemm_stream_kernel<T, 2, FAR>), cols, block, 0, stream, g);
+  else hipLaunchKernelGGL((gemm_stream_kernel<T, 4, FAR>), dim3(cols.x, (g.M + 63) / 64), block, 0, stream, g);
 }
+
+// 32-bit byte offsets reach 64 rows of so many elements and the reduction behind them.
+bool gemm_stream_far(const StreamArgs& g) { return std::max({g.lda, g.ldb, g.K}) > (1 << 22); }
 
 }  // namespace
 
@@ -148,14 +168,14 @@ void launch_stream(const StreamArgs& g, hipStream_t stream) {
 bool gemm_stream_wanted(const void* A, const void* B, int M, int N, int K, int lda, int ldb, int dtype) {
   const int vec = dtype == DT_BF16 ? 8 : 4;
   if (K % vec || lda % vec || ldb % vec || ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15)) return false;
-  if (lda > (1 << 22) || ldb > (1 << 22)) return false;  // 32-bit byte offsets inside 64 rows
   return M <= 128 && (int64_t)((N + 15) / 16) * (M <= 64 ? 1 : 2) <= 512;
 }
 
 hipError_t launch_gemm_stream(const void* A, const void* B, float* C, int M, int N, int K, int lda, int ldb, int dtype, hipStream_t stream) {
   const StreamArgs g{A, B, C, M, N, K, lda, ldb};
-  if (dtype == DT_BF16) launch_stream<uint16_t>(g, stream);
-  else launch_stream<float>(g, stream);
+  const bool far = gemm_stream_far(g);
+  if (dtype == DT_BF16) far ? launch_stream<uint16_t, true>(g, stream) : launch_stream<uint16_t, false>(g, stream);
+  else far ? launch_stream<float, true>(g, stream) : launch_stream<float, false>(g, stream);
   return hipGetLastError();
 }
 

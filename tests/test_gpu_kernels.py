@@ -116,6 +116,34 @@ def test_gemm_few_rows(dtype, M):
         assert np.abs(got - ref).max() <= 2e-5 * np.sqrt(K) * max(1.0, np.abs(ref).max()), (N, K)
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("M,N,K,lda,ldb", [(70, 1024, 72, 72, (1 << 22) + 8),            # rows of the weights past 32-bit byte offsets
+                                           (64, 33, 1160, (1 << 23) + 8, 1160),          # rows of x
+                                           (3, 20, (1 << 22) + 40, (1 << 22) + 40, (1 << 22) + 40),  # long reduction, its end inside a piece
+                                           (17, 5, 8, (1 << 25) + 8, (1 << 26) + 8), (40, 16, 64, 64, 1 << 22)])
+def test_gemm_few_far_rows(dtype, M, N, K, lda, ldb):
+    """The same kernel where rows are far apart.  Exact: -1, 0 and 1, sums below 2^24."""
+    torch = _torch()
+    t = torch.bfloat16 if dtype == wl.BF16 else torch.float32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M)
+
+    def rows(n, ld):  # the last row ends with the memory, what lies between rows is not read
+        mem = torch.empty((n - 1) * ld + K, dtype=t, device="cuda")
+        view = mem.as_strided((n, K), (ld, 1))
+        view.copy_(torch.randint(-1, 2, (n, K), generator=gen, device="cuda"))
+        if ld > K and n > 1:
+            mem.as_strided((n - 1, min(8, ld - K)), (ld, 1), K).fill_(float("nan"))
+        return mem, view
+    a, x = rows(M, lda)
+    w, k = rows(N, ldb)
+    ref = sum(x[:, i:i + (1 << 18)].float().contiguous() @ k[:, i:i + (1 << 18)].float().contiguous().T for i in range(0, K, 1 << 18))
+    got = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    b.cdp_k_gemm(dtype, 5, 1, 1, a.data_ptr(), w.data_ptr(), got.data_ptr(), M, N, K, lda, ldb)
+    torch.cuda.synchronize()
+    assert torch.equal(got, ref)
+
+
 CONV_CASES = [
     # B, H, W, Cin, Cout, ks, stride, pad
     (2, 8, 8, 8, 16, 3, 1, 1),
