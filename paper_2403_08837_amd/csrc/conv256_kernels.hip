@@ -68,9 +68,9 @@ struct SlabLoads {
     left = P.K / BK;
     tap = c0 = kh = kw = 0;
     records = 0xfffffff0u;
-    // a row's base is negative in the padding before the first image: offsets count from the lowest one
-    const int shift = mode == OP_CONV_FWD ? (g.pad * g.W + g.pad) * g.C : 0;
-    pa = first = static_cast<const char*>(P.A) - 2 * (int64_t)shift;
+    // offsets count from the lowest row's base (in the padding before the first image, or past its first positions)
+    const int lowest = mode == OP_PLAIN_K ? 0 : mode == OP_CONV_FWD ? -(g.pad * g.W + g.pad) * g.C : ((g.pad / g.stride) * g.W + g.pad / g.stride) * g.C;
+    pa = first = static_cast<const char*>(P.A) + 2 * (int64_t)lowest;
     pb = static_cast<const char*>(P.B);
     // block (wave * LPA + i) of RPB rows, row lane / CPR of it, slot lane % CPR; rows past the matrix repeat the last one: they only
     // reach results that are not stored
@@ -82,7 +82,7 @@ struct SlabLoads {
       amask[i] = 1u;
       if (mode == OP_PLAIN_K) base = r * P.lda;
       else conv_row(g, mode, r, base, amask[i]);
-      abase[i] = 2u * (unsigned)(base + shift + (ls ^ swz(tr)) * 8);
+      abase[i] = 2u * ((unsigned)base - (unsigned)lowest + (ls ^ swz(tr)) * 8);
     }
     at_tap();
 #pragma unroll
@@ -486,6 +486,15 @@ static void launch_dl(const GemmBatch& b, dim3 grid, hipStream_t stream) {
   else hipLaunchKernelGGL((conv_gemm_dl_kernel<BM, BN, WAVES_M, WAVES_N, BK, STAGES, WPS>), grid, dim3(WAVES_M * WAVES_N * 64), 0, stream, b);
 }
 
+// Elements between the first tap of the lowest and of the highest row that the gathered operand has.
+static int64_t conv_row_span(const GemmProb& p) {
+  const ConvGeom& g = p.g;
+  if (p.a_mode == OP_PLAIN_K) return (int64_t)(p.M - 1) * p.lda;
+  const int64_t images = p.M / (g.OH * g.OW) - 1;
+  auto reach = [&](int last) { return p.a_mode == OP_CONV_FWD ? (int64_t)last * g.stride : (int64_t)((last + g.pad) / g.stride - g.pad / g.stride); };
+  return ((images * g.H + reach(g.OH - 1)) * g.W + reach(g.OW - 1)) * g.C;
+}
+
 // A forward / data-gradient problem these tiles take: bf16, every reduction slab of `bk` inside one tap, 16-byte aligned
 // operands, 32-bit element offsets.
 static bool conv_dl_eligible(const GemmProb& p, int dtype, int bk) {
@@ -495,9 +504,10 @@ static bool conv_dl_eligible(const GemmProb& p, int dtype, int bk) {
   if ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B) | reinterpret_cast<uintptr_t>(p.out)) & 15) return false;
   if ((p.aux1 && (reinterpret_cast<uintptr_t>(p.aux1) & 15)) || (p.epi == EPI_DGRAD && p.aux0 && (reinterpret_cast<uintptr_t>(p.aux0) & 15)))
     return false;
-  // 32-bit byte offsets: of the operands below 2^32 - 16, the padding in front of the first row included, of results below 2^31
-  const int64_t a_elems = p.a_mode == OP_PLAIN_K ? (int64_t)p.M * p.lda : (int64_t)(p.M / (p.g.OH * p.g.OW) + 1) * p.g.H * p.g.W * p.g.C + (int64_t)(p.g.pad * p.g.W + p.g.pad) * p.g.C;
-  return a_elems < (1ll << 31) - 1024 && (int64_t)p.N * p.ldb < (1ll << 31) - 1024 && (int64_t)p.M * p.ldo < (1ll << 30) && p.ldo <= (1 << 20);
+  // 32-bit byte offsets: of the weights' rows, of the gathered rows from the lowest one (SlabLoads; they end a slab and a load below 2^32), and
+  // inside 32 rows of the result
+  const int64_t a_elems = p.a_mode == OP_PLAIN_K ? (int64_t)p.M * p.lda : (int64_t)(p.M / (p.g.OH * p.g.OW) + 1) * p.g.H * p.g.W * p.g.C;
+  return a_elems < (1ll << 31) && (int64_t)p.N * p.ldb < (1ll << 31) && conv_row_span(p) < (1ll << 31) - 64 && p.ldo < (1 << 26);
 }
 bool conv_gemm256_eligible(const GemmProb& p, int dtype) { return conv_dl_eligible(p, dtype, 64); }
 

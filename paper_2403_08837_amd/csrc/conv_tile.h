@@ -60,24 +60,27 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
   constexpr int VEC = 8, NS = 2 * NI, NT = NSUM + (MASK ? 1 : 0), AHEAD = MI * NI > 4 ? 1 : 2;
   const int l31 = lane & 31, hi = lane >> 5;
   const bool fwd = P.epi == EPI_FWD, relu = fwd && (P.flags & GF_RELU);
-  const unsigned ldo = P.ldo, bytes = (unsigned)P.M * ldo * 2u;  // below 2^31 (conv_dl_eligible)
-  auto buffer = [&](const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000); };
-  const auto out = buffer(P.out), out2 = buffer(GELU && !MASK ? P.aux2 : P.out);
-  const auto t0 = buffer(NSUM == 0 ? P.aux1 : fwd ? P.aux1 : P.aux0 ? P.aux0 : P.out), t1 = buffer(NSUM == 2 ? P.out : P.aux1), t2 = buffer(P.aux1);
-  unsigned off[NS];  // byte offset of the piece of the first row block; columns past the matrix are sent past the buffer
+  const unsigned ldo = P.ldo;
+  // A buffer per row block, so that 32-bit offsets reach rows of any number (conv_dl_eligible): rows of the block that the matrix has.
+  auto buffer = [&](const void* p, int i) {
+    const int r = row0 + 32 * i;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(p)) + 2 * (int64_t)r * ldo, (short)0, (unsigned)min(max(P.M - r, 0), 32) * ldo * 2u, 0x00020000);
+  };
+  const void* const t0 = NSUM == 0 ? P.aux1 : fwd ? P.aux1 : P.aux0 ? P.aux0 : P.out;
+  const void* const t1 = NSUM == 2 ? P.out : P.aux1;
+  unsigned off[NS];  // byte offset of the piece inside its block; columns past the matrix are sent past the buffer
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const int c = col0 + 2 * VEC * s + VEC * hi;
-    off[s] = c < P.N ? ((unsigned)(row0 + l31) * ldo + c) * 2u : 0x80000000u;
+    off[s] = c < P.N ? ((unsigned)l31 * ldo + c) * 2u : 0xfffffff0u;
   }
-  const unsigned block = 64u * ldo;
   v4u x[NT ? AHEAD : 1][NT ? NT : 1][NS];
   auto request = [&](int i) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      if constexpr (NT > 0) x[i % AHEAD][0][s] = __builtin_amdgcn_raw_buffer_load_b128(t0, off[s] + i * block, 0, 0);
-      if constexpr (NT > 1) x[i % AHEAD][1][s] = __builtin_amdgcn_raw_buffer_load_b128(t1, off[s] + i * block, 0, 0);
-      if constexpr (NT > 2) x[i % AHEAD][2][s] = __builtin_amdgcn_raw_buffer_load_b128(t2, off[s] + i * block, 0, 0);
+      if constexpr (NT > 0) x[i % AHEAD][0][s] = __builtin_amdgcn_raw_buffer_load_b128(buffer(t0, i), off[s], 0, 0);
+      if constexpr (NT > 1) x[i % AHEAD][1][s] = __builtin_amdgcn_raw_buffer_load_b128(buffer(t1, i), off[s], 0, 0);
+      if constexpr (NT > 2) x[i % AHEAD][2][s] = __builtin_amdgcn_raw_buffer_load_b128(buffer(P.aux1, i), off[s], 0, 0);
     }
   };
   if constexpr (NT > 0 && AHEAD == 2) request(0);
@@ -141,11 +144,11 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
       }
 #pragma unroll
       for (int e = 0; e < VEC; ++e) res.e[e] = E::from_f32(val[e]);
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, res.v), out, off[s] + i * block, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, res.v), buffer(P.out, i), off[s], 0, 0);
       if constexpr (GELU && !MASK) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) act.e[e] = E::from_f32(gelu_f<uint16_t>(E::to_f32(res.e[e])));
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, act.v), out2, off[s] + i * block, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, act.v), buffer(P.aux2, i), off[s], 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }

@@ -610,6 +610,31 @@ def test_conv_rounds_of_tiles(rows, out, slabs):
     _conv_1x1_bf16(0, rows, 64 * slabs, out)
 
 
+@pytest.mark.parametrize("which,rows,cin,cout", [(0, 1041000, 64, 1032), (3, 1041000, 64, 1032), (5, 1041000, 64, 1032), (10, 1041000, 64, 1032),
+                                                 (4, 1041000, 1032, 64),                                   # results of more than 2 GiB
+                                                 (0, 33554430, 64, 72), (3, 33554430, 64, 72)])            # an operand of 4 GiB less two rows
+def test_conv_tiles_of_large_tensors(which, rows, cin, cout):
+    """Exact: -1, 0 and 1, whole numbers of at most 64 in bf16."""
+    torch = _torch()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(which)
+    k, n = (cout, cin) if which == 4 else (cin, cout)
+    x = torch.randint(-1, 2, (rows, k), generator=gen, device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    w = torch.randint(-1, 2, (n, k), generator=gen, device="cuda").to(torch.bfloat16)
+    y = torch.full((rows, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    act = torch.full((rows, n) if which == 10 else (1, 1), float("nan"), dtype=torch.bfloat16, device="cuda")
+    b.cdp_k_conv(wl.BF16, which, x.data_ptr(), w.data_ptr(), y.data_ptr(), rows, 1, 1, cin, cout, 1, 1, 0, ws_ptr=act.data_ptr(), ws_bytes=act.numel() * 2)
+    torch.cuda.synchronize()
+    wf = w.float().T.contiguous()
+    for i in range(0, rows, 1 << 20):
+        assert torch.equal(y[i:i + (1 << 20)], (x[i:i + (1 << 20)].float() @ wf).to(torch.bfloat16)), i
+    if which == 10:
+        ref = torch.empty_like(y)
+        b.cdp_k_gelu(wl.BF16, 0, y.data_ptr(), 0, ref.data_ptr(), y.numel())
+        torch.cuda.synchronize()
+        assert torch.equal(act, ref)
+
+
 @pytest.mark.parametrize("rows,out,slabs", [(21800, 376, 1), (21800, 376, 2), (21800, 376, 3), (33000, 600, 5),   # walked: 513 tiles and 1290, odd numbers of
                                             (65500, 136, 9), (8200, 1992, 4), (140100, 72, 1),                    # slabs and even, columns past a tile
                                             (21800, 376, 17), (24000, 760, 34)])                                  # 256 x 256 or the tile of one round
