@@ -469,7 +469,7 @@ __global__ __launch_bounds__(256, 2) void conv_gemm_run_kernel(const GemmBatch b
     }
     int row0, col0;
     place(P, cur, row0, col0);
-    conv_epilogue_as<MI, NI, 0, false, false>(P, acc, row0 + wm * WT, col0 + wn * WT, lane);
+    conv_epilogue_as<MI, NI, true, 0, false, false>(P, acc, row0 + wm * WT, col0 + wn * WT, lane);
     stored = true;
     if (known == 0) break;
     cur = ahead[0];

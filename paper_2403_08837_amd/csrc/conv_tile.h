@@ -53,13 +53,13 @@ __device__ __forceinline__ void conv_row(const ConvGeom& g, int mode, int r, int
 // GELU's input.  Operands of the row block after this one are requested before this one's results leave.  Loads and stores
 // are buffer instructions: what lies outside the matrix is outside the buffer, no branch, and every tile stores the same number of
 // times (conv_gemm_run_kernel counts them).
-template <int MI, int NI, int NSUM, bool MASK, bool GELU>
+template <int MI, int NI, bool FWD, int NSUM, bool MASK, bool GELU>
 __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc)[MI][NI], int row0, int col0, int lane) {
   using E = Elem<uint16_t>;
   typedef unsigned v4u __attribute__((ext_vector_type(4)));
   constexpr int VEC = 8, NS = 2 * NI, NT = NSUM + (MASK ? 1 : 0), AHEAD = MI * NI > 4 ? 1 : 2;
   const int l31 = lane & 31, hi = lane >> 5;
-  const bool fwd = P.epi == EPI_FWD, relu = fwd && (P.flags & GF_RELU);
+  const bool fwd = P.epi == EPI_FWD, relu = FWD && fwd && (P.flags & GF_RELU);  // FWD also takes data gradients that read nothing
   const unsigned ldo = P.ldo;
   // A buffer per row block, so that 32-bit offsets reach rows of any number (conv_dl_eligible): rows of the block that the matrix has.  All of it is
   // uniform, and said to be: with a word of the descriptor in a vector register (the compiler clamps there) every access is a loop over the
@@ -70,7 +70,7 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
   auto place = [&](const void* p) { return const_cast<char*>(static_cast<const char*>(p)) + first_byte; };
   char* const out = place(P.out);
   char* const out2 = GELU && !MASK ? place(P.aux2) : out;
-  char* const t0 = NT == 0 ? out : place(NSUM == 0 || fwd ? P.aux1 : P.aux0 ? P.aux0 : P.out);
+  char* const t0 = NT == 0 ? out : place(NSUM == 0 || FWD ? P.aux1 : P.aux0 ? P.aux0 : P.out);
   char* const t1 = NT < 2 ? out : place(NSUM == 2 ? P.out : P.aux1);
   char* const t2 = NT < 3 ? out : place(P.aux1);
   auto buffer = [&](char* p, int i) {
@@ -93,24 +93,22 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
     }
   };
   if constexpr (NT > 0 && AHEAD == 2) request(0);
-  if (fwd && P.aux0) {  // all of it in one round: 32 j + 8 q + 4 hi are the columns of this lane as the products leave them
-    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
-    v4f b[NI][4];
+  // The bias of this lane's columns, in one round; none is -0, which changes no value it is added to.  (Waited for here: where it is used the compiler
+  // would wait again, for the stores too.  Added to the accumulators ahead of everything, 256 x 256 tiles spilled 66 registers, with a GELU 200:
+  // us so / now, 25088 x 2048 x 2048 with bias, residual and ReLU 276 / 248, GELU 268 / 250.)
+  typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+  const bool biased = FWD && fwd && P.aux0, act_in = biased || relu;
+  v4f bias[FWD ? NS : 1][2];
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+  for (int s = 0; s < (FWD ? NS : 1); ++s) bias[s][0] = bias[s][1] = v4f{-0.f, -0.f, -0.f, -0.f};
+  if (biased) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)  // N is a multiple of VEC on these paths
-        b[j][q] = *reinterpret_cast<const v4f*>(static_cast<const float*>(P.aux0) + min(col0 + 32 * j + 8 * q + 4 * hi, P.N - 4));
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += b[j][q][e];
-      }
+    for (int s = 0; s < (FWD ? NS : 0); ++s) {
+      const float* const from = static_cast<const float*>(P.aux0) + min(col0 + 2 * VEC * s + VEC * hi, P.N - VEC);  // N is a multiple of VEC on these paths
+      bias[s][0] = *reinterpret_cast<const v4f*>(from);
+      bias[s][1] = *reinterpret_cast<const v4f*>(from + 4);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
@@ -130,6 +128,14 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
         val[e] = __uint_as_float(y[0]);
         val[4 + e] = __uint_as_float(y[1]);
       }
+      if (act_in) {  // one branch for what a plain result has not
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) val[e] += bias[FWD ? s : 0][e >> 2][e & 3];
+        if (NSUM == 0 && relu) {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) val[e] = fmaxf(val[e], 0.f);
+        }
+      }
       Chunk16<uint16_t> a, b, c, res, act;
       if constexpr (NT > 0) a.v = __builtin_bit_cast(uint4, x[i % AHEAD][0][s]);
       if constexpr (NT > 1) b.v = __builtin_bit_cast(uint4, x[i % AHEAD][1][s]);
@@ -139,7 +145,7 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
         if constexpr (NSUM > 0) val[e] += E::to_f32(a.e[e]);
         if constexpr (NSUM > 1) val[e] += E::to_f32(b.e[e]);
       }
-      if (relu) {
+      if (NSUM > 0 && relu) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) val[e] = fmaxf(val[e], 0.f);
       }
@@ -168,29 +174,29 @@ __device__ __forceinline__ void conv_epilogue(const GemmProb& P, v16f_t (&acc)[M
   if (P.epi == EPI_FWD) {
     if constexpr (GELU) {
       if (P.flags & GF_GELU) {
-        if (P.aux1) return conv_epilogue_as<MI, NI, 1, false, true>(P, acc, row0, col0, lane);
-        return conv_epilogue_as<MI, NI, 0, false, true>(P, acc, row0, col0, lane);
+        if (P.aux1) return conv_epilogue_as<MI, NI, true, 1, false, true>(P, acc, row0, col0, lane);
+        return conv_epilogue_as<MI, NI, true, 0, false, true>(P, acc, row0, col0, lane);
       }
     }
-    if (P.aux1) return conv_epilogue_as<MI, NI, 1, false, false>(P, acc, row0, col0, lane);
-    return conv_epilogue_as<MI, NI, 0, false, false>(P, acc, row0, col0, lane);
+    if (P.aux1) return conv_epilogue_as<MI, NI, true, 1, false, false>(P, acc, row0, col0, lane);
+    return conv_epilogue_as<MI, NI, true, 0, false, false>(P, acc, row0, col0, lane);
   }
   const int nsum = (P.aux0 != nullptr) + ((P.flags & GF_ACCUM) != 0);
   if constexpr (GELU) {
     if (P.flags & GF_GELU) {
-      if (nsum == 2) return conv_epilogue_as<MI, NI, 2, true, true>(P, acc, row0, col0, lane);
-      if (nsum == 1) return conv_epilogue_as<MI, NI, 1, true, true>(P, acc, row0, col0, lane);
-      return conv_epilogue_as<MI, NI, 0, true, true>(P, acc, row0, col0, lane);
+      if (nsum == 2) return conv_epilogue_as<MI, NI, false, 2, true, true>(P, acc, row0, col0, lane);
+      if (nsum == 1) return conv_epilogue_as<MI, NI, false, 1, true, true>(P, acc, row0, col0, lane);
+      return conv_epilogue_as<MI, NI, false, 0, true, true>(P, acc, row0, col0, lane);
     }
   }
   if (P.aux1) {
-    if (nsum == 2) return conv_epilogue_as<MI, NI, 2, true, false>(P, acc, row0, col0, lane);
-    if (nsum == 1) return conv_epilogue_as<MI, NI, 1, true, false>(P, acc, row0, col0, lane);
-    return conv_epilogue_as<MI, NI, 0, true, false>(P, acc, row0, col0, lane);
+    if (nsum == 2) return conv_epilogue_as<MI, NI, false, 2, true, false>(P, acc, row0, col0, lane);
+    if (nsum == 1) return conv_epilogue_as<MI, NI, false, 1, true, false>(P, acc, row0, col0, lane);
+    return conv_epilogue_as<MI, NI, false, 0, true, false>(P, acc, row0, col0, lane);
   }
-  if (nsum == 2) return conv_epilogue_as<MI, NI, 2, false, false>(P, acc, row0, col0, lane);
-  if (nsum == 1) return conv_epilogue_as<MI, NI, 1, false, false>(P, acc, row0, col0, lane);
-  return conv_epilogue_as<MI, NI, 0, false, false>(P, acc, row0, col0, lane);
+  if (nsum == 2) return conv_epilogue_as<MI, NI, false, 2, false, false>(P, acc, row0, col0, lane);
+  if (nsum == 1) return conv_epilogue_as<MI, NI, false, 1, false, false>(P, acc, row0, col0, lane);
+  return conv_epilogue_as<MI, NI, false, 0, false, false>(P, acc, row0, col0, lane);
 }
 
 // Through LDS, 32 rows at a time and in fp32: every instruction then moves whole rows.  `stage`: conv_stage_floats(NI) floats of

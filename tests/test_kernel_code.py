@@ -105,3 +105,18 @@ def test_what_counts_as_a_short_wait():
     assert _short_waits(["v_readfirstlane_b32 s5, v2", "s_mov_b32 m0, s9", "s_nop 3", load]) == ([], 1)
     assert _short_waits(["v_readfirstlane_b32 s8, v2", "s_mov_b32 m0, s9", "s_nop 0", load]) == ([], 1)
     assert _short_waits(["s_mov_b32 s5, s20", "s_mov_b32 m0, s9", load]) == ([("s_mov_b32 m0, s9", 0, load)], 1)
+
+
+def test_convolution_tiles_do_not_spill(objects):
+    """Registers of the tiles that load straight into LDS: an epilogue variant that spills reloads between its stores, and a reload waits for them
+    (256 x 256 tiles with a residual 276 us, without spills 248)."""
+    readelf, spills = os.path.join(os.path.dirname(OBJDUMP), "llvm-readelf"), {}
+    for o in objects:
+        name = None
+        text = subprocess.run([readelf, "--notes", str(o)], check=True, capture_output=True, text=True, timeout=120).stdout
+        for key, value in re.findall(r"^\s+-?\s*\.(symbol|vgpr_spill_count):\s+(\S+)", text, flags=re.M):
+            if key == "symbol":
+                name = value
+            elif "conv_ge" in name and ("_dl_kernel" in name or "_run_kernel" in name):
+                spills[name] = int(value)
+    assert len(spills) >= 13 and not any(spills.values()), spills
