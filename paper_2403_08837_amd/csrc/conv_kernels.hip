@@ -274,8 +274,10 @@ __device__ __forceinline__ void conv_gemm_body(const GemmBatch& batch) {
   __syncthreads();  // the operand tiles are consumed
   conv_epilogue_rows<T, MI, NI, GELU>(P, acc, row0 + wm * WTM, col0 + wn * WTN, lane, reinterpret_cast<float*>(smem) + wave * conv_stage_floats(NI));
 }
+// Four workgroups per CU of the 128 x 128 tiles in bf16 with slabs of 32, although epilogues that read spill a few of the 128 registers then (us, three /
+// four: 100352 x 128 x 96 13.0 / 11.7, data gradient with mask and addend 20.2 / 19.2; 50176 x 136 x 96 11.2 / 10.1, with a mask 12.8 / 12.2).
 template <typename T, int BM, int BN, int BK, bool DB, bool RAGGED>
-__global__ __launch_bounds__(256, BM == 128 && BN == 128 ? 3 : 4) void conv_gemm_kernel(const GemmBatch batch) {
+__global__ __launch_bounds__(256, BM == 128 && BN == 128 ? (sizeof(T) == 2 && BK == 32 ? 4 : 3) : 4) void conv_gemm_kernel(const GemmBatch batch) {
   conv_gemm_body<T, BM, BN, BK, DB, RAGGED, false>(batch);
 }
 // A kernel of its own: with the second epilogue in conv_gemm_kernel its launches without a GELU lose 2 % (3x3 over 128 channels, three passes, 60.3 ->

@@ -200,25 +200,28 @@ __device__ __forceinline__ void conv_epilogue(const GemmProb& P, v16f_t (&acc)[M
 }
 
 // Through LDS, 32 rows at a time and in fp32: every instruction then moves whole rows.  `stage`: conv_stage_floats(NI) floats of
-// the wave's own, which no wave reads any more.  NT tensors are read (the sums, then the mask).  Everything that is read - one tensor of all
-// row blocks, two of one, three of half of one - is asked for in one round and waited for once, ahead of the stores, which count with the loads: a read on some
-// path between two stores had every store wait for the one before, and a bias read element by element was eight round trips
-// (us before / so: 100352 x 256 x 64 20.9 / 17.1, with bias, residual and ReLU 28.1 / 24.5; in fp32 6272 x 768 x 192 32.8 / 30.2).
+// the wave's own, which no wave reads any more.  NT tensors are read (the sums, then the mask).  Everything that is read - one tensor of all row
+// blocks, two or three of as many chunks as the registers of one - is asked for in one round and waited for once, ahead of the stores, which count
+// with the loads: a read on some path between two stores had every store wait for the one before, and a bias read element by element was eight
+// round trips (us before / so: 100352 x 256 x 64 19.2 / 15.5, with bias, residual and ReLU 25.8 / 21.9; in fp32 6272 x 768 x 192 32.1 / 29.9).
 constexpr int conv_stage_floats(int NI) { return 32 * (32 * NI + 4); }
-template <typename T, int MI, int NI, int NT, bool GELU>
+template <typename T, int MI, int NI, bool FWD, int NT, bool GELU>
 __device__ __forceinline__ void conv_epilogue_rows_as(const GemmProb& P, const v16f_t (&acc)[MI][NI], int row0, int col0, int lane, float* stage) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC, SP = 32 * NI + 4;                // pitch: rows 4 banks apart
   constexpr int CPS = 32 * NI / VEC, NCH = 32 * CPS / 64;      // chunks per staged row, per lane and pass
-  constexpr int BLOCKS = NT == 1 ? MI : 1, HELD = NT > 2 ? NCH / 2 : NCH;  // row blocks, and chunks of one, whose operands are held at once
+  // Row blocks, and chunks of one, whose operands are held at once: no more registers than one tensor of all row blocks takes (or 32), or launches
+  // that read nothing pay with their occupancy.
+  constexpr int ROOM = MI * NCH > 8 ? MI * NCH : 8, BLOCKS = NT == 1 ? MI : 1;
+  constexpr int HELD = NT * NCH <= ROOM || NT < 2 ? NCH : NT * NCH <= 2 * ROOM ? NCH / 2 : NCH / 4;
   static_assert(64 % CPS == 0, "a lane keeps its columns from chunk to chunk");
   const int l31 = lane & 31, hi = lane >> 5;
   const int c = col0 + (lane % CPS) * VEC;
-  const bool fwd = P.epi == EPI_FWD, relu = fwd && (P.flags & GF_RELU), masked = !fwd && P.aux1, accum = !fwd && (P.flags & GF_ACCUM);
+  const bool relu = FWD && (P.flags & GF_RELU), masked = !FWD && P.aux1, accum = !FWD && (P.flags & GF_ACCUM);
   const int M = P.M, N = P.N, ldo = P.ldo;
   T* const out = static_cast<T*>(P.out);
   T* const out2 = GELU ? static_cast<T*>(const_cast<void*>(P.aux2)) : nullptr;
-  const T* const t0 = static_cast<const T*>(fwd ? P.aux1 : P.aux0 ? P.aux0 : accum ? P.out : P.aux1);
+  const T* const t0 = static_cast<const T*>(FWD ? P.aux1 : P.aux0 ? P.aux0 : accum ? P.out : P.aux1);
   const T* const t1 = static_cast<const T*>(P.aux0 && accum ? P.out : P.aux1);
   const T* const t2 = static_cast<const T*>(P.aux1);
   uint4 x[NT ? NT : 1][BLOCKS][HELD];
@@ -236,7 +239,7 @@ __device__ __forceinline__ void conv_epilogue_rows_as(const GemmProb& P, const v
 #pragma unroll
     for (int i = 0; i < MI; ++i) request(i, 0);
   }
-  const bool biased = fwd && P.aux0;
+  const bool biased = FWD && P.aux0;
   float bias[VEC];
   if (biased) {
     typedef float vecf __attribute__((ext_vector_type(VEC), aligned(4)));
@@ -259,7 +262,7 @@ __device__ __forceinline__ void conv_epilogue_rows_as(const GemmProb& P, const v
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
     for (int t = 0; t < NCH; ++t) {
-      if (NT > 2 && t == HELD) request(i, HELD);
+      if (NT > 1 && t > 0 && t % HELD == 0) request(i, t);
       if (t % HELD == 0 && (i == 0 || NT > 1)) {
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
         __builtin_amdgcn_sched_barrier(0);
@@ -294,16 +297,14 @@ __device__ __forceinline__ void conv_epilogue_rows_as(const GemmProb& P, const v
       Chunk16<T> res, act;
 #pragma unroll
       for (int e = 0; e < VEC; ++e) res.e[e] = E::from_f32(val[e]);
-      if constexpr (GELU) {
-        if (fwd) {
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) act.e[e] = E::from_f32(gelu_f<T>(E::to_f32(res.e[e])));
-        }
-      }
       if (row(i, t) >= M || c >= N) continue;  // N is a multiple of VEC on these paths
       const int64_t o = (int64_t)row(i, t) * ldo + c;
       *reinterpret_cast<uint4*>(out + o) = res.v;
-      if (GELU && fwd) *reinterpret_cast<uint4*>(out2 + o) = act.v;
+      if constexpr (GELU && FWD) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) act.e[e] = E::from_f32(gelu_f<T>(E::to_f32(res.e[e])));
+        *reinterpret_cast<uint4*>(out2 + o) = act.v;
+      }
     }
   }
 }
@@ -313,16 +314,17 @@ __device__ __forceinline__ void conv_epilogue_rows(const GemmProb& P, const v16f
   const int nt = (P.aux1 != nullptr) + (!fwd && P.aux0) + (!fwd && (P.flags & GF_ACCUM));
   if constexpr (GELU) {
     if (P.flags & GF_GELU) {
-      if (nt == 0) return conv_epilogue_rows_as<T, MI, NI, 0, true>(P, acc, row0, col0, lane, stage);
-      if (nt == 1) return conv_epilogue_rows_as<T, MI, NI, 1, true>(P, acc, row0, col0, lane, stage);
-      if (nt == 2) return conv_epilogue_rows_as<T, MI, NI, 2, true>(P, acc, row0, col0, lane, stage);
-      return conv_epilogue_rows_as<T, MI, NI, 3, true>(P, acc, row0, col0, lane, stage);
+      if (fwd) return nt ? conv_epilogue_rows_as<T, MI, NI, true, 1, true>(P, acc, row0, col0, lane, stage) : conv_epilogue_rows_as<T, MI, NI, true, 0, true>(P, acc, row0, col0, lane, stage);
+      if (nt == 1) return conv_epilogue_rows_as<T, MI, NI, false, 1, true>(P, acc, row0, col0, lane, stage);
+      if (nt == 2) return conv_epilogue_rows_as<T, MI, NI, false, 2, true>(P, acc, row0, col0, lane, stage);
+      return conv_epilogue_rows_as<T, MI, NI, false, 3, true>(P, acc, row0, col0, lane, stage);
     }
   }
-  if (nt == 0) return conv_epilogue_rows_as<T, MI, NI, 0, false>(P, acc, row0, col0, lane, stage);
-  if (nt == 1) return conv_epilogue_rows_as<T, MI, NI, 1, false>(P, acc, row0, col0, lane, stage);
-  if (nt == 2) return conv_epilogue_rows_as<T, MI, NI, 2, false>(P, acc, row0, col0, lane, stage);
-  return conv_epilogue_rows_as<T, MI, NI, 3, false>(P, acc, row0, col0, lane, stage);
+  if (fwd) return nt ? conv_epilogue_rows_as<T, MI, NI, true, 1, false>(P, acc, row0, col0, lane, stage) : conv_epilogue_rows_as<T, MI, NI, true, 0, false>(P, acc, row0, col0, lane, stage);
+  if (nt == 0) return conv_epilogue_rows_as<T, MI, NI, false, 0, false>(P, acc, row0, col0, lane, stage);
+  if (nt == 1) return conv_epilogue_rows_as<T, MI, NI, false, 1, false>(P, acc, row0, col0, lane, stage);
+  if (nt == 2) return conv_epilogue_rows_as<T, MI, NI, false, 2, false>(P, acc, row0, col0, lane, stage);
+  return conv_epilogue_rows_as<T, MI, NI, false, 3, false>(P, acc, row0, col0, lane, stage);
 }
 
 }  // namespace cdp

@@ -108,8 +108,8 @@ def test_what_counts_as_a_short_wait():
 
 
 def test_convolution_tiles_do_not_spill(objects):
-    """Registers of the tiles that load straight into LDS: an epilogue variant that spills reloads between its stores, and a reload waits for them
-    (256 x 256 tiles with a residual 276 us, without spills 248)."""
+    """Registers of the tiles that load straight into LDS, and of those in fp32: an epilogue variant that spills reloads between its stores, and a
+    reload waits for them (256 x 256 tiles with a residual 276 us, without spills 248)."""
     readelf, spills = os.path.join(os.path.dirname(OBJDUMP), "llvm-readelf"), {}
     for o in objects:
         name = None
@@ -117,6 +117,6 @@ def test_convolution_tiles_do_not_spill(objects):
         for key, value in re.findall(r"^\s+-?\s*\.(symbol|vgpr_spill_count):\s+(\S+)", text, flags=re.M):
             if key == "symbol":
                 name = value
-            elif "conv_ge" in name and ("_dl_kernel" in name or "_run_kernel" in name):
+            elif "conv_ge" in name and ("_dl_kernel" in name or "_run_kernel" in name or "conv_gemm_kernelIf" in name):
                 spills[name] = int(value)
-    assert len(spills) >= 13 and not any(spills.values()), spills
+    assert len(spills) >= 25 and not any(spills.values()), spills
