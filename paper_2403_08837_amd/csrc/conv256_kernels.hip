@@ -585,15 +585,20 @@ int conv_dl_tile(const GemmProb* p, int n, int dtype, bool shared) {
 }
 
 // Launches of 512 tiles of 128 x 128 and more: conv_gemm_run_kernel, 256 x 256, or `named`, the tile conv_dl_tile names, by the time each takes:
-// full rounds (of 512 tiles for the first, of 256 for the others) times what a tile costs, fixed and per 1000 of the reduction, and the same for
-// the tiles themselves, whose last round has the memory to itself.  Coefficients (us) fitted to 176 products of 512 to 5720 tiles, N 72 to 3200,
-// K 64 to 3008, one to eight problems, rms 7 to 10 %.  What it takes is 7.6 % faster than conv_gemm_kernel and the tiles of conv_dl_tile on
-// average, 1.0 % slower than the best of the four (the slowest 1.15), conv_gemm_run_kernel alone 4.9 %.  us, conv_gemm_kernel / 256 x 256 / 256 x 128 / 192 x 128 / walked:
-//   6272 x 3072 x 768     45.8 / 45.7 / 46.3 / 49.4 / 40.0       18848 x 2768 x 192   41.1 / 43.4 / 48.6 / 49.0 / 37.7
-//   143204 x 168 x 192    30.3 / 32.3 / 36.5 / 35.5 / 26.1       7163 x 2384 x 2560   115 / 112 / 107 / 87 / 101
-//   36029 x 1672 x 2304   336 / 238 / 283 / 288 / 298            113066 x 496 x 1600  235 / 187 / 203 / 228 / 219
-// Below 640 walked, where 256 x 256 gains little and loses up to 15 %, but for one round of those (25088 x 512 x 128 16.7 / 12.6 / - / - / 16.6);
-// one slab of 64 is nothing to walk with (100352 x 256 x 64 17.1 / - / - / - / 21.7).
+// full rounds (of 512 tiles for the first, of 768 for conv_gemm_kernel, of 256 for the others) times what a tile costs, fixed and per 1000 of the
+// reduction, and the same for the tiles themselves, whose last round has the memory to itself.  Coefficients (us) fitted to 176 products of 512 to
+// 5720 tiles, N 72 to 3200, K 64 to 3008, one to eight problems, rms 7 to 10 %.  Over 193 other products of the same ranges what it takes is 2.7 %
+// faster than the tiles of conv_dl_tile on average and 1.5 % slower than the best of the five (1.35 for six problems of 64 to 1088 in one launch,
+// whose mean says little), conv_gemm_run_kernel alone 5.8 % slower.
+// us, conv_gemm_kernel / 256 x 256 / 256 x 128 / 192 x 128 / walked:
+//   6272 x 3072 x 768     45.7 / 46.9 / 47.3 / 51.1 / 40.2       32203 x 784 x 384    32.0 / 34.5 / 35.9 / 35.5 / 30.2
+//   36029 x 1672 x 2304   346 / 250 / 294 / 304 / 305            7163 x 2384 x 2560   113 / 115 / 108 / 88 / 100
+//   113066 x 496 x 1600   222 / 189 / 207 / 229 / 236            66517 x 824 x 1024   151 / 151 / 142 / 137 / 132
+// Below 640 walked, where 256 x 256 gains little and loses up to 15 %, but for one round of those (25088 x 512 x 128 12.9 / 12.0 / 14.9 / 16.8 / 14.9); below
+// 350 not walked: a slab or five are little to walk with, and conv_gemm_kernel has three workgroups per CU (walked against it, means over the products
+// of one problem: K 64 1.23, 128 1.13, 192 1.10, 256 1.02, 320 1.03, 384 0.98, 448 to 512 0.97).
+//   100352 x 256 x 64     15.7 / 19.4 / 24.0 / 24.6 / 18.5       14028 x 1656 x 128   16.8 / 21.3 / 22.8 / 23.7 / 20.5
+//   17073 x 1304 x 192    19.4 / 23.9 / 25.1 / 25.5 / 22.3       55962 x 296 x 320    24.2 / 27.9 / 26.5 / 26.3 / 25.0
 // Residuals, masks, addends and GELUs leave a launch where it was: their reads wait in line with the slabs requested ahead, and conv_gemm_kernel's
 // three workgroups per CU read whole rows.  Steps of ResNet-50 and ViT-B/16 shapes, ms per four, with all such launches walked / those of a mean
 // reduction of 512 and more / none / no launch walked at all: - / 78.2 / 77.4 / 77.5 and 206.2 / 206.2 / 204.9 / 208.6.
@@ -615,9 +620,12 @@ static int conv_many_tile(const GemmProb* p, int n, int named) {
   auto us = [&](double tiles, int slots, double a, double b, double c, double d, double e) {
     return a + std::ceil(tiles / slots) * (b + c * k) + tiles / slots * (d + e * k);
   };
-  if (k < 0.64 && wide > 256) return k < 0.1 ? named : DL_RUN;
+  if (k < 0.64 && wide > 256) return k < 0.35 ? named : DL_RUN;
   const double walked = us(t128, 512, 6.7, -1.3, 4.4, 3.8, 10.8), square = us(wide, 256, 3.7, 2.8, 10.3, 3.1, 13.7);
-  const double other = named == DL_256x128 ? us(t256, 256, 4.3, 2.4, 7.0, 1.5, 7.0) : named == DL_192x128 ? us(t192, 256, 3.7, 3.9, 2.3, -0.7, 8.5) : 1e30;
+  const double other = named == DL_256x128   ? us(t256, 256, 4.3, 2.4, 7.0, 1.5, 7.0)
+                       : named == DL_192x128 ? us(t192, 256, 3.7, 3.9, 2.3, -0.7, 8.5)
+                       : k < 0.35            ? us(t128, 768, 5.3, 0.5, 3.9, 2.0, 23.4)
+                                             : 1e30;
   return other < std::min(walked, square) ? named : square < walked ? DL_256x256 : DL_RUN;
 }
 int conv_launch_tile(const GemmProb* p, int n, int dtype, bool shared) {
