@@ -635,17 +635,95 @@ def test_conv_tiles_of_large_tensors(which, rows, cin, cout):
         assert torch.equal(act, ref)
 
 
-@pytest.mark.parametrize("rows,out,slabs", [(21800, 376, 1), (21800, 376, 2), (21800, 376, 3), (33000, 600, 5),   # walked: 513 tiles and 1290, odd numbers of
-                                            (65500, 136, 9), (8200, 1992, 4), (140100, 72, 1),                    # slabs and even, columns past a tile
-                                            (21800, 376, 17), (24000, 760, 34)])                                  # 256 x 256 or the tile of one round
-def test_conv_many_tiles(rows, out, slabs):
+def _launch_tile(rows, out, depth, beside=False):
+    """conv_launch_tile for one product, asked of the library as tests/launch_rules/tiles.cpp does."""
+    import os
+    import subprocess
+    here = os.path.dirname(os.path.abspath(b.__file__))
+    exe = os.path.join(_launch_tile.folder, "tiles")
+    if not os.path.exists(exe):
+        subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(here, "csrc"),
+                        os.path.join(os.path.dirname(os.path.abspath(__file__)), "launch_rules", "tiles.cpp"), "-o", exe, os.path.join(here, "libcdp.so"),
+                        "-Wl,-rpath," + here, "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True)
+    line = "%d %d %d 0 %d\n" % (rows, out, depth, 2 * beside)
+    return int(subprocess.run([exe], input=line, capture_output=True, text=True, check=True, timeout=60).stdout)
+
+
+@pytest.fixture(scope="module")
+def launch_tile(tmp_path_factory):
+    _launch_tile.folder = str(tmp_path_factory.mktemp("tiles"))
+    return _launch_tile
+
+
+# rows, columns, slabs of 64, tile
+@pytest.mark.parametrize("rows,out,slabs,tile", [(21800, 376, 6, 7), (21800, 376, 7, 7), (33000, 600, 9, 7), (140100, 72, 8, 7), (140100, 72, 7, 7),  # walked: odd
+                                                 (8200, 1992, 8, 7),                                  # numbers of slabs and even, columns past a tile
+                                                 (21800, 376, 1, 0), (33000, 600, 5, 0), (140100, 72, 1, 0),                       # conv_gemm_kernel
+                                                 (65500, 136, 5, 1), (65500, 136, 9, 1), (24000, 2040, 34, 1),                     # 256 x 256
+                                                 (21800, 376, 17, 6), (24000, 760, 34, 6)])                                        # 192 x 128
+def test_conv_many_tiles(launch_tile, rows, out, slabs, tile):
     """Launches of 512 tiles of 128 x 128 and more."""
+    assert launch_tile(rows, out, 64 * slabs) == tile
     _conv_1x1_bf16(0, rows, 64 * slabs, out)
 
 
-@pytest.mark.parametrize("case", [(16, 57, 57, 64, 136, 3, 1, 1), (24, 57, 57, 136, 64, 3, 2, 1), (24, 115, 113, 64, 136, 3, 2, 1)])
-def test_conv_many_tiles_taps(case):
-    """The same with taps, a stride and padding, forward and data gradient (814, 1220 and 1200 tiles)."""
+@pytest.fixture(scope="module")
+def many(tmp_path_factory):
+    """launch_conv_dl of several problems (tests/launch_rules/many.cpp)."""
+    import ctypes
+    import os
+    import subprocess
+    here = os.path.dirname(os.path.abspath(b.__file__))
+    so = str(tmp_path_factory.mktemp("many") / "many.so")
+    b.lib()
+    subprocess.run(["g++", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(here, "csrc"),
+                    os.path.join(os.path.dirname(os.path.abspath(__file__)), "launch_rules", "many.cpp"), "-o", so, os.path.join(here, "libcdp.so"),
+                    "-Wl,-rpath," + here, "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True)
+    f = ctypes.CDLL(so).many
+
+    def launch(tile, problems):  # (A, B, out)
+        mnk = [v for a, w, _ in problems for v in (a.shape[0], w.shape[0], a.shape[1])]
+        ptrs = [x.data_ptr() for p in problems for x in p]
+        assert f(len(problems), (ctypes.c_int * len(mnk))(*mnk), (ctypes.c_void_p * len(ptrs))(*ptrs), tile, None) == 0
+    return launch
+
+
+WALKED = 7
+
+
+@pytest.mark.parametrize("n,tiles", [(1, 63), (1, 513), (2, 64), (2, 511), (2, 513), (3, 575), (3, 1025), (5, 640), (5, 1999), (8, 512), (8, 700), (16, 1100), (24, 449), (24, 1600)])
+def test_conv_many_tiles_of_several_problems(many, n, tiles):
+    """Launches of several problems on the walked tiles: the workgroups' shares are every tile of every problem.  Reductions of 1 to 16 slabs, odd ones
+    among them, tile counts around whole rounds, one problem with most of the tiles, columns past a tile.  Exact: -1, 0 and 1, small whole sums."""
+    torch = _torch()
+    gen = torch.Generator(device="cuda")
+    for seed in range(3):
+        gen.manual_seed(100 * tiles + 10 * n + seed)
+        rng = np.random.default_rng(1000 * n + tiles + seed)
+        cuts = np.sort(rng.choice(np.arange(1, tiles), n - 1, replace=False)) if seed else np.arange(1, n)  # seed 0: all but the last have one tile
+        problems, refs = [], []
+        for count in np.diff(np.concatenate(([0], cuts, [tiles]))):
+            cols = max(c for c in (1, 2, 3, 4) if count % c == 0 and (seed or c == 1))
+            m, k = 128 * int(count // cols) - int(rng.integers(0, 127)), 64 * int(rng.integers(1, 17 if count < 300 else 6))
+            x = torch.randint(-1, 2, (m, k), generator=gen, device="cuda").to(torch.bfloat16)
+            w = torch.randint(-1, 2, (128 * cols - 8 * int(rng.integers(0, 15)), k), generator=gen, device="cuda").to(torch.bfloat16)
+            problems.append((x, w, torch.full((m, w.shape[0]), float("nan"), dtype=torch.bfloat16, device="cuda")))
+            refs.append((x.float() @ w.float().T.contiguous()).to(torch.bfloat16))
+        many(WALKED, problems)
+        torch.cuda.synchronize()
+        for (x, w, got), ref in zip(problems, refs):
+            assert torch.equal(got, ref), (seed, tuple(x.shape), tuple(w.shape))
+
+
+# tile of the forward and of the data gradient (0: also what is ragged)
+@pytest.mark.parametrize("case,forward,backward", [((16, 57, 57, 64, 136, 3, 1, 1), 1, 0), ((24, 57, 57, 64, 72, 3, 1, 1), 7, 0), ((24, 57, 57, 72, 64, 3, 1, 1), 0, 7),
+                                                   ((24, 57, 57, 136, 64, 3, 2, 1), 0, 7), ((24, 115, 113, 64, 136, 3, 2, 1), 7, 0)])
+def test_conv_many_tiles_taps(launch_tile, case, forward, backward):
+    """The same with taps, strides and padding."""
+    B, H, W, cin, cout, k, st, pad = case
+    out = B * ((H + 2 * pad - k) // st + 1) * ((W + 2 * pad - k) // st + 1)
+    for rows, n, c, tile in ((out, cout, cin, forward), (B * H * W, cin, cout, backward)):
+        assert (launch_tile(rows, n, k * k * c) if c % 64 == 0 else 0) == tile
     test_conv_passes_match_oracle(wl.BF16, case)
 
 
