@@ -20,9 +20,9 @@
 //     slabs all eight wavefronts waited for their first fragments at once;
 //   * fragments of the next 16-deep step are read between the products of the current one, in the order of the source (sched_barrier);
 //   * results leave out of the registers (conv_epilogue).
-// us, with compiler-ordered loads, the barrier between slabs and an epilogue whose stores waited for each other / so: 8192^3 985 / 859 (1279 TFLOP/s),
-// 3x3 over 512 channels with 25088 rows 116 / 101 (256 x 256); 6272 x 768 x 3072 38.0 / 33.4 (192 x 128); 25088 x 128 x 1152 13.9 / 12.3 (128 x 128);
-// 1568 x 512 x 4608 22.5 / 19.8, 6272 x 256 x 1024 9.4 / 8.1 (64 x 64).  Outputs bit for bit the same.
+// us, with compiler-ordered loads, the barrier between slabs and an epilogue whose stores waited for each other / so: 8192^3 936 / 804 (1367 TFLOP/s),
+// 3x3 over 512 channels with 25088 rows 111 / 97 (256 x 256); 6272 x 768 x 3072 37.5 / 33.6 (192 x 128); 25088 x 128 x 1152 14.6 / 14.0 (128 x 128);
+// 1568 x 512 x 4608 22.5 / 20.9, 6272 x 256 x 1024 9.4 / 8.6 (64 x 64).  Outputs bit for bit the same.
 // Same problem descriptors, same epilogues (bias, residual, ReLU; data gradient: addend, accumulate, mask).
 #include <algorithm>
 #include <cmath>

@@ -903,10 +903,11 @@ constexpr int conv_gemm_lds_bytes() {
 }
 
 // fp32, few tiles: a workgroup per 32 x 32 tile of the result, its four wavefronts take every fourth slab of 32 of the reduction
-// with both operands straight from memory (16-byte pieces of 32 rows, both sides' columns in the same order, the next slab's on
-// their way during the products), and add their tiles through LDS in wavefront order.  Bound by the address path, 32 bytes
-// of a row per access: 162 tiles, 1152 deep (3x3, stride 2, data gradient of 32 x 9 x 9 x 64) 38.6 us as 41 tiles of 64 x 64,
-// 12.6 us so; 100 tiles, 576 deep 20.6 -> 8.8 us.
+// with both operands straight from memory (16-byte pieces of 32 rows, both sides' columns in the same order), and add their tiles
+// through LDS in wavefront order.  Bound by the latency of memory: the zeros of a tap outside the image are put in right behind the
+// request, a use, so that the products of a slab wait for the gathered pieces of the next one, a round trip per slab of a wavefront.
+// 162 tiles, 1152 deep (3x3, stride 2, data gradient of 32 x 9 x 9 x 64: nine slabs each) 38.6 us as 41 tiles of 64 x 64,
+// 12.6 us so; 100 tiles, 576 deep (five) 20.6 -> 8.8 us.
 __global__ __launch_bounds__(256, 2) void conv_gemm_few_kernel(const GemmBatch batch) {
   __shared__ float red[4 * 16 * 64];
   const int tile = blockIdx.x;

@@ -204,7 +204,7 @@ void conv_gemm_tile(const GemmProb* p, int n, int* bm, int* bn);  // tile shape 
 hipError_t launch_conv_gemm(GemmBatch& batch, int dtype, int bm, int bn, hipStream_t stream);  // forward / data gradient
 // Direct-to-LDS variant for bf16 problems whose reduction slabs lie inside one tap: 256 x 256 tiles for large launches with
 // long reductions (_wanted: enough mostly-full tiles to fill the chip), smaller ones with a deeper prefetch for
-// launches short of workgroups (conv_dl_tile, 0: neither).
+// launches short of workgroups (conv_dl_tile, 0: neither), tiles walked by resident workgroups for launches of many (conv_launch_tile).
 enum ConvDlTile : int { DL_NONE = 0, DL_256x256, DL_256x128, DL_128x128, DL_64x64, DL_64x64_SHORT, DL_192x128, DL_RUN };
 bool conv_gemm256_eligible(const GemmProb& p, int dtype);
 bool conv_gemm256_wanted(const GemmProb* p, int n, int dtype);
