@@ -95,13 +95,32 @@ __device__ __forceinline__ void conv_epilogue_as(const GemmProb& P, v16f_t (&acc
   if constexpr (NT > 0 && AHEAD == 2) request(0);
   // The bias of this lane's columns, in one round; none is -0, which changes no value it is added to.  (Waited for here: where it is used the compiler
   // would wait again, for the stores too.  Added to the accumulators ahead of everything, 256 x 256 tiles spilled 66 registers, with a GELU 200:
-  // us so / now, 25088 x 2048 x 2048 with bias, residual and ReLU 276 / 248, GELU 268 / 250.)
+  // us so / now, 25088 x 2048 x 2048 with bias, residual and ReLU 276 / 248, GELU 268 / 250.  EARLY: small tiles with a GELU do it all the same, the
+  // pieces then have no branch: 3000 x 256 x 96 4.65 / 4.59, 25088 x 128 x 1152 with a bias 16.5 / 16.2.)
   typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
-  const bool biased = FWD && fwd && P.aux0, act_in = biased || relu;
+  constexpr bool EARLY = FWD && GELU && MI * NI <= 4;
+  const bool biased = FWD && fwd && P.aux0, act_in = (biased && !EARLY) || relu;
   v4f bias[FWD ? NS : 1][2];
 #pragma unroll
   for (int s = 0; s < (FWD ? NS : 1); ++s) bias[s][0] = bias[s][1] = v4f{-0.f, -0.f, -0.f, -0.f};
-  if (biased) {
+  if (EARLY && biased) {  // 32 j + 8 q + 4 hi are the columns of this lane as the products leave them
+    v4f b[NI][4];
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[j][q] = *reinterpret_cast<const v4f*>(static_cast<const float*>(P.aux0) + min(col0 + 32 * j + 8 * q + 4 * hi, P.N - 4));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += b[j][q][e];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (!EARLY && biased) {
 #pragma unroll
     for (int s = 0; s < (FWD ? NS : 0); ++s) {
       const float* const from = static_cast<const float*>(P.aux0) + min(col0 + 2 * VEC * s + VEC * hi, P.N - VEC);  // N is a multiple of VEC on these paths
